@@ -2,6 +2,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <initializer_list>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -79,8 +80,8 @@ size_t gkv_max_lds_bytes(const gkv_config* c) {
   // per-workgroup allowance itself when that passes 64 KiB: at the largest capacity it needs 96 KiB
   // of the 160 KiB a compute unit holds)
   upd(4 * cap + 64);                                                // pooled score / eviction log
-  if (c->dtype == GKV_BF16 && d == 128 && g <= 16)
-    upd(4 * (4 * g * 132 + 128) + (32 + 16 * g) * 16 + 16);         // attend_mfma: partial outputs + staged rows
+  if ((d == 64 || d == 128) && g <= 16)                             // attend_mfma: partial outputs + staged rows
+    upd(gkv_attend_mfma_lds(c->dtype == GKV_F32 ? 4 : 2, (int)d, (int)g, 4) + 16);
   return need;
 }
 
@@ -119,6 +120,7 @@ extern "C" gkv_status gkv_create(const gkv_config* cfg, gkv_ctx** out_ctx) {
   for (int i = 0; i < cfg->window; ++i) c->stats_step[i] = -1;
   c->stats_ws = c->stats_K = c->stats_qwin = nullptr;
   c->mfma_ok = cfg->dtype == GKV_BF16 && d.d == 128 && d.g <= 16;
+  c->attend_mfma_ok = (d.d == 64 || d.d == 128) && d.g <= 16;
   c->prof = new (std::nothrow) GkvProfile();
   *out_ctx = c;
   return GKV_OK;
@@ -155,11 +157,9 @@ static int max_splits(const gkv_ctx* ctx) {
 }
 
 int gkv_effective_splits(const gkv_ctx* ctx) {
-  const bool mfma = ctx->mfma_ok && !ctx->force_generic;
+  const bool mfma = ctx->attend_mfma_ok && !ctx->force_generic;
   if (!mfma) return 1;
-  const int64_t units = (int64_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
   int s = ctx->attend_splits;
-  (void)units;
   if (s <= 0) s = 1;   // measured: the cross-workgroup merge (device-scope fences over 8 XCDs) costs more than it saves, even at 4 units
   const int m = max_splits(ctx);
   return s > m ? m : s;
@@ -170,10 +170,10 @@ int gkv_effective_splits(const gkv_ctx* ctx) {
 // with 8 wavefronts per unit (measured: 4 to 128 units, 8-16% faster); from a few hundred units
 // on 4 and 8 are equal, and 4 keeps the LDS merge small.
 static int gkv_attend_waves(const gkv_ctx* ctx) {
-  if (ctx->attend_waves > 0) return ctx->attend_waves;
+  auto fits = [&](int waves) { return gkv_attend_mfma_lds(ctx->esz, ctx->dims.d, ctx->dims.g, waves) <= 65000; };
+  if (ctx->attend_waves > 0) return fits(ctx->attend_waves) ? ctx->attend_waves : 4;
   const int64_t units = (int64_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
-  const bool fits8 = 8 * ctx->dims.g * 132 * 4 + 8 * 128 + (32 + 16 * ctx->dims.g) * 16 <= 65000;
-  return (units <= 256 && fits8 && ctx->attend_tile == 16) ? 8 : 4;
+  return (units <= 256 && fits(8) && ctx->attend_tile == 16) ? 8 : 4;
 }
 
 static size_t ws_stats_bytes(const gkv_ctx* ctx) {
@@ -182,7 +182,7 @@ static size_t ws_stats_bytes(const gkv_ctx* ctx) {
 
 // Split-K partials for `splits` workgroups per unit (none when a unit is not split).
 static size_t ws_partials_bytes(const gkv_ctx* ctx, int splits) {
-  if (!ctx->mfma_ok || splits <= 1) return 0;
+  if (!ctx->attend_mfma_ok || splits <= 1) return 0;
   const size_t units = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
   return units * splits * ctx->dims.g * (ctx->dims.d + 2) * sizeof(float);
 }
@@ -284,7 +284,15 @@ extern "C" gkv_status gkv_advance_step_base(gkv_ctx* ctx, int32_t delta, void* s
 }
 
 // ---- the five calls -----------------------------------------------------------------------------
-static bool use_mfma_attend(const gkv_ctx* ctx) { return ctx->mfma_ok && !ctx->force_generic; }
+static bool use_mfma_redundancy(const gkv_ctx* ctx) { return ctx->mfma_ok && !ctx->force_generic; }
+// The matrix-core decode kernel moves 16-byte pieces; callers are asked for 16-byte aligned base
+// pointers, and shapes the plain kernel can also take fall back to it for others.
+static bool use_mfma_attend(const gkv_ctx* ctx, std::initializer_list<const void*> ptrs) {
+  if (!ctx->attend_mfma_ok || ctx->force_generic) return false;
+  uintptr_t bits = 0;
+  for (const void* p : ptrs) bits |= (uintptr_t)p;
+  return (bits & 15) == 0;
+}
 static bool use_mfma_score(const gkv_ctx* ctx) {
   return ctx->mfma_ok && !ctx->force_generic && gkv_score_mfma_supported(ctx->dims.g, ctx->dims.w, ctx->dims.cap);
 }
@@ -332,14 +340,14 @@ extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void*
     a.copy_q = (const char*)q != (const char*)qwin + (size_t)(step % ctx->dims.w) * slot_bytes;
   }
   GkvLaunch ln{ctx, GKV_K_ATTEND, (hipStream_t)stream};
-  if (use_mfma_attend(ctx)) {
+  if (use_mfma_attend(ctx, {q, k_new, v_new, K, V, qwin, out})) {
     a.splits = gkv_effective_splits(ctx);
     if (a.splits > ctx->ws_splits) return GKV_ERR_WORKSPACE;   // partials would not fit the workspace as sized
     // An unsplit appending step leaves (max, sum) of every query head's softmax in the ring slot
     // of this step; the window score can then skip its own pass over the keys for them.
     a.write_stats = a.splits == 1 && k_new != nullptr;
     note_stats(ctx, step, a.write_stats != 0, workspace, K, qwin);
-    return hip_status(gkv_launch_attend_mfma(ln, ctx->dims, a));
+    return hip_status(gkv_launch_attend_mfma(ln, ctx->dims, ctx->cfg.dtype, a));
   }
   note_stats(ctx, step, false, workspace, K, qwin);
   return hip_status(gkv_launch_attend_generic(ln, ctx->dims, ctx->cfg.dtype, a));
@@ -482,7 +490,7 @@ extern "C" gkv_status gkv_redundancy_combine(gkv_ctx* ctx, const void* K, const 
   gkv_status st = check_len(ctx, len_max_host, false);
   if (st != GKV_OK) return st;
   GkvLaunch ln{ctx, GKV_K_REDUNDANCY, (hipStream_t)stream};
-  return hip_status(gkv_launch_redundancy(ln, ctx->dims, ctx->cfg.dtype, use_mfma_attend(ctx), K, d_state, step, F,
+  return hip_status(gkv_launch_redundancy(ln, ctx->dims, ctx->cfg.dtype, use_mfma_redundancy(ctx), K, d_state, step, F,
                                           lambda, tau, eps, n_recent, R_norm, F_sel));
 }
 

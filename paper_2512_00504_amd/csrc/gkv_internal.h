@@ -39,6 +39,7 @@ struct gkv_ctx {
   int32_t compact_ppt;    // 16-byte pieces per thread and chunk round of the compaction kernel: 4, 8 or 16
   int32_t reuse_stats;    // window score may reuse the softmax statistics the decode kernel recorded
   bool mfma_ok;           // bf16, d == 128, g <= 16
+  bool attend_mfma_ok;    // d == 64 or 128, g <= 16: the matrix-core decode kernel covers it
   GkvProfile* prof;
   // Host record of which ring slots hold softmax statistics written by the matrix-core decode
   // kernel: stats_step[slot] = decode step whose statistics the slot holds (-1 = none), valid for
@@ -84,7 +85,9 @@ struct AttendArgs {
   int32_t waves;         // wavefronts per workgroup of the matrix-core kernel: 4, 8 or 16
 };
 hipError_t gkv_launch_attend_generic(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
-hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a);
+hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
+// LDS of a workgroup of that kernel (bytes)
+size_t gkv_attend_mfma_lds(int esz, int d, int g, int waves);
 
 struct ScoreArgs {
   const void* qwin; const void* K; const int32_t* d_state; int32_t step; float* S;
