@@ -119,8 +119,8 @@ extern "C" gkv_status gkv_create(const gkv_config* cfg, gkv_ctx** out_ctx) {
   if (!c->stats_step) { delete c; return GKV_ERR_INVALID_ARG; }
   for (int i = 0; i < cfg->window; ++i) c->stats_step[i] = -1;
   c->stats_ws = c->stats_K = c->stats_qwin = nullptr;
-  c->mfma_ok = cfg->dtype == GKV_BF16 && d.d == 128 && d.g <= 16;
-  c->attend_mfma_ok = (d.d == 64 || d.d == 128) && d.g <= 16;
+  c->mfma_redundancy = cfg->dtype == GKV_BF16 && d.d == 128 && d.g <= 16;
+  c->mfma_shape = (d.d == 64 || d.d == 128) && d.g <= 16;
   c->prof = new (std::nothrow) GkvProfile();
   *out_ctx = c;
   return GKV_OK;
@@ -157,7 +157,7 @@ static int max_splits(const gkv_ctx* ctx) {
 }
 
 int gkv_effective_splits(const gkv_ctx* ctx) {
-  const bool mfma = ctx->attend_mfma_ok && !ctx->force_generic;
+  const bool mfma = ctx->mfma_shape && !ctx->force_generic;
   if (!mfma) return 1;
   int s = ctx->attend_splits;
   if (s <= 0) s = 1;   // measured: the cross-workgroup merge (device-scope fences over 8 XCDs) costs more than it saves, even at 4 units
@@ -182,7 +182,7 @@ static size_t ws_stats_bytes(const gkv_ctx* ctx) {
 
 // Split-K partials for `splits` workgroups per unit (none when a unit is not split).
 static size_t ws_partials_bytes(const gkv_ctx* ctx, int splits) {
-  if (!ctx->attend_mfma_ok || splits <= 1) return 0;
+  if (!ctx->mfma_shape || splits <= 1) return 0;
   const size_t units = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
   return units * splits * ctx->dims.g * (ctx->dims.d + 2) * sizeof(float);
 }
@@ -284,17 +284,14 @@ extern "C" gkv_status gkv_advance_step_base(gkv_ctx* ctx, int32_t delta, void* s
 }
 
 // ---- the five calls -----------------------------------------------------------------------------
-static bool use_mfma_redundancy(const gkv_ctx* ctx) { return ctx->mfma_ok && !ctx->force_generic; }
-// The matrix-core decode kernel moves 16-byte pieces; callers are asked for 16-byte aligned base
-// pointers, and shapes the plain kernel can also take fall back to it for others.
-static bool use_mfma_attend(const gkv_ctx* ctx, std::initializer_list<const void*> ptrs) {
-  if (!ctx->attend_mfma_ok || ctx->force_generic) return false;
+static bool use_mfma_redundancy(const gkv_ctx* ctx) { return ctx->mfma_redundancy && !ctx->force_generic; }
+// The matrix-core decode and window-score kernels move 16-byte pieces; callers are asked for 16-byte
+// aligned base pointers, and others fall back to the plain kernels.
+static bool use_mfma(const gkv_ctx* ctx, std::initializer_list<const void*> ptrs) {
+  if (!ctx->mfma_shape || ctx->force_generic) return false;
   uintptr_t bits = 0;
   for (const void* p : ptrs) bits |= (uintptr_t)p;
   return (bits & 15) == 0;
-}
-static bool use_mfma_score(const gkv_ctx* ctx) {
-  return ctx->mfma_ok && !ctx->force_generic && gkv_score_mfma_supported(ctx->dims.g, ctx->dims.w, ctx->dims.cap);
 }
 static gkv_status check_len(const gkv_ctx* ctx, int32_t len_max_host, bool appending) {
   if (len_max_host < 0) return GKV_ERR_INVALID_ARG;
@@ -340,7 +337,7 @@ extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void*
     a.copy_q = (const char*)q != (const char*)qwin + (size_t)(step % ctx->dims.w) * slot_bytes;
   }
   GkvLaunch ln{ctx, GKV_K_ATTEND, (hipStream_t)stream};
-  if (use_mfma_attend(ctx, {q, k_new, v_new, K, V, qwin, out})) {
+  if (use_mfma(ctx, {q, k_new, v_new, K, V, qwin, out})) {
     a.splits = gkv_effective_splits(ctx);
     if (a.splits > ctx->ws_splits) return GKV_ERR_WORKSPACE;   // partials would not fit the workspace as sized
     // An unsplit appending step leaves (max, sum) of every query head's softmax in the ring slot
@@ -361,12 +358,12 @@ extern "C" gkv_status gkv_score_window(gkv_ctx* ctx, const void* qwin, const voi
   if (st != GKV_OK) return st;
   ScoreArgs a{qwin, K, d_state, step, S, nullptr, nullptr, nullptr};
   GkvLaunch ln{ctx, GKV_K_SCORE, (hipStream_t)stream};
-  if (use_mfma_score(ctx)) {
+  if (use_mfma(ctx, {qwin, K})) {
     // Under the causal reading of Eq. 1 a window row's softmax runs over exactly the keys its
     // query attended to when it was decoded: if the last w decode calls on these buffers were the
     // window's steps, their recorded (max, sum) are the row statistics and one pass suffices.
     if (stats_cover_window(ctx, step, workspace, K, qwin)) a.stats = gkv_carve_workspace(ctx, workspace).stats;
-    return hip_status(gkv_launch_score_mfma(ln, ctx->dims, a));
+    return hip_status(gkv_launch_score_mfma(ln, ctx->dims, ctx->cfg.dtype, a, len_max_host));
   }
   return hip_status(gkv_launch_score_generic(ln, ctx->dims, ctx->cfg.dtype, a));
 }
@@ -411,12 +408,12 @@ extern "C" gkv_status gkv_evict(gkv_ctx* ctx, const void* qwin, void* K, void* V
   if (F == F_hist) return GKV_ERR_INVALID_ARG;
   gkv_status st = check_len(ctx, len_max_host, false);
   if (st != GKV_OK) return st;
-  if (ctx->fuse_global && use_mfma_score(ctx)) {
+  if (ctx->fuse_global && use_mfma(ctx, {qwin, K})) {
     // local and global score in one launch: the score kernel keeps S in LDS and finishes with the update
     ScoreArgs a{qwin, K, d_state, step, S, nullptr, F_hist, F};
     if (stats_cover_window(ctx, step, workspace, K, qwin)) a.stats = gkv_carve_workspace(ctx, workspace).stats;
     GkvLaunch ln{ctx, GKV_K_SCORE, (hipStream_t)stream};
-    st = hip_status(gkv_launch_score_mfma(ln, ctx->dims, a));
+    st = hip_status(gkv_launch_score_mfma(ln, ctx->dims, ctx->cfg.dtype, a, len_max_host));
     if (st != GKV_OK) return st;
   } else {
     st = gkv_score_window(ctx, qwin, K, d_state, step, len_max_host, S, workspace, stream);

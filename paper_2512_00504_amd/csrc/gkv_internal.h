@@ -38,8 +38,8 @@ struct gkv_ctx {
   int32_t fuse_select;    // gkv_evict: global score at the head of the top-k kernel (default)
   int32_t compact_ppt;    // 16-byte pieces per thread and chunk round of the compaction kernel: 4, 8 or 16
   int32_t reuse_stats;    // window score may reuse the softmax statistics the decode kernel recorded
-  bool mfma_ok;           // bf16, d == 128, g <= 16
-  bool attend_mfma_ok;    // d == 64 or 128, g <= 16: the matrix-core decode kernel covers it
+  bool mfma_shape;        // d == 64 or 128, g <= 16: the matrix-core decode and window-score kernels cover it
+  bool mfma_redundancy;   // bf16, d == 128, g <= 16: the matrix-core redundancy kernel does
   GkvProfile* prof;
   // Host record of which ring slots hold softmax statistics written by the matrix-core decode
   // kernel: stats_step[slot] = decode step whose statistics the slot holds (-1 = none), valid for
@@ -95,8 +95,7 @@ struct ScoreArgs {
   const float* F_hist; float* F_out;   // non-null F_out: also the global score (matrix-core kernel only)
 };
 hipError_t gkv_launch_score_generic(const GkvLaunch& ln, const GkvDims& dm, int dtype, const ScoreArgs& a);
-hipError_t gkv_launch_score_mfma(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a);
-bool gkv_score_mfma_supported(int g, int w, int cap);
+hipError_t gkv_launch_score_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const ScoreArgs& a, int len_max);
 
 hipError_t gkv_launch_global_update(const GkvLaunch& ln, const GkvDims& dm, const float* S,
                                     const float* F_hist, const int32_t* d_state, int32_t step, float* F_out);

@@ -1,22 +1,33 @@
-// Local score of the observation window on the matrix cores: bf16, head_dim 128,
-// w a multiple of 16, group sizes instantiated below.
+// Local score of the observation window on the matrix cores: bf16 or fp32, head_dim 64 or 128,
+// group size g <= 16, any window.
 //
-// One workgroup (NW wavefronts) per unit.  The window queries of the group's G heads are
-// staged in LDS once, in window-row order.  A wavefront takes 16-key tiles of K (one 1 KiB
-// contiguous load per 32 channels, thanks to the tiled K layout) and for every (head, block
-// of 16 window rows) computes logits^T[key, row] with 4 MFMA 16x16x32.
+// One workgroup of NW wavefronts per (unit, key share).  The window queries of the group's heads
+// are staged in LDS in blocks of 16 rows, each 1 KiB piece laid out as the matrix cores' operand
+// (lane-contiguous: no bank conflicts).  A wavefront takes KT 16-key tiles of K at a time (one
+// contiguous 1 KiB load per 16-byte chunk column, thanks to the tiled K layout) and computes
+// logits^T[key, row] against every block of rows.
 //   row statistics (max, sum of exponentials) of Eq. 1 over the keys each window row saw: under
 //           the causal reading these are what the decode kernel computed when the row's query was
 //           decoded, and it records them next to the window ring; they are taken from there, or,
 //           when the last w decode calls were not this window's, computed by a first pass over K;
-//   scores: logits of the candidates, p = 2^(z*scale*log2e - max)/sum, running max over the
-//           heads in registers (group max-reduce), then the sum over the 16 lanes that hold the
-//           window rows (Eq. 2).  Only S leaves the chip; the [g, w, l] matrix never exists in memory.
+//   scores: a row's probability is 2^(z*scale*log2e - max)/sum = 2^y with the normaliser folded
+//           into the exponent, y = z*scale*log2e - (max + log2 sum).  The max over the heads of a
+//           group is taken on y, so there is one exponential per (window row, key) instead of one
+//           per (head, window row, key); then the sum over the lanes that hold the window rows
+//           (Eq. 2).  Only S leaves the chip; the [g, w, l] matrix never exists in memory.
+//
+// Precision of y.  scale*log2e is carried as hi + lo, and so is the offset c = max + log2 sum
+// (formed in fp64 once per row): y = fma(z, hi, -c_hi) + fma(z, lo, -c_lo).  The first term is the
+// small difference of two numbers of a few tens and is rounded as a small number; neither the
+// scale's nor the offset's own rounding enters.  c is lowered by 3 (and the sum scaled back by 2^-3 at
+// the end): probabilities between 1 and 1/64, which decide the error of S, then have |y| below 4,
+// where its rounding is smallest.  Error of S against 64 bits (2-norm): 2.1e-7 at 28 layers, b = 1024,
+// as with an exponential and a reciprocal per head (3.7e-7 with c lowered by 32).
+//
+// Blocks of rows: a window of more than 8 rows takes 16 lanes per head and 16 window rows (block =
+// one head); up to 8 rows, two heads share a block.  Rows beyond the window or the group have a
+// huge offset and add nothing.
 #include "gkv_internal.h"
-
-#ifndef GKV_SCORE_NW
-#define GKV_SCORE_NW 8      // wavefronts per workgroup
-#endif
 
 namespace {
 
@@ -24,223 +35,276 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-constexpr int D = 128;
-constexpr int ROW_BYTES = D * 2;
-constexpr int TILE_BYTES = 16 * ROW_BYTES;
-constexpr int QSTR = ROW_BYTES + 16;       // padded LDS row of a staged query (bank spread)
-
 __device__ __forceinline__ u32x4 ld16(const void* p) { return *(const u32x4*)p; }
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 
-// Probabilities are 2^(z*(hi+lo) - m) / sum with hi + lo = scale * log2(e) as an unevaluated sum
-// and the exponent formed as fma(z, lo, fma(z, hi, -m)): the result of each fma is a small
-// number (the distance from the row maximum in log2 units), so its rounding costs ~1e-7
-// relative in the probability, and the rounding of the scale itself, which would act like a
-// slightly different softmax temperature, is carried by lo.  The hardware exp2 is good to 1 ulp.
-// The decode kernel forms its exponents the same way from bit-identical logits (same matrix-core
-// instruction sequence over the same operands), which is what makes its recorded (max, sum) the
-// row statistics of this kernel.
-__device__ __forceinline__ float exp2_of(float z, float m, float hi, float lo) {
-  return __builtin_amdgcn_exp2f(fmaf(z, lo, fmaf(z, hi, -m)));
-}
+#define GKV_DPP_F(v, ctrl) __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xF, 0xF, false))
 
-// A operand of tile T: lane (row r, kblock kb) gets chunk 4c+kb of key 16T+r for c = 0..3; tiled
-// tiles are lane-contiguous, row-major tiles (rows appended since the last compaction) are not.
-// Sum over the 16 lanes of a DPP row (lanes 16i .. 16i+15), left in every one of them: lanes ^1
-// and ^2 of each quad, then the other quad of each 8 (mirror within 8: the four lanes of a quad
-// are equal by then), then the other 8 (mirror within 16).  Same pairs, same order as a butterfly
-// over lane ^1, ^2, ^4, ^8, so the same bits, without four dependent trips through LDS.
-__device__ __forceinline__ float row16_sum(float v) {
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x141, 0xF, 0xF, false));   // row_half_mirror
-  v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x140, 0xF, 0xF, false));   // row_mirror
-  return v;
-}
+template <typename T, int D>
+struct Geo {
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr int ROW_BYTES = D * (int)sizeof(T);
+  static constexpr int TILE_BYTES = 16 * ROW_BYTES;
+  static constexpr int NL = ROW_BYTES / 64;      // 1 KiB operand pieces per 16 rows
+  static constexpr int RP = ROW_BYTES / 16;      // 16-byte chunks per row
+};
 
-__device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int T, int n_tiled,
-                                            int lane, int r, int kb) {
-  const bool tiled = 16 * T < n_tiled;
-  const char* p = Kh + (size_t)T * TILE_BYTES + (tiled ? lane * 16 : r * ROW_BYTES + kb * 16);
+template <typename T, int D> using Tile = u32x4[Geo<T, D>::NL];
+
+// A operand of tile t: lane (row r, kb) gets chunk 4c+kb of key 16t+r; tiled tiles are
+// lane-contiguous, row-major tiles (rows appended since the last compaction) are not.
+template <typename T, int D, bool ONCE = false>
+__device__ __forceinline__ void load_k_tile(Tile<T, D>& kA, const char* Kh, int t, int n_tiled, int lane, int r, int kb) {
+  const bool tiled = 16 * t < n_tiled;
+  const char* p = Kh + (size_t)t * Geo<T, D>::TILE_BYTES + (tiled ? lane * 16 : r * Geo<T, D>::ROW_BYTES + kb * 16);
   const int step_off = tiled ? 1024 : 64;
 #pragma unroll
-  for (int c = 0; c < 4; ++c) kA[c] = ld16(p + c * step_off);
+  for (int c = 0; c < Geo<T, D>::NL; ++c)
+    kA[c] = ONCE ? __builtin_nontemporal_load((const u32x4*)(p + c * step_off)) : ld16(p + c * step_off);
 }
 
-// Dynamic LDS: char qs[G*w*QSTR]; float rowM[G*w]; float rowZ[G*w]; float sbuf[cap]; float red[8]; and,
-// when the row statistics are computed here, float redM[NW*G*w]; float redS[NW*G*w]
+// logits[row, key] of 16 staged rows and 16 keys: lane (key = lane % 16, kb) gets rows 4 kb + e
+template <typename T, int NL>
+__device__ __forceinline__ f32x4 logits(const u32x4 (&q)[NL], const u32x4 (&kA)[NL]) {
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int c = 0; c < NL; ++c) {
+    if constexpr (sizeof(T) == 4) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(q[c][i]), __uint_as_float(kA[c][i]), acc, 0, 0, 0);
+    } else {
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(q[c]), as_bf16x8(kA[c]), acc, 0, 0, 0);
+    }
+  }
+  return acc;
+}
+
+// How a launch is cut (host): heads per block, blocks per 16 window rows, 16-row window blocks in
+// all and per staging pass, key shares per unit, bytes of the LDS regions.
+struct ScorePlan {
+  int32_t pair_heads;      // 1: window of at most 8 rows, two heads per block
+  int32_t n_blk, nt, nt_pass, ksplit;
+  int32_t use_sbuf;        // S is collected in LDS (several passes, or the fused tail wants it)
+};
+
+// Dynamic LDS: q pieces [nt_pass*n_blk][NL][1 KiB]; float row_hi[rows], row_lo[rows]; float sbuf[cap] if
+// use_sbuf; float red[8]; and, when the row statistics are computed here, float2 red_ms[NW][rows].
 // HAVE_STATS: a.stats holds (max, sum) of every window row, recorded by the decode kernel.
-template <int NW, int G, int WT, bool HAVE_STATS>
-__global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreArgs a) {
+template <typename T, int D, int NW, int KT, bool HAVE_STATS>
+__global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreArgs a, ScorePlan pl) {
+  using G = Geo<T, D>;
+  constexpr int NL = G::NL;
   a.step = resolve_step(dm, a.step);
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kb = lane >> 4;
-  const int unit = blockIdx.x, j = unit % dm.Hkv, lb = unit / dm.Hkv;
-  const int cap = dm.cap;
-  constexpr int W = 16 * WT;
-  constexpr int ROWS = G * W;
+  const int unit = blockIdx.x / pl.ksplit, share = blockIdx.x % pl.ksplit;
+  const int j = unit % dm.Hkv, lb = unit / dm.Hkv;
+  const int cap = dm.cap, w = dm.w, g = dm.g;
+  const bool pair = pl.pair_heads;
 
   const SeqState seq = load_state(a.d_state, lb);
-  const int l = compression_length(seq, a.step, dm.b, W, cap);
+  const int l = compression_length(seq, a.step, dm.b, w, cap);
   if (l == 0) return;
-  const int cc = l - W;                     // number of candidates
+  const int cc = l - w;                     // number of candidates
 
+  const int rows_pass = pl.nt_pass * pl.n_blk * 16;
   char* qs = smem_raw;
-  float* rowM = (float*)(qs + ROWS * QSTR);
-  float* rowZ = rowM + ROWS;
-  float* sbuf = rowZ + ROWS;                // S of this unit, for the fused global-score tail
-  float* red = sbuf + cap;
+  float* row_hi = (float*)(qs + (size_t)rows_pass * G::ROW_BYTES);
+  float* row_lo = row_hi + rows_pass;
+  float* sbuf = row_lo + rows_pass;
+  float* red = sbuf + (pl.use_sbuf ? cap : 0);
+  float2* red_ms = (float2*)(red + 8);
 
-  // stage the window queries: LDS row h*W + k holds head h, window row k (k-th oldest)
-  for (int x = tid; x < ROWS * 16; x += NW * 64) {
-    const int row = x >> 4, ch = x & 15;
-    const int h = row / W, k = row % W;
-    const int t_row = a.step - W + 1 + k;
-    const int slot = ((t_row % W) + W) % W;
-    *(u32x4*)(qs + row * QSTR + ch * 16) =
-        ld16((const char*)a.qwin + (((size_t)slot * dm.L * dm.B + lb) * dm.Hq + j * G + h) * (size_t)ROW_BYTES + ch * 16);
-  }
-  if constexpr (HAVE_STATS) {
-    for (int x = tid; x < ROWS; x += NW * 64) {
-      const int h = x / W, k = x % W;
-      const int t_row = a.step - W + 1 + k;
-      const int slot = ((t_row % W) + W) % W;
-      const float2 ms = a.stats[((size_t)slot * dm.L * dm.B + lb) * dm.Hq + j * G + h];
-      rowM[x] = ms.x;
-      rowZ[x] = 1.f / ms.y;
-    }
-  }
-  __syncthreads();
-
-  const char* Kh = (const char*)a.K + (size_t)unit * cap * ROW_BYTES;
+  const char* Kh = (const char*)a.K + (size_t)unit * cap * G::ROW_BYTES;
   const float s_hi = dm.scale_l2_hi, s_lo = dm.scale_l2_lo;
-  float rm[G][WT], rs[G][WT];
+  float* So = a.S + (size_t)unit * cap;
 
-  if constexpr (!HAVE_STATS) {
-    // ---- pass 1: row max and row sum over the keys visible to each window row -----------------
-    // Only the last tiles (those reaching into the window) need the causal mask; the running sum
-    // is rescaled only when some lane's maximum moved.
-    float* redM = red + 8;
-    float* redS = redM + NW * ROWS;
-    const int n_tiles = (l + 15) >> 4;
-#pragma unroll
-    for (int h = 0; h < G; ++h)
-#pragma unroll
-      for (int nt = 0; nt < WT; ++nt) { rm[h][nt] = -1e30f; rs[h][nt] = 0.f; }
+  // this workgroup's groups of KT candidate tiles
+  const int groups = (((cc + 15) >> 4) + KT - 1) / KT;
+  const int per_share = (groups + pl.ksplit - 1) / pl.ksplit;
+  const int g0 = share * per_share, g1 = min(groups, g0 + per_share);
+  if (g0 >= g1) return;                     // (cc > 0: share 0 always has work)
 
-    for (int T = wave; T < n_tiles; T += NW) {
-      u32x4 kA[4];
-      load_k_tile(kA, Kh, T, seq.n_tiled, lane, r, kb);
-      const int key_base = 16 * T + 4 * kb;
-      const bool full = 16 * T + 15 <= cc;                    // every row sees all 16 keys of this tile
+  const int n_pass = (pl.nt + pl.nt_pass - 1) / pl.nt_pass;
+  for (int pass = 0; pass < n_pass; ++pass) {
+    const int nt0 = pass * pl.nt_pass, nts = min(pl.nt_pass, pl.nt - nt0);
+    const int rows = nts * pl.n_blk * 16;
+    if (pass) __syncthreads();              // the previous pass has been read
+
+    // head and window row (k-th oldest) of staged row x, and whether there is such a row
+    auto head_of = [&](int x) { return pair ? 2 * (x >> 4) + ((x >> 3) & 1) : (x >> 4) % pl.n_blk; };
+    auto k_of = [&](int x) { return pair ? (x & 7) : 16 * (nt0 + (x >> 4) / pl.n_blk) + (x & 15); };
+    auto slot_of = [&](int k) { const int t_row = a.step - w + 1 + k; return ((t_row % w) + w) % w; };
+
+    // stage the window queries; 16 lanes take the same chunk of 16 rows, so their LDS pieces are
+    // contiguous and a wavefront covers 64 bytes of every row
+    for (int x = tid; x < rows * G::RP; x += NW * 64) {
+      const int rr = x & 15, ch = (x >> 4) % G::RP, blk = (x >> 4) / G::RP, row = blk * 16 + rr;
+      const int h = head_of(row), k = k_of(row);
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (h < g && k < w)
+        v = ld16((const char*)a.qwin + (((size_t)slot_of(k) * dm.L * dm.B + lb) * dm.Hq + j * g + h) * (size_t)G::ROW_BYTES + ch * 16);
+      *(u32x4*)(qs + (size_t)blk * G::TILE_BYTES + (ch >> 2) * 1024 + ((ch & 3) * 16 + rr) * 16) = v;
+    }
+    auto store_offset = [&](int x, float m, float s) {
+      const int h = head_of(x), k = k_of(x);
+      float hi = -INFINITY, lo = 0.f;
+      if (h < g && k < w) {
+        const double off = 3.0 - ((double)m + log2((double)s));
+        hi = (float)off;
+        lo = (float)(off - (double)hi);
+      }
+      row_hi[x] = hi;
+      row_lo[x] = lo;
+    };
+    if constexpr (HAVE_STATS) {
+      for (int x = tid; x < rows; x += NW * 64) {
+        const int h = min(head_of(x), g - 1), k = min(k_of(x), w - 1);
+        const float2 ms = a.stats[((size_t)slot_of(k) * dm.L * dm.B + lb) * dm.Hq + j * g + h];
+        store_offset(x, ms.x, ms.y);
+      }
+    }
+    __syncthreads();
+
+    auto load_q = [&](u32x4 (&q)[NL], int blk) {
 #pragma unroll
-      for (int h = 0; h < G; ++h)
+      for (int c = 0; c < NL; ++c) q[c] = *(const u32x4*)(qs + (size_t)blk * G::TILE_BYTES + c * 1024 + lane * 16);
+    };
+
+    if constexpr (!HAVE_STATS) {
+      // ---- first pass over K: row max and row sum over the keys visible to each window row -----
+      // NB blocks at a time keep their running (max, sum) in registers; only the last tiles (those
+      // reaching into the window) need the causal mask, and a running sum is rescaled only when
+      // some lane's maximum moved.
+      constexpr int NB = 4;
+      const int n_tiles = (l + 15) >> 4;
+      const int n_blocks = nts * pl.n_blk;
+      for (int b0 = 0; b0 < n_blocks; b0 += NB) {
+        float rm[NB][4], rs[NB][4];                            // this lane's keys of rows 4 kb + e
+        int last_vis[NB][4];                                   // row k sees keys [0, cc + k]
 #pragma unroll
-        for (int nt = 0; nt < WT; ++nt) {
-          const char* qrow = qs + (h * W + 16 * nt + r) * QSTR;
-          f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < NB; ++i)
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kA[c]),
-                                                          as_bf16x8(*(const u32x4*)(qrow + (4 * c + kb) * 16)),
-                                                          acc, 0, 0, 0);
-          float z[4];
+          for (int e = 0; e < 4; ++e) {
+            rm[i][e] = -1e30f; rs[i][e] = 0.f;
+            last_vis[i][e] = cc + k_of(16 * min(b0 + i, n_blocks - 1) + 4 * kb + e);
+          }
+        for (int t = wave; t < n_tiles; t += NW) {
+          u32x4 kA[NL];
+          load_k_tile<T, D>(kA, Kh, t, seq.n_tiled, lane, r, kb);
+          const int key = 16 * t + r;
+          const bool full = 16 * t + 15 <= cc;                 // every row sees all 16 keys of this tile
 #pragma unroll
-          for (int e = 0; e < 4; ++e) z[e] = acc[e];
-          if (!full) {
-            const int last_vis = cc + 16 * nt + r;            // row k sees keys [0, cc + k]
+          for (int i = 0; i < NB; ++i) {
+            u32x4 q[NL];
+            load_q(q, min(b0 + i, n_blocks - 1));
+            f32x4 z = logits<T, NL>(q, kA);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              if (!full && key > last_vis[i][e]) z[e] = -1e30f;
+              const float tm = z[e] * s_hi;
+              if (__any(tm > rm[i][e])) {
+                const float mnew = fmaxf(rm[i][e], tm);
+                rs[i][e] *= __builtin_amdgcn_exp2f(rm[i][e] - mnew);
+                rm[i][e] = mnew;
+              }
+              rs[i][e] += __builtin_amdgcn_exp2f(fmaf(z[e], s_lo, fmaf(z[e], s_hi, -rm[i][e])));
+            }
+          }
+        }
+        // the 16 lanes of a row, then (below) the wavefronts
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float m = rm[i][e];
+#pragma unroll
+            for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o));
+            float sum = rs[i][e] * __builtin_amdgcn_exp2f(rm[i][e] - m);
+#pragma unroll
+            for (int o = 1; o < 16; o <<= 1) sum += __shfl_xor(sum, o);
+            if (r == 0 && b0 + i < n_blocks) red_ms[wave * rows_pass + 16 * (b0 + i) + 4 * kb + e] = make_float2(m, sum);
+          }
+      }
+      __syncthreads();
+      for (int x = tid; x < rows; x += NW * 64) {
+        float M = red_ms[x].x;
+#pragma unroll
+        for (int wv = 1; wv < NW; ++wv) M = fmaxf(M, red_ms[wv * rows_pass + x].x);
+        float Z = 0.f;
+#pragma unroll
+        for (int wv = 0; wv < NW; ++wv) {
+          const float2 ms = red_ms[wv * rows_pass + x];
+          Z += ms.y * __builtin_amdgcn_exp2f(ms.x - M);
+        }
+        store_offset(x, M, Z);
+      }
+      __syncthreads();
+    }
+
+    // ---- scores of this share's candidates ------------------------------------------------------
+    const float mean = 0x1p-3f / (float)w;
+    u32x4 kA[KT][NL], kN[KT][NL];
+    auto load_group = [&](u32x4 (&k)[KT][NL], int p) {
+#pragma unroll
+      for (int tt = 0; tt < KT; ++tt) load_k_tile<T, D>(k[tt], Kh, p * KT + tt, seq.n_tiled, lane, r, kb);
+    };
+    if (g0 + wave < g1) load_group(kA, g0 + wave);
+    for (int p = g0 + wave; p < g1; p += NW) {
+      // the wavefront's next tiles are requested before these are worked on (clamped at the end:
+      // the same number of requests in flight on every path keeps the wait for this group short)
+      load_group(kN, min(p + NW, g1 - 1));
+      float tot[KT];
+#pragma unroll
+      for (int tt = 0; tt < KT; ++tt) tot[tt] = 0.f;
+      for (int nt = 0; nt < nts; ++nt) {
+        f32x4 ymax[KT];
+#pragma unroll
+        for (int tt = 0; tt < KT; ++tt) ymax[tt] = f32x4{-1e30f, -1e30f, -1e30f, -1e30f};
+        for (int blk = nt * pl.n_blk; blk < (nt + 1) * pl.n_blk; ++blk) {
+          u32x4 q[NL];
+          load_q(q, blk);
+          const f32x4 c_hi = *(const f32x4*)(row_hi + blk * 16 + 4 * kb);
+          const f32x4 c_lo = *(const f32x4*)(row_lo + blk * 16 + 4 * kb);
+#pragma unroll
+          for (int tt = 0; tt < KT; ++tt) {
+            // candidates are visible to every window row; keys >= cc are discarded below
+            const f32x4 z = logits<T, NL>(q, kA[tt]);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (key_base + e > last_vis) z[e] = -1e30f;
+              ymax[tt][e] = fmaxf(ymax[tt][e], fmaf(z[e], s_hi, c_hi[e]) + fmaf(z[e], s_lo, c_lo[e]));
           }
-          const float tm = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])) * s_hi;
-          if (__any(tm > rm[h][nt])) {
-            const float mnew = fmaxf(rm[h][nt], tm);
-            rs[h][nt] *= __builtin_amdgcn_exp2f(rm[h][nt] - mnew);
-            rm[h][nt] = mnew;
-          }
-          rs[h][nt] += (exp2_of(z[0], rm[h][nt], s_hi, s_lo) + exp2_of(z[1], rm[h][nt], s_hi, s_lo)) +
-                       (exp2_of(z[2], rm[h][nt], s_hi, s_lo) + exp2_of(z[3], rm[h][nt], s_hi, s_lo));
         }
-    }
-    // merge the 4 lanes of a row, then the wavefronts
 #pragma unroll
-    for (int h = 0; h < G; ++h)
+        for (int tt = 0; tt < KT; ++tt) {
+          if (pair) {                                            // rows 8 .. 15 are the block's other head
 #pragma unroll
-      for (int nt = 0; nt < WT; ++nt) {
-        float m = rm[h][nt];
-        m = fmaxf(m, __shfl_xor(m, 16));
-        m = fmaxf(m, __shfl_xor(m, 32));
-        float s = rs[h][nt] * __builtin_amdgcn_exp2f(rm[h][nt] - m);
-        s += __shfl_xor(s, 16);
-        s += __shfl_xor(s, 32);
-        if (kb == 0) {
-          redM[wave * ROWS + h * W + 16 * nt + r] = m;
-          redS[wave * ROWS + h * W + 16 * nt + r] = s;
+            for (int e = 0; e < 4; ++e) ymax[tt][e] = fmaxf(ymax[tt][e], __shfl_xor(ymax[tt][e], 32));
+          }
+          tot[tt] += (__builtin_amdgcn_exp2f(ymax[tt][0]) + __builtin_amdgcn_exp2f(ymax[tt][1])) +
+                     (__builtin_amdgcn_exp2f(ymax[tt][2]) + __builtin_amdgcn_exp2f(ymax[tt][3]));
         }
       }
-    __syncthreads();
-    for (int x = tid; x < ROWS; x += NW * 64) {
-      float M = redM[x];
 #pragma unroll
-      for (int wv = 1; wv < NW; ++wv) M = fmaxf(M, redM[wv * ROWS + x]);
-      float Z = 0.f;
-#pragma unroll
-      for (int wv = 0; wv < NW; ++wv) Z += redS[wv * ROWS + x] * __builtin_amdgcn_exp2f(redM[wv * ROWS + x] - M);
-      rowM[x] = M;
-      rowZ[x] = 1.f / Z;                                       // one division per row, not per logit
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int h = 0; h < G; ++h)
-#pragma unroll
-    for (int nt = 0; nt < WT; ++nt) {
-      rm[h][nt] = rowM[h * W + 16 * nt + r];
-      rs[h][nt] = rowZ[h * W + 16 * nt + r];
-    }
-
-  // ---- probabilities of the candidates, max over heads, mean over window rows ---------------
-  float* So = a.S + (size_t)unit * cap;
-  const int cand_tiles = (cc + 15) >> 4;
-  const float wf = (float)W;
-  u32x4 kA[4], kN[4];
-  if (wave < cand_tiles) load_k_tile(kA, Kh, wave, seq.n_tiled, lane, r, kb);
-  for (int T = wave; T < cand_tiles; T += NW) {
-    // the wavefront's next tile is requested before this one is worked on (clamped at the end:
-    // the same number of requests in flight on every path keeps the wait for this tile short)
-    load_k_tile(kN, Kh, min(T + NW, cand_tiles - 1), seq.n_tiled, lane, r, kb);
-    f32x4 tot = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int nt = 0; nt < WT; ++nt) {
-      f32x4 amax = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int h = 0; h < G; ++h) {
-        const char* qrow = qs + (h * W + 16 * nt + r) * QSTR;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kA[c]),
-                                                        as_bf16x8(*(const u32x4*)(qrow + (4 * c + kb) * 16)),
-                                                        acc, 0, 0, 0);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          // candidates are visible to every window row; keys >= cc are discarded below
-          const float p = exp2_of(acc[e], rm[h][nt], s_hi, s_lo) * rs[h][nt];
-          amax[e] = fmaxf(amax[e], p);
+      for (int tt = 0; tt < KT; ++tt) {
+        float sv = tot[tt] + __shfl_xor(tot[tt], 16);
+        if (!pair) sv += __shfl_xor(sv, 32);
+        const int key = 16 * (p * KT + tt) + r;
+        if (kb == 0 && key < cc) {
+          sv *= mean;
+          if (pass) sv += sbuf[key];                           // this lane's own value of the pass before
+          if (pl.use_sbuf) sbuf[key] = sv;
+          if (pass == n_pass - 1) So[key] = sv;
         }
       }
-      tot += amax;
-    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float v = row16_sum(tot[e]);
-      const int key = 16 * T + 4 * kb + e;
-      if (r == 0 && key < cc) { const float sv = v / wf; So[key] = sv; sbuf[key] = sv; }
-    }
+      for (int tt = 0; tt < KT; ++tt)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) kA[c] = kN[c];
+        for (int c = 0; c < NL; ++c) kA[tt][c] = kN[tt][c];
+    }
   }
 
   // ---- optional tail: global score of the candidates (Section 4), S still in LDS ---------------
@@ -266,33 +330,208 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
   }
 }
 
-template <int G, int WT>
-hipError_t launch(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a) {
-  constexpr int NW = GKV_SCORE_NW;
-  constexpr int ROWS = G * 16 * WT;
-  const int units = dm.L * dm.B * dm.Hkv;
-  if (a.stats) {
-    const size_t shmem = (size_t)ROWS * QSTR + sizeof(float) * (2 * ROWS + dm.cap + 8);
-    return gkv_launch(ln, score_mfma_kernel<NW, G, WT, true>, dim3(units), dim3(NW * 64), shmem, dm, a);
+// The common case: bf16, recorded statistics, and so few blocks of window rows (NT sixteens of NB)
+// that a wavefront can hold all of their operands in registers.  The kernel above reads 1 KiB of
+// LDS per MFMA at one key tile per wavefront, which makes the CU's 128 B a cycle its bound; here LDS
+// only hands the queries round once.  K^T Q instead of Q^T K: a lane keeps one row's offset per
+// block (two registers, not eight), and the 16 window rows end up across the lanes.
+// Bound: HBM at several hundred units (28 layers, batch 16, b = 1024: 516 MB of K in 119 us; with one
+// block's arithmetic left of seven 97 us, staging and launch alone 18 us), arithmetic and the start
+// of a workgroup (state, queries, first tile: three dependent trips to memory) below.  Per launch
+// against a kernel that kept the queries in LDS and took an exponential per head and logit: 256 units
+// of 1088 rows, g = 5, w = 32 25.8 -> 20.0 us; 4608 such units 347 -> 307 us; 448 units of 640 rows,
+// g = 7, w = 16 20.8 -> 19.2 us; 4 units 9.7 -> 7.6 us.  Against the plain kernel: bf16 D = 64, 128 units
+// 2780 -> 7.7 us; fp32 D = 128, 32 units 3490 -> 20.5 us (kernel above, bound by fp32 MFMAs).
+// Dynamic LDS: q pieces [NT*NB][NL][1 KiB]; float2 row_c[16*NT*NB].
+template <int D, int NW, int NB, int NT, bool ONCE>
+__global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, ScoreArgs a, int pair, int ksplit) {
+  using T = uint16_t;
+  using G = Geo<T, D>;
+  constexpr int NL = G::NL;
+  a.step = resolve_step(dm, a.step);
+  extern __shared__ __attribute__((aligned(16))) char qs[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, kb = lane >> 4;
+  const int unit = blockIdx.x / ksplit, share = blockIdx.x % ksplit;
+  const int j = unit % dm.Hkv, lb = unit / dm.Hkv;
+  const int cap = dm.cap, w = dm.w, g = dm.g;
+  float2* row_c = (float2*)(qs + (size_t)NT * NB * G::TILE_BYTES);
+
+  // Requests that do not depend on the state record go out first: the queries, straight to LDS
+  // (wavefront `wave` fetches pieces wave, wave + NW, ...; rows beyond the window or the group repeat
+  // a valid one, their offset drops them), and the statistics, one row per thread.
+  auto row_src = [&](int nt, int i, int row, int& h, int& k) {
+    h = pair ? 2 * i + (row >> 3) : i;
+    k = pair ? (row & 7) : 16 * nt + row;
+    const bool valid = h < g && k < w;
+    h = min(h, g - 1); k = min(k, w - 1);
+    return valid;
+  };
+  const int t_first = a.step - w + 1;
+  int slot0 = t_first % w;
+  slot0 = slot0 < 0 ? slot0 + w : slot0;                 // slot of window row 0; row k sits in slot0 + k, wrapped
+  auto ring_row = [&](int h, int k) {
+    int slot = slot0 + k;
+    slot = slot >= w ? slot - w : slot;
+    return ((size_t)slot * dm.L * dm.B + lb) * dm.Hq + j * g + h;
+  };
+  for (int x = wave; x < NT * NB * NL; x += NW) {
+    const int blk = x / NL, c = x % NL;
+    int h, k;
+    row_src(blk / NB, blk % NB, r, h, k);
+    const char* src = (const char*)a.qwin + ring_row(h, k) * G::ROW_BYTES + (4 * c + kb) * 16;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                     (__attribute__((address_space(3))) void*)(qs + x * 1024), 16, 0, 0);
   }
-  const size_t shmem = (size_t)ROWS * QSTR + sizeof(float) * (2 * ROWS + dm.cap + 8 + 2 * NW * ROWS);
-  return gkv_launch(ln, score_mfma_kernel<NW, G, WT, false>, dim3(units), dim3(NW * 64), shmem, dm, a);
+  static_assert(NT * NB * 16 <= NW * 64, "a row per thread");
+  float2 ms = make_float2(0.f, 1.f);
+  bool row_valid = false;
+  if (tid < NT * NB * 16) {
+    int h, k;
+    row_valid = row_src((tid >> 4) / NB, (tid >> 4) % NB, tid & 15, h, k);
+    ms = a.stats[ring_row(h, k)];
+  }
+
+  const SeqState seq = load_state(a.d_state, lb);
+  const int l = compression_length(seq, a.step, dm.b, w, cap);
+  const int cc = l - w;                     // number of candidates
+  const int tiles = l == 0 ? 0 : (cc + 15) >> 4;
+  const int per_share = (tiles + ksplit - 1) / ksplit;
+  const int g0 = share * per_share, g1 = min(tiles, g0 + per_share);
+  const char* Kh = (const char*)a.K + (size_t)unit * cap * G::ROW_BYTES;
+  Tile<T, D> kA, kN;
+  if (g0 + wave < g1) load_k_tile<T, D, ONCE>(kA, Kh, g0 + wave, seq.n_tiled, lane, r, kb);
+  if (tid < NT * NB * 16) {
+    const double off = 3.0 - ((double)ms.x + log2((double)ms.y));
+    const float hi = (float)off;
+    row_c[tid] = row_valid ? make_float2(hi, (float)(off - (double)hi)) : make_float2(-INFINITY, 0.f);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the queries are in LDS
+  __syncthreads();
+  if (g0 >= g1) return;
+  float c_hi[NT * NB], c_lo[NT * NB];
+#pragma unroll
+  for (int b = 0; b < NT * NB; ++b) {
+    const float2 c = row_c[16 * b + r];
+    c_hi[b] = c.x; c_lo[b] = c.y;
+  }
+  u32x4 q[NT * NB][NL];
+#pragma unroll
+  for (int b = 0; b < NT * NB; ++b)
+#pragma unroll
+    for (int c = 0; c < NL; ++c) q[b][c] = *(const u32x4*)(qs + (b * NL + c) * 1024 + lane * 16);
+
+  const float s_hi = dm.scale_l2_hi, s_lo = dm.scale_l2_lo;
+  const float mean = 0x1p-3f / (float)w;
+  float* So = a.S + (size_t)unit * cap;
+  for (int t = g0 + wave; t < g1; t += NW) {
+    load_k_tile<T, D, ONCE>(kN, Kh, min(t + NW, g1 - 1), seq.n_tiled, lane, r, kb);
+    f32x4 tot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      f32x4 ymax = {-1e30f, -1e30f, -1e30f, -1e30f};
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int b = nt * NB + i;
+        const f32x4 z = logits<T, NL>(kA, q[b]);           // lane (row r, kb): keys 4 kb + e
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          ymax[e] = fmaxf(ymax[e], fmaf(z[e], s_hi, c_hi[b]) + fmaf(z[e], s_lo, c_lo[b]));
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float y = ymax[e];
+        if (pair) y = fmaxf(y, GKV_DPP_F(y, 0x128));       // row_ror:8: the block's other head
+        tot[e] += __builtin_amdgcn_exp2f(y);
+      }
+    }
+    // Sum of tot[e] over the 16 lanes of a quarter (over 8 of them with two heads in a block: both
+    // halves hold the same then): two exchange-and-add steps leave value e = r % 4 of a quad in each
+    // lane, rotations by 4 and 8 add the quads.
+    const bool odd = r & 1, upper = r & 2;
+    float p01 = odd ? tot[1] : tot[0], x01 = odd ? tot[0] : tot[1];
+    float p23 = odd ? tot[3] : tot[2], x23 = odd ? tot[2] : tot[3];
+    p01 += GKV_DPP_F(x01, 0xB1);                           // quad_perm [1,0,3,2]
+    p23 += GKV_DPP_F(x23, 0xB1);
+    float sv = upper ? p23 : p01, xs = upper ? p01 : p23;
+    sv += GKV_DPP_F(xs, 0x4E);                             // quad_perm [2,3,0,1]
+    sv += GKV_DPP_F(sv, 0x124);                            // row_ror:4
+    if (!pair) sv += GKV_DPP_F(sv, 0x128);                 // row_ror:8
+    const int key = 16 * t + 4 * kb + r;
+    if (r < 4 && key < cc) So[key] = sv * mean;
+#pragma unroll
+    for (int c = 0; c < NL; ++c) kA[c] = kN[c];
+  }
+}
+
+template <int D, int NB, int NT>
+hipError_t launch_regs(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a, int len_max, bool pair) {
+  constexpr int NW = 4;
+  const int units = dm.L * dm.B * dm.Hkv;
+  // Two workgroups of 4 wavefronts fit a CU at these register counts: fewer than 512 units are cut into
+  // key shares, down to one tile per wavefront (4 units of 640 rows: 9.7 us whole, 7.6 us in shares).
+  const int tiles = (len_max + 15) / 16, most = (tiles + NW - 1) / NW;
+  int ksplit = 512 / units;
+  ksplit = ksplit < 1 ? 1 : (ksplit > most ? (most < 1 ? 1 : most) : ksplit);
+  // K beyond the 256 MiB memory-side cache is read with non-temporal loads: right after a decode step
+  // 80 -> 67 us at 280 MB of K (1792 units), 134 -> 113 us at 504 MB, 305 -> 285 us at 1.2 GB; at 70 and
+  // 140 MB there is no difference then, and a second reader of the same K finds it cached.
+  const bool once = (size_t)units * len_max * Geo<uint16_t, D>::ROW_BYTES > (size_t)256 << 20;
+  auto kern = once ? score_regs_kernel<D, NW, NB, NT, true> : score_regs_kernel<D, NW, NB, NT, false>;
+  return gkv_launch(ln, kern, dim3(units * ksplit), dim3(NW * 64),
+                    (size_t)NT * NB * (Geo<uint16_t, D>::TILE_BYTES + 128), dm, a, (int)pair, ksplit);
+}
+
+// false: no such instantiation
+template <int D>
+bool try_launch_regs(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a, int len_max, hipError_t* e) {
+  const bool pair = dm.w <= 8;
+  const int nb = pair ? (dm.g + 1) / 2 : dm.g, nt = pair ? 1 : (dm.w + 15) / 16;
+#define GKV_CASE(NB_, NT_) if (nb == NB_ && nt == NT_) { *e = launch_regs<D, NB_, NT_>(ln, dm, a, len_max, pair); return true; }
+  GKV_CASE(1, 1) GKV_CASE(2, 1) GKV_CASE(3, 1) GKV_CASE(4, 1) GKV_CASE(5, 1) GKV_CASE(6, 1) GKV_CASE(7, 1) GKV_CASE(8, 1)
+  GKV_CASE(1, 2) GKV_CASE(2, 2) GKV_CASE(3, 2) GKV_CASE(4, 2) GKV_CASE(5, 2)
+#undef GKV_CASE
+  return false;
+}
+
+template <typename T, int D, int NW, int KT>
+hipError_t launch(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a, int len_max) {
+  using G = Geo<T, D>;
+  const int units = dm.L * dm.B * dm.Hkv;
+  ScorePlan pl;
+  pl.pair_heads = dm.w <= 8;
+  pl.n_blk = pl.pair_heads ? (dm.g + 1) / 2 : dm.g;
+  pl.nt = pl.pair_heads ? 1 : (dm.w + 15) / 16;
+  const int block_bytes = pl.n_blk * G::TILE_BYTES;
+  pl.nt_pass = 72 * 1024 / block_bytes;
+  pl.nt_pass = pl.nt_pass < 1 ? 1 : (pl.nt_pass > pl.nt ? pl.nt : pl.nt_pass);
+  pl.use_sbuf = pl.nt_pass < pl.nt || a.F_out != nullptr;
+  const int groups = ((len_max + 15) / 16 + KT - 1) / KT;
+  pl.ksplit = 1;
+  if (a.F_out == nullptr) {
+    int k = 512 / units, most = (groups + NW - 1) / NW;
+    pl.ksplit = k < 1 ? 1 : (k > most ? (most < 1 ? 1 : most) : k);
+  }
+  const size_t rows = (size_t)pl.nt_pass * pl.n_blk * 16;
+  const size_t shmem = rows * G::ROW_BYTES + rows * 8 + (pl.use_sbuf ? 4 * (size_t)dm.cap : 0) + 32 +
+                       (a.stats ? 0 : NW * rows * 8);
+  auto kern = a.stats ? score_mfma_kernel<T, D, NW, KT, true> : score_mfma_kernel<T, D, NW, KT, false>;
+  if (shmem > GKV_LDS_LIMIT) {                             // beyond the default per-workgroup limit: opt in (a CU holds 160 KiB)
+    const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    if (e != hipSuccess) return e;
+  }
+  return gkv_launch(ln, kern, dim3(units * pl.ksplit), dim3(NW * 64), shmem, dm, a, pl);
 }
 
 }  // namespace
 
-bool gkv_score_mfma_supported(int g, int w, int cap) {
-  const bool g_ok = (g == 1 || g == 2 || g == 4 || g == 5 || g == 7 || g == 8);
-  if (!g_ok || (w != 16 && w != 32)) return false;
-  const size_t rows = (size_t)g * w;                      // LDS the kernel needs; 64 KiB available
-  return rows * QSTR + sizeof(float) * (2 * rows + 2 * GKV_SCORE_NW * rows + cap + 8) <= 65536;
-}
-
-hipError_t gkv_launch_score_mfma(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a) {
-  const int wt = dm.w / 16;
-#define GKV_CASE(G_)                                                        \
-  if (dm.g == G_) return wt == 1 ? launch<G_, 1>(ln, dm, a) : launch<G_, 2>(ln, dm, a);
-  GKV_CASE(1) GKV_CASE(2) GKV_CASE(4) GKV_CASE(5) GKV_CASE(7) GKV_CASE(8)
-#undef GKV_CASE
-  return hipErrorInvalidValue;
+hipError_t gkv_launch_score_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const ScoreArgs& a, int len_max) {
+  if (dtype == GKV_F32)
+    return dm.d == 64 ? launch<float, 64, 4, 2>(ln, dm, a, len_max) : launch<float, 128, 4, 1>(ln, dm, a, len_max);
+  hipError_t e;
+  if (a.stats && !a.F_out &&
+      (dm.d == 64 ? try_launch_regs<64>(ln, dm, a, len_max, &e) : try_launch_regs<128>(ln, dm, a, len_max, &e)))
+    return e;
+  return dm.d == 64 ? launch<uint16_t, 64, 4, 2>(ln, dm, a, len_max) : launch<uint16_t, 128, 4, 2>(ln, dm, a, len_max);
 }

@@ -76,3 +76,55 @@ def test_whole_path_fp32_and_head_dim_64(over):
     wl = CONFIGS["cfg2_single_layer"].with_(n_steps=320, seed=61, **over)
     st = run_parity(wl, wl.n_steps, chunk=64)
     assert st["events"] >= 5
+
+
+# ---- window score -----------------------------------------------------------------------------
+# Elementwise 1e-5 of the fp64 score (plus 1e-30 absolute), the bound of the whole-path tests: fp32
+# sums of up to 128 products and one exponential.
+@pytest.mark.parametrize("dtype,d,g,w,params", [
+    ("bf16", 128, 7, 16, None),                       # two row pairs of tiles, one block per head
+    ("bf16", 128, 16, 32, None),                      # queries beyond one staging pass
+    ("bf16", 128, 3, 8, None), ("bf16", 128, 4, 5, None),     # two heads share a block, odd and even groups
+    ("bf16", 64, 1, 1, None), ("bf16", 64, 5, 33, None),      # a window row count just past a block
+    ("f32", 128, 7, 16, None), ("f32", 128, 16, 24, None),    # two staging passes of 128 KiB
+    ("f32", 64, 2, 8, None), ("f32", 64, 16, 40, None),
+    ("bf16", 128, 5, 32, {"evict_fuse_global": 1}),
+])
+@pytest.mark.parametrize("reuse", [1, 0])
+def test_window_score_at_tile_edges(dtype, d, g, w, params, reuse):
+    cap, b = 320, 48
+    lens = [b + 1, b + 15, b + 17, 100, 127, 160, 161, cap]           # rows the compression sees
+    lens = [max(n, w + 1) for n in lens]
+    B = len(lens)
+    st = DecodeState(make_config(1, B, g, 1, d, b, w, max(w, 8), cap, dtype), params=params)
+    st.ctx.set_param("score_reuse_stats", reuse)
+    gen = torch.Generator().manual_seed(100 * g + w)
+    rnd = lambda *s: torch.randn(*s, generator=gen).to(st.K.dtype)
+    K, q = 2 * rnd(1, B, 1, cap, d), rnd(w, 1, B, g, d)
+    n_tiled = [(n - w) // 32 * 16 for n in lens]                        # some of the candidate tiles are row-major
+    t0 = 7
+    for i, n in enumerate(lens):
+        Ki = K[0, i].clone(); Ki[:, n - w:] = float("nan")             # the window's rows come from the decode calls
+        st.K[0, i] = k_rows_to_cache(Ki, n_tiled[i]).cuda()
+    st.d_state.copy_(torch.tensor([[[n - w, t0, 0, m] for n, m in zip(lens, n_tiled)]], dtype=torch.int32))
+    for k in range(w):
+        kn = torch.stack([K[0, i, :, n - w + k] for i, n in enumerate(lens)])[None].contiguous()
+        st.ctx.attend_decode(q[k].cuda(), kn.cuda(), kn.cuda(), st.K, st.V, st.pos, t0 + k, st.qwin, st.d_state,
+                             cap - w + k, st.out, st.workspace)
+    t = t0 + w - 1
+    st.len_host = cap
+    st.S.fill_(-3.0)
+    if params:                                                            # the fused tail is only reached through gkv_evict
+        st.ctx.evict(st.qwin, st.K, st.V, st.F_hist, st.pos, st.d_state, t, cap, st.S, st.F, st.keep_idx, st.workspace)
+    else:
+        st.score_window(t)
+    S = st.S.double().cpu().numpy()
+    for i, n in enumerate(lens):
+        A = O.window_probs(q[:, 0, i].permute(1, 0, 2).double().numpy(), K[0, i].double().numpy(), n)
+        ref = O.local_score(A, 1)[:, : n - w]
+        err = np.abs(S[0, i, :, : n - w] - ref)
+        assert (err <= 1e-5 * ref + 1e-30).all(), (n, (err / (ref + 1e-300)).max())
+        assert (S[0, i, :, n - w:] == -3.0).all()
+        if params:
+            F = O.global_score(ref, np.zeros_like(ref), 0, 0.8, "max")
+            np.testing.assert_allclose(st.F[0, i, :, : n - w].double().cpu().numpy(), F, rtol=1e-5, atol=1e-30)
