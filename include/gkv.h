@@ -110,7 +110,8 @@ const char* gkv_status_string(gkv_status st);
 
 /* Bytes of device workspace the calls below need for this context with the tuning knobs as they
  * are now; the context remembers the "attend_splits" value the size covers, and
- * gkv_attend_decode returns GKV_ERR_WORKSPACE if the knob was raised afterwards. */
+ * gkv_attend_decode returns GKV_ERR_WORKSPACE if the knob was raised afterwards.  Calls that may
+ * overlap in time need a workspace each: it holds counters and partial results of the call. */
 gkv_status gkv_workspace_bytes(gkv_ctx* ctx, size_t* out_bytes);
 /* Enqueues a fill kernel that zeroes the workspace's counters (one per unit, used when a
  * unit's attention is split over several workgroups; one per (layer, sequence), used by the
@@ -129,9 +130,10 @@ gkv_status gkv_cache_bytes(const gkv_config* cfg, int32_t rows, int32_t score_el
 int64_t gkv_k_offset(const gkv_config* cfg, int32_t row, int32_t channel, int32_t n_tiled);
 
 /* Tuning knobs (host only): "attend_splits" (workgroups per unit in the matrix-core
- * attend kernel; 0 = default = 1; set it before gkv_workspace_bytes), "attend_tile" (16 or 32 keys per wavefront iteration of
+ * attend kernel; 0 = default: the library cuts long units of launches with few of them; set it before
+ * gkv_workspace_bytes), "attend_tile" (16 or 32 keys per wavefront iteration of
  * the matrix-core attend kernel), "attend_waves" (4, 8 or 16 wavefronts per workgroup of that
- * kernel; 0 = default: 8 for launches of at most 256 units, else 4), "force_generic" (1 = use the plain vector-ALU
+ * kernel; 0 = default: 4 or 8, by the number and length of the units), "force_generic" (1 = use the plain vector-ALU
  * kernels even where matrix-core kernels exist), "compact_ppt" (4, 8 or 16: 16-byte pieces
  * a thread of the compaction kernel keeps in flight per round), "score_reuse_stats" (0 = the
  * window score always computes its rows' softmax statistics itself instead of reusing the

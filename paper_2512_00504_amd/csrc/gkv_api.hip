@@ -108,6 +108,7 @@ extern "C" gkv_status gkv_create(const gkv_config* cfg, gkv_ctx** out_ctx) {
   c->esz = cfg->dtype == GKV_F32 ? 4 : 2;
   c->attend_splits = 0;
   c->ws_splits = 1;
+  c->ws_auto_splits = 1;
   c->attend_tile = 16;
   c->force_generic = 0;
   c->reuse_stats = 1;
@@ -156,24 +157,53 @@ static int max_splits(const gkv_ctx* ctx) {
   return m < 1 ? 1 : (m > 64 ? 64 : m);
 }
 
-int gkv_effective_splits(const gkv_ctx* ctx) {
-  const bool mfma = ctx->mfma_shape && !ctx->force_generic;
-  if (!mfma) return 1;
-  int s = ctx->attend_splits;
-  if (s <= 0) s = 1;   // measured: the cross-workgroup merge (device-scope fences over 8 XCDs) costs more than it saves, even at 4 units
+// Workgroups per unit asked for with "attend_splits" (1: not asked for).
+static int explicit_splits(const gkv_ctx* ctx) {
+  if (!ctx->mfma_shape || ctx->force_generic || ctx->attend_splits <= 1) return 1;
   const int m = max_splits(ctx);
-  return s > m ? m : s;
+  return ctx->attend_splits > m ? m : ctx->attend_splits;
 }
 
-// Wavefronts per workgroup of the matrix-core attend kernel.  A unit is one workgroup on one CU,
-// and a CU pulls only so many bytes per cycle: launches that leave most CUs idle finish sooner
-// with 8 wavefronts per unit (measured: 4 to 128 units, 8-16% faster); from a few hundred units
-// on 4 and 8 are equal, and 4 keeps the LDS merge small.
-static int gkv_attend_waves(const gkv_ctx* ctx) {
-  auto fits = [&](int waves) { return gkv_attend_mfma_lds(ctx->esz, ctx->dims.d, ctx->dims.g, waves) <= 65000; };
-  if (ctx->attend_waves > 0) return fits(ctx->attend_waves) ? ctx->attend_waves : 4;
-  const int64_t units = (int64_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
-  return (units <= 256 && fits(8) && ctx->attend_tile == 16) ? 8 : 4;
+// How the matrix-core decode kernel cuts a launch: wavefronts per workgroup, workgroups per unit at
+// most, and the slices a workgroup takes at least (0: every unit is cut into all of them).  Depends
+// on the configuration alone, so the same call gives the same bits whatever bound of the length the
+// caller passes.
+//
+// A CU with one workgroup of 8 wavefronts pulls about 75 GB/s (one 8 KiB slice per wavefront and trip
+// to memory), so up to 128 units leave most of the HBM rate unused.  Cut into workgroups of at least
+// 8 slices, up to 256 of them (bf16, d = 128, us per launch, unsplit with 8 wavefronts -> cut):
+//   4 units x 577 rows 8.5 -> 7.5, x 2113 21.0 -> 9.0, x 3900 31.2 -> 9.8; 32 x 1100 13.9 -> 10.2;
+//   64 x 1100 15.9 -> 12.3, x 3900 39.6 -> 24.3; 128 x 3900 48.4 -> 42.4, and with lengths from 470 to 3900
+//   44.5 -> 30.0 (the longest unit alone on its CU bounds an unsplit launch).
+// 2 or 3 pieces of a short unit cost more than they bring (128 x 577 12.3 -> 12.7), and from 256 units
+// on the chip is full anyway (256 x 577 17.0 -> 17.8, 512 x 1100 47.2 -> 49.6).
+// Long pieces take 8 wavefronts (48 slices and more: 128 ragged units 34.6 with 4, 30.0 with 8).  Unsplit,
+// 8 wavefronts serve up to 256 units (128 x 577 14.2 -> 12.3) and more than 512 units of 64 slices
+// (896 x 2113 167 -> 163, ragged to 3900 232 -> 211; 4608 x 1057 399 -> 392); in between 4 do
+// (512 x 2113 90.7 against 92.8).  fp32 at d = 128 has 16 KiB slices and stays at 4 (256 x 528 26.5, with
+// 8 27.7 us).
+struct AttendPlan { int waves, splits, iters; };
+
+static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
+  const GkvDims& d = ctx->dims;
+  auto fits = [&](int waves) { return gkv_attend_mfma_lds(ctx->esz, d.d, d.g, waves) <= 65000; };
+  const int64_t units = (int64_t)d.L * d.B * d.Hkv;
+  const int row_bytes = d.d * ctx->esz;
+  const bool wide = row_bytes > 256;                                  // 16 KiB slices
+  const int slices = (int)((int64_t)d.cap * 2 * row_bytes / 8192);    // in units of 8 KiB, at full capacity
+  AttendPlan p{4, 1, 0};
+  if (asked > 0) {
+    p.splits = explicit_splits(ctx);
+  } else {
+    int s = (int)(256 / units);
+    s = s > 16 ? 16 : s;
+    s = s > slices / 8 ? slices / 8 : s;
+    if (s >= 4 || (s >= 2 && slices >= 64)) { p.splits = s; p.iters = wide ? 4 : 8; }
+  }
+  const bool more = p.splits > 1 ? slices / p.splits >= 48 : units <= 256 || (units > 512 && slices >= 64);
+  if (more && !wide && fits(8) && ctx->attend_tile == 16) p.waves = 8;
+  if (ctx->attend_waves > 0) p.waves = fits(ctx->attend_waves) ? ctx->attend_waves : 4;
+  return p;
 }
 
 static size_t ws_stats_bytes(const gkv_ctx* ctx) {
@@ -201,11 +231,14 @@ GkvWorkspace gkv_carve_workspace(const gkv_ctx* ctx, void* base) {
 extern "C" gkv_status gkv_workspace_bytes(gkv_ctx* ctx, size_t* out_bytes) {
   if (!ctx || !out_bytes) return GKV_ERR_INVALID_ARG;
   const size_t units = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
-  // the workspace is sized for the split count in force now; the decode call refuses a larger one
-  ctx->ws_splits = gkv_effective_splits(ctx);
+  // the workspace is sized for the split counts in force now: the decode call refuses a larger one
+  // that was asked for, and does without one of its own choice
+  ctx->ws_splits = explicit_splits(ctx);
+  ctx->ws_auto_splits = ctx->mfma_shape && !ctx->force_generic ? attend_plan(ctx, 0).splits : 1;
+  const size_t automatic = ws_partials_bytes(ctx, ctx->ws_auto_splits);
   *out_bytes = gkv_align256(units * 4) + gkv_align256((size_t)ctx->dims.L * ctx->dims.B * 4) +
                gkv_align256(ws_stats_bytes(ctx)) +
-               gkv_align256(ws_partials_bytes(ctx, ctx->ws_splits)) + 256;
+               gkv_align256(automatic + ws_partials_bytes(ctx, ctx->ws_splits)) + 256;
   return GKV_OK;
 }
 
@@ -331,18 +364,23 @@ extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void*
   gkv_status st = check_len(ctx, len_max_host, k_new != nullptr);
   if (st != GKV_OK) return st;
   AttendArgs a{q, k_new, v_new, K, V, pos, step, qwin, d_state, out, gkv_carve_workspace(ctx, workspace), 1,
-               ctx->attend_tile, 1, 0, gkv_attend_waves(ctx)};
+               ctx->attend_tile, 1, 0, 4, 0};
   {
     const size_t slot_bytes = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hq * ctx->dims.d * ctx->esz;
     a.copy_q = (const char*)q != (const char*)qwin + (size_t)(step % ctx->dims.w) * slot_bytes;
   }
   GkvLaunch ln{ctx, GKV_K_ATTEND, (hipStream_t)stream};
   if (use_mfma(ctx, {q, k_new, v_new, K, V, qwin, out})) {
-    a.splits = gkv_effective_splits(ctx);
-    if (a.splits > ctx->ws_splits) return GKV_ERR_WORKSPACE;   // partials would not fit the workspace as sized
-    // An unsplit appending step leaves (max, sum) of every query head's softmax in the ring slot
+    AttendPlan plan = attend_plan(ctx, ctx->attend_splits);
+    if (ctx->attend_splits > 0) {
+      if (plan.splits > ctx->ws_splits) return GKV_ERR_WORKSPACE;   // partials would not fit the workspace as sized
+    } else if (plan.splits > ctx->ws_auto_splits) {
+      plan.splits = 1; plan.iters = 0;
+    }
+    a.waves = plan.waves; a.splits = plan.splits; a.split_iters = plan.iters;
+    // An appending step leaves (max, sum) of every query head's softmax in the ring slot
     // of this step; the window score can then skip its own pass over the keys for them.
-    a.write_stats = a.splits == 1 && k_new != nullptr;
+    a.write_stats = k_new != nullptr;
     note_stats(ctx, step, a.write_stats != 0, workspace, K, qwin);
     return hip_status(gkv_launch_attend_mfma(ln, ctx->dims, ctx->cfg.dtype, a));
   }

@@ -30,7 +30,8 @@ struct gkv_ctx {
   GkvDims dims;
   int32_t esz;            // bytes per element
   int32_t attend_splits;  // 0 = automatic
-  int32_t ws_splits;      // split count the workspace was sized for by gkv_workspace_bytes (1 = no partials)
+  int32_t ws_splits;      // "attend_splits" the workspace was sized for by gkv_workspace_bytes (1 = no partials)
+  int32_t ws_auto_splits; // the same for the library's own choice
   int32_t attend_tile;    // keys per wavefront iteration of the matrix-core attend kernel: 16 or 32
   int32_t force_generic;
   int32_t attend_waves;   // 0 = automatic
@@ -65,7 +66,6 @@ static inline size_t gkv_align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 constexpr size_t GKV_LDS_LIMIT = 65536;
 size_t gkv_max_lds_bytes(const gkv_config* cfg);
-int gkv_effective_splits(const gkv_ctx* ctx);
 GkvWorkspace gkv_carve_workspace(const gkv_ctx* ctx, void* base);
 
 // Launch record for profiling: the wrappers launch through gkv_launch() below.
@@ -83,6 +83,7 @@ struct AttendArgs {
   int32_t copy_q;   // 0 when q already is the ring slot of this step
   int32_t write_stats;   // record (max, sum) of every query head's softmax in ws.stats
   int32_t waves;         // wavefronts per workgroup of the matrix-core kernel: 4, 8 or 16
+  int32_t split_iters;   // slices a split takes at least (a unit uses as many splits as its length fills); 0 = all splits
 };
 hipError_t gkv_launch_attend_generic(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
 hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);

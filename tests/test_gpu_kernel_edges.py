@@ -128,3 +128,47 @@ def test_window_score_at_tile_edges(dtype, d, g, w, params, reuse):
         if params:
             F = O.global_score(ref, np.zeros_like(ref), 0, 0.8, "max")
             np.testing.assert_allclose(st.F[0, i, :, : n - w].double().cpu().numpy(), F, rtol=1e-5, atol=1e-30)
+
+
+# ---- units cut over several workgroups ----------------------------------------------------------
+@pytest.mark.parametrize("dtype,d,g,cap", [("bf16", 128, 7, 3936), ("bf16", 128, 16, 640), ("bf16", 64, 5, 1312), ("f32", 128, 7, 640),
+                                           ("f32", 64, 2, 1312)])
+def test_attend_cut_over_workgroups(dtype, d, g, cap):
+    # lengths around the borders of one, two and all pieces, on the same workspace call after call
+    lens = [0, 1, 127, 128, 129, 255, 256, 257, cap // 2, cap - 1]
+    st, *t = _attend_state(dtype, d, g, lens, cap, 64, seed=d)
+    for _ in range(2):
+        _check_attend(st, *t, lens, dtype, d, append=True)
+        tickets = st.workspace[: 4 * 2 * len(lens)].view(torch.int32)
+        assert int(tickets.abs().sum()) == 0                                # back at zero for the next call
+        st.len_host = max(lens)
+    # a context that never asked for the workspace's size does without the partials: same result
+    a = st.attend_decode(t[2].cuda(), t[3].cuda(), t[4].cuda(), 5).clone()
+    from paper_2512_00504_amd import Context
+    st.ctx = Context(st.cfg)
+    st.len_host = max(lens)
+    b = st.attend_decode(t[2].cuda(), t[3].cuda(), t[4].cuda(), 5)
+    tol = 1e-5 if dtype == "f32" else 2.0 ** -7
+    np.testing.assert_allclose(a.double().cpu().numpy(), b.double().cpu().numpy(), rtol=tol, atol=tol)
+
+
+def test_window_score_reuses_statistics_of_cut_units():
+    # a cut unit's (max, sum) come from the workgroup that merges it: same score as without the record
+    st, K, V, q, kn, vn = _attend_state("bf16", 128, 7, [1000, 700], 1056, 512, seed=9)
+    st.ctx = type(st.ctx)(make_config(1, 2, 14, 2, 128, 512, 16, 96, 1056, "bf16"))
+    st.cfg = st.ctx.cfg
+    st.workspace = torch.zeros(st.ctx.workspace_bytes(), dtype=torch.uint8, device="cuda")
+    st.ctx.workspace_init(st.workspace)
+    st.qwin = torch.zeros(16, 1, 2, 14, 128, dtype=torch.bfloat16, device="cuda")
+    st.K.nan_to_num_(); st.V.nan_to_num_()
+    for k in range(16):
+        st.ctx.attend_decode((q * (1 + k / 16)).cuda(), kn.cuda(), vn.cuda(), st.K, st.V, st.pos, 5 + k, st.qwin, st.d_state,
+                             1000 + k, st.out, st.workspace)
+    S = []
+    for reuse in (1, 0):
+        st.ctx.set_param("score_reuse_stats", reuse)
+        st.S.zero_()
+        st.ctx.score_window(st.qwin, st.K, st.d_state, 20, 1016, st.S, st.workspace)
+        S.append(st.S.double().cpu().numpy().copy())
+    assert (S[0][..., :700] > 0).all()
+    np.testing.assert_allclose(S[0], S[1], rtol=3e-6, atol=1e-30)
