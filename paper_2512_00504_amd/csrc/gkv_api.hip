@@ -76,6 +76,7 @@ size_t gkv_max_lds_bytes(const gkv_config* c) {
   upd(4 * (3 * cap + d));                                           // score_generic: at least one wavefront's float[3 cap + d]
   upd(4 * cap + 1024 + 64);                                         // select_topk: keys[cap] + histogram + scan scratch
   upd(16 * cap + 32);                                               // redundancy: double cs[cap], red[4], inv[cap]
+  if ((d == 64 || d == 128) && g <= 16) upd(16 * cap + 128);        // its 64-bit matrix-core form: a double per wavefront
   // (the matrix-core redundancy kernel adds a 32 KiB ring of row tiles and asks for the larger
   // per-workgroup allowance itself when that passes 64 KiB: at the largest capacity it needs 96 KiB
   // of the 160 KiB a compute unit holds)
@@ -525,7 +526,8 @@ extern "C" gkv_status gkv_redundancy_combine(gkv_ctx* ctx, const void* K, const 
   gkv_status st = check_len(ctx, len_max_host, false);
   if (st != GKV_OK) return st;
   GkvLaunch ln{ctx, GKV_K_REDUNDANCY, (hipStream_t)stream};
-  return hip_status(gkv_launch_redundancy(ln, ctx->dims, ctx->cfg.dtype, use_mfma_redundancy(ctx), K, d_state, step, F,
+  return hip_status(gkv_launch_redundancy(ln, ctx->dims, ctx->cfg.dtype, use_mfma_redundancy(ctx),
+                                          !ctx->mfma_redundancy && use_mfma(ctx, {K}), K, d_state, step, F,
                                           lambda, tau, eps, n_recent, R_norm, F_sel));
 }
 

@@ -107,7 +107,7 @@ hipError_t gkv_launch_update_and_select(const GkvLaunch& ln, const GkvDims& dm, 
 hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, const int32_t* keep_idx,
                               const float* F, void* K, void* V, float* F_hist, int32_t* pos,
                               int32_t* d_state, int32_t step, int32_t* state_ticket);
-hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dtype, bool mfma, const void* K,
+hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dtype, bool mfma, bool f64_mfma, const void* K,
                                  const int32_t* d_state, int32_t step, const float* F, float lambda, float tau,
                                  float eps, int32_t n_recent, float* R_norm, float* F_sel);
 hipError_t gkv_launch_pool_scores(const GkvLaunch& ln, const GkvDims& dm, const float* F, const int32_t* d_state,

@@ -31,27 +31,33 @@ struct RedArgs {
 // threshold decision may legitimately differ from fp64, and it averages out in the sums.  Sums
 // run in fp32 over a lane's four entries of a tile pair and in fp64 from there on; exp(col - max)
 // is fp64.  The plain kernel does everything in fp64.
+template <int NW>
 __device__ __forceinline__ double block_max_f64(double v, double* red) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
-  return fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
+  double m = red[0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) m = fmax(m, red[i]);
+  return m;
 }
 
-// Shared tail: R' from the column sums in LDS, then the combination.  cs[j] valid for j < l.
+// Shared tail: R' from the column sums in LDS, then the combination.  cs[j] valid for j < l; `red`
+// holds a double per wavefront.
+template <int NW>
 __device__ __forceinline__ void finish_unit(const GkvDims& dm, const RedArgs& a, int unit, int l,
                                             const double* cs, double* red) {
   const int tid = threadIdx.x;
   double mx = -1e300;
-  for (int j = tid; j < l; j += 256) mx = fmax(mx, cs[j]);
-  mx = block_max_f64(mx, red);
+  for (int j = tid; j < l; j += NW * 64) mx = fmax(mx, cs[j]);
+  mx = block_max_f64<NW>(mx, red);
   float* Ru = a.R_norm + (size_t)unit * dm.cap;
   float* Fs = a.F_sel + (size_t)unit * dm.cap;
   const float* Fu = a.F + (size_t)unit * dm.cap;
   const int c = l - dm.w;
-  for (int j = tid; j < l; j += 256) {
+  for (int j = tid; j < l; j += NW * 64) {
     const float rn = (float)exp(cs[j] - mx);
     Ru[j] = rn;
     if (j < c) Fs[j] = a.lambda * Fu[j] - (1.f - a.lambda) * rn;
@@ -99,7 +105,7 @@ __global__ __launch_bounds__(256) void redundancy_generic_kernel(GkvDims dm, Red
     cs[j] = col;
   }
   __syncthreads();
-  finish_unit(dm, a, unit, l, cs, red);
+  finish_unit<4>(dm, a, unit, l, cs, red);
 }
 
 // ---- bf16, d = 128, matrix cores ----------------------------------------------------------------
@@ -127,7 +133,7 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int 
 // wavefront fetches one tile of the next group while all four work on the current group, stores it
 // into the other half of a two-group ring, and one barrier per group hands the ring over.
 //
-// Dynamic LDS: double cs[cap]; double red[4]; double inv[cap]; then the ring, 2 groups x 4 tiles x 4 KiB
+// Dynamic LDS: double cs[cap]; double red[4]; double inv[cap]; float inv_f[cap]; then the ring, 2 groups x 4 tiles x 4 KiB
 constexpr int RED_NC = 5;
 
 // Sum over the 16 lanes of a DPP row (lanes 16i .. 16i+15), left in every one of them: lanes ^1
@@ -159,7 +165,8 @@ __global__ __launch_bounds__(256) void redundancy_mfma_kernel(GkvDims dm, RedArg
   double* cs = (double*)smem;
   double* red = cs + dm.cap;
   double* inv = red + 4;
-  char* ring = (char*)(inv + dm.cap);
+  float* inv_f = (float*)(inv + dm.cap);                 // the same rounded to fp32
+  char* ring = (char*)(inv_f + dm.cap);
   const SeqState st = load_state(a.d_state, lb);
   const int l = compression_length(st, a.step, dm.b, dm.w, dm.cap);
   if (l == 0) return;
@@ -210,7 +217,11 @@ __global__ __launch_bounds__(256) void redundancy_mfma_kernel(GkvDims dm, RedArg
     }
   }
   __syncthreads();
-  for (int n = tid; n < n_tiles * 16; n += 256) inv[n] = n < l ? 1.0 / (sqrt(inv[n]) + (double)a.eps) : 0.0;
+  for (int n = tid; n < n_tiles * 16; n += 256) {
+    const double v = n < l ? 1.0 / (sqrt(inv[n]) + (double)a.eps) : 0.0;
+    inv[n] = v;
+    inv_f[n] = (float)v;
+  }
   __syncthreads();
 
   const int first_recent = l - a.n_recent;
@@ -247,21 +258,25 @@ __global__ __launch_bounds__(256) void redundancy_mfma_kernel(GkvDims dm, RedArg
     // the entries with k == j are left out (wavefront-uniform, so the common case carries no test).
     auto row_tile = [&](const u32x4 (&rowA)[4], int T, auto diag) {
       constexpr bool DIAG = decltype(diag)::value;
-      const int k0 = 16 * T + 4 * kb;
-      float invk[4];                                     // rows >= l have inv = 0: their terms are 0 or fail the test
+      const f32x4 invk = *(const f32x4*)(inv_f + 16 * T + 4 * kb);   // rows >= l have inv = 0: their terms are 0 or fail the test
+      // all column tiles' products first, chunk by chunk: the chains of dependent MFMAs of one tile
+      // would each wait for their own results (with the norms read as fp32: 154 -> 150 us at 896 units
+      // of l = 640)
+      f32x4 acc[NC];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) invk[e] = (float)inv[k0 + e];
+      for (int cc = 0; cc < NC; ++cc) acc[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int cc = 0; cc < NC; ++cc)
+          acc[cc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rowA[c]),
+                                                            __builtin_bit_cast(bf16x8, colA[cc][c]), acc[cc], 0, 0, 0);
 #pragma unroll
       for (int cc = 0; cc < NC; ++cc) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rowA[c]),
-                                                        __builtin_bit_cast(bf16x8, colA[cc][c]), acc, 0, 0, 0);
         float part = 0.f;                               // the four entries of this lane, then fp64 across tiles
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float t = acc[e] * invk[e];
+          const float t = acc[cc][e] * invk[e];
           bool pass = t >= thr[cc];
           if (DIAG) pass = pass && !(T == J0 + cc && 4 * kb + e == r);
           part += pass ? t : 0.f;
@@ -303,25 +318,120 @@ __global__ __launch_bounds__(256) void redundancy_mfma_kernel(GkvDims dm, RedArg
     }
   }
   __syncthreads();
-  finish_unit(dm, a, unit, l, cs, red);
+  finish_unit<4>(dm, a, unit, l, cs, red);
+}
+
+// ---- fp32 at d = 64 or 128 and bf16 at d = 64: the matrix cores in 64 bits --------------------------
+// These shapes compute cosines and sums in fp64, here with MFMAs 16x16x4 of doubles: 2048 flops in 64
+// cycles per SIMD; a unit is one workgroup of NW wavefronts, 16, or 8 at 512-byte rows, whose three
+// tiles need the registers.  A wavefront takes column tiles wave, wave + NW, ... and walks all row tiles
+// for each; a 16-byte piece holds EPC channels of its key and feeds EPC MFMAs, the i-th with channel i
+// of every lane's piece.  The result lane (j = lane%16, kb) holds rows 4 i + kb in element i (not
+// 4 kb + i as the 32-bit results do).
+// Bound: fp64 matrix rate.  Against the plain kernel (a thread per column, scalar loads), per launch:
+// l = 332, fp32 d = 128, 16 units 13.6 ms -> 145 us; fp32 d = 64, 32 units 6.6 ms -> 77 us; bf16 d = 64, 32
+// units 6.0 ms -> 82 us; l = 152, 4 units 1.35 ms -> 23 us.
+template <typename T, int D, int NW>
+__global__ __launch_bounds__(NW * 64) void redundancy_f64_kernel(GkvDims dm, RedArgs a) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  constexpr int ROW_B = D * (int)sizeof(T), NL = ROW_B / 64, EPC = Elem<T>::EPC;
+  a.step = resolve_step(dm, a.step);
+  extern __shared__ double smem[];
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, kb = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int unit = blockIdx.x, lb = unit / dm.Hkv;
+  double* cs = smem;
+  double* inv = cs + dm.cap;
+  double* red = inv + dm.cap;
+  const SeqState st = load_state(a.d_state, lb);
+  const int l = compression_length(st, a.step, dm.b, dm.w, dm.cap);
+  if (l == 0) return;
+  const char* Kh = (const char*)a.K + (size_t)unit * dm.cap * ROW_B;
+  const int n_tiles = (l + 15) >> 4;
+  auto load_tile = [&](u32x4 (&k)[NL], int t) {
+    const bool tiled = 16 * t < st.n_tiled;
+    const char* p = Kh + (size_t)t * 16 * ROW_B + (tiled ? lane * 16 : r * ROW_B + kb * 16);
+    const int step_off = tiled ? 1024 : 64;
+#pragma unroll
+    for (int c = 0; c < NL; ++c) k[c] = *(const u32x4*)(p + c * step_off);
+  };
+  auto elem = [](const u32x4& v, int i) {
+    if constexpr (sizeof(T) == 4) return (double)__uint_as_float(v[i]);
+    else return (double)__uint_as_float((i & 1) ? (v[i >> 1] & 0xffff0000u) : (v[i >> 1] << 16));
+  };
+
+  // row norms: a tile per wavefront, the 4 lanes of a row each sum their pieces
+  for (int t = wave; t < n_tiles; t += NW) {
+    u32x4 k[NL];
+    load_tile(k, t);
+    double ss = 0.0;
+#pragma unroll
+    for (int c = 0; c < NL; ++c)
+#pragma unroll
+      for (int i = 0; i < EPC; ++i) { const double x = elem(k[c], i); ss = fma(x, x, ss); }
+    ss += __shfl_xor(ss, 16);
+    ss += __shfl_xor(ss, 32);
+    const int n = 16 * t + r;
+    if (kb == 0) inv[n] = n < l ? 1.0 / (sqrt(ss) + (double)a.eps) : 0.0;
+  }
+  __syncthreads();
+
+  const int first_recent = l - a.n_recent;
+  const double tau = (double)a.tau;
+  for (int J = wave; J < n_tiles; J += NW) {
+    u32x4 kj[NL], cur[NL], nxt[NL];
+    load_tile(kj, J);
+    load_tile(cur, 0);
+    const int j = 16 * J + r;
+    const double inv_j = inv[j];
+    double col = 0.0;
+    for (int t = 0; t < n_tiles; ++t) {
+      load_tile(nxt, min(t + 1, n_tiles - 1));
+      f64x4 dot = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int c = 0; c < NL; ++c)
+#pragma unroll
+        for (int i = 0; i < EPC; ++i)
+          dot = __builtin_amdgcn_mfma_f64_16x16x4f64(elem(cur[c], i), elem(kj[c], i), dot, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = 16 * t + 4 * i + kb;
+        const double cv = dot[i] * inv[k] * inv_j;
+        if (cv >= tau && k < l && k != j) col += cv;
+      }
+#pragma unroll
+      for (int c = 0; c < NL; ++c) cur[c] = nxt[c];
+    }
+    col += __shfl_xor(col, 16);
+    col += __shfl_xor(col, 32);
+    if (kb == 0 && j < l) cs[j] = j < first_recent ? col : 0.0;
+  }
+  __syncthreads();
+  finish_unit<NW>(dm, a, unit, l, cs, red);
 }
 
 }  // namespace
 
-hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dtype, bool mfma, const void* K,
+hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dtype, bool mfma, bool f64_mfma, const void* K,
                                  const int32_t* d_state, int32_t step, const float* F, float lambda, float tau,
                                  float eps, int32_t n_recent, float* R_norm, float* F_sel) {
   RedArgs a{K, d_state, step, F, lambda, tau, eps, n_recent, R_norm, F_sel};
   const int units = dm.L * dm.B * dm.Hkv;
   const size_t shmem = sizeof(double) * (2 * (size_t)dm.cap + 4);
   if (mfma) {
-    const size_t with_ring = shmem + RED_RING_BYTES;
+    const size_t with_ring = shmem + sizeof(float) * (size_t)dm.cap + RED_RING_BYTES;
     if (with_ring > 64 * 1024) {                         // beyond the default per-workgroup limit: opt in (a CU holds 160 KiB)
       const hipError_t e = hipFuncSetAttribute((const void*)redundancy_mfma_kernel,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)with_ring);
       if (e != hipSuccess) return e;
     }
     return gkv_launch(ln, redundancy_mfma_kernel, dim3(units), dim3(256), with_ring, dm, a);
+  }
+  if (f64_mfma) {
+    const bool wide = dtype == GKV_F32 && dm.d == 128;
+    auto kern = wide ? redundancy_f64_kernel<float, 128, 8>
+                     : dtype == GKV_F32 ? redundancy_f64_kernel<float, 64, 16> : redundancy_f64_kernel<uint16_t, 64, 16>;
+    return gkv_launch(ln, kern, dim3(units), dim3(wide ? 512 : 1024), sizeof(double) * (2 * (size_t)dm.cap + 16), dm, a);
   }
   if (dtype == GKV_F32)
     return gkv_launch(ln, redundancy_generic_kernel<float>, dim3(units), dim3(256), shmem, dm, a);

@@ -172,3 +172,41 @@ def test_window_score_reuses_statistics_of_cut_units():
         S.append(st.S.double().cpu().numpy().copy())
     assert (S[0][..., :700] > 0).all()
     np.testing.assert_allclose(S[0], S[1], rtol=3e-6, atol=1e-30)
+
+
+# ---- redundancy score in 64 bits ----------------------------------------------------------------
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+def test_redundancy_at_tile_edges(dtype, d):
+    # lengths around tile borders and one tile per wavefront, both K formats; keys in clusters so that
+    # cosines lie on both sides of the threshold and none near it
+    w, b, cap = 4, 20, 288
+    lens = [21, 31, 32, 33, 128, 129, 257, 288]
+    B = len(lens)
+    st = DecodeState(make_config(1, B, 2, 1, d, b, w, 8, cap, dtype))
+    rng = np.random.default_rng(d)
+    centres = rng.standard_normal((6, d))
+    K = torch.full((1, B, 1, cap, d), float("nan")).to(st.K.dtype)
+    for i, n in enumerate(lens):
+        rows = centres[rng.integers(0, 6, n)] + 0.05 * rng.standard_normal((n, d))
+        K[0, i, 0, :n] = torch.from_numpy(rows * rng.uniform(0.5, 20, (n, 1))).to(st.K.dtype)
+    n_tiled = [0, 16, 32, 16, 64, 128, 240, 288]
+    for i in range(B):
+        st.K[0, i] = k_rows_to_cache(K[0, i], n_tiled[i]).cuda()
+    st.d_state.copy_(torch.tensor([[[n - w, 100 - w, 0, min(m, (n - w) // 16 * 16)] for n, m in zip(lens, n_tiled)]],
+                                  dtype=torch.int32))
+    for i in range(B):                                     # the record's tiled prefix, not more
+        m = min(n_tiled[i], (lens[i] - w) // 16 * 16)
+        st.K[0, i] = k_rows_to_cache(K[0, i], m).cuda()
+    st.F.fill_(0.25)
+    st.len_host = cap
+    st.redundancy_combine(99, lam=0.5, tau=0.5, n_recent=3)
+    R, Fs = st.R.double().cpu().numpy(), st.F_sel.double().cpu().numpy()
+    for i, n in enumerate(lens):
+        Kn = K[0, i, :, :n].double().numpy()
+        Rr = O.redundancy_score(Kn, n, tau=0.5, n_recent=3, eps=float(np.float32(1e-8)))
+        ref = Rr / Rr.max()
+        # R' = exp(col - max): fp64 sums give fp32 rounding, the fp32 products of bf16 d = 128 the stated 1e-5
+        rel = 1e-5 if (dtype, d) == ("bf16", 128) else 1e-6
+        np.testing.assert_allclose(R[0, i, 0, :n], ref[0], rtol=rel, atol=1e-40)
+        # half of R' <= 1 with that error, and two roundings of numbers below 1
+        np.testing.assert_allclose(Fs[0, i, 0, : n - w], 0.125 - 0.5 * ref[0, : n - w], rtol=0, atol=0.5 * rel + 1.2e-7)
