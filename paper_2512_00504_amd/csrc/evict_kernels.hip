@@ -159,7 +159,9 @@ __global__ __launch_bounds__(256) void select_topk_kernel(GkvDims dm, const floa
 }
 
 // ---- compaction ----------------------------------------------------------------------------
-// grid (units, 2): y = 0 moves K, pos and F_hist; y = 1 moves V (row-major).
+// grid (units, 2 * shares): the first `shares` workgroups of a unit move K (the very first one
+// F_hist too), the others V (row-major); a share is a range of 16-byte columns of every row, so the
+// shares of a unit have nothing to do with each other.
 // K source rows are in tiled format below the old N_TILED and row-major above; destination rows
 // are tiled below nt_new = b rounded down to 16 and row-major above.  Both formats keep a
 // 16-row tile inside the same tile-sized block, so the stable-compaction argument still holds
@@ -168,21 +170,23 @@ __global__ __launch_bounds__(256) void select_topk_kernel(GkvDims dm, const floa
 // source index and sources ascend, so a chunk's stores (which stay inside the chunk's tiles)
 // never touch a row that a later chunk still has to read.
 // State record: every workgroup reads it at its start.  With a ticket array (one counter per
-// (layer, sequence), zero between launches) the workgroup that finishes last among the 2 h_kv of
-// a (layer, sequence) knows that all of them have read the record, and rewrites it; no data
+// (layer, sequence), zero between launches) the workgroup that finishes last among the 2 h_kv shares
+// of a (layer, sequence) knows that all of them have read the record, and rewrites it; no data
 // depends on that write inside this launch, so the counter needs no fence.  Without a ticket
 // array a separate launch rewrites the records.
 // Dynamic LDS: int keep_s[b - w]: the kept indices, read from memory once.
-template <int PPT>
-__global__ __launch_bounds__(256) void compact_kernel(GkvDims dm, int esz, const int32_t* __restrict__ keep_idx,
-                                                      const float* __restrict__ F, void* K, void* V,
-                                                      float* __restrict__ F_hist, int32_t* pos,
-                                                      int32_t* d_state, int step, int32_t* state_ticket) {
+template <int PPT, int NT>
+__global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, const int32_t* __restrict__ keep_idx,
+                                                     const float* __restrict__ F, void* K, void* V,
+                                                     float* __restrict__ F_hist, int32_t* pos,
+                                                     int32_t* d_state, int step, int32_t* state_ticket, int shares) {
   step = resolve_step(dm, step);
   extern __shared__ int keep_s[];
-  __shared__ int red_i[4];
+  __shared__ int red_i[NT / 64];
   const int unit = blockIdx.x, lb = unit / dm.Hkv, tid = threadIdx.x;
-  const bool isK = blockIdx.y == 0;
+  const bool isK = (int)blockIdx.y < shares;
+  const int share = isK ? blockIdx.y : blockIdx.y - shares;
+  const bool isPos = blockIdx.y == 0;
   const SeqState st = load_state(d_state, lb);
   const int l = compression_length(st, step, dm.b, dm.w, dm.cap);
   if (l == 0) return;
@@ -192,7 +196,7 @@ __global__ __launch_bounds__(256) void compact_kernel(GkvDims dm, int esz, const
 
   // first destination row whose source differs from it; a K format change rewrites everything
   int first = k;
-  for (int n = tid; n < k; n += 256) {
+  for (int n = tid; n < k; n += NT) {
     const int src = Ku[n];
     keep_s[n] = src;
     if (src != n && first == k) first = n;       // ascending per thread: the first hit is its minimum
@@ -200,14 +204,16 @@ __global__ __launch_bounds__(256) void compact_kernel(GkvDims dm, int esz, const
   for (int o = 32; o > 0; o >>= 1) first = min(first, __shfl_xor(first, o));
   if ((tid & 63) == 0) red_i[tid >> 6] = first;
   __syncthreads();
-  first = min(min(red_i[0], red_i[1]), min(red_i[2], red_i[3]));
+  first = red_i[0];
+#pragma unroll
+  for (int i = 1; i < NT / 64; ++i) first = min(first, red_i[i]);
   if (isK && nt_old != nt_new) first = 0;
   first &= ~15;                                  // chunks start on tile boundaries
 
-  if (isK) {
+  if (isPos) {
     float* Hu = F_hist + (size_t)unit * dm.cap;
     const float* Fu = F + (size_t)unit * dm.cap;
-    for (int n = tid; n < k; n += 256) {
+    for (int n = tid; n < k; n += NT) {
       int src = keep_s[n];
       src = src < 0 ? 0 : (src >= c ? c - 1 : src);
       Hu[n] = Fu[src];
@@ -215,48 +221,58 @@ __global__ __launch_bounds__(256) void compact_kernel(GkvDims dm, int esz, const
   }
 
   const int NP = dm.d * esz / 16;                // 16-byte pieces per row
-  int R = (256 * PPT) / NP;                      // rows per chunk: whole tiles, at most one per thread
-  R = (R > 256 ? 256 : R) & ~15;
+  const bool whole = isK && nt_old != nt_new;
+  const int PS = whole ? NP : NP / shares, p0 = whole ? 0 : share * PS;   // this share's
+  const int end = whole && share > 0 ? 0 : b;
+  constexpr int PR = NT > 256 ? 2 : 1;           // positions per thread and chunk
+  int R = (NT * PPT) / PS;                       // rows per chunk: whole tiles, at most PR per thread
+  R = (R > PR * NT ? PR * NT : R) & ~15;
   u32x4* base = (u32x4*)((char*)(isK ? K : V) + (size_t)unit * dm.cap * dm.d * esz);
   int32_t* pu = pos + (size_t)unit * dm.cap;
 
   // Every load of a round is issued before the first wait: the addresses are computed without
   // branches (pieces beyond the chunk or the budget read row 0, always in bounds, and are not
   // stored), so the PPT 16-byte loads of a thread are in flight together.
-  for (int r0 = first; r0 < b; r0 += R) {
+  auto source = [&](int row) {
+    int src = keep_s[row < k ? row : 0];
+    src = row < k ? src : c + (row - k);
+    return src < 0 ? 0 : (src >= l ? l - 1 : src);
+  };
+  for (int r0 = first; r0 < end; r0 += R) {
     u32x4 buf[PPT];
     int dst[PPT];
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
-      const int x = tid + 256 * i;
-      const int rr = x / NP, piece = x % NP;
+      const int x = tid + NT * i;
+      const int rr = x / PS, piece = p0 + x % PS;
       const int row = r0 + rr;
       const bool valid = rr < R && row < b;
-      int src = keep_s[row < k ? row : 0];
-      src = row < k ? src : c + (row - k);
-      src = src < 0 ? 0 : (src >= l ? l - 1 : src);
-      src = valid ? src : 0;
+      const int src = valid ? source(row) : 0;
       const int so = (isK && src < nt_old) ? ((src >> 4) * 16 * NP + piece * 16 + (src & 15)) : (src * NP + piece);
       const int d_o = (isK && row < nt_new) ? ((row >> 4) * 16 * NP + piece * 16 + (row & 15)) : (row * NP + piece);
       dst[i] = valid ? d_o : -1;
       buf[i] = base[so];
     }
-    const int prow = r0 + tid;
-    const bool do_pos = isK && tid < R && prow < b;
-    int psrc = keep_s[prow < k ? prow : 0];
-    psrc = prow < k ? psrc : c + (prow - k);
-    psrc = psrc < 0 ? 0 : (psrc >= l ? l - 1 : psrc);
-    const int pos_val = pu[do_pos ? psrc : 0];
+    int pos_val[PR];
+#pragma unroll
+    for (int i = 0; i < PR; ++i) {
+      const int rr = tid + NT * i;
+      pos_val[i] = pu[isPos && rr < R && r0 + rr < b ? source(r0 + rr) : 0];
+    }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PPT; ++i)
       if (dst[i] >= 0) base[dst[i]] = buf[i];
-    if (do_pos) pu[prow] = pos_val;
+#pragma unroll
+    for (int i = 0; i < PR; ++i) {
+      const int rr = tid + NT * i;
+      if (isPos && rr < R && r0 + rr < b) pu[r0 + rr] = pos_val[i];
+    }
   }
   // (every wavefront of this workgroup passed the barrier above after reading the record)
   if (state_ticket != nullptr && tid == 0) {
     const int done = atomicAdd(&state_ticket[lb], 1);
-    if (done == 2 * dm.Hkv - 1) {
+    if (done == 2 * shares * dm.Hkv - 1) {
       state_ticket[lb] = 0;
       *(int4*)(d_state + 4 * (size_t)lb) = make_int4(dm.b, step + 1, dm.b - dm.w, dm.b & ~15);
     }
@@ -371,9 +387,22 @@ hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, c
   const int units = dm.L * dm.B * dm.Hkv;
   const size_t shmem = sizeof(int) * (size_t)(dm.b - dm.w);
   const int ppt = ln.ctx ? ln.ctx->compact_ppt : 8;
-  auto kern = ppt == 16 ? compact_kernel<16> : ppt == 8 ? compact_kernel<8> : compact_kernel<4>;
-  hipError_t e = gkv_launch(ln, kern, dim3(units, 2), dim3(256), shmem, dm, esz, keep_idx, F, K, V,
-                            F_hist, pos, d_state, (int)step, state_ticket);
+  // A workgroup moves its rows in rounds of 32 KiB whose loads wait for the stores before them, about
+  // 2.5 us each; with few units the chip is empty meanwhile, so the rows' columns are shared out (at
+  // least 64 bytes of a row each) and a share of more than 64 KiB gets 1024 threads, four times the round.
+  // us per launch, whole -> shared (bf16, d = 128): 4 units of b = 512 13.8 -> 7.2, of b = 2048 43.1 -> 10.8;
+  // 32 of 2048 47.1 -> 14.6; 64 of 1024 26.1 -> 14.2; 128 of 2048 61.4 -> 51.2.  From 256 units on both
+  // cost more than they bring (256 of 2048 120.3 -> 120.9 in halves, 126 with 1024 threads).
+  const int row_bytes = dm.d * esz, pieces = row_bytes / 16;
+  const int64_t unit_bytes = (int64_t)dm.b * row_bytes;
+  int shares = units <= 16 || (units <= 32 && unit_bytes >= 256 * 1024) ? 4 : units <= 128 ? 2 : 1;
+  while (shares > 1 && (pieces % shares != 0 || pieces / shares < 4)) shares >>= 1;
+  const bool wide = ppt == 8 && units <= 128 && unit_bytes / shares > 64 * 1024;
+  auto kern = ppt == 16 ? compact_kernel<16, 256> : ppt == 4 ? compact_kernel<4, 256>
+            : wide ? compact_kernel<8, 1024> : compact_kernel<8, 256>;
+  const int threads = wide ? 1024 : 256;
+  hipError_t e = gkv_launch(ln, kern, dim3(units, 2 * shares), dim3(threads), shmem, dm, esz, keep_idx, F, K, V,
+                            F_hist, pos, d_state, (int)step, state_ticket, shares);
   if (e != hipSuccess || state_ticket != nullptr) return e;
   const int nlb = dm.L * dm.B;
   GkvLaunch plain{ln.ctx, -1, ln.stream};

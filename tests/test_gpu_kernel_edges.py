@@ -7,7 +7,7 @@ import torch
 from gkv_traces import CONFIGS
 from oracle import gkv_oracle as O
 from paper_2512_00504_amd import make_config
-from paper_2512_00504_amd.state import DecodeState, k_rows_to_cache
+from paper_2512_00504_amd.state import DecodeState, k_cache_to_rows, k_rows_to_cache
 
 from parity_utils import run_parity
 
@@ -210,3 +210,50 @@ def test_redundancy_at_tile_edges(dtype, d):
         np.testing.assert_allclose(R[0, i, 0, :n], ref[0], rtol=rel, atol=1e-40)
         # half of R' <= 1 with that error, and two roundings of numbers below 1
         np.testing.assert_allclose(Fs[0, i, 0, : n - w], 0.125 - 0.5 * ref[0, : n - w], rtol=0, atol=0.5 * rel + 1.2e-7)
+
+
+# ---- compaction in column shares ----------------------------------------------------------------
+@pytest.mark.parametrize("dtype,d,B,b", [
+    ("bf16", 128, 2, 512),        # 4 units: 4 shares, 256 threads
+    ("bf16", 128, 2, 2000),       # 4 shares, 1024 threads, b not a multiple of 16 per round
+    ("bf16", 128, 16, 1037),      # 32 units: 4 shares, 1024 threads, ragged b
+    ("bf16", 128, 33, 600),       # 66 units: 2 shares of 76 KiB, 1024 threads
+    ("bf16", 64, 3, 300),         # 128-byte rows: 2 shares
+    ("bf16", 96, 3, 300),         # 12 pieces a row: 2 shares (3 would be too narrow in 4)
+    ("bf16", 32, 3, 300),         # 64-byte rows: whole
+    ("f32", 128, 4, 700),
+    ("bf16", 128, 65, 512),       # 130 units: whole
+])
+def test_compaction_in_shares(dtype, d, B, b):
+    w, s_ = 16, 96
+    cap = (b + s_ + 31) // 32 * 32
+    st = DecodeState(make_config(1, B, 2, 2, d, b, w, s_, cap, dtype))
+    gen = torch.Generator().manual_seed(b)
+    K, V = torch.randn(st.K.shape, generator=gen).to(st.K.dtype), torch.randn(st.K.shape, generator=gen).to(st.K.dtype)
+    pos = torch.randint(0, 1 << 30, (1, B, 2, cap), generator=gen, dtype=torch.int32)
+    F = torch.rand(1, B, 2, cap, generator=gen)
+    k, nt = b - w, b // 16 * 16
+    for turn in range(2):                          # twice on the same workspace: the counters are back at zero
+        l = b + 1 + (s_ - 1) * turn                # one row to drop, then s
+        c = l - w
+        keep = torch.rand(B, 2, c, generator=gen).topk(k, dim=-1).indices.sort(dim=-1).values
+        tiled = [(l - w) // 16 * 16 if i % 2 else 32 for i in range(B)]      # never past the recorded length
+        st.K.copy_(torch.stack([k_rows_to_cache(K[0, i], tiled[i]) for i in range(B)])[None])
+        st.V.copy_(V); st.pos.copy_(pos); st.F.copy_(F); st.keep_idx.copy_(keep.int()[None])
+        st.d_state.copy_(torch.tensor([[[l - w, 200, 0, n] for n in tiled]], dtype=torch.int32))
+        if turn == 0:                              # sequence 0 is at the budget: left alone
+            st.d_state[0, 0, 0] = b - w
+        K0, pos0 = st.K[0, 0].clone(), st.pos[0, 0].clone()
+        st.ctx.compact(st.keep_idx, st.F, st.K, st.V, st.F_hist, st.pos, st.d_state, 200 + w - 1, st.workspace)
+        src = torch.cat([keep, torch.arange(c, l).expand(B, 2, w)], dim=-1)
+        first = 1 if turn == 0 else 0
+        if turn == 0:
+            assert torch.equal(st.K[0, 0], K0) and torch.equal(st.pos[0, 0], pos0)
+            assert st.d_state[0, 0].tolist() == [b - w, 200, 0, 32]
+        assert (st.d_state[0, first:].cpu() == torch.tensor([b, 200 + w, k, nt], dtype=torch.int32)).all()
+        rows = src[..., None].expand(B, 2, b, d)
+        Kr = k_cache_to_rows(st.K[0], nt)[:, :, :b].cpu()
+        assert torch.equal(Kr[first:], K[0].gather(2, rows)[first:])
+        assert torch.equal(st.V[0, :, :, :b].cpu()[first:], V[0].gather(2, rows)[first:])
+        assert torch.equal(st.pos[0, :, :, :b].cpu()[first:], pos[0].gather(2, src)[first:])
+        assert torch.equal(st.F_hist[0, :, :, :k].cpu()[first:], F[0].gather(2, keep)[first:])
