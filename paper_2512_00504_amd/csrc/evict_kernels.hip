@@ -31,137 +31,148 @@ __device__ __forceinline__ uint32_t sortable_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// ---- global score (Section 4) --------------------------------------------------------------
-__global__ __launch_bounds__(256) void global_update_kernel(GkvDims dm, const float* __restrict__ S,
-                                                            const float* __restrict__ F_hist,
-                                                            const int32_t* __restrict__ d_state, int step,
-                                                            float* __restrict__ F_out) {
+// ---- global score (Section 4) and top-(b-w) ---------------------------------------------------
+// One kernel for gkv_global_update (UPDATE), gkv_select_topk (SELECT) and the two in one launch.
+// A thread keeps its entries n = tid + 256 i, i < IPT, in registers.  They are requested before the
+// state record has arrived (every index is below the capacity), so a workgroup makes one trip to
+// memory, not three.
+//
+// UPDATE: Sn = S / max S, combined with alpha * F_hist, written to F_out (and selected on).
+//
+// SELECT: the k-th largest key bit pair by bit pair from the top.  With p the bits found so far, the
+// entries at or above p + 1, p + 2, p + 3 (in the pair's place) are counted with ballots, one word per
+// wavefront and count passes through LDS, and the largest of them with at least k entries becomes p;
+// as soon as exactly k entries are at or above p these are the kept ones, which scores that are
+// not tied reach after half the pairs.  Otherwise p ends as the k-th largest key, and of the entries
+// equal to it the first k - (number above it) by index are kept.  Kept entries are numbered by ballots
+// and one scan over the (i, wavefront) counts: ascending indices, always k of them, whatever the bits.
+// Bound: latency (launch, one memory trip, about ten barriers).  Against a radix select by 8-bit
+// digits in LDS (four passes of atomics, scans and six barriers), update and selection in one launch: 4 units
+// of 624 candidates 8.5 -> 7.0 us, 256 of 1056 12.7 -> 9.5; the update alone, which read S twice, 11.1 -> 7.0
+// at 1792 units of 1136; the selection alone there 15.5 -> 16.0 (by then the counting is the bound).
+template <int IPT, bool UPDATE, bool SELECT>
+__global__ __launch_bounds__(256) void score_topk_kernel(GkvDims dm, const float* __restrict__ S,
+                                                         const float* __restrict__ F_hist,
+                                                         const int32_t* __restrict__ d_state, int step,
+                                                         float* __restrict__ F_out, int32_t* __restrict__ keep_idx) {
   step = resolve_step(dm, step);
   __shared__ float red[8];
-  const int unit = blockIdx.x, lb = unit / dm.Hkv, tid = threadIdx.x;
+  __shared__ int cnt[2][4][4];
+  __shared__ int scan_s[64];
+  const int unit = blockIdx.x, lb = unit / dm.Hkv, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* Su = S + (size_t)unit * dm.cap;
+  float f[IPT], h[UPDATE ? IPT : 1];
+#pragma unroll
+  for (int i = 0; i < IPT; ++i) {
+    const int n = tid + 256 * i;
+    f[i] = n < dm.cap ? Su[n] : 0.f;
+    if constexpr (UPDATE) h[i] = n < dm.cap ? F_hist[(size_t)unit * dm.cap + n] : 0.f;
+  }
   const SeqState st = load_state(d_state, lb);
   const int l = compression_length(st, step, dm.b, dm.w, dm.cap);
   if (l == 0) return;
   const int c = l - dm.w;
-  int n_hist = st.n_hist;
-  n_hist = n_hist < 0 ? 0 : (n_hist > c ? c : n_hist);
-  const float* Su = S + (size_t)unit * dm.cap;
-  const float* Hu = F_hist + (size_t)unit * dm.cap;
-  float* Fu = F_out + (size_t)unit * dm.cap;
-  float mx = 0.f;
-  for (int n = tid; n < c; n += 256) mx = fmaxf(mx, Su[n]);
-  mx = block_max(mx, red);
-  for (int n = tid; n < c; n += 256) {
-    const float sn = mx > 0.f ? Su[n] / mx : 0.f;
-    float f = sn;
-    if (n < n_hist) {
-      const float h = dm.alpha * Hu[n];
-      f = dm.combine == GKV_COMBINE_MAX ? fmaxf(h, sn)
-        : dm.combine == GKV_COMBINE_AVG ? h + (1.f - dm.alpha) * sn
-                                        : h + sn;
+
+  if constexpr (UPDATE) {
+    int n_hist = st.n_hist;
+    n_hist = n_hist < 0 ? 0 : (n_hist > c ? c : n_hist);
+    float* Fu = F_out + (size_t)unit * dm.cap;
+    float mx = 0.f;
+#pragma unroll
+    for (int i = 0; i < IPT; ++i)
+      if (tid + 256 * i < c) mx = fmaxf(mx, f[i]);
+    mx = block_max(mx, red);
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+      const int n = tid + 256 * i;
+      const float sn = mx > 0.f ? f[i] / mx : 0.f;
+      f[i] = sn;
+      if (n < n_hist) {
+        const float hh = dm.alpha * h[i];
+        f[i] = dm.combine == GKV_COMBINE_MAX ? fmaxf(hh, sn)
+             : dm.combine == GKV_COMBINE_AVG ? hh + (1.f - dm.alpha) * sn
+                                             : hh + sn;
+      }
+      if (n < c) Fu[n] = f[i];
     }
-    Fu[n] = f;
+  }
+  if constexpr (SELECT) {
+    const int k = dm.b - dm.w;                   // c > k because l > b
+    uint32_t key[IPT];
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) key[i] = tid + 256 * i < c ? sortable_key(f[i]) : 0u;   // 0 is never counted below
+    uint32_t prefix = 0;
+    bool exact = false;                          // exactly k entries are at or above prefix
+    for (int pass = 15; pass >= 0 && !exact; --pass) {
+      int mine[3] = {0, 0, 0};
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const uint32_t t = prefix | ((uint32_t)(q + 1) << (2 * pass));
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) mine[q] += __popcll(__ballot(key[i] >= t));
+      }
+      int (&slot)[4][4] = cnt[pass & 1];         // two sets in turn: one barrier per pass
+      if (lane == 0) { slot[wave][0] = mine[0]; slot[wave][1] = mine[1]; slot[wave][2] = mine[2]; }
+      __syncthreads();
+      uint32_t digit = 0;
+      int got = 0;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        const int n_ge = slot[0][q] + slot[1][q] + slot[2][q] + slot[3][q];
+        if (n_ge >= k) { digit = q + 1; got = n_ge; }          // counts fall with q
+      }
+      prefix |= digit << (2 * pass);
+      exact = digit != 0 && got == k;
+    }
+    // Entries above prefix, and equal to it: counts per (i, wavefront) in index order.
+    uint64_t above[IPT], equal[IPT];
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+      const bool in = tid + 256 * i < c;
+      above[i] = __ballot(in && (exact ? key[i] >= prefix : key[i] > prefix));
+      equal[i] = __ballot(in && !exact && key[i] == prefix);
+      if (lane == 0) scan_s[4 * i + wave] = __popcll(above[i]) | (__popcll(equal[i]) << 16);
+    }
+    __syncthreads();
+    int v = lane < 4 * IPT ? scan_s[lane] : 0;   // low half: above, high half: equal (at most 4096 of each)
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(v, o);
+      if (lane >= o) v += t;
+    }
+    const int rest = k - (__shfl(v, 63) & 0xffff);             // how many of the equal ones are kept
+    int32_t* Ku = keep_idx + (size_t)unit * k;
+    const uint64_t below = (1ull << lane) - 1;
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+      const int at = 4 * i + wave - 1;
+      const int before = at < 0 ? 0 : __shfl(v, at < 0 ? 0 : at);
+      const int n_above = (before & 0xffff) + __popcll(above[i] & below);
+      const int n_equal = (before >> 16) + __popcll(equal[i] & below);
+      const bool is_above = (above[i] >> lane) & 1, is_equal = (equal[i] >> lane) & 1;
+      const int out = n_above + min(n_equal, rest);
+      if ((is_above || (is_equal && n_equal < rest)) && out < k) Ku[out] = tid + 256 * i;
+    }
   }
 }
 
-// ---- top-(b-w): exact radix select on the float bits, ties to the lower index ---------------
-// WITH_UPDATE: F points at the local score S instead, and the kernel first forms the global score
-// from it and F_hist exactly as global_update_kernel does (same expressions, same bits), writes
-// it to F_out and selects on it: one launch less per compression.
-// Dynamic LDS: uint32 keys[cap]
-template <bool WITH_UPDATE>
-__global__ __launch_bounds__(256) void select_topk_kernel(GkvDims dm, const float* __restrict__ F,
-                                                          const float* __restrict__ F_hist,
-                                                          const int32_t* __restrict__ d_state, int step,
-                                                          float* __restrict__ F_out,
-                                                          int32_t* __restrict__ keep_idx) {
-  step = resolve_step(dm, step);
-  extern __shared__ uint32_t keys[];
-  __shared__ int hist[256];
-  __shared__ int tmp[4];
-  __shared__ int sel[2];
-  const int unit = blockIdx.x, lb = unit / dm.Hkv, tid = threadIdx.x;
-  const SeqState st = load_state(d_state, lb);
-  const int l = compression_length(st, step, dm.b, dm.w, dm.cap);
-  if (l == 0) return;
-  const int c = l - dm.w;
-  const int k = dm.b - dm.w;                   // c > k because l > b
-  const float* Fu = F + (size_t)unit * dm.cap;
-  if constexpr (WITH_UPDATE) {
-    __shared__ float red[8];
-    int n_hist = st.n_hist;
-    n_hist = n_hist < 0 ? 0 : (n_hist > c ? c : n_hist);
-    const float* Hu = F_hist + (size_t)unit * dm.cap;
-    float* Fo = F_out + (size_t)unit * dm.cap;
-    float mx = 0.f;
-    for (int n = tid; n < c; n += 256) mx = fmaxf(mx, Fu[n]);
-    mx = block_max(mx, red);
-    for (int n = tid; n < c; n += 256) {
-      const float sn = mx > 0.f ? Fu[n] / mx : 0.f;
-      float f = sn;
-      if (n < n_hist) {
-        const float h = dm.alpha * Hu[n];
-        f = dm.combine == GKV_COMBINE_MAX ? fmaxf(h, sn)
-          : dm.combine == GKV_COMBINE_AVG ? h + (1.f - dm.alpha) * sn
-                                          : h + sn;
-      }
-      Fo[n] = f;
-      keys[n] = sortable_key(f);
-    }
-  } else {
-    for (int n = tid; n < c; n += 256) keys[n] = sortable_key(Fu[n]);
-  }
-
-  uint32_t prefix = 0, mask = 0;
-  int krem = k;
-  for (int pass = 3; pass >= 0; --pass) {
-    const int shift = 8 * pass;
-    hist[tid] = 0;
-    __syncthreads();                            // also orders keys[] writes before the first pass
-    for (int n = tid; n < c; n += 256) {
-      const uint32_t key = keys[n];
-      if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255u], 1);
-    }
-    __syncthreads();
-    const int v = hist[255 - tid];              // thread t looks at bin 255-t: descending bins
-    const int incl = block_inclusive_scan(v, tmp);   // entries in bins >= 255-t
-    if (incl >= krem && incl - v < krem) { sel[0] = 255 - tid; sel[1] = krem - (incl - v); }
-    __syncthreads();
-    prefix |= ((uint32_t)sel[0]) << shift;
-    mask |= 255u << shift;
-    krem = sel[1];
-    __syncthreads();
-  }
-  // prefix is now the k-th largest key; keep everything above it and the first `krem` equal to it.
-  const int per = (c + 255) / 256;
-  const int lo = tid * per, hi = min(c, lo + per);
-  int n_eq = 0;
-  for (int n = lo; n < hi; ++n) n_eq += (keys[n] == prefix);
-  int eq_before = block_inclusive_scan(n_eq, tmp) - n_eq;
-  int n_keep = 0;
-  {
-    int eq = eq_before;
-    for (int n = lo; n < hi; ++n) {
-      const uint32_t key = keys[n];
-      if (key > prefix) ++n_keep;
-      else if (key == prefix) { n_keep += (eq < krem); ++eq; }
-    }
-  }
-  int out = block_inclusive_scan(n_keep, tmp) - n_keep;
-  int32_t* Ku = keep_idx + (size_t)unit * k;
-  int eq = eq_before;
-  for (int n = lo; n < hi; ++n) {
-    const uint32_t key = keys[n];
-    bool keep = key > prefix;
-    if (key == prefix) { keep = eq < krem; ++eq; }
-    if (keep && out < k) Ku[out++] = n;
-  }
+template <bool UPDATE, bool SELECT>
+hipError_t launch_score_topk(const GkvLaunch& ln, const GkvDims& dm, const float* S, const float* F_hist,
+                             const int32_t* d_state, int32_t step, float* F_out, int32_t* keep_idx) {
+  const int per = (dm.cap + 255) / 256;                          // capacity <= 4096: at most 16
+  auto kern = per <= 1 ? score_topk_kernel<1, UPDATE, SELECT> : per <= 2 ? score_topk_kernel<2, UPDATE, SELECT>
+            : per <= 3 ? score_topk_kernel<3, UPDATE, SELECT> : per <= 5 ? score_topk_kernel<5, UPDATE, SELECT>
+            : per <= 9 ? score_topk_kernel<9, UPDATE, SELECT> : score_topk_kernel<16, UPDATE, SELECT>;
+  return gkv_launch(ln, kern, dim3(dm.L * dm.B * dm.Hkv), dim3(256), 0, dm, S, F_hist, d_state, (int)step, F_out, keep_idx);
 }
 
 // ---- compaction ----------------------------------------------------------------------------
-// grid (units, 2 * shares): the first `shares` workgroups of a unit move K (the very first one
+// grid (units, 2 * shares): the first `shares` workgroups of a unit move K (the very first one pos and
 // F_hist too), the others V (row-major); a share is a range of 16-byte columns of every row, so the
-// shares of a unit have nothing to do with each other.
+// shares of a unit have nothing to do with each other.  Not so where K changes its format (N_TILED is
+// not the new one, as in a prompt's first compression): a tile's columns then land on other columns of
+// its own rows, and the first share moves them all.
 // K source rows are in tiled format below the old N_TILED and row-major above; destination rows
 // are tiled below nt_new = b rounded down to 16 and row-major above.  Both formats keep a
 // 16-row tile inside the same tile-sized block, so the stable-compaction argument still holds
@@ -363,22 +374,17 @@ __global__ void fill_zero_kernel(int32_t* p, size_t n) {
 
 hipError_t gkv_launch_global_update(const GkvLaunch& ln, const GkvDims& dm, const float* S,
                                     const float* F_hist, const int32_t* d_state, int32_t step, float* F_out) {
-  const int units = dm.L * dm.B * dm.Hkv;
-  return gkv_launch(ln, global_update_kernel, dim3(units), dim3(256), 0, dm, S, F_hist, d_state, (int)step, F_out);
+  return launch_score_topk<true, false>(ln, dm, S, F_hist, d_state, step, F_out, nullptr);
 }
 
 hipError_t gkv_launch_select_topk(const GkvLaunch& ln, const GkvDims& dm, const float* F,
                                   const int32_t* d_state, int32_t step, int32_t* keep_idx) {
-  const int units = dm.L * dm.B * dm.Hkv;
-  return gkv_launch(ln, select_topk_kernel<false>, dim3(units), dim3(256), sizeof(uint32_t) * dm.cap, dm, F,
-                    (const float*)nullptr, d_state, (int)step, (float*)nullptr, keep_idx);
+  return launch_score_topk<false, true>(ln, dm, F, nullptr, d_state, step, nullptr, keep_idx);
 }
 
 hipError_t gkv_launch_update_and_select(const GkvLaunch& ln, const GkvDims& dm, const float* S, const float* F_hist,
                                         const int32_t* d_state, int32_t step, float* F_out, int32_t* keep_idx) {
-  const int units = dm.L * dm.B * dm.Hkv;
-  return gkv_launch(ln, select_topk_kernel<true>, dim3(units), dim3(256), sizeof(uint32_t) * dm.cap, dm, S, F_hist,
-                    d_state, (int)step, F_out, keep_idx);
+  return launch_score_topk<true, true>(ln, dm, S, F_hist, d_state, step, F_out, keep_idx);
 }
 
 hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, const int32_t* keep_idx,

@@ -74,7 +74,6 @@ size_t gkv_max_lds_bytes(const gkv_config* c) {
   size_t need = 16 * (cap + 1 + d);                                 // attend_generic: 4 wavefronts x float[cap + 1 + d]
   auto upd = [&](size_t x) { if (x > need) need = x; };
   upd(4 * (3 * cap + d));                                           // score_generic: at least one wavefront's float[3 cap + d]
-  upd(4 * cap + 1024 + 64);                                         // select_topk: keys[cap] + histogram + scan scratch
   upd(16 * cap + 32);                                               // redundancy: double cs[cap], red[4], inv[cap]
   if ((d == 64 || d == 128) && g <= 16) upd(16 * cap + 128);        // its 64-bit matrix-core form: a double per wavefront
   // (the matrix-core redundancy kernel adds a 32 KiB ring of row tiles and asks for the larger
@@ -179,7 +178,7 @@ static int explicit_splits(const gkv_ctx* ctx) {
 // 2 or 3 pieces of a short unit cost more than they bring (128 x 577 12.3 -> 12.7), and from 256 units
 // on the chip is full anyway (256 x 577 17.0 -> 17.8, 512 x 1100 47.2 -> 49.6).
 // Long pieces take 8 wavefronts (48 slices and more: 128 ragged units 34.6 with 4, 30.0 with 8).  Unsplit,
-// 8 wavefronts serve up to 256 units (128 x 577 14.2 -> 12.3) and more than 512 units of 64 slices
+// 8 wavefronts serve up to 256 units that give each a slice (128 x 577 14.2 -> 12.3; 2 x 100 4.6 -> 4.8) and more than 512 units of 64 slices
 // (896 x 2113 167 -> 163, ragged to 3900 232 -> 211; 4608 x 1057 399 -> 392); in between 4 do
 // (512 x 2113 90.7 against 92.8).  fp32 at d = 128 has 16 KiB slices and stays at 4 (256 x 528 26.5, with
 // 8 27.7 us).
@@ -201,7 +200,7 @@ static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
     s = s > slices / 8 ? slices / 8 : s;
     if (s >= 4 || (s >= 2 && slices >= 64)) { p.splits = s; p.iters = wide ? 4 : 8; }
   }
-  const bool more = p.splits > 1 ? slices / p.splits >= 48 : units <= 256 || (units > 512 && slices >= 64);
+  const bool more = p.splits > 1 ? slices / p.splits >= 48 : (units <= 256 && slices >= 12) || (units > 512 && slices >= 64);
   if (more && !wide && fits(8) && ctx->attend_tile == 16) p.waves = 8;
   if (ctx->attend_waves > 0) p.waves = fits(ctx->attend_waves) ? ctx->attend_waves : 4;
   return p;
