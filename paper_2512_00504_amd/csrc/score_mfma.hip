@@ -335,13 +335,13 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
 // LDS per MFMA at one key tile per wavefront, which makes the CU's 128 B a cycle its bound; here LDS
 // only hands the queries round once.  K^T Q instead of Q^T K: a lane keeps one row's offset per
 // block (two registers, not eight), and the 16 window rows end up across the lanes.
-// Bound: HBM at several hundred units (28 layers, batch 16, b = 1024: 516 MB of K in 119 us; with one
+// Bound: HBM at several hundred units (28 layers, batch 16, b = 1024: 516 MB of K in 117 us; with one
 // block's arithmetic left of seven 97 us, staging and launch alone 18 us), arithmetic and the start
 // of a workgroup (state, queries, first tile: three dependent trips to memory) below.  Per launch
 // against a kernel that kept the queries in LDS and took an exponential per head and logit: 256 units
-// of 1088 rows, g = 5, w = 32 25.8 -> 20.0 us; 4608 such units 347 -> 307 us; 448 units of 640 rows,
-// g = 7, w = 16 20.8 -> 19.2 us; 4 units 9.7 -> 7.6 us.  Against the plain kernel: bf16 D = 64, 128 units
-// 2780 -> 7.7 us; fp32 D = 128, 32 units 3490 -> 20.5 us (kernel above, bound by fp32 MFMAs).
+// of 1088 rows, g = 5, w = 32 25.8 -> 20.0 us; 4608 such units 347 -> 310 us; 448 units of 640 rows,
+// g = 7, w = 16 20.8 -> 17.8 us; 4 units 9.7 -> 5.3 us.  Against the plain kernel: bf16 D = 64, 128 units
+// 2780 -> 7.4 us; fp32 D = 128, 32 units 3490 -> 20.5 us (kernel above, bound by fp32 MFMAs).
 // Dynamic LDS: q pieces [NT*NB][NL][1 KiB]; float2 row_c[16*NT*NB].
 template <int D, int NW, int NB, int NT, bool ONCE>
 __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, ScoreArgs a, int pair, int ksplit) {
@@ -425,8 +425,7 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   const float s_hi = dm.scale_l2_hi, s_lo = dm.scale_l2_lo;
   const float mean = 0x1p-3f / (float)w;
   float* So = a.S + (size_t)unit * cap;
-  for (int t = g0 + wave; t < g1; t += NW) {
-    load_k_tile<T, D, ONCE>(kN, Kh, min(t + NW, g1 - 1), seq.n_tiled, lane, r, kb);
+  auto tile = [&](const Tile<T, D>& kT, int t) {
     f32x4 tot = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -434,7 +433,7 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         const int b = nt * NB + i;
-        const f32x4 z = logits<T, NL>(kA, q[b]);           // lane (row r, kb): keys 4 kb + e
+        const f32x4 z = logits<T, NL>(kT, q[b]);           // lane (row r, kb): keys 4 kb + e
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           ymax[e] = fmaxf(ymax[e], fmaf(z[e], s_hi, c_hi[b]) + fmaf(z[e], s_lo, c_lo[b]));
@@ -460,8 +459,15 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
     if (!pair) sv += GKV_DPP_F(sv, 0x128);                 // row_ror:8
     const int key = 16 * t + 4 * kb + r;
     if (r < 4 && key < cc) So[key] = sv * mean;
-#pragma unroll
-    for (int c = 0; c < NL; ++c) kA[c] = kN[c];
+  };
+  // two tiles in turn: the next one is always requested before one is worked on, and stays where it lands
+  // (copied over at the end of each round instead: 121 -> 117 us at 1792 units of b = 1024)
+  for (int t = g0 + wave; t < g1; t += 2 * NW) {
+    load_k_tile<T, D, ONCE>(kN, Kh, min(t + NW, g1 - 1), seq.n_tiled, lane, r, kb);
+    tile(kA, t);
+    if (t + NW >= g1) break;
+    load_k_tile<T, D, ONCE>(kA, Kh, min(t + 2 * NW, g1 - 1), seq.n_tiled, lane, r, kb);
+    tile(kN, t + NW);
   }
 }
 
