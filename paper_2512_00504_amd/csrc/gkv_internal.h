@@ -200,6 +200,13 @@ template <> struct Elem<uint16_t> {     // bf16 bit patterns
   __device__ static __forceinline__ void st(uint16_t* p, float v) { *p = float_to_bf16_bits(v); }
 };
 
+// z * (hi + lo) - m, the exponent of 2 of a logit's weight under the running maximum m.  Two roundings
+// of a small number; a logit of -inf gives -inf (weight 0) whatever the sign of lo, one of +inf or NaN
+// gives NaN, as exp(z - max) does.
+__device__ __forceinline__ float log2_weight(float z, float hi, float lo, float m) {
+  return fmaf(fmaxf(z, -3.402823466e38f), lo, fmaf(z, hi, -m));
+}
+
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));

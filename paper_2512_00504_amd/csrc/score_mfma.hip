@@ -204,14 +204,15 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
             f32x4 z = logits<T, NL>(q, kA);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              if (!full && key > last_vis[i][e]) z[e] = -1e30f;
+              // a key the row did not see has the logit -inf: it never becomes the maximum and adds 0
+              if (!full && key > last_vis[i][e]) z[e] = -INFINITY;
               const float tm = z[e] * s_hi;
               if (__any(tm > rm[i][e])) {
                 const float mnew = fmaxf(rm[i][e], tm);
                 rs[i][e] *= __builtin_amdgcn_exp2f(rm[i][e] - mnew);
                 rm[i][e] = mnew;
               }
-              rs[i][e] += __builtin_amdgcn_exp2f(fmaf(z[e], s_lo, fmaf(z[e], s_hi, -rm[i][e])));
+              rs[i][e] += __builtin_amdgcn_exp2f(log2_weight(z[e], s_hi, s_lo, rm[i][e]));
             }
           }
         }

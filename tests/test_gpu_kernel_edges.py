@@ -79,24 +79,12 @@ def test_whole_path_fp32_and_head_dim_64(over):
 
 
 # ---- window score -----------------------------------------------------------------------------
-# Elementwise 1e-5 of the fp64 score (plus 1e-30 absolute), the bound of the whole-path tests: fp32
-# sums of up to 128 products and one exponential.
-@pytest.mark.parametrize("dtype,d,g,w,params", [
-    ("bf16", 128, 7, 16, None),                       # two row pairs of tiles, one block per head
-    ("bf16", 128, 16, 32, None),                      # queries beyond one staging pass
-    ("bf16", 128, 3, 8, None), ("bf16", 128, 4, 5, None),     # two heads share a block, odd and even groups
-    ("bf16", 64, 1, 1, None), ("bf16", 64, 5, 33, None),      # a window row count just past a block
-    ("f32", 128, 7, 16, None), ("f32", 128, 16, 24, None),    # two staging passes of 128 KiB
-    ("f32", 64, 2, 8, None), ("f32", 64, 16, 40, None),
-    ("bf16", 128, 5, 32, {"evict_fuse_global": 1}),
-])
-@pytest.mark.parametrize("reuse", [1, 0])
-def test_window_score_at_tile_edges(dtype, d, g, w, params, reuse):
+def _check_window_score(dtype, d, g, w, params, reuse, scale=0.0):
     cap, b = 320, 48
     lens = [b + 1, b + 15, b + 17, 100, 127, 160, 161, cap]           # rows the compression sees
     lens = [max(n, w + 1) for n in lens]
     B = len(lens)
-    st = DecodeState(make_config(1, B, g, 1, d, b, w, max(w, 8), cap, dtype), params=params)
+    st = DecodeState(make_config(1, B, g, 1, d, b, w, max(w, 8), cap, dtype, softmax_scale=scale), params=params)
     st.ctx.set_param("score_reuse_stats", reuse)
     gen = torch.Generator().manual_seed(100 * g + w)
     rnd = lambda *s: torch.randn(*s, generator=gen).to(st.K.dtype)
@@ -120,7 +108,8 @@ def test_window_score_at_tile_edges(dtype, d, g, w, params, reuse):
         st.score_window(t)
     S = st.S.double().cpu().numpy()
     for i, n in enumerate(lens):
-        A = O.window_probs(q[:, 0, i].permute(1, 0, 2).double().numpy(), K[0, i].double().numpy(), n)
+        A = O.window_probs(q[:, 0, i].permute(1, 0, 2).double().numpy(), K[0, i].double().numpy(), n,
+                           float(np.float32(scale)) if scale else None)
         ref = O.local_score(A, 1)[:, : n - w]
         err = np.abs(S[0, i, :, : n - w] - ref)
         assert (err <= 1e-5 * ref + 1e-30).all(), (n, (err / (ref + 1e-300)).max())
@@ -128,6 +117,31 @@ def test_window_score_at_tile_edges(dtype, d, g, w, params, reuse):
         if params:
             F = O.global_score(ref, np.zeros_like(ref), 0, 0.8, "max")
             np.testing.assert_allclose(st.F[0, i, :, : n - w].double().cpu().numpy(), F, rtol=1e-5, atol=1e-30)
+
+
+# Elementwise 1e-5 of the fp64 score (plus 1e-30 absolute), the bound of the whole-path tests: fp32
+# sums of up to 128 products and one exponential.
+@pytest.mark.parametrize("dtype,d,g,w,params", [
+    ("bf16", 128, 7, 16, None),                       # two row pairs of tiles, one block per head
+    ("bf16", 128, 16, 32, None),                      # queries beyond one staging pass
+    ("bf16", 128, 3, 8, None), ("bf16", 128, 4, 5, None),     # two heads share a block, odd and even groups
+    ("bf16", 64, 1, 1, None), ("bf16", 64, 5, 33, None),      # a window row count just past a block
+    ("f32", 128, 7, 16, None), ("f32", 128, 16, 24, None),    # two staging passes of 128 KiB
+    ("f32", 64, 2, 8, None), ("f32", 64, 16, 40, None),
+    ("bf16", 128, 5, 32, {"evict_fuse_global": 1}),
+])
+@pytest.mark.parametrize("reuse", [1, 0])
+def test_window_score_at_tile_edges(dtype, d, g, w, params, reuse):
+    _check_window_score(dtype, d, g, w, params, reuse)
+
+
+# The window rows' own statistics with keys hidden from some rows, at scales whose low part (scale *
+# log2 e rounded to fp32) has either sign: a hidden key must add nothing, whatever the residue of its
+# masked logit.  Same bound.
+@pytest.mark.parametrize("scale", [0.1, 0.05, 0.2, 0.125])
+@pytest.mark.parametrize("dtype,d,g,w", [("bf16", 128, 7, 16), ("bf16", 64, 5, 8), ("f32", 128, 3, 16), ("f32", 64, 2, 24)])
+def test_window_score_own_statistics_other_scales(dtype, d, g, w, scale):
+    _check_window_score(dtype, d, g, w, None, 0, scale)
 
 
 # ---- units cut over several workgroups ----------------------------------------------------------
