@@ -195,7 +195,7 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
     sv[i] = sc[i >> 2][i & 3];
     if constexpr (EDGE) {
       const int key = key0 + (i >> 2) * 16 + 4 * kb + (i & 3);
-      if (key >= n_tot) sv[i] = -1e30f;              // finite: -inf times the (signed) low part of the scale would be NaN
+      if (key >= n_tot) sv[i] = -INFINITY;
     }
   }
   float mx = sv[0];
@@ -217,7 +217,7 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
   for (int i = 0; i < NS; ++i) {
     // exponent of 2 = z * (hi + lo) - m: the window-score kernel forms its own from the same
     // logits, so the sums recorded below are the normalisers of its probabilities
-    pf[i] = __builtin_amdgcn_exp2f(fmaf(sv[i], scale_log2_lo, fmaf(sv[i], scale_log2, -st.m_run)));
+    pf[i] = __builtin_amdgcn_exp2f(log2_weight(sv[i], scale_log2, scale_log2_lo, st.m_run));
     psum += pf[i];
   }
   st.l_run += psum;
@@ -284,9 +284,10 @@ __device__ __forceinline__ float2 load_agent(const float* p) {
   const uint64_t v = __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
 }
-// 1/l: bf16 results are rounded to 8 bits anyway, fp32 results get the full division
-template <typename T> __device__ __forceinline__ float inv_sum(float l) {
-  if (!(l > 0.f)) return 0.f;
+// 1/l: bf16 results are rounded to 8 bits anyway, fp32 results get the full division.  Nothing
+// attended to: 0; keys whose logits are all -inf: NaN, as softmax gives.
+template <typename T> __device__ __forceinline__ float inv_sum(float l, bool any_key) {
+  if (!(l > 0.f)) return any_key && l == 0.f ? __builtin_nanf("") : 0.f;
   return sizeof(T) == 2 ? __builtin_amdgcn_rcpf(l) : 1.f / l;
 }
 
@@ -435,7 +436,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
       o += *(const f32x4*)(so + (wv * g + h) * OSTR + c4) * f;
     }
     if (ns == 1) {
-      store_row4(out + h * D + c4, o * inv_sum<T>(Lsum));
+      store_row4(out + h * D + c4, o * inv_sum<T>(Lsum, n_tot > 0));
       // softmax statistics of this head's row (running max in log2 units, sum), into the ring slot
       // that also receives q: the window score of the next compression reuses them
       if (c4 == 0 && a.write_stats) stats[h] = make_float2(M, Lsum);
@@ -498,7 +499,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
           Lsum = Lsum * f0 + ml.y * f;
           o = o * f0 + f32x4{a0.x, a0.y, a1.x, a1.y} * f;
         }
-        store_row4(out + h * D + c4, o * inv_sum<T>(Lsum));
+        store_row4(out + h * D + c4, o * inv_sum<T>(Lsum, n_tot > 0));
         if (c4 == 0 && a.write_stats) stats[h] = make_float2(M, Lsum);
       }
     }

@@ -67,6 +67,42 @@ def test_attend_at_tile_edges(dtype, d, g, append):
         _check_attend(st, *t, lens, dtype, d, append)
 
 
+# every instantiation of the decode kernel: wavefronts, keys per slice, whole and cut units
+DECODE_FORMS = [("f32", 64, 3, 256, None), ("f32", 128, 7, 256, None), ("bf16", 64, 5, 256, None), ("bf16", 128, 7, 256, None),
+                ("f32", 128, 2, 640, None), ("bf16", 64, 5, 1312, None), ("bf16", 128, 7, 3936, None),      # cut
+                ("f32", 64, 2, 256, {"attend_waves": 16}), ("f32", 128, 2, 256, {"attend_waves": 8}),
+                ("bf16", 64, 2, 256, {"attend_waves": 16}), ("bf16", 128, 2, 256, {"attend_waves": 16}),
+                ("bf16", 64, 2, 256, {"attend_waves": 8}), ("f32", 64, 2, 256, {"attend_waves": 8}),
+                ("bf16", 128, 2, 640, {"attend_tile": 32, "attend_splits": 2}), ("f32", 64, 2, 640, {"force_generic": 1})]
+
+
+@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
+def test_attend_logits_of_minus_infinity(dtype, d, g, cap, params):
+    # a key whose logit is -inf has weight 0, wherever it stands: the cache's first half, the newest row,
+    # whole slices; a row of nothing else is NaN, as softmax gives; the others keep their accuracy
+    lens = [1, 17, 33, 34, 65, 250, cap - 1]
+    st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 64, seed=7, params=params)
+    q = q.abs() + 0.125                                                 # so that no other logit is inf * 0
+    for i, n in enumerate(lens):
+        K[0, i, :, : n // 2, 3] = -float("inf")
+        K[0, i, :, n // 2 + 1: n: 5, 3] = -float("inf")
+        st.K[0, i] = k_rows_to_cache(K[0, i], min(64, n // 16 * 16)).cuda()
+    kn[0, 1, :, 3] = kn[0, 5, :, 3] = -float("inf")
+    K[0, 2, :, :33, 3] = kn[0, 2, :, 3] = -float("inf")                 # sequence 2: nothing else
+    st.K[0, 2] = k_rows_to_cache(K[0, 2], 32).cuda()
+    out = st.attend_decode(q.cuda(), kn.cuda(), vn.cuda(), 5).double().cpu().numpy()
+    for i, n in enumerate(lens):
+        Ki, Vi = K[0, i].double().numpy().copy(), V[0, i].double().numpy().copy()
+        Ki[:, n], Vi[:, n] = kn[0, i].double().numpy(), vn[0, i].double().numpy()
+        if i == 2:
+            assert np.isnan(out[0, i]).all()
+            continue
+        ref = O.attend(q[0, i].double().numpy(), Ki[:, : n + 1], Vi[:, : n + 1], n + 1)
+        assert np.isfinite(ref).all()
+        err = np.abs(out[0, i] - ref)
+        assert (err <= _bound(dtype, d, ref, Vi[:, : n + 1])).all(), (n, err.max())
+
+
 @pytest.mark.parametrize("over", [
     dict(dtype="f32", n_layers=2, batch=2, n_q_heads=14, n_kv_heads=2, budget=96, window=16, interval=32),    # fp32, d = 128, g = 7
     dict(dtype="f32", n_layers=1, batch=2, n_q_heads=6, n_kv_heads=2, budget=70, window=5, interval=24, head_dim=64),
@@ -79,7 +115,7 @@ def test_whole_path_fp32_and_head_dim_64(over):
 
 
 # ---- window score -----------------------------------------------------------------------------
-def _check_window_score(dtype, d, g, w, params, reuse, scale=0.0):
+def _check_window_score(dtype, d, g, w, params, reuse, scale=0.0, hidden=False):
     cap, b = 320, 48
     lens = [b + 1, b + 15, b + 17, 100, 127, 160, 161, cap]           # rows the compression sees
     lens = [max(n, w + 1) for n in lens]
@@ -89,6 +125,9 @@ def _check_window_score(dtype, d, g, w, params, reuse, scale=0.0):
     gen = torch.Generator().manual_seed(100 * g + w)
     rnd = lambda *s: torch.randn(*s, generator=gen).to(st.K.dtype)
     K, q = 2 * rnd(1, B, 1, cap, d), rnd(w, 1, B, g, d)
+    if hidden:                                                          # logits of -inf, for some keys of candidates and window
+        q = q.abs() + 0.125
+        K[..., 1::3, 3] = -float("inf")
     n_tiled = [(n - w) // 32 * 16 for n in lens]                        # some of the candidate tiles are row-major
     t0 = 7
     for i, n in enumerate(lens):
@@ -142,6 +181,13 @@ def test_window_score_at_tile_edges(dtype, d, g, w, params, reuse):
 @pytest.mark.parametrize("dtype,d,g,w", [("bf16", 128, 7, 16), ("bf16", 64, 5, 8), ("f32", 128, 3, 16), ("f32", 64, 2, 24)])
 def test_window_score_own_statistics_other_scales(dtype, d, g, w, scale):
     _check_window_score(dtype, d, g, w, None, 0, scale)
+
+
+@pytest.mark.parametrize("reuse", [1, 0])
+@pytest.mark.parametrize("dtype,d,g,w", [("bf16", 128, 7, 16), ("bf16", 64, 5, 8), ("f32", 128, 3, 16), ("f32", 64, 2, 24)])
+def test_window_score_logits_of_minus_infinity(dtype, d, g, w, reuse):
+    # probability 0 for those keys, with the statistics recorded by the decode calls and with its own
+    _check_window_score(dtype, d, g, w, None, reuse, hidden=True)
 
 
 # ---- units cut over several workgroups ----------------------------------------------------------
