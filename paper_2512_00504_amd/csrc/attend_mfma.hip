@@ -19,8 +19,8 @@
 //      O^T[channel, head] += V^T[channel, key] . P^T[key, head], with P already in the right lanes:
 //        bf16: an in-register transpose (v_perm_b32) makes the A operands, D/16 MFMAs per slice;
 //        fp32: the loaded words are the A operands, MFMA 16x16x4 per (e, channel of the lane).
-//      bf16 rounds P to bf16 at D = 128; at D = 64 it enters as high + low bf16 halves (16 bits of
-//      mantissa), fp32 keeps it as it is.
+//      bf16 rounds P to bf16 at D = 128; at D = 64 it enters as the sum of three bf16 numbers, which
+//      hold its 24 bits; fp32 keeps it as it is.
 // Bound: HBM at launches of a few hundred units and more, latency below.  fp32 has 8 KiB (D = 64)
 // or 16 KiB (D = 128) per slice against 1024 or 2048 cycles of MFMA, so four wavefronts can take
 // 32 B a cycle and CU, four times the CU's share of the HBM rate; bf16 needs a tenth of that.
@@ -234,10 +234,11 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
 #pragma unroll
     for (int i = 0; i < 8; ++i) p8[i] = pf[i];
     const bf16x8 pB = __builtin_convertvector(p8, bf16x8);
-    bf16x8 pL;
+    bf16x8 pM, pL;                               // D = 64: P = pB + pM + pL, all of its 24 bits
     if constexpr (D == 64) {
-      const f32x8 hi = __builtin_convertvector(pB, f32x8);
-      pL = __builtin_convertvector(p8 - hi, bf16x8);
+      const f32x8 r1 = p8 - __builtin_convertvector(pB, f32x8);
+      pM = __builtin_convertvector(r1, bf16x8);
+      pL = __builtin_convertvector(r1 - __builtin_convertvector(pM, f32x8), bf16x8);
     }
 #pragma unroll
     for (int m = 0; m < G::NC; ++m) {
@@ -247,8 +248,10 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
         t[y] = __builtin_amdgcn_perm(s.vR[2 * y + 1].w[m >> 1], s.vR[2 * y].w[m >> 1],
                                      (m & 1) ? 0x07060302u : 0x05040100u);
       st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t), pB, st.oacc[m], 0, 0, 0);
-      if constexpr (D == 64)
+      if constexpr (D == 64) {
+        st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t), pM, st.oacc[m], 0, 0, 0);
         st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t), pL, st.oacc[m], 0, 0, 0);
+      }
     }
   } else {
     f32x4 p4;
@@ -284,11 +287,11 @@ __device__ __forceinline__ float2 load_agent(const float* p) {
   const uint64_t v = __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
 }
-// 1/l: bf16 results are rounded to 8 bits anyway, fp32 results get the full division.  Nothing
-// attended to: 0; keys whose logits are all -inf: NaN, as softmax gives.
-template <typename T> __device__ __forceinline__ float inv_sum(float l, bool any_key) {
+// 1/l in full precision; `fast`: v_rcp_f32, for uncut bf16 units at D = 128, whose P is rounded to 8
+// bits as it is.  Nothing attended to: 0; keys whose logits are all -inf: NaN, as softmax gives.
+__device__ __forceinline__ float inv_sum(float l, bool any_key, bool fast) {
   if (!(l > 0.f)) return any_key && l == 0.f ? __builtin_nanf("") : 0.f;
-  return sizeof(T) == 2 ? __builtin_amdgcn_rcpf(l) : 1.f / l;
+  return fast ? __builtin_amdgcn_rcpf(l) : 1.f / l;
 }
 
 // KT = 16-key tiles per wavefront iteration (1 or 2)
@@ -436,7 +439,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
       o += *(const f32x4*)(so + (wv * g + h) * OSTR + c4) * f;
     }
     if (ns == 1) {
-      store_row4(out + h * D + c4, o * inv_sum<T>(Lsum, n_tot > 0));
+      store_row4(out + h * D + c4, o * inv_sum(Lsum, n_tot > 0, !G::F32 && D == 128));
       // softmax statistics of this head's row (running max in log2 units, sum), into the ring slot
       // that also receives q: the window score of the next compression reuses them
       if (c4 == 0 && a.write_stats) stats[h] = make_float2(M, Lsum);
@@ -499,7 +502,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
           Lsum = Lsum * f0 + ml.y * f;
           o = o * f0 + f32x4{a0.x, a0.y, a1.x, a1.y} * f;
         }
-        store_row4(out + h * D + c4, o * inv_sum<T>(Lsum, n_tot > 0));
+        store_row4(out + h * D + c4, o * inv_sum(Lsum, n_tot > 0, false));
         if (c4 == 0 && a.write_stats) stats[h] = make_float2(M, Lsum);
       }
     }

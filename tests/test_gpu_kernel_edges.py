@@ -103,6 +103,39 @@ def test_attend_logits_of_minus_infinity(dtype, d, g, cap, params):
         assert (err <= _bound(dtype, d, ref, Vi[:, : n + 1])).all(), (n, err.max())
 
 
+@pytest.mark.parametrize("dtype,d,g,cap,params", [f for f in DECODE_FORMS if f[:2] != ("bf16", 128)])
+def test_attend_probabilities_keep_32_bits(dtype, d, g, cap, params):
+    # Values whose weighted sum cancels to about 2^-27 of its terms leave the rounding of the weights in
+    # the output.  Small logits: their own rounding and the exponential's are about 2^-23.  The 2-norm of
+    # the error over that of the terms: 2^-23 and less for weights in fp32 (bound 2^-21), 2^-18.5 for 16 bits.
+    lens = [60, 61, 63, 120, 200, 250, cap - 1]
+    st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 64, seed=3, params=params)
+    q = (q * 0.0625).to(q.dtype)
+    err2 = terms2 = 0.0
+    for i, n in enumerate(lens):
+        for j in range(2):
+            k = np.concatenate([K[0, i, j, :n].double().numpy(), kn[0, i, j : j + 1].double().numpy()])
+            z = k @ q[0, i, j * g].double().numpy() / np.sqrt(d)            # head 0 of the group
+            p = np.exp(z - z.max()); p /= p.sum()
+            v = V[0, i, j, :n].double().numpy()
+            v = np.concatenate([v, vn[0, i, j : j + 1].double().numpy()])
+            for x in range(n - 3, n):                                       # the last three cached rows take what is left
+                v[x] = 0.0
+                v[x] = torch.from_numpy(-(p @ v) / p[x]).to(q.dtype).double().numpy()
+            V[0, i, j, :n] = torch.from_numpy(v[:n]).to(q.dtype)
+    st.V.copy_(V)
+    out = st.attend_decode(q.cuda(), kn.cuda(), vn.cuda(), 5).double().cpu().numpy()
+    for i, n in enumerate(lens):
+        for j in range(2):
+            k = np.concatenate([K[0, i, j, :n].double().numpy(), kn[0, i, j : j + 1].double().numpy()])
+            v = np.concatenate([V[0, i, j, :n].double().numpy(), vn[0, i, j : j + 1].double().numpy()])
+            z = k @ q[0, i, j * g].double().numpy() / np.sqrt(d)
+            p = np.exp(z - z.max()); p /= p.sum()
+            err2 += ((out[0, i, j * g] - p @ v) ** 2).sum()
+            terms2 += ((p[:, None] * v) ** 2).sum()
+    assert err2 <= 2.0 ** -42 * terms2, 0.5 * np.log2(err2 / terms2)
+
+
 @pytest.mark.parametrize("over", [
     dict(dtype="f32", n_layers=2, batch=2, n_q_heads=14, n_kv_heads=2, budget=96, window=16, interval=32),    # fp32, d = 128, g = 7
     dict(dtype="f32", n_layers=1, batch=2, n_q_heads=6, n_kv_heads=2, budget=70, window=5, interval=24, head_dim=64),
