@@ -37,6 +37,8 @@
 // stores and atomics each cost several microseconds per launch on this memory system.
 #include "gkv_internal.h"
 
+#include <type_traits>
+
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -138,7 +140,8 @@ struct Running {
 
 // EDGE = the slice may contain the newest token's row and rows past the end: substitute k/v of
 // the newest token from the inputs, mask the rest.  The common path has none of that.
-template <typename T, int D, int KT, bool EDGE>
+// F32P (bf16): the product with V as fp32 MFMAs, V converted word by word and P whole.
+template <typename T, int D, int KT, bool EDGE, bool F32P>
 __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16>& st,
                                               const u32x4 (&qB)[Geo<T, D>::NL], int it,
                                               float scale_log2, float scale_log2_lo, int r, int kb, bool has_new, int len0,
@@ -229,6 +232,15 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
 #pragma unroll
       for (int m = 0; m < G::NC; ++m)
         st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(s.vR[i].w[m]), pf[i], st.oacc[m], 0, 0, 0);
+  } else if constexpr (F32P) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+      for (int m = 0; m < G::NC; ++m) {
+        const uint32_t w = s.vR[i].w[m >> 1];
+        st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float((m & 1) ? w & 0xffff0000u : w << 16), pf[i],
+                                                          st.oacc[m], 0, 0, 0);
+      }
   } else if constexpr (KT == 2) {
     f32x8 p8;
 #pragma unroll
@@ -374,10 +386,9 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
 
   // First slice in flight, then stage k_new / v_new in LDS for whoever owns the last slice.
   const int n_iter = (n_tot + KEYS - 1) / KEYS;
-  const int stride = ns * NW;
-  int it = sp * NW + wave;
+  const int stride = ns * NW, it0 = sp * NW + wave;
   Slice<T, D, KT> s;
-  if (it < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it, seq.n_tiled, lane, r, kb);
+  if (it0 < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it0, seq.n_tiled, lane, r, kb);
   // stage: 16-byte pieces [0,RP) k_new, [RP,2RP) v_new, [2RP, 2RP+RP*g) q rows; kept in LDS, not
   // in registers, until they are stored at the end
   char* stage = (char*)(smem + NW * g * OSTR + NW * 16 + NW * 16);
@@ -389,11 +400,34 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
     if (x < 2 * RP + RP * g) *(u32x4*)(stage + x * 16) = ap[rd];
   }
   __syncthreads();
-  while (it < n_iter) {
-    if ((it + 1) * KEYS > len0) process_slice<T, D, KT, true>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
-    else process_slice<T, D, KT, false>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
-    it += stride;
-    if (it < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it, seq.n_tiled, lane, r, kb);
+  // this wavefront's slices, the first one already requested
+  auto slices = [&](auto f32p) {
+    constexpr bool F32P = decltype(f32p)::value;
+    int it = it0;
+    while (it < n_iter) {
+      if ((it + 1) * KEYS > len0) process_slice<T, D, KT, true, F32P>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
+      else process_slice<T, D, KT, false, F32P>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
+      it += stride;
+      if (it < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it, seq.n_tiled, lane, r, kb);
+    }
+  };
+  slices(std::false_type{});
+  if constexpr (!G::F32 && D == 64) {
+    // P as a sum of bf16 numbers: an infinite V times a part that is zero or negative is NaN where the
+    // whole P gives an infinity.  Seldom, and then the slices are gone through again with P whole.
+    bool nan = false;
+#pragma unroll
+    for (int m = 0; m < G::NC; ++m)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) nan |= st.oacc[m][e] != st.oacc[m][e];
+    if (__any(nan)) {
+      st.m_run = -1e30f;
+      st.l_run = 0.f;
+#pragma unroll
+      for (int m = 0; m < G::NC; ++m) st.oacc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (it0 < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it0, seq.n_tiled, lane, r, kb);
+      slices(std::true_type{});
+    }
   }
   const float m_run = st.m_run, l_run = st.l_run;
   f32x4 (&oacc)[G::NC] = st.oacc;

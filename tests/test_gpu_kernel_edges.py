@@ -103,6 +103,34 @@ def test_attend_logits_of_minus_infinity(dtype, d, g, cap, params):
         assert (err <= _bound(dtype, d, ref, Vi[:, : n + 1])).all(), (n, err.max())
 
 
+@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
+def test_attend_infinite_values(dtype, d, g, cap, params):
+    # an infinite value with a weight above zero makes its channel infinite, two of opposite sign NaN, and
+    # neither touches the other channels
+    lens = [1, 17, 33, 65, 250, cap - 1]
+    st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 64, seed=13, params=params)
+    q = (q * 0.125).to(q.dtype)                                         # every weight well above zero
+    for i, n in enumerate(lens):
+        V[0, i, :, n // 2, 3] = float("inf")
+        V[0, i, :, n // 2, d - 2] = -float("inf")
+        V[0, i, :, 0, 17] = float("inf")
+        if n > 1:
+            V[0, i, :, n - 1, 17] = -float("inf")
+    vn[0, 2, :, 5] = -float("inf")
+    st.V.copy_(V)
+    out = st.attend_decode(q.cuda(), kn.cuda(), vn.cuda(), 5).double().cpu().numpy()
+    for i, n in enumerate(lens):
+        Ki, Vi = K[0, i].double().numpy().copy(), V[0, i].double().numpy().copy()
+        Ki[:, n], Vi[:, n] = kn[0, i].double().numpy(), vn[0, i].double().numpy()
+        ref = O.attend(q[0, i].double().numpy(), Ki[:, : n + 1], Vi[:, : n + 1], n + 1)
+        assert np.isinf(ref).any() and (n == 1 or np.isnan(ref).any())
+        bad = ~np.isfinite(ref)
+        np.testing.assert_array_equal(out[0, i][bad], ref[bad])
+        fin = np.where(bad, 0.0, ref)
+        Vf = np.where(np.isfinite(Vi[:, : n + 1]), Vi[:, : n + 1], 0.0)
+        assert (np.abs(np.where(bad, 0.0, out[0, i]) - fin) <= _bound(dtype, d, fin, Vf)).all()
+
+
 @pytest.mark.parametrize("dtype,d,g,cap,params", [f for f in DECODE_FORMS if f[:2] != ("bf16", 128)])
 def test_attend_probabilities_keep_32_bits(dtype, d, g, cap, params):
     # Values whose weighted sum cancels to about 2^-27 of its terms leave the rounding of the weights in
