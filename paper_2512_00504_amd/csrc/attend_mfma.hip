@@ -140,8 +140,10 @@ struct Running {
 
 // EDGE = the slice may contain the newest token's row and rows past the end: substitute k/v of
 // the newest token from the inputs, mask the rest.  The common path has none of that.
-// F32P (bf16): the product with V as fp32 MFMAs, V converted word by word and P whole.
-template <typename T, int D, int KT, bool EDGE, bool F32P>
+// EXACT: right for every logit and value, infinities and finite ones of any size among them.  Without
+// it, which is what a wavefront tries first, a logit of -inf may give NaN (the scale's low part times -inf), a
+// huge maximum any weight (see log2_weight), and at bf16, D = 64 an infinite value NaN; all of them show at the end.
+template <typename T, int D, int KT, bool EDGE, bool EXACT>
 __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16>& st,
                                               const u32x4 (&qB)[Geo<T, D>::NL], int it,
                                               float scale_log2, float scale_log2_lo, int r, int kb, bool has_new, int len0,
@@ -198,7 +200,7 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
     sv[i] = sc[i >> 2][i & 3];
     if constexpr (EDGE) {
       const int key = key0 + (i >> 2) * 16 + 4 * kb + (i & 3);
-      if (key >= n_tot) sv[i] = -INFINITY;
+      if (key >= n_tot) sv[i] = EXACT ? -INFINITY : -1e30f;
     }
   }
   float mx = sv[0];
@@ -220,7 +222,10 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
   for (int i = 0; i < NS; ++i) {
     // exponent of 2 = z * (hi + lo) - m: the window-score kernel forms its own from the same
     // logits, so the sums recorded below are the normalisers of its probabilities
-    pf[i] = __builtin_amdgcn_exp2f(log2_weight(sv[i], scale_log2, scale_log2_lo, st.m_run));
+    float y;
+    if constexpr (EXACT) y = log2_weight(sv[i], scale_log2, scale_log2_lo, st.m_run);
+    else y = fmaf(sv[i], scale_log2_lo, fmaf(sv[i], scale_log2, -st.m_run));
+    pf[i] = __builtin_amdgcn_exp2f(y);
     psum += pf[i];
   }
   st.l_run += psum;
@@ -232,7 +237,7 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
 #pragma unroll
       for (int m = 0; m < G::NC; ++m)
         st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(s.vR[i].w[m]), pf[i], st.oacc[m], 0, 0, 0);
-  } else if constexpr (F32P) {
+  } else if constexpr (EXACT && D == 64) {       // P whole, V converted word by word
 #pragma unroll
     for (int i = 0; i < NS; ++i)
 #pragma unroll
@@ -252,18 +257,20 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
       pM = __builtin_convertvector(r1, bf16x8);
       pL = __builtin_convertvector(r1 - __builtin_convertvector(pM, f32x8), bf16x8);
     }
+    u32x4 t[G::NC];
 #pragma unroll
     for (int m = 0; m < G::NC; ++m) {
-      u32x4 t;
 #pragma unroll
       for (int y = 0; y < 4; ++y)
-        t[y] = __builtin_amdgcn_perm(s.vR[2 * y + 1].w[m >> 1], s.vR[2 * y].w[m >> 1],
-                                     (m & 1) ? 0x07060302u : 0x05040100u);
-      st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t), pB, st.oacc[m], 0, 0, 0);
-      if constexpr (D == 64) {
-        st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t), pM, st.oacc[m], 0, 0, 0);
-        st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t), pL, st.oacc[m], 0, 0, 0);
-      }
+        t[m][y] = __builtin_amdgcn_perm(s.vR[2 * y + 1].w[m >> 1], s.vR[2 * y].w[m >> 1],
+                                        (m & 1) ? 0x07060302u : 0x05040100u);
+      st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t[m]), pB, st.oacc[m], 0, 0, 0);
+    }
+    if constexpr (D == 64) {                     // term by term: an accumulator's products don't wait for each other
+#pragma unroll
+      for (int m = 0; m < G::NC; ++m) st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t[m]), pM, st.oacc[m], 0, 0, 0);
+#pragma unroll
+      for (int m = 0; m < G::NC; ++m) st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t[m]), pL, st.oacc[m], 0, 0, 0);
     }
   } else {
     f32x4 p4;
@@ -379,7 +386,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
   const float scale_log2 = dm.scale_l2_hi, scale_log2_lo = dm.scale_l2_lo;
 
   Running<G::NC> st;
-  st.m_run = -1e30f;
+  st.m_run = GKV_NO_MAX;
   st.l_run = 0.f;
 #pragma unroll
   for (int m = 0; m < G::NC; ++m) st.oacc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -401,31 +408,34 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
   }
   __syncthreads();
   // this wavefront's slices, the first one already requested
-  auto slices = [&](auto f32p) {
-    constexpr bool F32P = decltype(f32p)::value;
+  auto slices = [&](auto exact) {
+    constexpr bool EXACT = decltype(exact)::value;
     int it = it0;
     while (it < n_iter) {
-      if ((it + 1) * KEYS > len0) process_slice<T, D, KT, true, F32P>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
-      else process_slice<T, D, KT, false, F32P>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
+      if ((it + 1) * KEYS > len0) process_slice<T, D, KT, true, EXACT>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
+      else process_slice<T, D, KT, false, EXACT>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
       it += stride;
       if (it < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it, seq.n_tiled, lane, r, kb);
     }
   };
   slices(std::false_type{});
-  if constexpr (!G::F32 && D == 64) {
-    // P as a sum of bf16 numbers: an infinite V times a part that is zero or negative is NaN where the
-    // whole P gives an infinity.  Seldom, and then the slices are gone through again with P whole.
-    bool nan = false;
+  if (it0 < n_iter) {
+    // Seldom: a maximum that the short form of the weights is not right for, or a NaN that may be its
+    // doing (a logit of -inf; at bf16, D = 64 an infinite value that met a part of P that is zero or
+    // negative).  The slices are gone through again.
+    bool again = fabsf(st.m_run) >= GKV_HUGE_LOG2 || st.l_run != st.l_run;
+    if constexpr (!G::F32 && D == 64) {
 #pragma unroll
-    for (int m = 0; m < G::NC; ++m)
+      for (int m = 0; m < G::NC; ++m)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) nan |= st.oacc[m][e] != st.oacc[m][e];
-    if (__any(nan)) {
-      st.m_run = -1e30f;
+        for (int e = 0; e < 4; ++e) again |= st.oacc[m][e] != st.oacc[m][e];
+    }
+    if (__any(again)) {
+      st.m_run = GKV_NO_MAX;
       st.l_run = 0.f;
 #pragma unroll
       for (int m = 0; m < G::NC; ++m) st.oacc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (it0 < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it0, seq.n_tiled, lane, r, kb);
+      issue_slice<T, D, KT>(s, Kh, Vh, it0, seq.n_tiled, lane, r, kb);
       slices(std::true_type{});
     }
   }
@@ -461,7 +471,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
   for (int x = tid; x < g * (D / 4); x += NW * 64) {
     const int h = x / (D / 4), c4 = (x % (D / 4)) * 4;
     float mw[NW];
-    float M = -1e30f;
+    float M = GKV_NO_MAX;
 #pragma unroll
     for (int wv = 0; wv < NW; ++wv) { mw[wv] = sm[wv * 16 + h]; M = fmaxf(M, mw[wv]); }
     float Lsum = 0.f;
@@ -524,7 +534,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
       const float* pu = a.ws.partials + (size_t)unit * splits * g * PSTR;
       for (int x = tid; x < g * (D / 4); x += NW * 64) {
         const int h = x / (D / 4), c4 = (x % (D / 4)) * 4;
-        float M = -1e30f, Lsum = 0.f;
+        float M = GKV_NO_MAX, Lsum = 0.f;
         f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
         for (int s2 = 0; s2 < ns; ++s2) {

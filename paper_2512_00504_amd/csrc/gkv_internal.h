@@ -200,10 +200,21 @@ template <> struct Elem<uint16_t> {     // bf16 bit patterns
   __device__ static __forceinline__ void st(uint16_t* p, float v) { *p = float_to_bf16_bits(v); }
 };
 
-// z * (hi + lo) - m, the exponent of 2 of a logit's weight under the running maximum m.  Two roundings
-// of a small number; a logit of -inf gives -inf (weight 0) whatever the sign of lo, one of +inf or NaN
-// gives NaN, as exp(z - max) does.
+// Running maximum (log2 units) before the first key.
+constexpr float GKV_NO_MAX = -3.402823466e38f;
+// From this magnitude of a running maximum on, products with the scale are rounded one by one.
+constexpr float GKV_HUGE_LOG2 = 0x1p22f;
+__device__ __forceinline__ float rounded_product(float a, float b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+// z * (hi + lo) - m, the exponent of 2 of a logit's weight under the running maximum m = round(max z * hi),
+// with two roundings of a small number.  For the largest logit that is what rounding m left over, up to
+// |m| * 2^-24, which must not reach the exponential once m is in the millions: there the product is rounded
+// as m was (as the plain kernels round theirs), which gives the largest logit exactly 0.  A logit of -inf
+// gives -inf (weight 0) whatever the sign of lo, one of +inf or NaN gives NaN, as exp(z - max) does.
 __device__ __forceinline__ float log2_weight(float z, float hi, float lo, float m) {
+  if (fabsf(m) >= GKV_HUGE_LOG2) return rounded_product(z, hi) - m;
   return fmaf(fmaxf(z, -3.402823466e38f), lo, fmaf(z, hi, -m));
 }
 

@@ -80,6 +80,27 @@ __device__ __forceinline__ f32x4 logits(const u32x4 (&q)[NL], const u32x4 (&kA)[
   return acc;
 }
 
+// Offset of a window row with maximum m (log2 units) and sum s, as hi + lo; a row that is not there has a
+// huge negative one.  Rows with a huge maximum keep it as it is in hi, for log2_score<true>.
+__device__ __forceinline__ float2 row_offset(bool valid, float m, float s) {
+  if (!valid) return make_float2(-INFINITY, 0.f);
+  const double l = log2((double)s);
+  if (fabsf(m) >= GKV_HUGE_LOG2) return make_float2(-m, (float)(3.0 - l));
+  const double off = 3.0 - ((double)m + l);
+  const float hi = (float)off;
+  return make_float2(hi, (float)(off - (double)hi));
+}
+// Whether an offset may be that of a row with a huge maximum.
+__device__ __forceinline__ bool huge_offset(float hi) { return fabsf(hi) >= GKV_HUGE_LOG2 && hi != -INFINITY; }
+
+// y of a logit.  HUGE_ROWS: some row of the workgroup has a huge maximum, and all of them round the
+// product as such a row's maximum and sum were formed (1e-6 less exact for the others).
+template <bool HUGE_ROWS>
+__device__ __forceinline__ float log2_score(float z, float s_hi, float s_lo, float c_hi, float c_lo) {
+  if constexpr (HUGE_ROWS) return (rounded_product(z, s_hi) + c_hi) + c_lo;
+  return fmaf(z, s_hi, c_hi) + fmaf(z, s_lo, c_lo);
+}
+
 // How a launch is cut (host): heads per block, blocks per 16 window rows, 16-row window blocks in
 // all and per staging pass, key shares per unit, bytes of the LDS regions.
 struct ScorePlan {
@@ -150,15 +171,9 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
       *(u32x4*)(qs + (size_t)blk * G::TILE_BYTES + (ch >> 2) * 1024 + ((ch & 3) * 16 + rr) * 16) = v;
     }
     auto store_offset = [&](int x, float m, float s) {
-      const int h = head_of(x), k = k_of(x);
-      float hi = -INFINITY, lo = 0.f;
-      if (h < g && k < w) {
-        const double off = 3.0 - ((double)m + log2((double)s));
-        hi = (float)off;
-        lo = (float)(off - (double)hi);
-      }
-      row_hi[x] = hi;
-      row_lo[x] = lo;
+      const float2 c = row_offset(head_of(x) < g && k_of(x) < w, m, s);
+      row_hi[x] = c.x;
+      row_lo[x] = c.y;
     };
     if constexpr (HAVE_STATS) {
       for (int x = tid; x < rows; x += NW * 64) {
@@ -189,7 +204,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
         for (int i = 0; i < NB; ++i)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            rm[i][e] = -1e30f; rs[i][e] = 0.f;
+            rm[i][e] = GKV_NO_MAX; rs[i][e] = 0.f;
             last_vis[i][e] = cc + k_of(16 * min(b0 + i, n_blocks - 1) + 4 * kb + e);
           }
         for (int t = wave; t < n_tiles; t += NW) {
@@ -206,7 +221,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
             for (int e = 0; e < 4; ++e) {
               // a key the row did not see has the logit -inf: it never becomes the maximum and adds 0
               if (!full && key > last_vis[i][e]) z[e] = -INFINITY;
-              const float tm = z[e] * s_hi;
+              const float tm = rounded_product(z[e], s_hi);
               if (__any(tm > rm[i][e])) {
                 const float mnew = fmaxf(rm[i][e], tm);
                 rs[i][e] *= __builtin_amdgcn_exp2f(rm[i][e] - mnew);
@@ -248,6 +263,47 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
 
     // ---- scores of this share's candidates ------------------------------------------------------
     const float mean = 0x1p-3f / (float)w;
+    // S of tile t from this lane's sum over its window rows
+    auto finish = [&](float tot, int t) {
+      float sv = tot + __shfl_xor(tot, 16);
+      if (!pair) sv += __shfl_xor(sv, 32);
+      const int key = 16 * t + r;
+      if (kb == 0 && key < cc) {
+        sv *= mean;
+        if (pass) sv += sbuf[key];                             // this lane's own value of the pass before
+        if (pl.use_sbuf) sbuf[key] = sv;
+        if (pass == n_pass - 1) So[key] = sv;
+      }
+    };
+    bool huge = false;
+    for (int x = lane; x < rows; x += 64) huge |= huge_offset(row_hi[x]);
+    if (__any(huge)) {
+      // seldom: a tile at a time, by the wavefront that has it in the other passes too
+      for (int t = (g0 + wave) * KT; t < g1 * KT; t = t % KT == KT - 1 ? t + (NW - 1) * KT + 1 : t + 1) {
+        u32x4 kT[NL];
+        load_k_tile<T, D>(kT, Kh, t, seq.n_tiled, lane, r, kb);
+        float tot = 0.f;
+#pragma unroll 1
+        for (int nt = 0; nt < nts; ++nt) {
+          f32x4 ymax = {-1e30f, -1e30f, -1e30f, -1e30f};
+#pragma unroll 1
+          for (int blk = nt * pl.n_blk; blk < (nt + 1) * pl.n_blk; ++blk) {
+            u32x4 q[NL];
+            load_q(q, blk);
+            const f32x4 z = logits<T, NL>(q, kT);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              const int x = blk * 16 + 4 * kb + e;
+              ymax[e] = fmaxf(ymax[e], log2_score<true>(z[e], s_hi, s_lo, row_hi[x], row_lo[x]));
+            }
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) tot += __builtin_amdgcn_exp2f(pair ? fmaxf(ymax[e], __shfl_xor(ymax[e], 32)) : ymax[e]);
+        }
+        finish(tot, t);
+      }
+      continue;
+    }
     u32x4 kA[KT][NL], kN[KT][NL];
     auto load_group = [&](u32x4 (&k)[KT][NL], int p) {
 #pragma unroll
@@ -276,7 +332,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
             const f32x4 z = logits<T, NL>(q, kA[tt]);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              ymax[tt][e] = fmaxf(ymax[tt][e], fmaf(z[e], s_hi, c_hi[e]) + fmaf(z[e], s_lo, c_lo[e]));
+              ymax[tt][e] = fmaxf(ymax[tt][e], log2_score<false>(z[e], s_hi, s_lo, c_hi[e], c_lo[e]));
           }
         }
 #pragma unroll
@@ -290,17 +346,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
         }
       }
 #pragma unroll
-      for (int tt = 0; tt < KT; ++tt) {
-        float sv = tot[tt] + __shfl_xor(tot[tt], 16);
-        if (!pair) sv += __shfl_xor(sv, 32);
-        const int key = 16 * (p * KT + tt) + r;
-        if (kb == 0 && key < cc) {
-          sv *= mean;
-          if (pass) sv += sbuf[key];                           // this lane's own value of the pass before
-          if (pl.use_sbuf) sbuf[key] = sv;
-          if (pass == n_pass - 1) So[key] = sv;
-        }
-      }
+      for (int tt = 0; tt < KT; ++tt) finish(tot[tt], p * KT + tt);
 #pragma unroll
       for (int tt = 0; tt < KT; ++tt)
 #pragma unroll
@@ -404,48 +450,16 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   Tile<T, D> kA, kN;
   if (g0 + wave < g1) load_k_tile<T, D, ONCE>(kA, Kh, g0 + wave, seq.n_tiled, lane, r, kb);
   if (tid < NT * NB * 16) {
-    const double off = 3.0 - ((double)ms.x + log2((double)ms.y));
-    const float hi = (float)off;
-    row_c[tid] = row_valid ? make_float2(hi, (float)(off - (double)hi)) : make_float2(-INFINITY, 0.f);
+    row_c[tid] = row_offset(row_valid, ms.x, ms.y);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the queries are in LDS
   __syncthreads();
   if (g0 >= g1) return;
-  float c_hi[NT * NB], c_lo[NT * NB];
-#pragma unroll
-  for (int b = 0; b < NT * NB; ++b) {
-    const float2 c = row_c[16 * b + r];
-    c_hi[b] = c.x; c_lo[b] = c.y;
-  }
-  u32x4 q[NT * NB][NL];
-#pragma unroll
-  for (int b = 0; b < NT * NB; ++b)
-#pragma unroll
-    for (int c = 0; c < NL; ++c) q[b][c] = *(const u32x4*)(qs + (b * NL + c) * 1024 + lane * 16);
-
   const float s_hi = dm.scale_l2_hi, s_lo = dm.scale_l2_lo;
   const float mean = 0x1p-3f / (float)w;
   float* So = a.S + (size_t)unit * cap;
-  auto tile = [&](const Tile<T, D>& kT, int t) {
-    f32x4 tot = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      f32x4 ymax = {-1e30f, -1e30f, -1e30f, -1e30f};
-#pragma unroll
-      for (int i = 0; i < NB; ++i) {
-        const int b = nt * NB + i;
-        const f32x4 z = logits<T, NL>(kT, q[b]);           // lane (row r, kb): keys 4 kb + e
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          ymax[e] = fmaxf(ymax[e], fmaf(z[e], s_hi, c_hi[b]) + fmaf(z[e], s_lo, c_lo[b]));
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float y = ymax[e];
-        if (pair) y = fmaxf(y, GKV_DPP_F(y, 0x128));       // row_ror:8: the block's other head
-        tot[e] += __builtin_amdgcn_exp2f(y);
-      }
-    }
+  // S of tile t from tot[e], the sum over the sixteens of window rows of row r's probability of key 4 kb + e
+  auto finish = [&](const f32x4& tot, int t) {
     // Sum of tot[e] over the 16 lanes of a quarter (over 8 of them with two heads in a block: both
     // halves hold the same then): two exchange-and-add steps leave value e = r % 4 of a quad in each
     // lane, rotations by 4 and 8 add the quads.
@@ -461,6 +475,39 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
     const int key = 16 * t + 4 * kb + r;
     if (r < 4 && key < cc) So[key] = sv * mean;
   };
+  float c_hi[NT * NB], c_lo[NT * NB];
+#pragma unroll
+  for (int b = 0; b < NT * NB; ++b) {
+    const float2 c = row_c[16 * b + r];
+    c_hi[b] = c.x; c_lo[b] = c.y;
+  }
+  u32x4 q[NT * NB][NL];
+#pragma unroll
+  for (int b = 0; b < NT * NB; ++b)
+#pragma unroll
+    for (int c = 0; c < NL; ++c) q[b][c] = *(const u32x4*)(qs + (b * NL + c) * 1024 + lane * 16);
+  auto tile = [&](const Tile<T, D>& kT, int t) {
+    f32x4 tot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      f32x4 ymax = {-1e30f, -1e30f, -1e30f, -1e30f};
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const int b = nt * NB + i;
+        const f32x4 z = logits<T, NL>(kT, q[b]);           // lane (row r, kb): keys 4 kb + e
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          ymax[e] = fmaxf(ymax[e], log2_score<false>(z[e], s_hi, s_lo, c_hi[b], c_lo[b]));
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float y = ymax[e];
+        if (pair) y = fmaxf(y, GKV_DPP_F(y, 0x128));       // row_ror:8: the block's other head
+        tot[e] += __builtin_amdgcn_exp2f(y);
+      }
+    }
+    finish(tot, t);
+  };
   // two tiles in turn: the next one is always requested before one is worked on, and stays where it lands
   // (copied over at the end of each round instead: 121 -> 117 us at 1792 units of b = 1024)
   for (int t = g0 + wave; t < g1; t += 2 * NW) {
@@ -469,6 +516,35 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
     if (t + NW >= g1) break;
     load_k_tile<T, D, ONCE>(kA, Kh, min(t + 2 * NW, g1 - 1), seq.n_tiled, lane, r, kb);
     tile(kN, t + NW);
+  }
+  bool huge = false;
+#pragma unroll
+  for (int x = 0; x < NT * NB * 16; x += 64) huge |= huge_offset(row_c[min(x + lane, NT * NB * 16 - 1)].x);
+  if (__any(huge)) {
+    // seldom: block by block from LDS, a tile at a time, over what the loop above stored
+    for (int t = g0 + wave; t < g1; t += NW) {
+      Tile<T, D> kT;
+      load_k_tile<T, D>(kT, Kh, t, seq.n_tiled, lane, r, kb);
+      f32x4 tot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int nt = 0; nt < NT; ++nt) {
+        f32x4 ymax = {-1e30f, -1e30f, -1e30f, -1e30f};
+#pragma unroll 1
+        for (int b = nt * NB; b < (nt + 1) * NB; ++b) {
+          u32x4 qb[NL];
+#pragma unroll
+          for (int c = 0; c < NL; ++c) qb[c] = *(const u32x4*)(qs + (b * NL + c) * 1024 + lane * 16);
+          const float2 c = row_c[16 * b + r];
+          const f32x4 z = logits<T, NL>(kT, qb);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ymax[e] = fmaxf(ymax[e], log2_score<true>(z[e], s_hi, s_lo, c.x, c.y));
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          tot[e] += __builtin_amdgcn_exp2f(pair ? fmaxf(ymax[e], GKV_DPP_F(ymax[e], 0x128)) : ymax[e]);
+      }
+      finish(tot, t);
+    }
   }
 }
 

@@ -103,6 +103,29 @@ def test_attend_logits_of_minus_infinity(dtype, d, g, cap, params):
         assert (err <= _bound(dtype, d, ref, Vi[:, : n + 1])).all(), (n, err.max())
 
 
+@pytest.mark.parametrize("size", [1e9, -1e9, 3e33, -3e33])
+@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
+def test_attend_huge_logits(dtype, d, g, cap, params, size):
+    # finite logits of any size: keys are multiples of one vector, so every logit is a known share of the
+    # largest (whichever its sign) and the softmax is one-hot; the output is that key's V, to the bit
+    lens = [1, 17, 33, 65, 250, cap - 1]
+    st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 64, seed=19, params=params)
+    q = q.abs() + 0.125
+    u = torch.rand(d, generator=torch.Generator().manual_seed(4)) + 0.5
+    best = []
+    for i, n in enumerate(lens):
+        mult = (torch.randperm(n + 1, generator=torch.Generator().manual_seed(i)) % 32 + 2) * 0.5     # 1 .. 16.5
+        top = (7 * i) % (n + 1)                               # one that stands out: 20 if positive, 0.25 if negative
+        mult[top] = 20.0 if size > 0 else 0.25
+        rows = (mult[:, None] * size * u).to(q.dtype)
+        K[0, i, :, :n], kn[0, i] = rows[:n], rows[n]
+        st.K[0, i] = k_rows_to_cache(K[0, i], min(64, n // 16 * 16)).cuda()
+        best.append(vn[0, i] if top == n else V[0, i, :, top])
+    out = st.attend_decode(q.cuda(), kn.cuda(), vn.cuda(), 5).cpu()
+    for i, n in enumerate(lens):
+        assert torch.equal(out[0, i].view(2, g, d), best[i][:, None].expand(2, g, d)), n
+
+
 @pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
 def test_attend_infinite_values(dtype, d, g, cap, params):
     # an infinite value with a weight above zero makes its channel infinite, two of opposite sign NaN, and
@@ -176,7 +199,7 @@ def test_whole_path_fp32_and_head_dim_64(over):
 
 
 # ---- window score -----------------------------------------------------------------------------
-def _check_window_score(dtype, d, g, w, params, reuse, scale=0.0, hidden=False):
+def _check_window_score(dtype, d, g, w, params, reuse, scale=0.0, hidden=False, size=None):
     cap, b = 320, 48
     lens = [b + 1, b + 15, b + 17, 100, 127, 160, 161, cap]           # rows the compression sees
     lens = [max(n, w + 1) for n in lens]
@@ -189,6 +212,11 @@ def _check_window_score(dtype, d, g, w, params, reuse, scale=0.0, hidden=False):
     if hidden:                                                          # logits of -inf, for some keys of candidates and window
         q = q.abs() + 0.125
         K[..., 1::3, 3] = -float("inf")
+    if size:                    # logits that are known shares of the largest one: one-hot window rows, in or out of the candidates
+        q = q.abs() + 0.125
+        mult = torch.arange(cap, dtype=torch.float32) % 37 * 0.25 + 1.0
+        mult[[11, 30]] = torch.tensor([20.0, 0.25])
+        K[:] = (mult[:, None] * size * (torch.rand(d, generator=gen) + 0.5)).to(K.dtype)
     n_tiled = [(n - w) // 32 * 16 for n in lens]                        # some of the candidate tiles are row-major
     t0 = 7
     for i, n in enumerate(lens):
@@ -249,6 +277,14 @@ def test_window_score_own_statistics_other_scales(dtype, d, g, w, scale):
 def test_window_score_logits_of_minus_infinity(dtype, d, g, w, reuse):
     # probability 0 for those keys, with the statistics recorded by the decode calls and with its own
     _check_window_score(dtype, d, g, w, None, reuse, hidden=True)
+
+
+@pytest.mark.parametrize("size", [1e9, -1e9, 3e33, -3e33])
+@pytest.mark.parametrize("reuse", [1, 0])
+@pytest.mark.parametrize("dtype,d,g,w", [("bf16", 128, 7, 16), ("bf16", 64, 5, 8), ("f32", 128, 3, 16), ("f32", 64, 2, 24)])
+def test_window_score_huge_logits(dtype, d, g, w, reuse, size):
+    # every window row has one key of probability 1 (row 11 for positive logits, row 30 for negative)
+    _check_window_score(dtype, d, g, w, None, reuse, size=size)
 
 
 # ---- units cut over several workgroups ----------------------------------------------------------
