@@ -110,11 +110,16 @@ const char* gkv_status_string(gkv_status st);
 
 /* Bytes of device workspace the calls below need for this context with the tuning knobs as they
  * are now; the context remembers the "attend_splits" value the size covers, and
- * gkv_attend_decode returns GKV_ERR_WORKSPACE if the knob was raised afterwards.  Calls that may
- * overlap in time need a workspace each: it holds counters and partial results of the call. */
+ * gkv_attend_decode returns GKV_ERR_WORKSPACE if the knob was raised afterwards.
+ * A workspace may be shared by gkv_attend_decode calls of one context that overlap in time (other
+ * streams, other buffers): a call that the library cuts over several workgroups by its own choice has
+ * its partial results in a set of its stream's, or of its capture's if it is recorded.  There are sets
+ * for the first 8 streams and captures a context meets; calls on others, and calls whose workspace was not
+ * prepared by gkv_workspace_init of the same context, are not cut (slower, and summed in another
+ * order).  Calls cut by "attend_splits" and compressions that may overlap need a workspace each. */
 gkv_status gkv_workspace_bytes(gkv_ctx* ctx, size_t* out_bytes);
 /* Enqueues a fill kernel that zeroes the workspace's counters (one per unit, used when a
- * unit's attention is split over several workgroups; one per (layer, sequence), used by the
+ * unit's attention is split over several workgroups, in every set; one per (layer, sequence), used by the
  * compaction to find the workgroup that finishes last).  The kernels leave them at zero.
  * Call once, before the first call that takes the workspace. */
 gkv_status gkv_workspace_init(gkv_ctx* ctx, void* workspace, void* stream);

@@ -109,6 +109,8 @@ extern "C" gkv_status gkv_create(const gkv_config* cfg, gkv_ctx** out_ctx) {
   c->attend_splits = 0;
   c->ws_splits = 1;
   c->ws_auto_splits = 1;
+  c->split_ws = nullptr;
+  c->n_split_keys = 0;
   c->attend_tile = 16;
   c->force_generic = 0;
   c->reuse_stats = 1;
@@ -217,26 +219,34 @@ static size_t ws_partials_bytes(const gkv_ctx* ctx, int splits) {
   return units * splits * ctx->dims.g * (ctx->dims.d + 2) * sizeof(float);
 }
 
-GkvWorkspace gkv_carve_workspace(const gkv_ctx* ctx, void* base) {
+// Sets for the library's own cuts (attend_plan cuts up to 128 units); the set of "attend_splits" follows them.
+static int auto_sets(const gkv_ctx* ctx) {
+  return ctx->mfma_shape && (int64_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv <= 128 ? GKV_SPLIT_SETS : 0;
+}
+static size_t ws_ticket_bytes(const gkv_ctx* ctx) {
+  const size_t units = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
+  return gkv_align256(units * (auto_sets(ctx) + 1) * 4);
+}
+
+GkvWorkspace gkv_carve_workspace(const gkv_ctx* ctx, void* base, int split_set) {
   GkvWorkspace w;
   char* p = (char*)base;
   const size_t units = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
-  w.split_ticket = (int32_t*)p; p += gkv_align256(units * 4);
+  w.split_ticket = (int32_t*)p + split_set * units; p += ws_ticket_bytes(ctx);
   w.state_ticket = (int32_t*)p; p += gkv_align256((size_t)ctx->dims.L * ctx->dims.B * 4);
   w.stats = (float2*)p; p += gkv_align256(ws_stats_bytes(ctx));
-  w.partials = (float*)p;
+  w.partials = (float*)(p + split_set * ws_partials_bytes(ctx, ctx->ws_auto_splits));
   return w;
 }
 
 extern "C" gkv_status gkv_workspace_bytes(gkv_ctx* ctx, size_t* out_bytes) {
   if (!ctx || !out_bytes) return GKV_ERR_INVALID_ARG;
-  const size_t units = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
   // the workspace is sized for the split counts in force now: the decode call refuses a larger one
   // that was asked for, and does without one of its own choice
   ctx->ws_splits = explicit_splits(ctx);
   ctx->ws_auto_splits = ctx->mfma_shape && !ctx->force_generic ? attend_plan(ctx, 0).splits : 1;
-  const size_t automatic = ws_partials_bytes(ctx, ctx->ws_auto_splits);
-  *out_bytes = gkv_align256(units * 4) + gkv_align256((size_t)ctx->dims.L * ctx->dims.B * 4) +
+  const size_t automatic = auto_sets(ctx) * ws_partials_bytes(ctx, ctx->ws_auto_splits);
+  *out_bytes = ws_ticket_bytes(ctx) + gkv_align256((size_t)ctx->dims.L * ctx->dims.B * 4) +
                gkv_align256(ws_stats_bytes(ctx)) +
                gkv_align256(automatic + ws_partials_bytes(ctx, ctx->ws_splits)) + 256;
   return GKV_OK;
@@ -245,9 +255,10 @@ extern "C" gkv_status gkv_workspace_bytes(gkv_ctx* ctx, size_t* out_bytes) {
 extern "C" gkv_status gkv_workspace_init(gkv_ctx* ctx, void* workspace, void* stream) {
   if (!ctx) return GKV_ERR_INVALID_ARG;
   if (!workspace) return GKV_ERR_WORKSPACE;
-  const size_t units = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
-  const size_t n = (gkv_align256(units * 4) + gkv_align256((size_t)ctx->dims.L * ctx->dims.B * 4)) / 4;   // both ticket arrays
-  return gkv_launch_fill_zero((hipStream_t)stream, (int32_t*)workspace, n) == hipSuccess ? GKV_OK : GKV_ERR_HIP;
+  const size_t n = (ws_ticket_bytes(ctx) + gkv_align256((size_t)ctx->dims.L * ctx->dims.B * 4)) / 4;   // both ticket arrays
+  if (gkv_launch_fill_zero((hipStream_t)stream, (int32_t*)workspace, n) != hipSuccess) return GKV_ERR_HIP;
+  ctx->split_ws = workspace;
+  return GKV_OK;
 }
 
 extern "C" gkv_status gkv_cache_bytes(const gkv_config* cfg, int32_t rows, int32_t score_elem_bytes,
@@ -354,6 +365,31 @@ static bool stats_cover_window(const gkv_ctx* ctx, int32_t step, const void* ws,
   return true;
 }
 
+// What distinguishes calls that follow each other on the GPU from calls that may overlap.  false: unknown
+// (the per-thread default stream is another stream in every thread).
+static bool stream_key(hipStream_t stream, GkvStreamKey* key) {
+  if (stream == hipStreamPerThread) return false;
+  *key = GkvStreamKey{stream, 0};
+  if (stream == nullptr) return true;                    // the legacy stream cannot be captured
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  if (hipStreamGetCaptureInfo(stream, &status, &id) != hipSuccess) { (void)hipGetLastError(); return false; }
+  if (status == hipStreamCaptureStatusInvalidated) return false;
+  if (status == hipStreamCaptureStatusActive) key->capture = id + 1;
+  return true;
+}
+
+// The set of the stream a cut decode call goes to, or -1: no set left, or not this context's workspace.
+static int split_set(gkv_ctx* ctx, const void* workspace, hipStream_t stream) {
+  GkvStreamKey key;
+  if (workspace != ctx->split_ws || !stream_key(stream, &key)) return -1;
+  for (int i = 0; i < ctx->n_split_keys; ++i)
+    if (ctx->split_key[i].stream == key.stream && ctx->split_key[i].capture == key.capture) return i;
+  if (ctx->n_split_keys == GKV_SPLIT_SETS) return -1;
+  ctx->split_key[ctx->n_split_keys] = key;
+  return ctx->n_split_keys++;
+}
+
 extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void* k_new, const void* v_new,
                                         void* K, void* V, int32_t* pos, int32_t step, void* qwin,
                                         const int32_t* d_state, int32_t len_max_host, void* out,
@@ -372,11 +408,14 @@ extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void*
   GkvLaunch ln{ctx, GKV_K_ATTEND, (hipStream_t)stream};
   if (use_mfma(ctx, {q, k_new, v_new, K, V, qwin, out})) {
     AttendPlan plan = attend_plan(ctx, ctx->attend_splits);
+    int set = auto_sets(ctx);                                       // "attend_splits"
     if (ctx->attend_splits > 0) {
       if (plan.splits > ctx->ws_splits) return GKV_ERR_WORKSPACE;   // partials would not fit the workspace as sized
-    } else if (plan.splits > ctx->ws_auto_splits) {
-      plan.splits = 1; plan.iters = 0;
+    } else if (plan.splits > 1) {
+      set = plan.splits > ctx->ws_auto_splits ? -1 : split_set(ctx, workspace, (hipStream_t)stream);
+      if (set < 0) { plan = attend_plan(ctx, 1); set = 0; }         // not cut
     }
+    a.ws = gkv_carve_workspace(ctx, workspace, set);
     a.waves = plan.waves; a.splits = plan.splits; a.split_iters = plan.iters;
     // An appending step leaves (max, sum) of every query head's softmax in the ring slot
     // of this step; the window score can then skip its own pass over the keys for them.

@@ -25,6 +25,13 @@ struct GkvDims {
 
 struct GkvProfile;   // event pools, defined in gkv_api.hip
 
+// Decode calls that the library cuts by its own choice use one of this many sets of tickets and partial
+// results in the workspace, by the stream they are enqueued on: calls on one stream follow each other,
+// calls on different ones may overlap.  A recorded call runs later than what is enqueued on its stream
+// now, so each capture counts as a stream of its own.
+constexpr int GKV_SPLIT_SETS = 8;
+struct GkvStreamKey { const void* stream; unsigned long long capture; };
+
 struct gkv_ctx {
   gkv_config cfg;
   GkvDims dims;
@@ -32,6 +39,9 @@ struct gkv_ctx {
   int32_t attend_splits;  // 0 = automatic
   int32_t ws_splits;      // "attend_splits" the workspace was sized for by gkv_workspace_bytes (1 = no partials)
   int32_t ws_auto_splits; // the same for the library's own choice
+  const void* split_ws;   // workspace whose tickets gkv_workspace_init of this context zeroed
+  int32_t n_split_keys;   // streams that have a set so far; they keep it for the context's life, recorded calls being replayed at any time
+  GkvStreamKey split_key[GKV_SPLIT_SETS];
   int32_t attend_tile;    // keys per wavefront iteration of the matrix-core attend kernel: 16 or 32
   int32_t force_generic;
   int32_t attend_waves;   // 0 = automatic
@@ -50,13 +60,15 @@ struct gkv_ctx {
 };
 
 // Workspace layout (bytes from the base):
-//   [0, 4*units)                    split tickets (int32, self-resetting)
+//   [0, 4*units*sets)               split tickets (int32, self-resetting); sets = GKV_SPLIT_SETS and one for
+//                                   "attend_splits", or the latter alone where the library never cuts
+//   [.., + 4*L*B)                   compaction tickets
 //   [.., + 8*w*L*B*h_q)             softmax statistics ring: per (slot, layer, sequence, query head)
 //                                   the running max (log2 units) and the sum of the decode step
 //                                   whose q sits in that slot of the window ring
-//   [.., + 4*units*splits*g*(d+2))  split-K partials (float)
+//   [.., + 4*units*splits*g*(d+2) per set)  split-K partials (float)
 struct GkvWorkspace {
-  int32_t* split_ticket;
+  int32_t* split_ticket;  // of the call's set, as partials
   int32_t* state_ticket;  // [L*B]: compaction workgroups of a (layer, sequence) that have finished; zero between launches
   float2* stats;
   float* partials;
@@ -66,7 +78,7 @@ static inline size_t gkv_align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 constexpr size_t GKV_LDS_LIMIT = 65536;
 size_t gkv_max_lds_bytes(const gkv_config* cfg);
-GkvWorkspace gkv_carve_workspace(const gkv_ctx* ctx, void* base);
+GkvWorkspace gkv_carve_workspace(const gkv_ctx* ctx, void* base, int split_set = 0);
 
 // Launch record for profiling: the wrappers launch through gkv_launch() below.
 struct GkvLaunch {

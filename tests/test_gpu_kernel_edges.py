@@ -296,7 +296,7 @@ def test_attend_cut_over_workgroups(dtype, d, g, cap):
     st, *t = _attend_state(dtype, d, g, lens, cap, 64, seed=d)
     for _ in range(2):
         _check_attend(st, *t, lens, dtype, d, append=True)
-        tickets = st.workspace[: 4 * 2 * len(lens)].view(torch.int32)
+        tickets = st.workspace[: 4 * 2 * len(lens) * 9].view(torch.int32)    # 8 sets and that of "attend_splits"
         assert int(tickets.abs().sum()) == 0                                # back at zero for the next call
         st.len_host = max(lens)
     # a context that never asked for the workspace's size does without the partials: same result
@@ -307,6 +307,85 @@ def test_attend_cut_over_workgroups(dtype, d, g, cap):
     b = st.attend_decode(t[2].cuda(), t[3].cuda(), t[4].cuda(), 5)
     tol = 1e-5 if dtype == "f32" else 2.0 ** -7
     np.testing.assert_allclose(a.double().cpu().numpy(), b.double().cpu().numpy(), rtol=tol, atol=tol)
+
+
+# One context and one workspace, several streams with buffers of their own: decode calls that the library
+# cuts by its own choice stay independent.
+def _call(st, ctx, ws, q, kn, vn, out, t=5):
+    ctx.attend_decode(q, kn, vn, st.K, st.V, st.pos, t, st.qwin, st.d_state, 1000, out, ws)
+
+
+def _two_users(dtype="bf16", d=128, g=7, cap=1056):
+    users = []
+    for seed in (21, 22):
+        st, K, V, q, kn, vn = _attend_state(dtype, d, g, [1000, 700, 930], cap, 512, seed=seed)
+        users.append((st, q.cuda(), kn.cuda(), vn.cuda()))
+    torch.cuda.synchronize()
+    return users
+
+
+def test_cut_calls_of_different_streams_have_partial_results_of_their_own():
+    # without a new row a call changes nothing in the workspace but partial results: what the first
+    # stream's call left there is still there after the other's, and after a recorded one's
+    (a, qa, _, _), (b, qb, _, _) = _two_users()
+    ctx, ws = a.ctx, a.workspace
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    before = ws.clone()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(streams[0]):
+        _call(a, ctx, ws, qa, None, None, a.out)
+    torch.cuda.synchronize()
+    mine = ws != before
+    assert int(mine.sum()) > 0                                              # it was cut
+    held = ws.clone()
+    with torch.cuda.stream(streams[1]):
+        _call(b, ctx, ws, qb, None, None, b.out)
+    torch.cuda.synchronize()
+    assert torch.equal(ws[mine], held[mine]) and not torch.equal(ws, held)
+    held = ws.clone()
+    graph = torch.cuda.CUDAGraph()
+    streams[1].wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=streams[1]):                        # a capture on a stream that has a set
+        _call(b, ctx, ws, qb, None, None, b.out)
+    want = b.out.clone()
+    for _ in range(3):
+        b.out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(b.out, want)
+    changed = held != before
+    assert torch.equal(ws[changed], held[changed]) and not torch.equal(ws, held)
+
+
+@pytest.mark.parametrize("dtype,d,g", [("bf16", 128, 7), ("f32", 128, 7), ("bf16", 64, 5), ("f32", 64, 2)])
+def test_overlapping_decode_calls_share_a_workspace(dtype, d, g):
+    users = _two_users(dtype, d, g)
+    ctx, ws = users[0][0].ctx, users[0][0].workspace
+    want = []
+    for st, q, kn, vn in users:                                             # one after the other
+        _call(st, ctx, ws, q, kn, vn, st.out)
+        torch.cuda.synchronize()
+        want.append(st.out.clone())
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    for _ in range(20):
+        outs = [[torch.zeros_like(st.out) for _ in range(10)] for st, *_ in users]
+        torch.cuda.synchronize()
+        for i in range(10):
+            for (st, q, kn, vn), stream, out in zip(users, streams, outs):
+                with torch.cuda.stream(stream):
+                    _call(st, ctx, ws, q, kn, vn, out[i])
+        torch.cuda.synchronize()
+        for got, ref in zip(outs, want):
+            assert all(torch.equal(x, ref) for x in got)
+    # more streams than there are sets: not cut, the same up to the order of the sums
+    st, q, kn, vn = users[0]
+    for stream in [torch.cuda.Stream() for _ in range(10)]:
+        stream.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(stream):
+            _call(st, ctx, ws, q, kn, vn, st.out)
+        torch.cuda.synchronize()
+        tol = 1e-5 if dtype == "f32" else 2.0 ** -7
+        np.testing.assert_allclose(st.out.double().cpu().numpy(), want[0].double().cpu().numpy(), rtol=tol, atol=tol)
 
 
 def test_window_score_reuses_statistics_of_cut_units():
