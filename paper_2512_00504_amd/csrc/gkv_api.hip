@@ -122,6 +122,8 @@ extern "C" gkv_status gkv_create(const gkv_config* cfg, gkv_ctx** out_ctx) {
   if (!c->stats_step) { delete c; return GKV_ERR_INVALID_ARG; }
   for (int i = 0; i < cfg->window; ++i) c->stats_step[i] = -1;
   c->stats_ws = c->stats_K = c->stats_qwin = nullptr;
+  c->stats_key = GkvStreamKey{nullptr, 0};
+  c->stats_mixed = false;
   c->mfma_redundancy = cfg->dtype == GKV_BF16 && d.d == 128 && d.g <= 16;
   c->mfma_shape = (d.d == 64 || d.d == 128) && d.g <= 16;
   c->prof = new (std::nothrow) GkvProfile();
@@ -344,27 +346,6 @@ static gkv_status check_len(const gkv_ctx* ctx, int32_t len_max_host, bool appen
 }
 static inline gkv_status hip_status(hipError_t e) { return e == hipSuccess ? GKV_OK : GKV_ERR_HIP; }
 
-// Host bookkeeping of the statistics ring: which decode step each slot's statistics belong to,
-// and for which buffers.  Everything is stream-ordered, so "enqueued" is as good as "written".
-static void note_stats(gkv_ctx* ctx, int32_t step, bool written, const void* ws, const void* K, const void* qwin) {
-  const int w = ctx->dims.w;
-  if (ws != ctx->stats_ws || K != ctx->stats_K || qwin != ctx->stats_qwin) {
-    for (int i = 0; i < w; ++i) ctx->stats_step[i] = -1;
-    ctx->stats_ws = ws; ctx->stats_K = K; ctx->stats_qwin = qwin;
-  }
-  ctx->stats_step[step % w] = written ? step : -1;
-}
-static bool stats_cover_window(const gkv_ctx* ctx, int32_t step, const void* ws, const void* K, const void* qwin) {
-  const int w = ctx->dims.w;
-  if (!ctx->reuse_stats || !ws || ws != ctx->stats_ws || K != ctx->stats_K || qwin != ctx->stats_qwin) return false;
-  if (step + 1 < w) return false;
-  for (int k = 0; k < w; ++k) {
-    const int t = step - w + 1 + k;
-    if (ctx->stats_step[t % w] != t) return false;
-  }
-  return true;
-}
-
 // What distinguishes calls that follow each other on the GPU from calls that may overlap.  false: unknown
 // (the per-thread default stream is another stream in every thread).
 static bool stream_key(hipStream_t stream, GkvStreamKey* key) {
@@ -376,6 +357,35 @@ static bool stream_key(hipStream_t stream, GkvStreamKey* key) {
   if (hipStreamGetCaptureInfo(stream, &status, &id) != hipSuccess) { (void)hipGetLastError(); return false; }
   if (status == hipStreamCaptureStatusInvalidated) return false;
   if (status == hipStreamCaptureStatusActive) key->capture = id + 1;
+  return true;
+}
+
+// Host bookkeeping of the statistics ring: which decode step each slot's statistics belong to,
+// and for which buffers.  Calls on the same buffers are ordered by the caller, so "enqueued" is as good as
+// "written".  Calls on other buffers and another stream need not be: what they write to the ring may
+// land at any time, and from then on nothing is taken from it.
+static void note_stats(gkv_ctx* ctx, int32_t step, bool written, const void* ws, const void* K, const void* qwin,
+                       hipStream_t stream) {
+  const int w = ctx->dims.w;
+  GkvStreamKey key;
+  const bool known = stream_key(stream, &key);
+  const bool same_stream = known && key.stream == ctx->stats_key.stream && key.capture == ctx->stats_key.capture;
+  ctx->stats_key = known ? key : GkvStreamKey{hipStreamPerThread, 0};   // never equal to a known one
+  if (ws != ctx->stats_ws || K != ctx->stats_K || qwin != ctx->stats_qwin) {
+    if (ctx->stats_ws && !same_stream) ctx->stats_mixed = true;
+    for (int i = 0; i < w; ++i) ctx->stats_step[i] = -1;
+    ctx->stats_ws = ws; ctx->stats_K = K; ctx->stats_qwin = qwin;
+  }
+  ctx->stats_step[step % w] = written ? step : -1;
+}
+static bool stats_cover_window(const gkv_ctx* ctx, int32_t step, const void* ws, const void* K, const void* qwin) {
+  const int w = ctx->dims.w;
+  if (!ctx->reuse_stats || ctx->stats_mixed || !ws || ws != ctx->stats_ws || K != ctx->stats_K || qwin != ctx->stats_qwin) return false;
+  if (step + 1 < w) return false;
+  for (int k = 0; k < w; ++k) {
+    const int t = step - w + 1 + k;
+    if (ctx->stats_step[t % w] != t) return false;
+  }
   return true;
 }
 
@@ -420,10 +430,10 @@ extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void*
     // An appending step leaves (max, sum) of every query head's softmax in the ring slot
     // of this step; the window score can then skip its own pass over the keys for them.
     a.write_stats = k_new != nullptr;
-    note_stats(ctx, step, a.write_stats != 0, workspace, K, qwin);
+    note_stats(ctx, step, a.write_stats != 0, workspace, K, qwin, (hipStream_t)stream);
     return hip_status(gkv_launch_attend_mfma(ln, ctx->dims, ctx->cfg.dtype, a));
   }
-  note_stats(ctx, step, false, workspace, K, qwin);
+  note_stats(ctx, step, false, workspace, K, qwin, (hipStream_t)stream);
   return hip_status(gkv_launch_attend_generic(ln, ctx->dims, ctx->cfg.dtype, a));
 }
 

@@ -57,6 +57,8 @@ struct gkv_ctx {
   // exactly these buffers.
   int32_t* stats_step;    // [w]
   const void* stats_ws; const void* stats_K; const void* stats_qwin;
+  GkvStreamKey stats_key;   // stream of the last decode call
+  bool stats_mixed;         // the context has decoded other buffers on other streams
 };
 
 // Workspace layout (bytes from the base):

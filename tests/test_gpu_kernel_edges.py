@@ -388,6 +388,45 @@ def test_overlapping_decode_calls_share_a_workspace(dtype, d, g):
         np.testing.assert_allclose(st.out.double().cpu().numpy(), want[0].double().cpu().numpy(), rtol=tol, atol=tol)
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("other_stream", [True, False])
+def test_recorded_statistics_of_another_stream_are_not_trusted(dtype, d, other_stream):
+    # a decode call on other buffers and another stream may write its statistics at any time; here what
+    # it would write is put there by hand after the window's calls.  On one stream the record is used.
+    w, b, cap = 4, 40, 96
+    st = [DecodeState(make_config(1, 2, 4, 2, d, b, w, 8, cap, dtype)) for _ in range(2)]
+    ctx, ws = st[0].ctx, st[0].workspace
+    gen = torch.Generator().manual_seed(5)
+    rnd = lambda *s: torch.randn(*s, generator=gen).to(st[0].K.dtype)
+    K, q, kn = rnd(1, 2, 2, cap, d), rnd(w, 1, 2, 4, d), rnd(w, 1, 2, 2, d)
+    for x in st:
+        x.K.copy_(K)
+        x.d_state.copy_(torch.tensor([60, 8, 0, 0], dtype=torch.int32).expand(1, 2, 4))
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    if not other_stream:
+        streams[0] = streams[1]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(streams[0]):
+        ctx.attend_decode(q[0].cuda(), None, None, st[0].K, st[0].V, st[0].pos, 8, st[0].qwin, st[0].d_state, 60, st[0].out, ws)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(streams[1]):
+        for i in range(w):
+            ctx.attend_decode(q[i].cuda(), kn[i].cuda(), kn[i].cuda(), st[1].K, st[1].V, st[1].pos, 8 + i, st[1].qwin,
+                              st[1].d_state, 60 + i, st[1].out, ws)
+        torch.cuda.synchronize()
+        ws.view(torch.float32).mul_(1.5)                                    # statistics; the counters are zero
+        ctx.score_window(st[1].qwin, st[1].K, st[1].d_state, 8 + w - 1, 60 + w, st[1].S, ws)
+        torch.cuda.synchronize()
+    S = st[1].S.double().cpu().numpy()
+    right = True
+    for i in range(2):
+        Ki = K[0, i].double().numpy().copy()
+        Ki[:, 60 : 60 + w] = kn[:, 0, i].permute(1, 0, 2).double().numpy()
+        ref = O.local_score(O.window_probs(q[:, 0, i].permute(1, 0, 2).double().numpy(), Ki, 60 + w), 2)[:, :60]
+        right &= bool((np.abs(S[0, i, :, :60] - ref) <= 1e-5 * ref + 1e-30).all())
+    assert right == other_stream
+
+
 def test_window_score_reuses_statistics_of_cut_units():
     # a cut unit's (max, sum) come from the workgroup that merges it: same score as without the record
     st, K, V, q, kn, vn = _attend_state("bf16", 128, 7, [1000, 700], 1056, 512, seed=9)
