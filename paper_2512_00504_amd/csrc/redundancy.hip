@@ -133,7 +133,12 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int 
 // wavefront fetches one tile of the next group while all four work on the current group, stores it
 // into the other half of a two-group ring, and one barrier per group hands the ring over.
 //
-// Dynamic LDS: double cs[cap]; double red[4]; double inv[cap]; float inv_f[cap]; then the ring, 2 groups x 4 tiles x 4 KiB
+// A column's own reciprocal norm is wanted until its sum is finished, so the sums take the norms' place: 12
+// bytes of LDS a row, and two workgroups fit a compute unit at every capacity (12 cap + 32 KiB: at most 78 KiB
+// of 160).  With both arrays (20 cap + 32 KiB) capacities above 2458 had one: 512 units of 2496 rows 1216 us,
+// of 2996 rows 1780 us, now 985 and 1456.
+//
+// Dynamic LDS: double cs[cap]; double red[4]; float inv_f[cap]; then the ring, 2 groups x 4 tiles x 4 KiB
 constexpr int RED_NC = 5;
 
 // Sum over the 16 lanes of a DPP row (lanes 16i .. 16i+15), left in every one of them: lanes ^1
@@ -163,9 +168,9 @@ __global__ __launch_bounds__(256) void redundancy_mfma_kernel(GkvDims dm, RedArg
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int unit = blockIdx.x, lb = unit / dm.Hkv;
   double* cs = (double*)smem;
+  double* inv = cs;                                      // until the column's sum is finished
   double* red = cs + dm.cap;
-  double* inv = red + 4;
-  float* inv_f = (float*)(inv + dm.cap);                 // the same rounded to fp32
+  float* inv_f = (float*)(red + 4);                      // the norms rounded to fp32
   char* ring = (char*)(inv_f + dm.cap);
   const SeqState st = load_state(a.d_state, lb);
   const int l = compression_length(st, a.step, dm.b, dm.w, dm.cap);
@@ -247,10 +252,10 @@ __global__ __launch_bounds__(256) void redundancy_mfma_kernel(GkvDims dm, RedArg
     double col[NC];
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc) {
-      const int J = min(J0 + cc, n_tiles - 1);
-      inv_j[cc] = inv[16 * J + r];
+      // a duplicate's norm may have given way to its sum already: its own column must not look
+      inv_j[cc] = J0 + cc < J_end ? inv[16 * (J0 + cc) + r] : 0.0;
       // C = dot * inv_k * inv_j >= tau  <=>  dot * inv_k >= tau / inv_j: one product per entry, the
-      // column's factor applied once to the sum (columns >= l have inv_j = 0 and are dropped below)
+      // column's factor applied once to the sum (columns >= l and duplicates have inv_j = 0 and are dropped below)
       thr[cc] = inv_j[cc] > 0.0 ? (float)(tau / inv_j[cc]) : 3e38f;
       col[cc] = 0.0;
     }
@@ -417,9 +422,8 @@ hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dty
                                  float eps, int32_t n_recent, float* R_norm, float* F_sel) {
   RedArgs a{K, d_state, step, F, lambda, tau, eps, n_recent, R_norm, F_sel};
   const int units = dm.L * dm.B * dm.Hkv;
-  const size_t shmem = sizeof(double) * (2 * (size_t)dm.cap + 4);
   if (mfma) {
-    const size_t with_ring = shmem + sizeof(float) * (size_t)dm.cap + RED_RING_BYTES;
+    const size_t with_ring = sizeof(double) * ((size_t)dm.cap + 4) + sizeof(float) * (size_t)dm.cap + RED_RING_BYTES;
     if (with_ring > 64 * 1024) {                         // beyond the default per-workgroup limit: opt in (a CU holds 160 KiB)
       const hipError_t e = hipFuncSetAttribute((const void*)redundancy_mfma_kernel,
                                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)with_ring);
@@ -433,6 +437,7 @@ hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dty
                      : dtype == GKV_F32 ? redundancy_f64_kernel<float, 64, 16> : redundancy_f64_kernel<uint16_t, 64, 16>;
     return gkv_launch(ln, kern, dim3(units), dim3(wide ? 512 : 1024), sizeof(double) * (2 * (size_t)dm.cap + 16), dm, a);
   }
+  const size_t shmem = sizeof(double) * (2 * (size_t)dm.cap + 4);
   if (dtype == GKV_F32)
     return gkv_launch(ln, redundancy_generic_kernel<float>, dim3(units), dim3(256), shmem, dm, a);
   return gkv_launch(ln, redundancy_generic_kernel<uint16_t>, dim3(units), dim3(256), shmem, dm, a);
