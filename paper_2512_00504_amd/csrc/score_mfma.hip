@@ -29,6 +29,8 @@
 // huge offset and add nothing.
 #include "gkv_internal.h"
 
+#include <type_traits>
+
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -78,6 +80,23 @@ __device__ __forceinline__ f32x4 logits(const u32x4 (&q)[NL], const u32x4 (&kA)[
     }
   }
   return acc;
+}
+
+// One logit into a lane's running maximum m (log2 units) and sum of a row; rescaled only when some lane's
+// maximum moved.  EXACT: right for every logit; without it (what is tried first, a fifth less work) logits of
+// -inf and maxima of huge size may leave a wrong sum, and stats_in_doubt tells.
+template <bool EXACT>
+__device__ __forceinline__ void add_to_stats(float z, float s_hi, float s_lo, float& m, float& sum) {
+  const float tm = rounded_product(z, s_hi);
+  if (__any(tm > m)) {
+    const float mnew = fmaxf(m, tm);
+    sum *= __builtin_amdgcn_exp2f(m - mnew);
+    m = mnew;
+  }
+  sum += __builtin_amdgcn_exp2f(EXACT ? log2_weight(z, s_hi, s_lo, m) : fmaf(z, s_lo, fmaf(z, s_hi, -m)));
+}
+__device__ __forceinline__ bool stats_in_doubt(float m, float sum) {
+  return sum != sum || (fabsf(m) >= GKV_HUGE_LOG2 && m != GKV_NO_MAX);
 }
 
 // Offset of a window row with maximum m (log2 units) and sum s, as hi + lo; a row that is not there has a
@@ -192,10 +211,9 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
     if constexpr (!HAVE_STATS) {
       // ---- first pass over K: row max and row sum over the keys visible to each window row -----
       // NB blocks at a time keep their running (max, sum) in registers; only the last tiles (those
-      // reaching into the window) need the causal mask, and a running sum is rescaled only when
-      // some lane's maximum moved.
+      // reaching into the window) need the causal mask.
       constexpr int NB = 4;
-      const int n_tiles = (l + 15) >> 4;
+      const int n_tiles = (l + 15) >> 4, n_full = (cc + 1) >> 4;   // the first n_full: every row sees all of their keys
       const int n_blocks = nts * pl.n_blk;
       for (int b0 = 0; b0 < n_blocks; b0 += NB) {
         float rm[NB][4], rs[NB][4];                            // this lane's keys of rows 4 kb + e
@@ -207,11 +225,9 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
             rm[i][e] = GKV_NO_MAX; rs[i][e] = 0.f;
             last_vis[i][e] = cc + k_of(16 * min(b0 + i, n_blocks - 1) + 4 * kb + e);
           }
-        for (int t = wave; t < n_tiles; t += NW) {
-          u32x4 kA[NL];
-          load_k_tile<T, D>(kA, Kh, t, seq.n_tiled, lane, r, kb);
+        auto stats_tile = [&](const u32x4 (&kA)[NL], int t, auto exact) {
+          constexpr bool EXACT = decltype(exact)::value;
           const int key = 16 * t + r;
-          const bool full = 16 * t + 15 <= cc;                 // every row sees all 16 keys of this tile
 #pragma unroll
           for (int i = 0; i < NB; ++i) {
             u32x4 q[NL];
@@ -220,17 +236,37 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               // a key the row did not see has the logit -inf: it never becomes the maximum and adds 0
-              if (!full && key > last_vis[i][e]) z[e] = -INFINITY;
-              const float tm = rounded_product(z[e], s_hi);
-              if (__any(tm > rm[i][e])) {
-                const float mnew = fmaxf(rm[i][e], tm);
-                rs[i][e] *= __builtin_amdgcn_exp2f(rm[i][e] - mnew);
-                rm[i][e] = mnew;
-              }
-              rs[i][e] += __builtin_amdgcn_exp2f(log2_weight(z[e], s_hi, s_lo, rm[i][e]));
+              if (EXACT && key > last_vis[i][e]) z[e] = -INFINITY;
+              add_to_stats<EXACT>(z[e], s_hi, s_lo, rm[i][e], rs[i][e]);
             }
           }
+        };
+        auto exact_tiles = [&](int t0) {
+          for (int t = t0; t < n_tiles; t += NW) {
+            u32x4 kA[NL];
+            load_k_tile<T, D>(kA, Kh, t, seq.n_tiled, lane, r, kb);
+            stats_tile(kA, t, std::true_type{});
+          }
+        };
+        int t = wave;
+        for (; t < n_full; t += NW) {
+          u32x4 kA[NL];
+          load_k_tile<T, D>(kA, Kh, t, seq.n_tiled, lane, r, kb);
+          stats_tile(kA, t, std::false_type{});
         }
+        bool again = false;
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) again |= stats_in_doubt(rm[i][e], rs[i][e]);
+        if (__any(again)) {
+#pragma unroll
+          for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { rm[i][e] = GKV_NO_MAX; rs[i][e] = 0.f; }
+          t = wave;
+        }
+        exact_tiles(t);
         // the 16 lanes of a row, then (below) the wavefronts
 #pragma unroll
         for (int i = 0; i < NB; ++i)
@@ -377,8 +413,8 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
   }
 }
 
-// The common case: bf16, recorded statistics, and so few blocks of window rows (NT sixteens of NB)
-// that a wavefront can hold all of their operands in registers.  The kernel above reads 1 KiB of
+// The common case: bf16 and so few blocks of window rows (NT sixteens of NB) that a wavefront can hold all
+// of their operands in registers; OWN computes the rows' statistics first.  The kernel above reads 1 KiB of
 // LDS per MFMA at one key tile per wavefront, which makes the CU's 128 B a cycle its bound; here LDS
 // only hands the queries round once.  K^T Q instead of Q^T K: a lane keeps one row's offset per
 // block (two registers, not eight), and the 16 window rows end up across the lanes.
@@ -389,8 +425,8 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
 // of 1088 rows, g = 5, w = 32 25.8 -> 20.0 us; 4608 such units 347 -> 310 us; 448 units of 640 rows,
 // g = 7, w = 16 20.8 -> 17.8 us; 4 units 9.7 -> 5.3 us.  Against the plain kernel: bf16 D = 64, 128 units
 // 2780 -> 7.4 us; fp32 D = 128, 32 units 3490 -> 20.5 us (kernel above, bound by fp32 MFMAs).
-// Dynamic LDS: q pieces [NT*NB][NL][1 KiB]; float2 row_c[16*NT*NB].
-template <int D, int NW, int NB, int NT, bool ONCE>
+// Dynamic LDS: q pieces [NT*NB][NL][1 KiB]; float2 row_c[16*NT*NB]; OWN: float2 red_ms[NW][16*NT*NB].
+template <int D, int NW, int NB, int NT, bool ONCE, bool OWN>
 __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, ScoreArgs a, int pair, int ksplit) {
   using T = uint16_t;
   using G = Geo<T, D>;
@@ -437,7 +473,7 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   if (tid < NT * NB * 16) {
     int h, k;
     row_valid = row_src((tid >> 4) / NB, (tid >> 4) % NB, tid & 15, h, k);
-    ms = a.stats[ring_row(h, k)];
+    if constexpr (!OWN) ms = a.stats[ring_row(h, k)];
   }
 
   const SeqState seq = load_state(a.d_state, lb);
@@ -448,14 +484,110 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   const int g0 = share * per_share, g1 = min(tiles, g0 + per_share);
   const char* Kh = (const char*)a.K + (size_t)unit * cap * G::ROW_BYTES;
   Tile<T, D> kA, kN;
-  if (g0 + wave < g1) load_k_tile<T, D, ONCE>(kA, Kh, g0 + wave, seq.n_tiled, lane, r, kb);
-  if (tid < NT * NB * 16) {
-    row_c[tid] = row_offset(row_valid, ms.x, ms.y);
+  const int n_full = OWN ? (cc + 1) >> 4 : 0;            // tiles whose keys every window row sees
+  if constexpr (OWN) {
+    if (wave < n_full) load_k_tile<T, D>(kA, Kh, wave, seq.n_tiled, lane, r, kb);
+  } else {
+    if (g0 + wave < g1) load_k_tile<T, D, ONCE>(kA, Kh, g0 + wave, seq.n_tiled, lane, r, kb);
+    if (tid < NT * NB * 16) row_c[tid] = row_offset(row_valid, ms.x, ms.y);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the queries are in LDS
   __syncthreads();
   if (g0 >= g1) return;
   const float s_hi = dm.scale_l2_hi, s_lo = dm.scale_l2_lo;
+  u32x4 q[NT * NB][NL];
+  auto load_q = [&](u32x4 (&x)[NL], int b) {
+#pragma unroll
+    for (int c = 0; c < NL; ++c) x[c] = *(const u32x4*)(qs + (b * NL + c) * 1024 + lane * 16);
+  };
+  // ten blocks of 16 x 256 bytes and the first pass of OWN need more registers than there are: it takes two of them from LDS each time
+  constexpr int HELD = OWN && NL == 4 && NT * NB > 8 ? 8 : NT * NB;
+#pragma unroll
+  for (int b = 0; b < HELD; ++b) load_q(q[b], b);
+
+  if constexpr (OWN) {
+    // ---- the rows' own statistics: a first pass over all keys, a row's (max, sum) in four lanes --------
+    float rm[NT * NB], rs[NT * NB];
+    auto reset = [&]() {
+#pragma unroll
+      for (int b = 0; b < NT * NB; ++b) { rm[b] = GKV_NO_MAX; rs[b] = 0.f; }
+    };
+    auto stats_tile = [&](const Tile<T, D>& kT, int t, auto exact) {
+      constexpr bool EXACT = decltype(exact)::value;
+#pragma unroll
+      for (int b = 0; b < NT * NB; ++b) {
+        if (b >= HELD) {
+          asm volatile("" ::: "memory");                 // read here, not once before the loop
+          load_q(q[b], b);
+        }
+        f32x4 z = logits<T, NL>(kT, q[b]);
+        if constexpr (EXACT) {
+          // a key the row did not see has the logit -inf: it never becomes the maximum and adds 0
+          const int seen = cc + (pair ? (r & 7) : 16 * (b / NB) + r);
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (16 * t + 4 * kb + e > seen) z[e] = -INFINITY;
+        }
+        const float tm = rounded_product(fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3])), s_hi);
+        if (__any(tm > rm[b])) {
+          const float mnew = fmaxf(rm[b], tm);
+          rs[b] *= __builtin_amdgcn_exp2f(rm[b] - mnew);
+          rm[b] = mnew;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          rs[b] += __builtin_amdgcn_exp2f(EXACT ? log2_weight(z[e], s_hi, s_lo, rm[b])
+                                                : fmaf(z[e], s_lo, fmaf(z[e], s_hi, -rm[b])));
+      }
+    };
+    const int n_tiles = (l + 15) >> 4;
+    auto exact_tiles = [&](int t0) {
+      for (int t = t0; t < n_tiles; t += NW) {
+        Tile<T, D> kT;
+        load_k_tile<T, D>(kT, Kh, t, seq.n_tiled, lane, r, kb);
+        stats_tile(kT, t, std::true_type{});
+      }
+    };
+    reset();
+    for (int t = wave; t < n_full; t += 2 * NW) {
+      load_k_tile<T, D>(kN, Kh, min(t + NW, n_full - 1), seq.n_tiled, lane, r, kb);
+      stats_tile(kA, t, std::false_type{});
+      if (t + NW >= n_full) break;
+      load_k_tile<T, D>(kA, Kh, min(t + 2 * NW, n_full - 1), seq.n_tiled, lane, r, kb);
+      stats_tile(kN, t + NW, std::false_type{});
+    }
+    bool again = false;
+#pragma unroll
+    for (int b = 0; b < NT * NB; ++b) again |= stats_in_doubt(rm[b], rs[b]);
+    if (__any(again)) reset();
+    exact_tiles(__any(again) ? wave : n_full + (wave + NW - n_full % NW) % NW);
+    if (g0 + wave < g1) load_k_tile<T, D>(kA, Kh, g0 + wave, seq.n_tiled, lane, r, kb);
+    float2* red_ms = row_c + NT * NB * 16;               // [NW][rows]
+#pragma unroll
+    for (int b = 0; b < NT * NB; ++b) {
+      float m = fmaxf(rm[b], __shfl_xor(rm[b], 16));
+      m = fmaxf(m, __shfl_xor(m, 32));
+      float sum = rs[b] * __builtin_amdgcn_exp2f(rm[b] - m);
+      sum += __shfl_xor(sum, 16);
+      sum += __shfl_xor(sum, 32);
+      if (kb == 0) red_ms[wave * (NT * NB * 16) + 16 * b + r] = make_float2(m, sum);
+    }
+    __syncthreads();
+    if (tid < NT * NB * 16) {
+      float M = GKV_NO_MAX, Z = 0.f;
+#pragma unroll
+      for (int wv = 0; wv < NW; ++wv) M = fmaxf(M, red_ms[wv * (NT * NB * 16) + tid].x);
+#pragma unroll
+      for (int wv = 0; wv < NW; ++wv) {
+        const float2 part = red_ms[wv * (NT * NB * 16) + tid];
+        Z += part.y * __builtin_amdgcn_exp2f(part.x - M);
+      }
+      row_c[tid] = row_offset(row_valid, M, Z);
+    }
+#pragma unroll
+    for (int b = HELD; b < NT * NB; ++b) load_q(q[b], b);
+    __syncthreads();
+  }
   const float mean = 0x1p-3f / (float)w;
   float* So = a.S + (size_t)unit * cap;
   // S of tile t from tot[e], the sum over the sixteens of window rows of row r's probability of key 4 kb + e
@@ -481,11 +613,6 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
     const float2 c = row_c[16 * b + r];
     c_hi[b] = c.x; c_lo[b] = c.y;
   }
-  u32x4 q[NT * NB][NL];
-#pragma unroll
-  for (int b = 0; b < NT * NB; ++b)
-#pragma unroll
-    for (int c = 0; c < NL; ++c) q[b][c] = *(const u32x4*)(qs + (b * NL + c) * 1024 + lane * 16);
   auto tile = [&](const Tile<T, D>& kT, int t) {
     f32x4 tot = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -532,8 +659,7 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
 #pragma unroll 1
         for (int b = nt * NB; b < (nt + 1) * NB; ++b) {
           u32x4 qb[NL];
-#pragma unroll
-          for (int c = 0; c < NL; ++c) qb[c] = *(const u32x4*)(qs + (b * NL + c) * 1024 + lane * 16);
+          load_q(qb, b);
           const float2 c = row_c[16 * b + r];
           const f32x4 z = logits<T, NL>(kT, qb);
 #pragma unroll
@@ -548,8 +674,26 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   }
 }
 
+// Own statistics: every workgroup goes through all of its unit's keys first, so units are shared out only
+// while there are fewer than compute units, and 8 wavefronts share that pass.  us per launch, the kernel
+// above (4 wavefronts, a sweep over K per four blocks) -> this one: 4 units of 640 rows, g = 7, w = 16 40 -> 13; of
+// 2176 rows, g = 8 91 -> 32; 256 of 1088, g = 5, w = 32 127 -> 38; 896 of 640, g = 7, w = 16 122 -> 73; 18432 of 1088,
+// g = 5, w = 32 4670 -> 2480.  Bound: the arithmetic of two passes (the second alone, with recorded statistics:
+// 38 us at 896 units).
+template <int D, int NB, int NT>
+hipError_t launch_regs_own(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a, int len_max, bool pair) {
+  constexpr int NW = 8, ROWS = NT * NB * 16;
+  const int units = dm.L * dm.B * dm.Hkv;
+  const int tiles = (len_max + 15) / 16, most = (tiles + NW - 1) / NW;
+  int ksplit = 256 / units;
+  ksplit = ksplit < 1 ? 1 : (ksplit > most ? (most < 1 ? 1 : most) : ksplit);
+  return gkv_launch(ln, score_regs_kernel<D, NW, NB, NT, false, true>, dim3(units * ksplit), dim3(NW * 64),
+                    (size_t)ROWS * (Geo<uint16_t, D>::ROW_BYTES + 8 + 8 * NW), dm, a, (int)pair, ksplit);
+}
+
 template <int D, int NB, int NT>
 hipError_t launch_regs(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a, int len_max, bool pair) {
+  if (!a.stats) return launch_regs_own<D, NB, NT>(ln, dm, a, len_max, pair);
   constexpr int NW = 4;
   const int units = dm.L * dm.B * dm.Hkv;
   // Two workgroups of 4 wavefronts fit a CU at these register counts: fewer than 512 units are cut into
@@ -561,7 +705,7 @@ hipError_t launch_regs(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& 
   // 80 -> 67 us at 280 MB of K (1792 units), 134 -> 113 us at 504 MB, 305 -> 285 us at 1.2 GB; at 70 and
   // 140 MB there is no difference then, and a second reader of the same K finds it cached.
   const bool once = (size_t)units * len_max * Geo<uint16_t, D>::ROW_BYTES > (size_t)256 << 20;
-  auto kern = once ? score_regs_kernel<D, NW, NB, NT, true> : score_regs_kernel<D, NW, NB, NT, false>;
+  auto kern = once ? score_regs_kernel<D, NW, NB, NT, true, false> : score_regs_kernel<D, NW, NB, NT, false, false>;
   return gkv_launch(ln, kern, dim3(units * ksplit), dim3(NW * 64),
                     (size_t)NT * NB * (Geo<uint16_t, D>::TILE_BYTES + 128), dm, a, (int)pair, ksplit);
 }
@@ -613,7 +757,7 @@ hipError_t gkv_launch_score_mfma(const GkvLaunch& ln, const GkvDims& dm, int dty
   if (dtype == GKV_F32)
     return dm.d == 64 ? launch<float, 64, 4, 2>(ln, dm, a, len_max) : launch<float, 128, 4, 1>(ln, dm, a, len_max);
   hipError_t e;
-  if (a.stats && !a.F_out &&
+  if (!a.F_out &&
       (dm.d == 64 ? try_launch_regs<64>(ln, dm, a, len_max, &e) : try_launch_regs<128>(ln, dm, a, len_max, &e)))
     return e;
   return dm.d == 64 ? launch<uint16_t, 64, 4, 2>(ln, dm, a, len_max) : launch<uint16_t, 128, 4, 2>(ln, dm, a, len_max);

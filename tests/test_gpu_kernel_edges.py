@@ -267,7 +267,9 @@ def test_window_score_at_tile_edges(dtype, d, g, w, params, reuse):
 # log2 e rounded to fp32) has either sign: a hidden key must add nothing, whatever the residue of its
 # masked logit.  Same bound.
 @pytest.mark.parametrize("scale", [0.1, 0.05, 0.2, 0.125])
-@pytest.mark.parametrize("dtype,d,g,w", [("bf16", 128, 7, 16), ("bf16", 64, 5, 8), ("f32", 128, 3, 16), ("f32", 64, 2, 24)])
+@pytest.mark.parametrize("dtype,d,g,w", [("bf16", 128, 7, 16), ("bf16", 64, 5, 8), ("f32", 128, 3, 16), ("f32", 64, 2, 24),
+                                         ("bf16", 128, 5, 32), ("bf16", 64, 5, 30), ("bf16", 128, 8, 9), ("bf16", 128, 15, 4),
+                                         ("bf16", 128, 16, 16)])
 def test_window_score_own_statistics_other_scales(dtype, d, g, w, scale):
     _check_window_score(dtype, d, g, w, None, 0, scale)
 
