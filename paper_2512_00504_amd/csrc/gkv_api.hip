@@ -443,7 +443,7 @@ extern "C" gkv_status gkv_score_window(gkv_ctx* ctx, const void* qwin, const voi
   if (!ctx || !qwin || !K || !d_state || !S || step < 0) return GKV_ERR_INVALID_ARG;
   gkv_status st = check_len(ctx, len_max_host, false);
   if (st != GKV_OK) return st;
-  ScoreArgs a{qwin, K, d_state, step, S, nullptr, nullptr, nullptr};
+  ScoreArgs a{qwin, K, d_state, step, S, nullptr};
   GkvLaunch ln{ctx, GKV_K_SCORE, (hipStream_t)stream};
   if (use_mfma(ctx, {qwin, K})) {
     // Under the causal reading of Eq. 1 a window row's softmax runs over exactly the keys its
@@ -495,27 +495,18 @@ extern "C" gkv_status gkv_evict(gkv_ctx* ctx, const void* qwin, void* K, void* V
   if (F == F_hist) return GKV_ERR_INVALID_ARG;
   gkv_status st = check_len(ctx, len_max_host, false);
   if (st != GKV_OK) return st;
-  if (ctx->fuse_global && use_mfma(ctx, {qwin, K})) {
-    // local and global score in one launch: the score kernel keeps S in LDS and finishes with the update
-    ScoreArgs a{qwin, K, d_state, step, S, nullptr, F_hist, F};
-    if (stats_cover_window(ctx, step, workspace, K, qwin)) a.stats = gkv_carve_workspace(ctx, workspace).stats;
-    GkvLaunch ln{ctx, GKV_K_SCORE, (hipStream_t)stream};
-    st = hip_status(gkv_launch_score_mfma(ln, ctx->dims, ctx->cfg.dtype, a, len_max_host));
+  st = gkv_score_window(ctx, qwin, K, d_state, step, len_max_host, S, workspace, stream);
+  if (st != GKV_OK) return st;
+  if (ctx->fuse_select || ctx->fuse_global) {
+    // the global score is formed at the head of the selection kernel (same arithmetic as
+    // gkv_global_update, F written as well): one launch less per compression
+    GkvLaunch ln{ctx, GKV_K_TOPK, (hipStream_t)stream};
+    st = hip_status(gkv_launch_update_and_select(ln, ctx->dims, S, F_hist, d_state, step, F, keep_idx));
     if (st != GKV_OK) return st;
-  } else {
-    st = gkv_score_window(ctx, qwin, K, d_state, step, len_max_host, S, workspace, stream);
-    if (st != GKV_OK) return st;
-    if (ctx->fuse_select) {
-      // the global score is formed at the head of the selection kernel (same arithmetic as
-      // gkv_global_update, F written as well): one launch less per compression
-      GkvLaunch ln{ctx, GKV_K_TOPK, (hipStream_t)stream};
-      st = hip_status(gkv_launch_update_and_select(ln, ctx->dims, S, F_hist, d_state, step, F, keep_idx));
-      if (st != GKV_OK) return st;
-      return gkv_compact(ctx, keep_idx, F, K, V, F_hist, pos, d_state, step, workspace, stream);
-    }
-    st = gkv_global_update(ctx, S, F_hist, d_state, step, len_max_host, F, stream);
-    if (st != GKV_OK) return st;
+    return gkv_compact(ctx, keep_idx, F, K, V, F_hist, pos, d_state, step, workspace, stream);
   }
+  st = gkv_global_update(ctx, S, F_hist, d_state, step, len_max_host, F, stream);
+  if (st != GKV_OK) return st;
   st = gkv_select_topk(ctx, F, d_state, step, len_max_host, keep_idx, workspace, stream);
   if (st != GKV_OK) return st;
   return gkv_compact(ctx, keep_idx, F, K, V, F_hist, pos, d_state, step, workspace, stream);

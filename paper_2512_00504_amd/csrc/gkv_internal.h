@@ -45,7 +45,7 @@ struct gkv_ctx {
   int32_t attend_tile;    // keys per wavefront iteration of the matrix-core attend kernel: 16 or 32
   int32_t force_generic;
   int32_t attend_waves;   // 0 = automatic
-  int32_t fuse_global;    // gkv_evict: global score in the tail of the window-score kernel
+  int32_t fuse_global;    // gkv_evict: as fuse_select (the global score is not a launch of its own)
   int32_t fuse_select;    // gkv_evict: global score at the head of the top-k kernel (default)
   int32_t compact_ppt;    // 16-byte pieces per thread and chunk round of the compaction kernel: 4, 8 or 16
   int32_t reuse_stats;    // window score may reuse the softmax statistics the decode kernel recorded
@@ -107,7 +107,6 @@ size_t gkv_attend_mfma_lds(int esz, int d, int g, int waves);
 struct ScoreArgs {
   const void* qwin; const void* K; const int32_t* d_state; int32_t step; float* S;
   const float2* stats;   // softmax statistics of the window's decode steps, or null: compute them
-  const float* F_hist; float* F_out;   // non-null F_out: also the global score (matrix-core kernel only)
 };
 hipError_t gkv_launch_score_generic(const GkvLaunch& ln, const GkvDims& dm, int dtype, const ScoreArgs& a);
 hipError_t gkv_launch_score_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const ScoreArgs& a, int len_max);

@@ -125,11 +125,11 @@ __device__ __forceinline__ float log2_score(float z, float s_hi, float s_lo, flo
 struct ScorePlan {
   int32_t pair_heads;      // 1: window of at most 8 rows, two heads per block
   int32_t n_blk, nt, nt_pass, ksplit;
-  int32_t use_sbuf;        // S is collected in LDS (several passes, or the fused tail wants it)
+  int32_t use_sbuf;        // S is collected in LDS over several passes
 };
 
 // Dynamic LDS: q pieces [nt_pass*n_blk][NL][1 KiB]; float row_hi[rows], row_lo[rows]; float sbuf[cap] if
-// use_sbuf; float red[8]; and, when the row statistics are computed here, float2 red_ms[NW][rows].
+// use_sbuf; and, when the row statistics are computed here, float2 red_ms[NW][rows].
 // HAVE_STATS: a.stats holds (max, sum) of every window row, recorded by the decode kernel.
 template <typename T, int D, int NW, int KT, bool HAVE_STATS>
 __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreArgs a, ScorePlan pl) {
@@ -155,8 +155,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
   float* row_hi = (float*)(qs + (size_t)rows_pass * G::ROW_BYTES);
   float* row_lo = row_hi + rows_pass;
   float* sbuf = row_lo + rows_pass;
-  float* red = sbuf + (pl.use_sbuf ? cap : 0);
-  float2* red_ms = (float2*)(red + 8);
+  float2* red_ms = (float2*)(sbuf + (pl.use_sbuf ? cap : 0));
 
   const char* Kh = (const char*)a.K + (size_t)unit * cap * G::ROW_BYTES;
   const float s_hi = dm.scale_l2_hi, s_lo = dm.scale_l2_lo;
@@ -387,28 +386,6 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
       for (int tt = 0; tt < KT; ++tt)
 #pragma unroll
         for (int c = 0; c < NL; ++c) kA[tt][c] = kN[tt][c];
-    }
-  }
-
-  // ---- optional tail: global score of the candidates (Section 4), S still in LDS ---------------
-  if (a.F_out != nullptr) {
-    __syncthreads();
-    float mx = 0.f;
-    for (int n = tid; n < cc; n += NW * 64) mx = fmaxf(mx, sbuf[n]);
-    mx = block_max(mx, red);
-    const int n_hist = seq.n_hist < 0 ? 0 : (seq.n_hist > cc ? cc : seq.n_hist);
-    const float* Hu = a.F_hist + (size_t)unit * cap;
-    float* Fu = a.F_out + (size_t)unit * cap;
-    for (int n = tid; n < cc; n += NW * 64) {
-      const float sn = mx > 0.f ? sbuf[n] / mx : 0.f;
-      float f = sn;
-      if (n < n_hist) {
-        const float h = dm.alpha * Hu[n];
-        f = dm.combine == GKV_COMBINE_MAX ? fmaxf(h, sn)
-          : dm.combine == GKV_COMBINE_AVG ? h + (1.f - dm.alpha) * sn
-                                          : h + sn;
-      }
-      Fu[n] = f;
     }
   }
 }
@@ -733,15 +710,12 @@ hipError_t launch(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a, in
   const int block_bytes = pl.n_blk * G::TILE_BYTES;
   pl.nt_pass = 72 * 1024 / block_bytes;
   pl.nt_pass = pl.nt_pass < 1 ? 1 : (pl.nt_pass > pl.nt ? pl.nt : pl.nt_pass);
-  pl.use_sbuf = pl.nt_pass < pl.nt || a.F_out != nullptr;
+  pl.use_sbuf = pl.nt_pass < pl.nt;
   const int groups = ((len_max + 15) / 16 + KT - 1) / KT;
-  pl.ksplit = 1;
-  if (a.F_out == nullptr) {
-    int k = 512 / units, most = (groups + NW - 1) / NW;
-    pl.ksplit = k < 1 ? 1 : (k > most ? (most < 1 ? 1 : most) : k);
-  }
+  const int k = 512 / units, most = (groups + NW - 1) / NW;
+  pl.ksplit = k < 1 ? 1 : (k > most ? (most < 1 ? 1 : most) : k);
   const size_t rows = (size_t)pl.nt_pass * pl.n_blk * 16;
-  const size_t shmem = rows * G::ROW_BYTES + rows * 8 + (pl.use_sbuf ? 4 * (size_t)dm.cap : 0) + 32 +
+  const size_t shmem = rows * G::ROW_BYTES + rows * 8 + (pl.use_sbuf ? 4 * (size_t)dm.cap : 0) +
                        (a.stats ? 0 : NW * rows * 8);
   auto kern = a.stats ? score_mfma_kernel<T, D, NW, KT, true> : score_mfma_kernel<T, D, NW, KT, false>;
   if (shmem > GKV_LDS_LIMIT) {                             // beyond the default per-workgroup limit: opt in (a CU holds 160 KiB)
@@ -757,8 +731,6 @@ hipError_t gkv_launch_score_mfma(const GkvLaunch& ln, const GkvDims& dm, int dty
   if (dtype == GKV_F32)
     return dm.d == 64 ? launch<float, 64, 4, 2>(ln, dm, a, len_max) : launch<float, 128, 4, 1>(ln, dm, a, len_max);
   hipError_t e;
-  if (!a.F_out &&
-      (dm.d == 64 ? try_launch_regs<64>(ln, dm, a, len_max, &e) : try_launch_regs<128>(ln, dm, a, len_max, &e)))
-    return e;
+  if (dm.d == 64 ? try_launch_regs<64>(ln, dm, a, len_max, &e) : try_launch_regs<128>(ln, dm, a, len_max, &e)) return e;
   return dm.d == 64 ? launch<uint16_t, 64, 4, 2>(ln, dm, a, len_max) : launch<uint16_t, 128, 4, 2>(ln, dm, a, len_max);
 }

@@ -230,7 +230,7 @@ def _check_window_score(dtype, d, g, w, params, reuse, scale=0.0, hidden=False, 
     t = t0 + w - 1
     st.len_host = cap
     st.S.fill_(-3.0)
-    if params:                                                            # the fused tail is only reached through gkv_evict
+    if params:                                                            # through gkv_evict
         st.ctx.evict(st.qwin, st.K, st.V, st.F_hist, st.pos, st.d_state, t, cap, st.S, st.F, st.keep_idx, st.workspace)
     else:
         st.score_window(t)

@@ -84,11 +84,13 @@ def test_cfg3_shape_evict_entry_point(form):
     assert st["events"] == 4
 
 
-def test_cfg3_shape_evict_with_the_global_score_in_the_score_kernels_tail():
-    # optional one-launch local + global score (S stays in LDS for the update): same results
+def test_cfg3_shape_evict_with_fuse_global():
+    # the global score is never a launch of its own: same results
     wl = CONFIGS["cfg3_28layer_b512"].with_(n_layers=2, batch=2)
-    st = run_parity(wl, 1024, fused_evict=True, params={"evict_fuse_global": 1}, check_state_every_event=False)
-    assert st["events"] == 4
+    for select in (1, 0):
+        st = run_parity(wl, 1024, fused_evict=True, params={"evict_fuse_global": 1, "evict_fuse_select": select},
+                        check_state_every_event=False)
+        assert st["events"] == 4
     wl5 = CONFIGS["cfg5_large_batch"].with_(n_layers=1, batch=2)
     st = run_parity(wl5, 1216, fused_evict=True, params={"evict_fuse_global": 1, "score_reuse_stats": 0},
                     check_state_every_event=False)
