@@ -11,11 +11,12 @@ from paper_2512_00504_amd.state import DecodeState
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("name,over", [
-    ("cfg3_28layer_b512", dict(n_layers=2, batch=2)),                    # matrix-core kernels
-    ("cfg1_tiny", dict(budget=64, interval=16, window=8)),               # plain kernels, fp32
+@pytest.mark.parametrize("name,over,params", [
+    ("cfg3_28layer_b512", dict(n_layers=2, batch=2), None),              # bf16, units cut over workgroups
+    ("cfg1_tiny", dict(budget=64, interval=16, window=8), None),         # fp32
+    ("cfg1_tiny", dict(budget=64, interval=16, window=8), {"force_generic": 1}),     # plain kernels
 ])
-def test_recorded_cycle_replays_match_eager_steps(name, over):
+def test_recorded_cycle_replays_match_eager_steps(name, over, params):
     wl = CONFIGS[name].with_(**over)
     s, b, w = wl.interval, wl.budget, wl.window
     assert b % s == 0 and s % w == 0
@@ -27,7 +28,7 @@ def test_recorded_cycle_replays_match_eager_steps(name, over):
     q, k, v = [torch.from_numpy(x).to(dt).cuda() for x in tr.batch_steps(0, T)]
 
     # eager reference: absolute steps, ordinary calls
-    ref = DecodeState.from_workload(wl)
+    ref = DecodeState.from_workload(wl, params=params)
     outs_ref = []
     for t in range(T):
         outs_ref.append(ref.attend_decode(q[t], k[t], v[t], t).clone())
@@ -36,7 +37,7 @@ def test_recorded_cycle_replays_match_eager_steps(name, over):
     torch.cuda.synchronize()
 
     # the graph path: eager up to the steady state, then one recorded cycle replayed n_cycles times
-    st = DecodeState.from_workload(wl)
+    st = DecodeState.from_workload(wl, params=params)
     for t in range(t0):
         st.attend_decode(q[t], k[t], v[t], t)
         if st.is_trigger(t):

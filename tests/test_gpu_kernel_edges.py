@@ -514,7 +514,10 @@ def test_compaction_in_shares(dtype, d, B, b):
         l = b + 1 + (s_ - 1) * turn                # one row to drop, then s
         c = l - w
         keep = torch.rand(B, 2, c, generator=gen).topk(k, dim=-1).indices.sort(dim=-1).values
-        tiled = [(l - w) // 16 * 16 if i % 2 else 32 for i in range(B)]      # never past the recorded length
+        # K's format as it stays (the shares move their own columns) and as it changes (one share moves all);
+        # never past the recorded length, so on the first turn only where b is that far from its multiple of 16
+        tiled = [nt if i % 2 and nt <= l - w else (l - w) // 16 * 16 if i % 3 == 0 else 32 for i in range(B)]
+        assert turn == 0 or {n == nt for n in tiled} == {True, False}
         st.K.copy_(torch.stack([k_rows_to_cache(K[0, i], tiled[i]) for i in range(B)])[None])
         st.V.copy_(V); st.pos.copy_(pos); st.F.copy_(F); st.keep_idx.copy_(keep.int()[None])
         st.d_state.copy_(torch.tensor([[[l - w, 200, 0, n] for n in tiled]], dtype=torch.int32))
@@ -526,7 +529,7 @@ def test_compaction_in_shares(dtype, d, B, b):
         first = 1 if turn == 0 else 0
         if turn == 0:
             assert torch.equal(st.K[0, 0], K0) and torch.equal(st.pos[0, 0], pos0)
-            assert st.d_state[0, 0].tolist() == [b - w, 200, 0, 32]
+            assert st.d_state[0, 0].tolist() == [b - w, 200, 0, tiled[0]]
         assert (st.d_state[0, first:].cpu() == torch.tensor([b, 200 + w, k, nt], dtype=torch.int32)).all()
         rows = src[..., None].expand(B, 2, b, d)
         Kr = k_cache_to_rows(st.K[0], nt)[:, :, :b].cpu()

@@ -41,10 +41,11 @@ def test_cfg1_other_combine_forms(form):
     assert st["events"] == 6
 
 
-def test_cfg1_shape_in_bf16_generic_kernels():
-    # bf16 with d = 64 is not covered by the matrix-core kernels: exercises the generic bf16 path
+@pytest.mark.parametrize("params", [{"force_generic": 1}, None])
+def test_cfg1_shape_in_bf16(params):
+    # bf16 with d = 64, on the plain kernels and on the matrix cores
     wl = CONFIGS["cfg1_tiny"].with_(dtype="bf16", seed=11)
-    st = run_parity(wl, 160)
+    st = run_parity(wl, 160, params=params)
     assert st["events"] == 6
 
 
@@ -318,15 +319,18 @@ def test_cfg5_shape_many_events_heavy_tails():
 @pytest.mark.parametrize("shape", [
     dict(n_q_heads=4, n_kv_heads=4, budget=96, window=16, interval=32),          # MHA, g = 1
     dict(n_q_heads=16, n_kv_heads=2, budget=100, window=16, interval=40),        # g = 8, b and s not multiples of 16, w does not divide s
-    dict(n_q_heads=32, n_kv_heads=2, budget=80, window=16, interval=16),         # g = 16 (generic score kernel), w = s
-    dict(n_q_heads=12, n_kv_heads=4, budget=72, window=32, interval=56),         # g = 3 (generic score), w = 32
-    dict(n_q_heads=10, n_kv_heads=2, budget=64, window=32, interval=32, head_dim=64),   # d = 64: generic everywhere
+    dict(n_q_heads=32, n_kv_heads=2, budget=80, window=16, interval=16),         # g = 16 (score kernel with queries in LDS), w = s
+    dict(n_q_heads=12, n_kv_heads=4, budget=72, window=32, interval=56),         # g = 3, w = 32
+    dict(n_q_heads=10, n_kv_heads=2, budget=64, window=32, interval=32, head_dim=64),   # d = 64
+    dict(n_q_heads=6, n_kv_heads=2, budget=64, window=32, interval=32, head_dim=96),    # d = 96: plain kernels everywhere
+    dict(n_q_heads=34, n_kv_heads=2, budget=64, window=8, interval=32),          # g = 17: plain kernels everywhere
 ])
-def test_odd_shapes_bf16(shape):
+@pytest.mark.parametrize("params", [None, {"force_generic": 1}])
+def test_odd_shapes_bf16(shape, params):
     kw = dict(n_layers=2, batch=3, head_dim=128, dtype="bf16", n_steps=400, seed=21)
     kw.update(shape)
     wl = CONFIGS["cfg2_single_layer"].with_(**kw)
-    st = run_parity(wl, wl.n_steps, chunk=64)
+    st = run_parity(wl, wl.n_steps, params=params, chunk=64)
     assert st["events"] >= 3
 
 
@@ -392,9 +396,10 @@ def test_cfg5_shape_medium_batch_sampled():
 
 
 # ------------------------------------------------------------------ redundancy score (full G-KV)
-def test_redundancy_cfg1_generic_fp32():
+@pytest.mark.parametrize("params", [{"force_generic": 1}, None])
+def test_redundancy_cfg1_fp32(params):
     wl = CONFIGS["cfg1_tiny"]
-    st = run_parity(wl, 160, redundancy=dict(lam=0.7, tau=0.1, n_recent=wl.window))
+    st = run_parity(wl, 160, params=params, redundancy=dict(lam=0.7, tau=0.1, n_recent=wl.window))
     assert st["events"] == 6
     _say(f"  entries on the threshold {st['ambiguous']} (decided the other way: {st['flipped']}) swaps {st['swaps']}")
     assert st["ambiguous"] <= 2
