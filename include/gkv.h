@@ -137,8 +137,10 @@ int64_t gkv_k_offset(const gkv_config* cfg, int32_t row, int32_t channel, int32_
 /* Tuning knobs (host only): "attend_splits" (workgroups per unit in the matrix-core
  * attend kernel; 0 = default: the library cuts long units of launches with few of them; set it before
  * gkv_workspace_bytes), "attend_tile" (16 or 32 keys per wavefront iteration of
- * the matrix-core attend kernel), "attend_waves" (4, 8 or 16 wavefronts per workgroup of that
- * kernel; 0 = default: 4 or 8, by the number and length of the units), "force_generic" (1 = use the plain vector-ALU
+ * the matrix-core attend kernel at bf16, head_dim 128; 32 goes with 4 wavefronts and changes nothing
+ * elsewhere), "attend_waves" (4, 8 or 16 wavefronts per workgroup of that kernel; 0 = default: 4 or 8, by
+ * the number and length of the units; 16 is taken as 8 at fp32, head_dim 128, and a number whose partial
+ * results would not fit 64 KiB of LDS at this dtype, head_dim and group size as 4), "force_generic" (1 = use the plain vector-ALU
  * kernels even where matrix-core kernels exist), "compact_ppt" (4, 8 or 16: 16-byte pieces
  * a thread of the compaction kernel keeps in flight per round), "score_reuse_stats" (0 = the
  * window score always computes its rows' softmax statistics itself instead of reusing the

@@ -205,7 +205,8 @@ static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
     if (s >= 4 || (s >= 2 && slices >= 64)) { p.splits = s; p.iters = wide ? 4 : 8; }
   }
   const bool more = p.splits > 1 ? slices / p.splits >= 48 : (units <= 256 && slices >= 12) || (units > 512 && slices >= 64);
-  if (more && !wide && fits(8) && ctx->attend_tile == 16) p.waves = 8;
+  const bool long_slices = ctx->attend_tile == 32 && ctx->cfg.dtype == GKV_BF16 && d.d == 128;   // 4 wavefronts only
+  if (more && !wide && fits(8) && !long_slices) p.waves = 8;
   if (ctx->attend_waves > 0) p.waves = fits(ctx->attend_waves) ? ctx->attend_waves : 4;
   return p;
 }

@@ -198,6 +198,15 @@ def test_whole_path_fp32_and_head_dim_64(over):
     assert st["events"] >= 5
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_attend_tile_changes_nothing_at_head_dim_64(dtype):
+    outs = []
+    for tile in (16, 32):
+        st, _, _, q, kn, vn = _attend_state(dtype, 64, 3, [600, 333], 640, 64, seed=2, params={"attend_tile": tile, "attend_splits": 1})
+        outs.append(st.attend_decode(q.cuda(), kn.cuda(), vn.cuda(), 5))
+    assert torch.equal(*outs)
+
+
 # ---- window score -----------------------------------------------------------------------------
 def _check_window_score(dtype, d, g, w, params, reuse, scale=0.0, hidden=False, size=None):
     cap, b = 320, 48
