@@ -2,8 +2,8 @@
 // One workgroup of 4 wavefronts per unit (layer, sequence, KV head); each wavefront takes the
 // query heads hi = wave, wave + 4, ... of the group and does a whole head on its own (logits,
 // softmax, output) with wavefront-level reductions only, so the heads of a group run side by
-// side.  fp32 arithmetic throughout.  Used for the fp32 configuration and for shapes the
-// matrix-core kernel does not cover.
+// side.  fp32 arithmetic throughout.  Used for shapes the matrix-core kernel does not cover (head_dim
+// other than 64 and 128, more than 16 heads a group) and for pointers that are not 16-byte aligned.
 #include "gkv_internal.h"
 
 namespace {

@@ -1,5 +1,6 @@
-// Global-score update, top-(b-w) selection and in-place compaction.  One workgroup of 256
-// threads per unit; all score arithmetic in fp32, all index work in integers.
+// Global-score update, top-(b-w) selection and in-place compaction.  The first two take one workgroup of
+// 256 threads per unit, compaction two or more of 256 or 1024; all score arithmetic in fp32, all index
+// work in integers.
 #include "gkv_internal.h"
 
 namespace {
@@ -48,8 +49,9 @@ __device__ __forceinline__ uint32_t sortable_key(float f) {
 // and one scan over the (i, wavefront) counts: ascending indices, always k of them, whatever the bits.
 // Bound: latency (launch, one memory trip, about ten barriers).  Against a radix select by 8-bit
 // digits in LDS (four passes of atomics, scans and six barriers), update and selection in one launch: 4 units
-// of 624 candidates 8.5 -> 7.0 us, 256 of 1056 12.7 -> 9.5; the update alone, which read S twice, 11.1 -> 7.0
-// at 1792 units of 1136; the selection alone there 15.5 -> 16.0 (by then the counting is the bound).
+// of 624 candidates 8.5 -> 7.0 us, 256 of 1056 12.7 -> 9.5; the update alone, which read S twice, 11.2 -> 6.3
+// at 1792 units of 1136; the selection alone there 16.7 to 18.6 -> 16.4 to 19.0 by the scores (by then the
+// counting is the bound), 896 units of 624 9.1 -> 8.4.
 template <int IPT, bool UPDATE, bool SELECT>
 __global__ __launch_bounds__(256) void score_topk_kernel(GkvDims dm, const float* __restrict__ S,
                                                          const float* __restrict__ F_hist,

@@ -169,23 +169,25 @@ static int explicit_splits(const gkv_ctx* ctx) {
 }
 
 // How the matrix-core decode kernel cuts a launch: wavefronts per workgroup, workgroups per unit at
-// most, and the slices a workgroup takes at least (0: every unit is cut into all of them).  Depends
-// on the configuration alone, so the same call gives the same bits whatever bound of the length the
-// caller passes.
+// most, and the slices per piece (0: every unit is cut into all of its pieces; n slices make
+// ceil(n / iters) of them, so the last may be shorter).  Depends on the configuration alone, so the same
+// call gives the same bits whatever bound of the length the caller passes.
 //
-// A CU with one workgroup of 8 wavefronts pulls about 75 GB/s (one 8 KiB slice per wavefront and trip
-// to memory), so up to 128 units leave most of the HBM rate unused.  Cut into workgroups of at least
-// 8 slices, up to 256 of them (bf16, d = 128, us per launch, unsplit with 8 wavefronts -> cut):
-//   4 units x 577 rows 8.5 -> 7.5, x 2113 21.0 -> 9.0, x 3900 31.2 -> 9.8; 32 x 1100 13.9 -> 10.2;
-//   64 x 1100 15.9 -> 12.3, x 3900 39.6 -> 24.3; 128 x 3900 48.4 -> 42.4, and with lengths from 470 to 3900
-//   44.5 -> 30.0 (the longest unit alone on its CU bounds an unsplit launch).
-// 2 or 3 pieces of a short unit cost more than they bring (128 x 577 12.3 -> 12.7), and from 256 units
-// on the chip is full anyway (256 x 577 17.0 -> 17.8, 512 x 1100 47.2 -> 49.6).
-// Long pieces take 8 wavefronts (48 slices and more: 128 ragged units 34.6 with 4, 30.0 with 8).  Unsplit,
+// A workgroup of 8 wavefronts alone on a CU pulls 64 GB/s (4 units of 3900 rows uncut: 8 MB in 31.2 us; one
+// 8 KiB slice per wavefront and trip to memory), so a few dozen units leave most of the HBM rate unused, and
+// at 128 units, 5.3 TB/s, half of the CUs idle.  Cut into pieces of 8 slices, up to 256 of them (bf16,
+// d = 128, us per launch, uncut with 8 wavefronts -> cut):
+//   4 units x 577 rows 8.5 -> 7.2, x 2113 21.0 -> 9.0, x 3900 31.2 -> 9.8; 32 x 1100 13.9 -> 10.2;
+//   64 x 1100 15.9 -> 11.0, x 3900 39.6 -> 24.3; 128 x 3900 48.4 -> 42.4, and with lengths from 470 to 3900
+//   44.5 -> 30.0 (the longest unit alone on its CU bounds an uncut launch).
+// Pieces of 4 slices, twice as many: 4 x 577 7.1 -> 7.8, 32 x 577 7.9 -> 8.3, 64 x 577 8.8 -> 8.9; fp32 and
+// d = 64 within 0.5 us either way.  2 or 3 pieces of a short unit cost more than they bring (128 x 577
+// 12.3 -> 12.7), and from 256 units on the chip is full anyway (256 x 577 17.0 -> 17.8, 512 x 1100 47.2 -> 49.6).
+// Long pieces take 8 wavefronts (48 slices and more: 128 ragged units 34.6 with 4, 30.0 with 8).  Uncut,
 // 8 wavefronts serve up to 256 units that give each a slice (128 x 577 14.2 -> 12.3; 2 x 100 4.6 -> 4.8) and more than 512 units of 64 slices
 // (896 x 2113 167 -> 163, ragged to 3900 232 -> 211; 4608 x 1057 399 -> 392); in between 4 do
-// (512 x 2113 90.7 against 92.8).  fp32 at d = 128 has 16 KiB slices and stays at 4 (256 x 528 26.5, with
-// 8 27.7 us).
+// (512 x 2113 90.7 against 92.8).  fp32 at d = 128 has 16 KiB slices and stays at 4: uncut 256 x 528 26.5, with
+// 8 27.7; cut 32 x 528 9.6 / 11.9, 64 x 1050 17.0 / 18.3, 128 x 1050 25.5 / 26.7, 4 x 2100 12.3 / 12.1.
 struct AttendPlan { int waves, splits, iters; };
 
 static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {

@@ -97,7 +97,7 @@ struct AttendArgs {
   int32_t copy_q;   // 0 when q already is the ring slot of this step
   int32_t write_stats;   // record (max, sum) of every query head's softmax in ws.stats
   int32_t waves;         // wavefronts per workgroup of the matrix-core kernel: 4, 8 or 16
-  int32_t split_iters;   // slices a split takes at least (a unit uses as many splits as its length fills); 0 = all splits
+  int32_t split_iters;   // slices per piece (a unit of n slices is cut into ceil(n / split_iters)); 0 = all splits
 };
 hipError_t gkv_launch_attend_generic(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
 hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);

@@ -4,8 +4,9 @@
 //   the n_recent newest rows are zeroed;  col_j = sum_k C'_kj;  R = softmax_j(col);
 //   R' = R / max_j R = exp(col_j - max_j col)   (the softmax denominator cancels);
 //   F_sel = lambda * F - (1 - lambda) * R'  over the candidates.
-// One workgroup per unit.  The l x l x d contraction runs on the matrix cores for bf16, d = 128;
-// a plain vector-ALU kernel covers every other dtype / shape.
+// One workgroup per unit.  The l x l x d contraction runs on the matrix cores: in 32 bits for bf16,
+// d = 128, in 64 bits for fp32 at d = 64 or 128 and bf16 at d = 64 (groups of at most 16 heads, K 16-byte
+// aligned); a plain vector-ALU kernel covers the rest.
 #include "gkv_internal.h"
 #include <type_traits>
 
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(256) void redundancy_mfma_kernel(GkvDims dm, RedArg
       constexpr bool DIAG = decltype(diag)::value;
       const f32x4 invk = *(const f32x4*)(inv_f + 16 * T + 4 * kb);   // rows >= l have inv = 0: their terms are 0 or fail the test
       // all column tiles' products first, chunk by chunk: the chains of dependent MFMAs of one tile
-      // would each wait for their own results (with the norms read as fp32: 154 -> 150 us at 896 units
+      // would each wait for their own results (with the norms read as fp32: 167 -> 162 us at 896 units
       // of l = 640)
       f32x4 acc[NC];
 #pragma unroll

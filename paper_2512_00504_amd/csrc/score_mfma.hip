@@ -395,13 +395,13 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
 // LDS per MFMA at one key tile per wavefront, which makes the CU's 128 B a cycle its bound; here LDS
 // only hands the queries round once.  K^T Q instead of Q^T K: a lane keeps one row's offset per
 // block (two registers, not eight), and the 16 window rows end up across the lanes.
-// Bound: HBM at several hundred units (28 layers, batch 16, b = 1024: 516 MB of K in 117 us; with one
+// Bound: HBM at several hundred units (28 layers, batch 16, b = 1024: 516 MB of K in 115 to 118 us; with one
 // block's arithmetic left of seven 97 us, staging and launch alone 18 us), arithmetic and the start
 // of a workgroup (state, queries, first tile: three dependent trips to memory) below.  Per launch
 // against a kernel that kept the queries in LDS and took an exponential per head and logit: 256 units
 // of 1088 rows, g = 5, w = 32 25.8 -> 20.0 us; 4608 such units 347 -> 310 us; 448 units of 640 rows,
-// g = 7, w = 16 20.8 -> 17.8 us; 4 units 9.7 -> 5.3 us.  Against the plain kernel: bf16 D = 64, 128 units
-// 2780 -> 7.4 us; fp32 D = 128, 32 units 3490 -> 20.5 us (kernel above, bound by fp32 MFMAs).
+// g = 7, w = 16 20.8 -> 17.8 us; 4 units 11.1 -> 5.8 us.  Against the plain kernel: bf16 D = 64, 128 units
+// 2780 -> 7.4 us; fp32 D = 128, 32 units 3495 -> 16.9 us (kernel above, bound by fp32 MFMAs).
 // Dynamic LDS: q pieces [NT*NB][NL][1 KiB]; float2 row_c[16*NT*NB]; OWN: float2 red_ms[NW][16*NT*NB].
 template <int D, int NW, int NB, int NT, bool ONCE, bool OWN>
 __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, ScoreArgs a, int pair, int ksplit) {
@@ -674,7 +674,8 @@ hipError_t launch_regs(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& 
   constexpr int NW = 4;
   const int units = dm.L * dm.B * dm.Hkv;
   // Two workgroups of 4 wavefronts fit a CU at these register counts: fewer than 512 units are cut into
-  // key shares, down to one tile per wavefront (4 units of 640 rows: 9.7 us whole, 7.6 us in shares).
+  // key shares, down to one tile per wavefront (4 units of 640 rows: 11.0 us whole, 5.8 us in shares; 256 of
+  // 1088 21.6 / 20.0).
   const int tiles = (len_max + 15) / 16, most = (tiles + NW - 1) / NW;
   int ksplit = 512 / units;
   ksplit = ksplit < 1 ? 1 : (ksplit > most ? (most < 1 ? 1 : most) : ksplit);
