@@ -201,8 +201,8 @@ gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void* k_new, con
  * (max, sum) in the workspace, and when the last w gkv_attend_decode calls on this context
  * with these same K, qwin and workspace pointers were the steps step-w+1 .. step (each
  * appending a row), this call takes the rows' statistics from there and reads K once instead
- * of twice.  Otherwise it computes them itself, as it always does on a context that has decoded other
- * buffers on another stream (their statistics may arrive at any time).  The caller must not change K
+ * of twice.  Otherwise it computes them itself, as it always does on a context that has decoded another
+ * K cache on another stream (those statistics may arrive at any time).  The caller must not change K
  * rows or ring slots between those decode calls and this one (or sets "score_reuse_stats" to 0).
  */
 gkv_status gkv_score_window(gkv_ctx* ctx, const void* qwin, const void* K, const int32_t* d_state,

@@ -364,9 +364,9 @@ static bool stream_key(hipStream_t stream, GkvStreamKey* key) {
 }
 
 // Host bookkeeping of the statistics ring: which decode step each slot's statistics belong to,
-// and for which buffers.  Calls on the same buffers are ordered by the caller, so "enqueued" is as good as
-// "written".  Calls on other buffers and another stream need not be: what they write to the ring may
-// land at any time, and from then on nothing is taken from it.
+// and for which buffers.  Calls on one K cache are ordered by the caller (each appends to it), so "enqueued"
+// is as good as "written".  Calls on another cache and another stream need not be: what they write to
+// the statistics ring may land at any time, and from then on nothing is taken from it.
 static void note_stats(gkv_ctx* ctx, int32_t step, bool written, const void* ws, const void* K, const void* qwin,
                        hipStream_t stream) {
   const int w = ctx->dims.w;
@@ -374,8 +374,8 @@ static void note_stats(gkv_ctx* ctx, int32_t step, bool written, const void* ws,
   const bool known = stream_key(stream, &key);
   const bool same_stream = known && key.stream == ctx->stats_key.stream && key.capture == ctx->stats_key.capture;
   ctx->stats_key = known ? key : GkvStreamKey{hipStreamPerThread, 0};   // never equal to a known one
+  if (ctx->stats_K && K != ctx->stats_K && !same_stream) ctx->stats_mixed = true;
   if (ws != ctx->stats_ws || K != ctx->stats_K || qwin != ctx->stats_qwin) {
-    if (ctx->stats_ws && !same_stream) ctx->stats_mixed = true;
     for (int i = 0; i < w; ++i) ctx->stats_step[i] = -1;
     ctx->stats_ws = ws; ctx->stats_K = K; ctx->stats_qwin = qwin;
   }

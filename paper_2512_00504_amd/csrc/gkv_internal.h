@@ -58,7 +58,7 @@ struct gkv_ctx {
   int32_t* stats_step;    // [w]
   const void* stats_ws; const void* stats_K; const void* stats_qwin;
   GkvStreamKey stats_key;   // stream of the last decode call
-  bool stats_mixed;         // the context has decoded other buffers on other streams
+  bool stats_mixed;         // the context has decoded another K cache on another stream
 };
 
 // Workspace layout (bytes from the base):

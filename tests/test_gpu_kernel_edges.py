@@ -400,10 +400,11 @@ def test_overlapping_decode_calls_share_a_workspace(dtype, d, g):
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 64), ("bf16", 128)])
-@pytest.mark.parametrize("other_stream", [True, False])
-def test_recorded_statistics_of_another_stream_are_not_trusted(dtype, d, other_stream):
-    # a decode call on other buffers and another stream may write its statistics at any time; here what
-    # it would write is put there by hand after the window's calls.  On one stream the record is used.
+@pytest.mark.parametrize("other_cache,other_stream", [(True, True), (True, False), (False, True)])
+def test_recorded_statistics_of_another_stream_are_not_trusted(dtype, d, other_cache, other_stream):
+    # a decode call on another K cache and another stream may write its statistics at any time; here what
+    # it would write is put there by hand after the window's calls.  On one stream, or on one cache (with
+    # another ring), the record is used.
     w, b, cap = 4, 40, 96
     st = [DecodeState(make_config(1, 2, 4, 2, d, b, w, 8, cap, dtype)) for _ in range(2)]
     ctx, ws = st[0].ctx, st[0].workspace
@@ -416,6 +417,8 @@ def test_recorded_statistics_of_another_stream_are_not_trusted(dtype, d, other_s
     streams = [torch.cuda.Stream(), torch.cuda.Stream()]
     if not other_stream:
         streams[0] = streams[1]
+    if not other_cache:
+        st[0].K = st[1].K
     torch.cuda.synchronize()
     with torch.cuda.stream(streams[0]):
         ctx.attend_decode(q[0].cuda(), None, None, st[0].K, st[0].V, st[0].pos, 8, st[0].qwin, st[0].d_state, 60, st[0].out, ws)
@@ -435,7 +438,7 @@ def test_recorded_statistics_of_another_stream_are_not_trusted(dtype, d, other_s
         Ki[:, 60 : 60 + w] = kn[:, 0, i].permute(1, 0, 2).double().numpy()
         ref = O.local_score(O.window_probs(q[:, 0, i].permute(1, 0, 2).double().numpy(), Ki, 60 + w), 2)[:, :60]
         right &= bool((np.abs(S[0, i, :, :60] - ref) <= 1e-5 * ref + 1e-30).all())
-    assert right == other_stream
+    assert right == (other_cache and other_stream)
 
 
 def test_window_score_reuses_statistics_of_cut_units():
