@@ -50,7 +50,8 @@
  *     softmax statistics): use it from one thread at a time, one context per set of buffers.
  *   - Return value: GKV_OK or an error code; arguments are validated on the
  *     host before anything is enqueued, a failed call enqueues nothing.
- *     Results are deterministic: same inputs, same bits.
+ *     Results are deterministic: same inputs, same bits (a decode call that the library would cut and
+ *     that has no place for partial results, see gkv_workspace_bytes, adds in another order).
  *   - A compression call is a no-op for every (layer, sequence) whose length is
  *     not above the budget, so ragged batches are legal.  It is also a no-op while
  *     fewer than w steps have been decoded since LEN_STEP (the observation window
