@@ -320,7 +320,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
   a.step = resolve_step(dm, a.step);
   constexpr int KEYS = 16 * KT;             // keys per iteration
   constexpr int RP = G::RP, ROW_BYTES = G::ROW_BYTES, OSTR = G::OSTR, PSTR = G::PSTR;
-  extern __shared__ float smem[];
+  extern __shared__ __attribute__((aligned(16))) float smem[];   // behind s_last: 16-byte pieces want the alignment
   __shared__ int s_last;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, kb = lane >> 4;
