@@ -122,47 +122,45 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int 
   for (int c = 0; c < 4; ++c) kA[c] = *(const u32x4*)(p + c * step_off);
 }
 
-// A wavefront owns a contiguous quarter of the column tiles and holds NC of them in registers per
-// pass; in each pass the workgroup walks all row tiles T together.  The A operand of a tile
-// (lane = key + 16*kblock, 8 channels) is also a valid B operand, so C[k, j] = sum_c mfma(A_T[c], A_J[c])
-// lands as lane (j = lane%16, blk): rows k = 16T + 4 blk + e.
+// MFMA 32x32x16: the A operand of a 32-key tile (lane = key + 32 * half, 8 channels) is also a valid B
+// operand, so C[k, j] = sum_c mfma(A_T[c], A_J[c]) lands as lane (j = lane % 32, half): element i holds row
+// k = 32 T + 8 (i / 4) + 4 half + i % 4.  The column tiles are shared out over eight wavefronts, each of
+// which holds up to three in registers per pass; in each pass the workgroup walks all row tiles T together.
+//
+// What bounds it is how vector instructions and matrix products share a SIMD.  Measured with two
+// wavefronts per SIMD: a 16x16x32 product takes 16 cycles and hides two vector instructions, with four it
+// takes 27; a 32x32x16 product takes 32 and hides six, with eight 45.  An entry needs a product with the
+// row's norm, a comparison and a sum, 16 of them per lane and 8 products: so the large tiles, and the
+// comparison as a clamp (below).  The entries of one column tile are worked on between the products of the
+// next one, and those of the last between the first products of the next row tile.
 //
 // Row tiles reach the wavefronts through LDS: every wavefront needs every row tile in every pass,
 // and if each fetched them itself a unit's keys (l * 256 bytes) would be read 4 * passes times; the
 // units resident on one XCD together exceed its L2, so those re-reads would come from memory and
 // bound the kernel.  Instead the workgroup moves through the row tiles in groups of four: each
-// wavefront fetches one tile of the next group while all four work on the current group, stores it
-// into the other half of a two-group ring, and one barrier per group hands the ring over.
+// wavefront fetches 16 rows of the next group while all work on the current group, stores them
+// into the other half of a two-group ring, and one barrier per group hands the ring over.  Eight wavefronts
+// instead of two workgroups of four halve the passes, and the keys that the units resident on an XCD
+// send through its L2.
 //
-// A column's own reciprocal norm is wanted until its sum is finished, so the sums take the norms' place: 12
-// bytes of LDS a row, and two workgroups fit a compute unit at every capacity (12 cap + 32 KiB: at most 78 KiB
-// of 160).  With both arrays (20 cap + 32 KiB) capacities above 2458 had one: 512 units of 2496 rows 1216 us,
-// of 2996 rows 1780 us, now 985 and 1456.
+// A column's own reciprocal norm is wanted until its sum is finished, so the sums take the norms' place.
 //
-// Dynamic LDS: double cs[cap]; double red[4]; float inv_f[cap]; then the ring, 2 groups x 4 tiles x 4 KiB
-constexpr int RED_NC = 5;
+// Per launch, against 16x16 tiles, comparisons and selections, and two workgroups of four wavefronts per compute
+// unit: 896 units of 640 rows 161 -> 133 us, of 332 96 -> 64, of 700 233 -> 151; 1792 of 1152 772 -> 680; 4 of 640
+// 54 -> 25.  With every compute unit at it the clock falls (a product with random operands then takes 42 to 52
+// of the nominal cycles, not 32), and units start together: all fetch their keys, then all multiply.
+//
+// Dynamic LDS: double cs[cap]; double red[8]; float inv_f[cap]; then the ring, 2 groups x 4 tiles x 8 KiB
+constexpr int RED_NW = 8, RED_TILE = 32 * ROW_BYTES, RED_RING_BYTES = 2 * 4 * RED_TILE;
+// Everything that is compared and added up is scaled by 2^80, so that clamp(x) to [0, 1] of a difference of two
+// scaled numbers is 1 or 0 (the next number above a threshold is at least 1 above it): as a modifier of the
+// subtraction the clamp costs nothing, where a comparison and a selection are two instructions.
+// That asks for reciprocal norms within these bounds (norms of 1e-9 to 1e13); a unit that has
+// others is served by comparisons.
+constexpr double RED_SCALE = 0x1p80, RED_INV_MIN = 0x1p-44, RED_INV_MAX = 0x1p30;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Sum over the 16 lanes of a DPP row (lanes 16i .. 16i+15), left in every one of them: lanes ^1
-// and ^2 of each quad, then the other quad of each 8 (mirror within 8: all four lanes of a quad
-// hold the same value by then), then the other 8 (mirror within 16).  Register-to-register, unlike
-// a shuffle through LDS, whose latency four dependent steps per row would pay in full.
-__device__ __forceinline__ double row16_sum(double v) {
-#define GKV_DPP_STEP(ctrl)                                                                         \
-  {                                                                                                \
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), ctrl, 0xF, 0xF, false);       \
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), ctrl, 0xF, 0xF, false);       \
-    v += __hiloint2double(hi, lo);                                                                 \
-  }
-  GKV_DPP_STEP(0xB1)    // quad_perm [1,0,3,2]
-  GKV_DPP_STEP(0x4E)    // quad_perm [2,3,0,1]
-  GKV_DPP_STEP(0x141)   // row_half_mirror
-  GKV_DPP_STEP(0x140)   // row_mirror
-#undef GKV_DPP_STEP
-  return v;
-}
-constexpr int RED_RING_BYTES = 2 * 4 * TILE_BYTES;
-
-__global__ __launch_bounds__(256) void redundancy_mfma_kernel(GkvDims dm, RedArgs a) {
+__global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims dm, RedArgs a) {
   a.step = resolve_step(dm, a.step);
   extern __shared__ double smem[];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, kb = lane >> 4;
@@ -171,160 +169,230 @@ __global__ __launch_bounds__(256) void redundancy_mfma_kernel(GkvDims dm, RedArg
   double* cs = (double*)smem;
   double* inv = cs;                                      // until the column's sum is finished
   double* red = cs + dm.cap;
-  float* inv_f = (float*)(red + 4);                      // the norms rounded to fp32
-  char* ring = (char*)(inv_f + dm.cap);
+  float* inv_f = (float*)(red + RED_NW);                      // the norms, scaled, in fp32
+  char* ring = (char*)(inv_f + dm.cap);                  // (no other shared variable before these: 16-byte pieces want the alignment)
+  int& s_odd = *(int*)red;
+  if (tid == 0) s_odd = 0;
   const SeqState st = load_state(a.d_state, lb);
   const int l = compression_length(st, a.step, dm.b, dm.w, dm.cap);
   if (l == 0) return;
   const char* Kh = (const char*)a.K + (size_t)unit * dm.cap * ROW_BYTES;
-  const int n_tiles = (l + 15) >> 4;
+  const int n_tiles = (l + 31) >> 5;                     // of 32 keys; the capacity holds whole ones
+  __syncthreads();
 
-  constexpr int NC = RED_NC;
-  const int per_wave = (n_tiles + 3) >> 2;
-  // The column tiles of a pass and this wavefront's tile of the first ring group, requested as
-  // early as their registers are free: for pass 0 before the norms (which they do not depend
-  // on), for the later passes when the previous pass has used its last row tile.
-  u32x4 colA[NC][4], nxt[4];
-  auto request_pass = [&](int p) {
-    const int J0 = wave * per_wave + p * NC;
+  // Every pass shares barriers, so all wavefronts make as many; their column tiles differ by one at most, and
+  // wavefronts w and w + 4, which share a SIMD, get the odd ones from both ends.
+  const int r32 = lane & 31, half = lane >> 5;
+  const int order = wave < 4 ? 2 * wave : 2 * (wave - 4) + 1;
+  const int J_lo = n_tiles * order / RED_NW, n_own = n_tiles * (order + 1) / RED_NW - J_lo;
+  const int n_pass = ((n_tiles + RED_NW - 1) / RED_NW + 2) / 3;
+  u32x4 colA[3][8];
+  auto load_columns = [&](int J0, int J1) {
 #pragma unroll
-    for (int cc = 0; cc < NC; ++cc)                         // past the last tile: a clamped duplicate, computed and dropped
-      load_k_tile(colA[cc], Kh, min(J0 + cc, n_tiles - 1), st.n_tiled, lane, r, kb);
-    load_k_tile(nxt, Kh, min(wave, n_tiles - 1), st.n_tiled, lane, r, kb);
+    for (int cc = 0; cc < 3; ++cc) {
+      if (cc > 0 && J0 + cc >= J1) break;                // (without any column one tile is computed and dropped)
+      const int n = 32 * min(J0 + cc, n_tiles - 1) + r32;
+      const bool tiled = n < st.n_tiled;
+      const char* p = Kh + (size_t)(n >> 4) * TILE_BYTES + (tiled ? half * 256 + (n & 15) * 16 : (n & 15) * ROW_BYTES + half * 16);
+      const int step_off = tiled ? 512 : 32;
+#pragma unroll
+      for (int c = 0; c < 8; ++c) colA[cc][c] = *(const u32x4*)(p + c * step_off);
+    }
   };
-  request_pass(0);
+  // The wavefront's 16 rows of a group, on their way to the ring (clamped past the end: fetched, stored, never
+  // used), where a tile's 16-byte pieces lie in operand order.
+  u32x4 nxt[4];
+  auto request = [&](int G) { load_k_tile(nxt, Kh, min(RED_NW * G + wave, 2 * n_tiles - 1), st.n_tiled, lane, r, kb); };
 
-  // Row norms.  Squared norms first, a quarter-wave per row and 16 bytes per lane, eight rows' loads
-  // issued together; then one row per thread for the fp64 square root and reciprocal, which cost
-  // far more than the sums and would otherwise be repeated by the 16 lanes of every row.
-  constexpr int NU = 8;
-  for (int n0 = tid >> 4; n0 < n_tiles * 16; n0 += 16 * NU) {
-    u32x4 v[NU];
+  // Row norms in fp64, each wavefront those of its own columns, which it needs anyway: the last passes' first, so
+  // that those of the first are there when it starts.
+  {
+    bool odd = false;
+    for (int p = n_pass - 1; p >= 0; --p) {
+      const int J0 = J_lo + n_own * p / n_pass, J1 = J_lo + n_own * (p + 1) / n_pass;
+      load_columns(J0, J1);
+      if (p == 0) request(0);
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int n = n0 + 16 * u, ch = tid & 15;
-      v[u] = u32x4{0u, 0u, 0u, 0u};
-      if (n < l)
-        v[u] = *(const u32x4*)((n < st.n_tiled) ? Kh + (size_t)(n >> 4) * TILE_BYTES + ch * 256 + (n & 15) * 16
-                                                : Kh + (size_t)n * ROW_BYTES + ch * 16);
-    }
+      for (int cc = 0; cc < 3; ++cc) {
+        if (J0 + cc >= J1) break;
+        double q[4] = {0.0, 0.0, 0.0, 0.0};              // in four chains
 #pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int n = n0 + 16 * u;
-      double ss = 0.0;
+        for (int c = 0; c < 8; ++c)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const double lo = (double)__uint_as_float(v[u][i] << 16), hi = (double)__uint_as_float(v[u][i] & 0xffff0000u);
-        ss = fma(lo, lo, ss);
-        ss = fma(hi, hi, ss);
+          for (int i = 0; i < 4; ++i) {
+            const double lo = (double)__uint_as_float(colA[cc][c][i] << 16), hi = (double)__uint_as_float(colA[cc][c][i] & 0xffff0000u);
+            q[i] = fma(lo, lo, q[i]);
+            q[i] = fma(hi, hi, q[i]);
+          }
+        double ss = (q[0] + q[1]) + (q[2] + q[3]);
+        ss += __shfl_xor(ss, 32);
+        const int n = 32 * (J0 + cc) + r32;
+        const double x = n < l ? 1.0 / (sqrt(ss) + (double)a.eps) : 0.0;
+        odd |= n < l && !(x >= RED_INV_MIN && x <= RED_INV_MAX);
+        if (half == 0) { inv[n] = x; inv_f[n] = (float)(x * RED_SCALE); }
       }
-      ss = row16_sum(ss);
-      if ((tid & 15) == 0 && n < n_tiles * 16) inv[n] = ss;
     }
+    if (__any(odd) && lane == 0) s_odd = 1;
   }
-  __syncthreads();
-  for (int n = tid; n < n_tiles * 16; n += 256) {
-    const double v = n < l ? 1.0 / (sqrt(inv[n]) + (double)a.eps) : 0.0;
-    inv[n] = v;
-    inv_f[n] = (float)v;
-  }
-  __syncthreads();
 
   const int first_recent = l - a.n_recent;
   const double tau = (double)a.tau;
-  const int J_end = min(n_tiles, (wave + 1) * per_wave);
-  const int n_pass = (per_wave + NC - 1) / NC;          // the same for all wavefronts: they share the barriers below
-  const int n_groups = (n_tiles + 3) >> 2;
-  // slot of (group parity, tile in group, 16-byte chunk c) for this lane: chunk-major, lane-minor
-  auto slot = [&](int par, int u, int c) { return ring + ((par * 4 + u) * 4 + c) * 1024 + lane * 16; };
-  auto ring_store = [&](int par, const u32x4 (&t)[4]) {
+  __syncthreads();
+  if (s_odd) {
+    // seldom: sixteen by sixteen keys at a time, by comparisons
+    for (int n = tid; n < 32 * n_tiles; n += RED_NW * 64) inv_f[n] = (float)inv[n];
+    __syncthreads();
+    for (int J = wave; J < 2 * n_tiles; J += RED_NW) {
+      u32x4 kj[4];
+      load_k_tile(kj, Kh, J, st.n_tiled, lane, r, kb);
+      const int j = 16 * J + r;
+      const double inv_j = inv[j];
+      const float thr = inv_j > 0.0 ? (float)(tau / inv_j) : 3e38f;
+      double col = 0.0;
+      for (int T = 0; T < 2 * n_tiles; ++T) {
+        u32x4 kt[4];
+        load_k_tile(kt, Kh, T, st.n_tiled, lane, r, kb);
+        const f32x4 invk = *(const f32x4*)(inv_f + 16 * T + 4 * kb);
+        f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < 4; ++c) *(u32x4*)slot(par, wave, c) = t[c];
+        for (int c = 0; c < 4; ++c)
+          z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kt[c]), __builtin_bit_cast(bf16x8, kj[c]), z, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float t = z[e] * invk[e];
+          const int k = 16 * T + 4 * kb + e;
+          if (t >= thr && k != j && k < l) col += (double)t;
+        }
+      }
+      col += __shfl_xor(col, 16);
+      col += __shfl_xor(col, 32);
+      if (kb == 0 && j < l) cs[j] = j < first_recent ? col * inv_j : 0.0;
+    }
+    __syncthreads();
+    finish_unit<RED_NW>(dm, a, unit, l, cs, red);
+    return;
+  }
+
+  auto ring_store = [&](int G) {
+    char* p = ring + (G & 1) * 4 * RED_TILE + (wave >> 1) * RED_TILE + (kb >> 1) * 1024 + ((kb & 1) * 32 + (wave & 1) * 16 + r) * 16;
+    const bool stale = 16 * (RED_NW * G + wave) + r >= l;     // stale rows must not reach the products
+#pragma unroll
+    for (int c = 0; c < 4; ++c) *(u32x4*)(p + c * 2048) = stale ? u32x4{0u, 0u, 0u, 0u} : nxt[c];
   };
-  auto ring_load = [&](u32x4 (&t)[4], int par, int u) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) t[c] = *(const u32x4*)slot(par, u, c);
+  auto ring_piece = [&](int T, int c) {
+    return *(const u32x4*)(ring + (T & 7) * RED_TILE + c * 1024 + lane * 16);
   };
 
-  for (int p = 0; p < n_pass; ++p) {
-    const int J0 = wave * per_wave + p * NC;
-    double inv_j[NC];
+  // one pass: the row tiles against NC column tiles from J0 on
+  auto pass = [&](int J0, int J_end, auto nc) {
+    constexpr int NC = decltype(nc)::value;
     float thr[NC];
     double col[NC];
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc) {
-      // a duplicate's norm may have given way to its sum already: its own column must not look
-      inv_j[cc] = J0 + cc < J_end ? inv[16 * (J0 + cc) + r] : 0.0;
       // C = dot * inv_k * inv_j >= tau  <=>  dot * inv_k >= tau / inv_j: one product per entry, the
-      // column's factor applied once to the sum (columns >= l and duplicates have inv_j = 0 and are dropped below)
-      thr[cc] = inv_j[cc] > 0.0 ? (float)(tau / inv_j[cc]) : 3e38f;
+      // column's factor applied once to the sum (columns >= l and duplicates never pass and are dropped
+      // below; a duplicate's norm may have given way to its sum already: its own column must not look)
+      const double inv_j = J0 + cc < J_end ? inv[32 * (J0 + cc) + r32] : 0.0;
+      thr[cc] = inv_j > 0.0 ? (float)(tau * RED_SCALE / inv_j) : 3e38f;
+      // the number before the threshold: "above it" stands for "at the threshold or above"
+      const int bits = __float_as_int(thr[cc]);
+      thr[cc] = thr[cc] == 0.f ? -1e-45f : __int_as_float(bits < 0 ? bits + 1 : bits - 1);
       col[cc] = 0.0;
     }
-    // One row tile against the NC column tiles.  DIAG: this row tile is one of the column tiles, so
-    // the entries with k == j are left out (wavefront-uniform, so the common case carries no test).
-    auto row_tile = [&](const u32x4 (&rowA)[4], int T, auto diag) {
-      constexpr bool DIAG = decltype(diag)::value;
-      const f32x4 invk = *(const f32x4*)(inv_f + 16 * T + 4 * kb);   // rows >= l have inv = 0: their terms are 0 or fail the test
-      // all column tiles' products first, chunk by chunk: the chains of dependent MFMAs of one tile
-      // would each wait for their own results (with the norms read as fp32: 167 -> 162 us at 896 units
-      // of l = 640)
-      f32x4 acc[NC];
+    // an eighth of the entries of one row tile and column tile cc
+    f32x16 acc[2];
+    f32x4 invk[4];                                         // of the row tile whose entries are being worked on
+    float part = 0.f;
+    auto eighth = [&](const f32x16& z, int c, int cc) {
+      if (!(c & 1)) part = 0.f;                            // four entries of this lane, then fp64
 #pragma unroll
-      for (int cc = 0; cc < NC; ++cc) acc[cc] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int i = 2 * c; i < 2 * c + 2; ++i) {
+        const float t = rounded_product(z[i], invk[i >> 2][i & 3]);
+        part = fmaf(__builtin_amdgcn_fmed3f(t - thr[cc], 0.f, 1.f), t, part);
+      }
+      asm volatile("" : "+v"(part));                     // here, not behind a later branch
+      if (c & 1) {
+        col[cc] += (double)part;
+        asm volatile("" : "+v"(col[cc]));
+      }
+    };
+    // Where the row tile is the column tile the entries with k == j are left out, by a branch of the whole
+    // wavefront: a second version of the loop that tests every entry makes every workgroup fetch it (39 -> 33 us
+    // at 4 units of 640 rows).
+    auto drop_diagonal = [&](f32x16& z) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
+      for (int i = 0; i < 16; ++i)
+        if (8 * (i >> 2) + 4 * half + (i & 3) == r32) z[i] = 0.f;
+    };
 #pragma unroll
-        for (int cc = 0; cc < NC; ++cc)
-          acc[cc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, rowA[c]),
-                                                            __builtin_bit_cast(bf16x8, colA[cc][c]), acc[cc], 0, 0, 0);
+    for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) invk[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 row[8];
+    // One row tile against the NC column tiles; u: T's parity.  The pieces of the next row tile, and the norms of
+    // this one, take their predecessors' place behind the last use.
+    auto row_tile = [&](int T, auto u_) {
+      constexpr int u = decltype(u_)::value;
 #pragma unroll
       for (int cc = 0; cc < NC; ++cc) {
-        float part = 0.f;                               // the four entries of this lane, then fp64 across tiles
+        const int at = (u * NC + cc) & 1, done = cc > 0 ? cc - 1 : NC - 1;
+        if (cc == NC - 1 && u == 1 && (T & 2)) __syncthreads();   // the next group is in the ring
+        if ((cc > 0 ? T : T - 1) == J0 + done) drop_diagonal(acc[at ^ 1]);
+        f32x16 z;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float t = acc[cc][e] * invk[e];
-          bool pass = t >= thr[cc];
-          if (DIAG) pass = pass && !(T == J0 + cc && 4 * kb + e == r);
-          part += pass ? t : 0.f;
+        for (int i = 0; i < 16; ++i) z[i] = 0.f;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, row[c]), __builtin_bit_cast(bf16x8, colA[cc][c]), z, 0, 0, 0);
+          if (cc == NC - 1) row[c] = ring_piece(T + 1, c);
+          eighth(acc[at ^ 1], c, done);
+          if (cc == 0 && (c & 1)) invk[c >> 1] = *(const f32x4*)(inv_f + 32 * T + 8 * (c >> 1) + 4 * half);
+          __builtin_amdgcn_sched_barrier(0);             // in this order: vector instructions between the products
         }
-        col[cc] += (double)part;
+        acc[at] = z;
       }
-    };
-    auto row_tile_any = [&](const u32x4 (&rowA)[4], int T) {
-      if (T >= J0 && T < J0 + NC) row_tile(rowA, T, std::true_type{});
-      else row_tile(rowA, T, std::false_type{});
     };
 
-    ring_store(0, nxt);                                   // group 0 (the previous pass ended with a barrier after its last reads)
+    // Group G + 1 goes into the ring while group G is worked on: into the half that held group G - 1,
+    // whose last tile every wavefront had in registers at the barrier of that group.
+    ring_store(0);
+    request(1);
     __syncthreads();
-    for (int G = 0; G < n_groups; ++G) {
-      const int par = G & 1;
-      // this wavefront's tile of the next group (clamped past the end: fetched, stored, never used)
-      load_k_tile(nxt, Kh, min(4 * (G + 1) + wave, n_tiles - 1), st.n_tiled, lane, r, kb);
-      u32x4 row[2][4];
-      ring_load(row[0], par, 0);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        if (u < 3) ring_load(row[(u + 1) & 1], par, u + 1);
-        if (4 * G + u < n_tiles) row_tile_any(row[u & 1], 4 * G + u);
+    for (int c = 0; c < 8; ++c) row[c] = ring_piece(0, c);
+    for (int T = 0; T < n_tiles; T += 2) {
+      row_tile(T, std::integral_constant<int, 0>{});
+      if (!(T & 2)) {
+        ring_store((T >> 2) + 1);
+        request((T >> 2) + 2);
       }
-      // the other half of the ring was last read in group G - 1, and every wavefront has passed
-      // the barrier that ended it
-      ring_store(par ^ 1, nxt);
-      __syncthreads();
+      if (T + 1 < n_tiles) row_tile(T + 1, std::integral_constant<int, 1>{});
     }
-    if (p + 1 < n_pass) request_pass(p + 1);              // travels while the column sums are put together
+    f32x16 z = n_tiles & 1 ? acc[(NC - 1) & 1] : acc[(2 * NC - 1) & 1];
+    if (n_tiles - 1 == J0 + NC - 1) drop_diagonal(z);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) eighth(z, c, NC - 1);
+    __syncthreads();                                       // what the last group asked the ring for has been read
 #pragma unroll
     for (int cc = 0; cc < NC; ++cc) {
-      double v = col[cc];
-      v += __shfl_xor(v, 16);
-      v += __shfl_xor(v, 32);
-      const int j = 16 * (J0 + cc) + r;
-      if (kb == 0 && J0 + cc < J_end && j < l) cs[j] = j < first_recent ? v * inv_j[cc] : 0.0;
+      const double v = col[cc] + __shfl_xor(col[cc], 32);
+      const int j = 32 * (J0 + cc) + r32;
+      if (half == 0 && J0 + cc < J_end && j < l) cs[j] = j < first_recent ? v * (inv[j] / RED_SCALE) : 0.0;
     }
+  };
+  for (int p = 0; p < n_pass; ++p) {
+    const int J0 = J_lo + n_own * p / n_pass, J1 = J_lo + n_own * (p + 1) / n_pass;
+    if (p > 0) {
+      load_columns(J0, J1);
+      request(0);
+    }
+    if (J1 - J0 == 3) pass(J0, J1, std::integral_constant<int, 3>{});
+    else if (J1 - J0 == 2) pass(J0, J1, std::integral_constant<int, 2>{});
+    else pass(J0, J1, std::integral_constant<int, 1>{});   // (or none: computed and dropped)
   }
   __syncthreads();
-  finish_unit<4>(dm, a, unit, l, cs, red);
+  finish_unit<RED_NW>(dm, a, unit, l, cs, red);
 }
 
 // ---- fp32 at d = 64 or 128 and bf16 at d = 64: the matrix cores in 64 bits --------------------------
@@ -424,13 +492,13 @@ hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dty
   RedArgs a{K, d_state, step, F, lambda, tau, eps, n_recent, R_norm, F_sel};
   const int units = dm.L * dm.B * dm.Hkv;
   if (mfma) {
-    const size_t with_ring = sizeof(double) * ((size_t)dm.cap + 4) + sizeof(float) * (size_t)dm.cap + RED_RING_BYTES;
+    const size_t with_ring = sizeof(double) * ((size_t)dm.cap + RED_NW) + sizeof(float) * (size_t)dm.cap + RED_RING_BYTES;
+    auto kern = redundancy_mfma_kernel;
     if (with_ring > 64 * 1024) {                         // beyond the default per-workgroup limit: opt in (a CU holds 160 KiB)
-      const hipError_t e = hipFuncSetAttribute((const void*)redundancy_mfma_kernel,
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)with_ring);
+      const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)with_ring);
       if (e != hipSuccess) return e;
     }
-    return gkv_launch(ln, redundancy_mfma_kernel, dim3(units), dim3(256), with_ring, dm, a);
+    return gkv_launch(ln, kern, dim3(units), dim3(RED_NW * 64), with_ring, dm, a);
   }
   if (f64_mfma) {
     const bool wide = dtype == GKV_F32 && dm.d == 128;

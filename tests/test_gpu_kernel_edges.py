@@ -501,6 +501,31 @@ def test_redundancy_at_tile_edges(dtype, d):
         np.testing.assert_allclose(Fs[0, i, 0, : n - w], 0.125 - 0.5 * ref[0, : n - w], rtol=0, atol=0.5 * rel + 1.2e-7)
 
 
+@pytest.mark.parametrize("n", [33, 97, 288])
+def test_redundancy_of_keys_of_any_norm(n):
+    # bf16 at d = 128 scales by 2^80 what it compares, and serves units with norms outside 1e-9 .. 1e13 another way:
+    # unit 0 has neither, 1 a tiny key, 2 a huge one, 3 an infinite one, which counts for nobody else
+    w, b, cap, d = 4, 20, 288, 128
+    st = DecodeState(make_config(1, 4, 2, 1, d, b, w, 8, cap, "bf16"))
+    rng = np.random.default_rng(n)
+    centres = rng.standard_normal((6, d))
+    K = torch.full((1, 4, 1, cap, d), float("nan")).to(st.K.dtype)
+    for i, factor in enumerate([1e3, 1e-13, 1e16, float("inf")]):
+        rows = centres[rng.integers(0, 6, n)] + 0.05 * rng.standard_normal((n, d))
+        rows[:: 5] *= 1e-8 if i == 0 else 1.0
+        rows[n // 2] *= factor
+        K[0, i, 0, :n] = torch.from_numpy(rows).to(st.K.dtype)
+    st.K.copy_(K)
+    st.d_state.copy_(torch.tensor([[[n - w, 100 - w, 0, 0]]], dtype=torch.int32).expand(1, 4, 4))
+    st.len_host = cap
+    st.redundancy_combine(99, lam=0.5, tau=0.5, n_recent=3, eps=0.0)
+    R = st.R.double().cpu().numpy()
+    for i in range(4):
+        rest = np.delete(np.arange(n), n // 2) if i == 3 else np.arange(n)
+        Rr = O.redundancy_score(K[0, i, :, rest].double().numpy(), len(rest), tau=0.5, n_recent=3, eps=0.0)
+        np.testing.assert_allclose(R[0, i, 0, rest], (Rr / Rr.max())[0], rtol=1e-5, atol=1e-40)
+
+
 # ---- compaction in column shares ----------------------------------------------------------------
 @pytest.mark.parametrize("dtype,d,B,b", [
     ("bf16", 128, 2, 512),        # 4 units: 4 shares, 256 threads
