@@ -108,13 +108,11 @@ struct Slice {
 // memory-side cache), both non-temporal 76%, one stream of each kind 80-85% at every cache size
 // tried (0.3 to 10 GB), whichever of the two is the non-temporal one.
 template <typename T, int D, int KT>
-__device__ __forceinline__ void issue_slice(Slice<T, D, KT>& s, const char* Kh, const char* Vh, int it,
-                                            int n_tiled, int lane, int r, int kb) {
+__device__ __forceinline__ void issue_k(Slice<T, D, KT>& s, const char* Kh, int it, int n_tiled, int lane, int r, int kb) {
   using G = Geo<T, D>;
-  const int key0 = it * 16 * KT;
 #pragma unroll
   for (int tt = 0; tt < KT; ++tt) {
-    const int row0 = key0 + 16 * tt;
+    const int row0 = it * 16 * KT + 16 * tt;
     const char* Kt = Kh + (size_t)(row0 >> 4) * G::TILE_BYTES;
     const bool tiled = row0 < n_tiled;                     // wave-uniform
     const int lane_off = tiled ? lane * 16 : r * G::ROW_BYTES + kb * 16;
@@ -122,11 +120,20 @@ __device__ __forceinline__ void issue_slice(Slice<T, D, KT>& s, const char* Kh, 
 #pragma unroll
     for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = ld16(Kt + lane_off + c * step_off);
   }
+}
+template <typename T, int D, int KT>
+__device__ __forceinline__ void issue_v(Slice<T, D, KT>& s, const char* Vh, int it, int r, int kb) {
 #pragma unroll
   for (int jj = 0; jj < 4 * KT; ++jj) {
-    const int key = key0 + (jj & 3) + 4 * kb + (jj >> 2) * 16;
-    ld_v<T, D>(s.vR[jj], Vh + (size_t)key * G::ROW_BYTES, r);
+    const int key = it * 16 * KT + (jj & 3) + 4 * kb + (jj >> 2) * 16;
+    ld_v<T, D>(s.vR[jj], Vh + (size_t)key * Geo<T, D>::ROW_BYTES, r);
   }
+}
+template <typename T, int D, int KT>
+__device__ __forceinline__ void issue_slice(Slice<T, D, KT>& s, const char* Kh, const char* Vh, int it,
+                                            int n_tiled, int lane, int r, int kb) {
+  issue_k<T, D, KT>(s, Kh, it, n_tiled, lane, r, kb);
+  issue_v<T, D, KT>(s, Vh, it, r, kb);
 }
 
 // Flash-decoding state of one wavefront: lane (head = lane%16, blk = lane/16) holds the running
@@ -313,11 +320,15 @@ __device__ __forceinline__ float inv_sum(float l, bool any_key, bool fast) {
   return fast ? __builtin_amdgcn_rcpf(l) : 1.f / l;
 }
 
-// KT = 16-key tiles per wavefront iteration (1 or 2)
-template <typename T, int D, int NW, int KT, int OCC>
-__global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, AttendArgs a) {
+// x / d for 0 <= x < 2^31.  An integer division is some twenty instructions, at the start of a kernel whose first
+// requests wait for it.
+__device__ __forceinline__ int quotient(int x, GkvDivisor d) { return (int)(__umulhi(2u * (uint32_t)x, d.mul) >> d.shift); }
+
+// KT = 16-key tiles per wavefront iteration (1 or 2).  AHEAD: two slices in flight per wavefront,
+// the first requested ahead of the state record.
+template <typename T, int D, int NW, int KT, int OCC, bool AHEAD>
+__global__ __launch_bounds__(NW * 64, AHEAD ? 2 : OCC) void attend_mfma_kernel(GkvDims dm, AttendArgs a) {
   using G = Geo<T, D>;
-  a.step = resolve_step(dm, a.step);
   constexpr int KEYS = 16 * KT;             // keys per iteration
   constexpr int RP = G::RP, ROW_BYTES = G::ROW_BYTES, OSTR = G::OSTR, PSTR = G::PSTR;
   extern __shared__ __attribute__((aligned(16))) float smem[];   // behind s_last: 16-byte pieces want the alignment
@@ -325,64 +336,68 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = lane & 15, kb = lane >> 4;
   const int splits = a.splits;
-  const int unit = blockIdx.x / splits, sp = blockIdx.x % splits;
-  const int j = unit % dm.Hkv, lb = unit / dm.Hkv;
+  const int unit = quotient(blockIdx.x, a.by_splits), sp = (int)blockIdx.x - unit * splits;
+  const int lb = quotient(unit, a.by_hkv), j = unit - lb * dm.Hkv;
   const int g = dm.g, cap = dm.cap;
   const char* Kh = (const char*)a.K + (size_t)unit * cap * ROW_BYTES;
   const char* Vh = (const char*)a.V + (size_t)unit * cap * ROW_BYTES;
-
-  // Splits this unit is really cut into: as many as its own length fills with `split_iters` slices
-  // each (an explicit split count sets split_iters = 0: always all of them).  A workgroup beyond them
-  // leaves before it has asked for anything else.
-  int ns = splits;
-  if (splits > 1 && a.split_iters > 0) {
-    const int l0 = length_before_step(load_state(a.d_state, lb), a.step, cap);
-    const int n = (l0 + (a.k_new != nullptr && l0 < cap ? 1 : 0) + KEYS - 1) / KEYS;
-    ns = max(1, min(splits, (n + a.split_iters - 1) / a.split_iters));
-    if (sp >= ns) return;
-  }
-  // Requests whose addresses do not depend on the state record go out first: the group's
-  // queries (B operand of the QK product: lane (head r, kb) holds chunks 4c+kb of q[r]) and the
-  // rows stored at the end of the workgroup, one 16-byte piece per thread and round: pieces
-  // [0,RP) k_new, [RP,2RP) v_new (every workgroup: the wavefront that owns the last slice
-  // substitutes them for cache row `len`), [2RP, 2RP + RP g) the group's q rows for the window
-  // ring (split 0 only).
-  u32x4 qB[G::NL];
-  {
-    const char* qh = (const char*)a.q + ((size_t)lb * dm.Hq + j * g + r) * ROW_BYTES;
-#pragma unroll
-    for (int c = 0; c < G::NL; ++c) {
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (r < g) v = ld16(qh + (4 * c + kb) * 16);
-      qB[c] = v;
-    }
-  }
-  constexpr int AP_ROUNDS = (2 * RP + RP * 16 + NW * 64 - 1) / (NW * 64);
-  u32x4 ap[AP_ROUNDS];
+  const char* knew_g = (const char*)a.k_new + (size_t)unit * ROW_BYTES;
+  const char* vnew_g = (const char*)a.v_new + (size_t)unit * ROW_BYTES;
+  const char* q_g = (const char*)a.q + ((size_t)lb * dm.Hq + j * g) * ROW_BYTES;
   const bool appender = sp == 0;
   const bool ring_copy = appender && a.copy_q;   // q may already live in its ring slot
   const bool may_grow = a.k_new != nullptr;
+
+  // A launch of few units is one trip to memory after the other, so everything whose address the arguments
+  // give is requested before anything is waited for: the state record and the step counter (scalar loads; no
+  // branch on whether there is a counter), the group's queries (B operand of the QK product: lane (head r, kb)
+  // holds chunks 4c+kb of q[r]), the rows stored at the end of the workgroup, and with AHEAD the first slice.
+  int4 rec = *(const int4*)(a.d_state + 4 * (size_t)lb);
+  const int32_t base = *(dm.step_base ? dm.step_base : a.d_state);
+  __builtin_amdgcn_sched_barrier(0);
+  u32x4 qB[G::NL];
   {
-    // one load a round under one condition: with a branch per source the register allocation may make a
-    // load wait for those before it (a trip to memory: 128 steps of 4 units 970 -> 1010 us)
-    const char* knew_g = (const char*)a.k_new + (size_t)unit * ROW_BYTES;
-    const char* vnew_g = (const char*)a.v_new + (size_t)unit * ROW_BYTES - ROW_BYTES;
-    const char* q_g = (const char*)a.q + ((size_t)lb * dm.Hq + j * g) * ROW_BYTES - 2 * ROW_BYTES;
+    const char* qh = q_g + min(r, g - 1) * ROW_BYTES;      // (lanes beyond the group repeat its last head and are ignored)
 #pragma unroll
-    for (int rd = 0; rd < AP_ROUNDS; ++rd) {
-      const int x = tid + rd * NW * 64;
-      ap[rd] = u32x4{0u, 0u, 0u, 0u};
-      const char* src = x < RP ? knew_g : x < 2 * RP ? vnew_g : q_g;
-      if (x < 2 * RP ? may_grow : ring_copy && x < 2 * RP + RP * g) ap[rd] = ld16(src + x * 16);
-    }
+    for (int c = 0; c < G::NL; ++c) qB[c] = ld16(qh + (4 * c + kb) * 16);
   }
+  // one 16-byte piece per thread and round: pieces [0,RP) k_new, [RP,2RP) v_new (every workgroup: the wavefront
+  // that owns the last slice substitutes them for cache row `len`), [2RP, 2RP + RP g) the group's q rows for
+  // the window ring (split 0 only); others read a valid address and are not used
+  constexpr int AP_ROUNDS = (2 * RP + RP * 16 + NW * 64 - 1) / (NW * 64);
+  u32x4 ap[AP_ROUNDS];
+#pragma unroll
+  for (int rd = 0; rd < AP_ROUNDS; ++rd) {
+    const int x = tid + rd * NW * 64;
+    const char* src = q_g + (x < 2 * RP + RP * g && x >= 2 * RP ? x - 2 * RP : 0) * 16;
+    if (may_grow && x < 2 * RP) src = (x < RP ? knew_g : vnew_g - ROW_BYTES) + x * 16;
+    ap[rd] = ld16(src);
+  }
+  const int it0 = sp * NW + wave;
+  Slice<T, D, KT> s, s2;
+  __builtin_amdgcn_sched_barrier(0);           // loads come back in order: these before the slice's
+  if constexpr (AHEAD) {                       // rows below the capacity, whatever the length
+    issue_k<T, D, KT>(s, Kh, min(it0, cap / KEYS - 1), a.guess, lane, r, kb);
+    issue_v<T, D, KT>(s, Vh, min(it0, cap / KEYS - 1), r, kb);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" : "+s"(rec.x), "+s"(rec.y), "+s"(rec.w));   // one load, not one for each of them
+  const SeqState seq = state_record(rec);
+  if (dm.step_base) a.step += base;
 
   // The length comes from the state record and the step number; nothing is written back, so
   // the workgroups of a (layer, sequence) need no ordering among themselves.
-  const SeqState seq = load_state(a.d_state, lb);
   const int len0 = length_before_step(seq, a.step, cap);
   const bool has_new = may_grow && (len0 < cap);
   const int n_tot = len0 + (has_new ? 1 : 0);
+  const int n_iter = (n_tot + KEYS - 1) / KEYS;
+  // Splits this unit is really cut into: as many as its own length fills with `split_iters` slices
+  // each (an explicit split count sets split_iters = 0: always all of them).
+  int ns = splits;
+  if (splits > 1 && a.split_iters > 0) {
+    ns = max(1, min(splits, (n_iter + a.split_iters - 1) / a.split_iters));
+    if (sp >= ns) return;
+  }
   const float scale_log2 = dm.scale_l2_hi, scale_log2_lo = dm.scale_l2_lo;
 
   Running<G::NC> st;
@@ -392,10 +407,15 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
   for (int m = 0; m < G::NC; ++m) st.oacc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // First slice in flight, then stage k_new / v_new in LDS for whoever owns the last slice.
-  const int n_iter = (n_tot + KEYS - 1) / KEYS;
-  const int stride = ns * NW, it0 = sp * NW + wave;
-  Slice<T, D, KT> s;
-  if (it0 < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it0, seq.n_tiled, lane, r, kb);
+  const int stride = ns * NW;
+  if constexpr (AHEAD) {
+    // the last compression left b rows tiled; in a prompt's rows, which are not, the guess was wrong
+    auto tiled_rows = [&](int n_tiled) { return max(0, min(KEYS, n_tiled - it0 * KEYS)); };
+    if (it0 < n_iter && tiled_rows(a.guess) != tiled_rows(seq.n_tiled)) issue_k<T, D, KT>(s, Kh, it0, seq.n_tiled, lane, r, kb);
+    if (it0 + stride < n_iter) issue_slice<T, D, KT>(s2, Kh, Vh, it0 + stride, seq.n_tiled, lane, r, kb);
+  } else {
+    if (it0 < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it0, seq.n_tiled, lane, r, kb);
+  }
   // stage: 16-byte pieces [0,RP) k_new, [RP,2RP) v_new, [2RP, 2RP+RP*g) q rows; kept in LDS, not
   // in registers, until they are stored at the end
   char* stage = (char*)(smem + NW * g * OSTR + NW * 16 + NW * 16);
@@ -408,17 +428,31 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
   }
   __syncthreads();
   // this wavefront's slices, the first one already requested
-  auto slices = [&](auto exact) {
+  auto process = [&](Slice<T, D, KT>& x, int it, auto exact) {
     constexpr bool EXACT = decltype(exact)::value;
-    int it = it0;
-    while (it < n_iter) {
-      if ((it + 1) * KEYS > len0) process_slice<T, D, KT, true, EXACT>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
-      else process_slice<T, D, KT, false, EXACT>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
-      it += stride;
-      if (it < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it, seq.n_tiled, lane, r, kb);
+    if ((it + 1) * KEYS > len0) process_slice<T, D, KT, true, EXACT>(x, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
+    else process_slice<T, D, KT, false, EXACT>(x, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
+  };
+  auto request = [&](Slice<T, D, KT>& x, int it) {
+    if (it < n_iter) issue_slice<T, D, KT>(x, Kh, Vh, it, seq.n_tiled, lane, r, kb);
+  };
+  auto slices = [&](auto exact) {
+    for (int it = it0; it < n_iter; it += stride) {
+      process(s, it, exact);
+      request(s, it + stride);
     }
   };
-  slices(std::false_type{});
+  if constexpr (AHEAD) {
+    for (int it = it0; it < n_iter; it += 2 * stride) {
+      process(s, it, std::false_type{});
+      request(s, it + 2 * stride);
+      if (it + stride >= n_iter) break;
+      process(s2, it + stride, std::false_type{});
+      request(s2, it + 3 * stride);
+    }
+  } else {
+    slices(std::false_type{});
+  }
   if (it0 < n_iter) {
     // Seldom: a maximum that the short form of the weights is not right for, or a NaN that may be its
     // doing (a logit of -inf; at bf16, D = 64 an infinite value that met a part of P that is zero or
@@ -560,10 +594,21 @@ size_t gkv_attend_mfma_lds(int esz, int d, int g, int waves) {
 }
 
 template <typename T, int D, int NW, int KT, int OCC>
-static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a) {
+static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, AttendArgs a) {
   const int units = dm.L * dm.B * dm.Hkv;
+  a.by_splits = gkv_divisor(a.splits);
+  a.by_hkv = gkv_divisor(dm.Hkv);
   const size_t shmem = gkv_attend_mfma_lds(sizeof(T), D, dm.g, NW);
-  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);
+  // Two slices in flight, the first requested ahead, while the launch leaves the chip room: us per launch in a
+  // graph, one slice requested behind the state record -> two: 4 units x 577 rows 6.38 -> 6.28, 32 x 1100 8.74 -> 8.22,
+  // 128 x 2112 25.1 -> 24.6, 256 x 1056 23.2 -> 22.7; fp32 32 x 528 9.53 -> 9.17; 128 steps of 4 units with their
+  // compression 885 -> 860, 64 of 256 1590 -> 1569.  Not above: 400 x 577 20.9 -> 21.4, 896 x 576 41.0 -> 42.2
+  // (more requests in flight make a full memory system slower); nor at bf16, d = 64 (128 x 528 6.31 -> 6.59).
+  if constexpr (NW <= 8 && KT == 1) {
+    if (units <= 256)
+      return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, true>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);
+  }
+  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, false>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);
 }
 
 hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a) {

@@ -90,6 +90,14 @@ struct GkvLaunch {
 };
 
 // ---- launch wrappers implemented in the kernel files -------------------------------------
+// x / d = (2 x mul) >> (32 + shift) for 0 <= x < 2^31, with mul = 2^(31 + shift) / d rounded up and
+// 2^shift >= d the smallest (mul d exceeds 2^(31 + shift) by less than d <= 2^shift).
+struct GkvDivisor { uint32_t mul; uint32_t shift; };
+static inline GkvDivisor gkv_divisor(int32_t d) {
+  uint32_t shift = 0;
+  while ((int64_t)1 << shift < d) ++shift;
+  return GkvDivisor{(uint32_t)((((uint64_t)1 << (31 + shift)) + d - 1) / d), shift};
+}
 struct AttendArgs {
   const void* q; const void* k_new; const void* v_new;
   void* K; void* V; int32_t* pos; int32_t step; void* qwin; const int32_t* d_state; void* out;
@@ -97,7 +105,9 @@ struct AttendArgs {
   int32_t copy_q;   // 0 when q already is the ring slot of this step
   int32_t write_stats;   // record (max, sum) of every query head's softmax in ws.stats
   int32_t waves;         // wavefronts per workgroup of the matrix-core kernel: 4, 8 or 16
+  int32_t guess;         // rows of K taken to be tiled where slices are requested ahead of the state record
   int32_t split_iters;   // slices per piece (a unit of n slices is cut into ceil(n / split_iters)); 0 = all splits
+  GkvDivisor by_splits, by_hkv;   // set by the launch wrapper
 };
 hipError_t gkv_launch_attend_generic(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
 hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
@@ -155,13 +165,15 @@ static inline hipError_t gkv_launch(const GkvLaunch& ln, F kernel, dim3 grid, di
 struct SeqState {
   int32_t len, len_step, n_hist, n_tiled;
 };
-__device__ __forceinline__ SeqState load_state(const int32_t* d_state, int lb) {
-  const int4 v = *(const int4*)(d_state + 4 * (size_t)lb);
+__device__ __forceinline__ SeqState state_record(const int4& v) {
   // the tiled prefix is whole tiles and never reaches past the stored length
   int nt = v.w & ~15;
   const int lim = (v.x > 0 ? v.x : 0) & ~15;
   nt = nt < 0 ? 0 : (nt > lim ? lim : nt);
   return SeqState{v.x, v.y, v.z, nt};
+}
+__device__ __forceinline__ SeqState load_state(const int32_t* d_state, int lb) {
+  return state_record(*(const int4*)(d_state + 4 * (size_t)lb));
 }
 // Length before decode step `t` (every step since len_step appended one row), kept inside [0, cap].
 __device__ __forceinline__ int length_before_step(const SeqState& s, int t, int cap) {

@@ -57,6 +57,34 @@ def _check_attend(st, K, V, q, kn, vn, lens, dtype, d, append):
     assert torch.equal(st.qwin[5 % 4].cpu(), q)
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
+@pytest.mark.parametrize("B,hkv,n_tiled", [(85, 3, 16), (87, 3, 48), (52, 5, 0)])   # 255, 261 and 260 units
+def test_attend_on_both_sides_of_256_units(dtype, d, B, hkv, n_tiled):
+    # up to 256 units a wavefront asks for its first slice ahead of the state record, taking b // 16 * 16 rows of K
+    # to be tiled: right and wrong guesses, lengths from nothing to the last row, a group of 5 and rows
+    # of NaN behind every length; KV heads and workgroups that are no power of two
+    g, b, cap = 5, 40, 96
+    st = DecodeState(make_config(1, B, hkv * g, hkv, d, b, 4, 8, cap, dtype))
+    gen = torch.Generator().manual_seed(B * d)
+    rnd = lambda *s: torch.randn(*s, generator=gen).to(st.K.dtype)
+    K, V, q, kn, vn = rnd(1, B, hkv, cap, d), rnd(1, B, hkv, cap, d), rnd(1, B, hkv * g, d), rnd(1, B, hkv, d), rnd(1, B, hkv, d)
+    lens = [i % cap for i in range(B)]
+    for i, n in enumerate(lens):
+        K[0, i, :, n:] = float("nan"); V[0, i, :, n:] = float("nan")
+        st.K[0, i] = k_rows_to_cache(K[0, i], min(n_tiled, n // 16 * 16)).cuda()
+    st.V.copy_(V)
+    st.d_state.copy_(torch.tensor([[[n, 5, 0, min(n_tiled, n // 16 * 16)] for n in lens]], dtype=torch.int32))
+    st.len_host = max(lens)
+    out = st.attend_decode(q.cuda(), kn.cuda(), vn.cuda(), 5).double().cpu().numpy()
+    for i, n in enumerate(lens):
+        Ki, Vi = K[0, i].double().numpy().copy(), V[0, i].double().numpy().copy()
+        Ki[:, n], Vi[:, n] = kn[0, i].double().numpy(), vn[0, i].double().numpy()
+        ref = O.attend(q[0, i].double().numpy(), Ki[:, : n + 1], Vi[:, : n + 1], n + 1)
+        assert (np.abs(out[0, i] - ref) <= _bound(dtype, d, ref, Vi[:, : n + 1])).all(), n
+        assert torch.equal(st.V[0, i, :, n].cpu(), vn[0, i]) and (st.pos[0, i, :, n] == 5).all()
+    assert torch.equal(st.qwin[5 % 4].cpu(), q)
+
+
 @pytest.mark.parametrize("append", [True, False])
 @pytest.mark.parametrize("dtype,d,g", [("f32", 64, 1), ("f32", 64, 16), ("f32", 128, 7), ("f32", 128, 16),
                                        ("bf16", 64, 5), ("bf16", 64, 16), ("bf16", 128, 3)])
