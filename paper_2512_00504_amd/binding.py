@@ -3,7 +3,9 @@
 Every step of the path runs in the HIP kernels behind the C ABI declared in
 include/gkv.h; the functions here have the same names and pass device
 pointers of torch tensors and the current torch stream straight through.
-There is no fallback: if the library is missing, loading raises.
+The calls a program makes per decode step or compression are marshalled by
+_gkv_call (csrc/call.cpp); what it does not take, ctypes converts or refuses.
+There is no fallback: if a library is missing, loading raises.
 """
 from __future__ import annotations
 
@@ -113,6 +115,23 @@ def _stream():
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
+_call = None
+
+
+def _load_call():
+    """The native marshalling, bound to the entry points of the library that ctypes loaded."""
+    global _call
+    if _call is None:
+        lib = load_library()
+        import torch  # noqa: F401  (the extension's libraries)
+        from . import _gkv_call
+        for name in dir(_gkv_call):
+            if name.startswith("gkv_"):
+                _gkv_call.bind(name, ctypes.cast(getattr(lib, name), c_void_p).value)
+        _call = _gkv_call
+    return _call
+
+
 class Context:
     """Owns a gkv_ctx.  Methods mirror the C entry points one to one."""
 
@@ -124,11 +143,13 @@ class Context:
         if st != 0:
             raise GkvError(st, "gkv_create")
         self.h = h
+        self._handle = h.value
+        self._call = _load_call()
 
     def close(self):
         if getattr(self, "h", None):
             self.lib.gkv_destroy(self.h)
-            self.h = None
+            self.h = self._handle = None
 
     def __del__(self):
         try:
@@ -159,31 +180,54 @@ class Context:
         self._check(self.lib.gkv_workspace_init(self.h, _ptr(workspace), _stream()), "gkv_workspace_init")
 
     def attend_decode(self, q, k_new, v_new, K, V, pos, step, qwin, d_state, len_max_host, out, workspace):
-        self._check(self.lib.gkv_attend_decode(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(K), _ptr(V),
-                                               _ptr(pos), step, _ptr(qwin), _ptr(d_state), len_max_host,
-                                               _ptr(out), _ptr(workspace), _stream()), "gkv_attend_decode")
+        st = self._call.gkv_attend_decode(self._handle, q, k_new, v_new, K, V, pos, step, qwin, d_state, len_max_host, out, workspace)
+        if st is None:
+            st = self.lib.gkv_attend_decode(self.h, _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(K), _ptr(V),
+                                            _ptr(pos), step, _ptr(qwin), _ptr(d_state), len_max_host,
+                                            _ptr(out), _ptr(workspace), _stream())
+        if st:
+            raise GkvError(st, "gkv_attend_decode")
 
     def score_window(self, qwin, K, d_state, step, len_max_host, S, workspace):
-        self._check(self.lib.gkv_score_window(self.h, _ptr(qwin), _ptr(K), _ptr(d_state), step, len_max_host,
-                                              _ptr(S), _ptr(workspace), _stream()), "gkv_score_window")
+        st = self._call.gkv_score_window(self._handle, qwin, K, d_state, step, len_max_host, S, workspace)
+        if st is None:
+            st = self.lib.gkv_score_window(self.h, _ptr(qwin), _ptr(K), _ptr(d_state), step, len_max_host,
+                                           _ptr(S), _ptr(workspace), _stream())
+        if st:
+            raise GkvError(st, "gkv_score_window")
 
     def global_update(self, S, F_hist, d_state, step, len_max_host, F_out):
-        self._check(self.lib.gkv_global_update(self.h, _ptr(S), _ptr(F_hist), _ptr(d_state), step,
-                                               len_max_host, _ptr(F_out), _stream()), "gkv_global_update")
+        st = self._call.gkv_global_update(self._handle, S, F_hist, d_state, step, len_max_host, F_out)
+        if st is None:
+            st = self.lib.gkv_global_update(self.h, _ptr(S), _ptr(F_hist), _ptr(d_state), step,
+                                            len_max_host, _ptr(F_out), _stream())
+        if st:
+            raise GkvError(st, "gkv_global_update")
 
     def select_topk(self, F, d_state, step, len_max_host, keep_idx, workspace):
-        self._check(self.lib.gkv_select_topk(self.h, _ptr(F), _ptr(d_state), step, len_max_host, _ptr(keep_idx),
-                                             _ptr(workspace), _stream()), "gkv_select_topk")
+        st = self._call.gkv_select_topk(self._handle, F, d_state, step, len_max_host, keep_idx, workspace)
+        if st is None:
+            st = self.lib.gkv_select_topk(self.h, _ptr(F), _ptr(d_state), step, len_max_host, _ptr(keep_idx),
+                                          _ptr(workspace), _stream())
+        if st:
+            raise GkvError(st, "gkv_select_topk")
 
     def compact(self, keep_idx, F, K, V, F_hist, pos, d_state, step, workspace):
-        self._check(self.lib.gkv_compact(self.h, _ptr(keep_idx), _ptr(F), _ptr(K), _ptr(V), _ptr(F_hist),
-                                         _ptr(pos), _ptr(d_state), step, _ptr(workspace), _stream()),
-                    "gkv_compact")
+        st = self._call.gkv_compact(self._handle, keep_idx, F, K, V, F_hist, pos, d_state, step, workspace)
+        if st is None:
+            st = self.lib.gkv_compact(self.h, _ptr(keep_idx), _ptr(F), _ptr(K), _ptr(V), _ptr(F_hist),
+                                      _ptr(pos), _ptr(d_state), step, _ptr(workspace), _stream())
+        if st:
+            raise GkvError(st, "gkv_compact")
 
     def evict(self, qwin, K, V, F_hist, pos, d_state, step, len_max_host, S, F, keep_idx, workspace):
-        self._check(self.lib.gkv_evict(self.h, _ptr(qwin), _ptr(K), _ptr(V), _ptr(F_hist), _ptr(pos),
-                                       _ptr(d_state), step, len_max_host, _ptr(S), _ptr(F),
-                                       _ptr(keep_idx), _ptr(workspace), _stream()), "gkv_evict")
+        st = self._call.gkv_evict(self._handle, qwin, K, V, F_hist, pos, d_state, step, len_max_host, S, F, keep_idx, workspace)
+        if st is None:
+            st = self.lib.gkv_evict(self.h, _ptr(qwin), _ptr(K), _ptr(V), _ptr(F_hist), _ptr(pos),
+                                    _ptr(d_state), step, len_max_host, _ptr(S), _ptr(F),
+                                    _ptr(keep_idx), _ptr(workspace), _stream())
+        if st:
+            raise GkvError(st, "gkv_evict")
 
     def evict_static(self, qwin, K, V, F_hist, pos, d_state, step, len_max_host, workspace):
         self._check(self.lib.gkv_evict_static(self.h, _ptr(qwin), _ptr(K), _ptr(V), _ptr(F_hist), _ptr(pos),
@@ -191,17 +235,25 @@ class Context:
                     "gkv_evict_static")
 
     def redundancy_combine(self, K, d_state, step, len_max_host, F, lam, tau, eps, n_recent, R_norm, F_sel, workspace):
-        self._check(self.lib.gkv_redundancy_combine(self.h, _ptr(K), _ptr(d_state), step, len_max_host, _ptr(F),
-                                                    lam, tau, eps, n_recent, _ptr(R_norm), _ptr(F_sel),
-                                                    _ptr(workspace), _stream()), "gkv_redundancy_combine")
+        st = self._call.gkv_redundancy_combine(self._handle, K, d_state, step, len_max_host, F, lam, tau, eps, n_recent, R_norm, F_sel, workspace)
+        if st is None:
+            st = self.lib.gkv_redundancy_combine(self.h, _ptr(K), _ptr(d_state), step, len_max_host, _ptr(F),
+                                                 lam, tau, eps, n_recent, _ptr(R_norm), _ptr(F_sel),
+                                                 _ptr(workspace), _stream())
+        if st:
+            raise GkvError(st, "gkv_redundancy_combine")
 
     def pool_scores(self, F, d_state, step, kernel, F_out):
         self._check(self.lib.gkv_pool_scores(self.h, _ptr(F), _ptr(d_state), step, kernel, _ptr(F_out), _stream()),
                     "gkv_pool_scores")
 
     def evicted_positions(self, keep_idx, pos, d_state, step, evicted):
-        self._check(self.lib.gkv_evicted_positions(self.h, _ptr(keep_idx), _ptr(pos), _ptr(d_state), step,
-                                                   _ptr(evicted), _stream()), "gkv_evicted_positions")
+        st = self._call.gkv_evicted_positions(self._handle, keep_idx, pos, d_state, step, evicted)
+        if st is None:
+            st = self.lib.gkv_evicted_positions(self.h, _ptr(keep_idx), _ptr(pos), _ptr(d_state), step,
+                                                _ptr(evicted), _stream())
+        if st:
+            raise GkvError(st, "gkv_evicted_positions")
 
     def profile_enable(self, on: bool):
         self._check(self.lib.gkv_profile_enable(self.h, int(on)), "gkv_profile_enable")

@@ -68,9 +68,9 @@ class DecodeState:
         self.workspace = torch.zeros(self.ctx.workspace_bytes(), dtype=torch.uint8, device=dev)
         self.ctx.workspace_init(self.workspace)
         # host mirror of the device records, for launch sizing and the trigger only: per sequence,
-        # the cache length and the steps decoded since the cache was loaded or last compacted
-        self._len = [0] * B
-        self._since = [0] * B
+        # the cache length and the steps decoded since the cache was loaded or last compacted, both as
+        # of the last time they were set apart; _grown rows and _stepped steps later for all of them
+        self._set_host([0] * B, [0] * B)
 
     @classmethod
     def from_workload(cls, wl, device="cuda:0", params=None, **over):
@@ -80,16 +80,27 @@ class DecodeState:
         kw.update(over)
         return cls(make_config(**kw), device=device, params=params)
 
+    def _set_host(self, lengths, since):
+        self._len0, self._since0, self._max0 = lengths, since, max(lengths)
+        self._grown = self._stepped = 0
+
+    @property
+    def _len(self):
+        return [x + self._grown for x in self._len0]
+
+    @property
+    def _since(self):
+        return [x + self._stepped for x in self._since0]
+
     @property
     def len_host(self) -> int:
         """Upper bound of every sequence's length, as the calls' len_max_host wants it."""
-        return max(self._len)
+        return self._max0 + self._grown
 
     @len_host.setter
     def len_host(self, value: int):
         """Declare every sequence `value` rows long with a full observation window."""
-        self._len = [int(value)] * self.cfg.batch
-        self._since = [self.cfg.window] * self.cfg.batch
+        self._set_host([int(value)] * self.cfg.batch, [self.cfg.window] * self.cfg.batch)
 
     # lengths as the kernels see them ---------------------------------------------------------
     def lengths(self, next_step: int) -> torch.Tensor:
@@ -102,8 +113,7 @@ class DecodeState:
         self.d_state[..., ST_LEN_STEP] = len_step
         self.d_state[..., ST_N_HIST] = n_hist
         self.d_state[..., ST_N_TILED] = n_tiled
-        self._len = [int(length)] * self.cfg.batch
-        self._since = [0] * self.cfg.batch
+        self._set_host([int(length)] * self.cfg.batch, [0] * self.cfg.batch)
 
     def load_prefix(self, k, v, t0=0):
         """Place tokens t0..t0+n-1 (k, v: [n, L, B, h_kv, d]) as cache rows 0..n-1 with positions
@@ -141,23 +151,21 @@ class DecodeState:
         """Records {P_i, t0, 0, 0}: sequence i holds P_i prompt rows before decode step t0."""
         rec = torch.tensor([[P, t0, 0, 0] for P in prompt_lens], dtype=torch.int32)
         self.d_state.copy_(rec.to(self.device).expand(self.cfg.n_layers, -1, -1))
-        self._len = [int(P) for P in prompt_lens]
-        self._since = [0] * self.cfg.batch
+        self._set_host([int(P) for P in prompt_lens], [0] * len(prompt_lens))
 
     def _after_compression(self):
         """Host mirror of what the compression kernels decide per sequence."""
         b, w = self.cfg.budget, self.cfg.window
-        for i in range(self.cfg.batch):
-            if self._len[i] > b and self._since[i] >= w:
-                self._len[i], self._since[i] = b, 0
+        done = [n > b and k >= w for n, k in zip(self._len, self._since)]
+        self._set_host([b if x else n for x, n in zip(done, self._len)], [0 if x else k for x, k in zip(done, self._since)])
 
     # one call each -------------------------------------------------------------------------
     def attend_decode(self, q, k_new, v_new, step):
         self.ctx.attend_decode(q, k_new, v_new, self.K, self.V, self.pos, step, self.qwin, self.d_state,
                                self.len_host, self.out, self.workspace)
         if k_new is not None:
-            self._len = [x + 1 for x in self._len]
-        self._since = [x + 1 for x in self._since]
+            self._grown += 1
+        self._stepped += 1
         return self.out
 
     def score_window(self, step):

@@ -150,3 +150,25 @@ def test_benchmark_refuses_more_than_one_gpu():
                          timeout=120)
     assert res.returncode != 0
     assert "--gpus must be 1" in (res.stdout + res.stderr)
+
+
+@pytest.mark.parametrize("change", [
+    {}, {0: None}, {0: 0}, {0: 1.0}, {2: 1 << 31}, {2: -(1 << 31) - 1}, {2: True}, {2: 3.0}, {2: None}, {1: 5}, {1: "x"},
+    {1: torch.zeros(4).t()}, {1: torch.nn.Parameter(torch.zeros(4))}, {1: torch.zeros(4, device="meta")}, {-1: "drop"}, {-1: "add"},
+])
+def test_native_call_leaves_other_arguments_to_ctypes(change):
+    # nothing here is a tensor on a GPU (not even in the first case): the native half must return None, without a call
+    from paper_2512_00504_amd import binding
+    call = binding._load_call()
+    z = torch.zeros(4)
+    full = [1 << 40, z, z, 3, 4, z, z]                     # a handle that must not be looked at
+    for at, value in change.items():
+        if value == "drop":
+            full = full[:-1]
+        elif value == "add":
+            full = full + [None]
+        else:
+            full[{0: 0, 1: 1, 2: 3}[at]] = value
+    assert call.gkv_select_topk(*full) is None
+    with pytest.raises(KeyError):
+        call.bind("gkv_destroy", 1)
