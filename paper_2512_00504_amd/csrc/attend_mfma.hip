@@ -320,10 +320,6 @@ __device__ __forceinline__ float inv_sum(float l, bool any_key, bool fast) {
   return fast ? __builtin_amdgcn_rcpf(l) : 1.f / l;
 }
 
-// x / d for 0 <= x < 2^31.  An integer division is some twenty instructions, at the start of a kernel whose first
-// requests wait for it.
-__device__ __forceinline__ int quotient(int x, GkvDivisor d) { return (int)(__umulhi(2u * (uint32_t)x, d.mul) >> d.shift); }
-
 // KT = 16-key tiles per wavefront iteration (1 or 2).  AHEAD: two slices in flight per wavefront,
 // the first requested ahead of the state record.
 template <typename T, int D, int NW, int KT, int OCC, bool AHEAD>
@@ -337,7 +333,7 @@ __global__ __launch_bounds__(NW * 64, AHEAD ? 2 : OCC) void attend_mfma_kernel(G
   const int r = lane & 15, kb = lane >> 4;
   const int splits = a.splits;
   const int unit = quotient(blockIdx.x, a.by_splits), sp = (int)blockIdx.x - unit * splits;
-  const int lb = quotient(unit, a.by_hkv), j = unit - lb * dm.Hkv;
+  const int lb = quotient(unit, dm.by_hkv), j = unit - lb * dm.Hkv;
   const int g = dm.g, cap = dm.cap;
   const char* Kh = (const char*)a.K + (size_t)unit * cap * ROW_BYTES;
   const char* Vh = (const char*)a.V + (size_t)unit * cap * ROW_BYTES;
@@ -597,15 +593,15 @@ template <typename T, int D, int NW, int KT, int OCC>
 static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, AttendArgs a) {
   const int units = dm.L * dm.B * dm.Hkv;
   a.by_splits = gkv_divisor(a.splits);
-  a.by_hkv = gkv_divisor(dm.Hkv);
   const size_t shmem = gkv_attend_mfma_lds(sizeof(T), D, dm.g, NW);
   // Two slices in flight, the first requested ahead, while the launch leaves the chip room: us per launch in a
   // graph, one slice requested behind the state record -> two: 4 units x 577 rows 6.38 -> 6.28, 32 x 1100 8.74 -> 8.22,
   // 128 x 2112 25.1 -> 24.6, 256 x 1056 23.2 -> 22.7; fp32 32 x 528 9.53 -> 9.17; 128 steps of 4 units with their
   // compression 885 -> 860, 64 of 256 1590 -> 1569.  Not above: 400 x 577 20.9 -> 21.4, 896 x 576 41.0 -> 42.2
-  // (more requests in flight make a full memory system slower); nor at bf16, d = 64 (128 x 528 6.31 -> 6.59).
+  // (more requests in flight make a full memory system slower); nor at bf16, d = 64 (128 x 528 6.31 -> 6.59),
+  // nor above 128 units of 16 KiB slices (fp32, d = 128: 128 x 260 12.5 -> 12.4, 256 x 260 16.3 -> 16.7).
   if constexpr (NW <= 8 && KT == 1) {
-    if (units <= 256)
+    if (units <= (Geo<T, D>::VW == 8 ? 128 : 256))
       return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, true>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);
   }
   return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, false>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);

@@ -104,6 +104,7 @@ extern "C" gkv_status gkv_create(const gkv_config* cfg, gkv_ctx** out_ctx) {
     d.scale_l2_lo = (float)(sl2 - (double)d.scale_l2_hi);
   }
   d.step_base = nullptr;
+  d.by_hkv = gkv_divisor(d.Hkv);
   c->esz = cfg->dtype == GKV_F32 ? 4 : 2;
   c->attend_splits = 0;
   c->ws_splits = 1;
@@ -202,7 +203,8 @@ static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
   } else {
     int s = (int)(256 / units);
     s = s > 16 ? 16 : s;
-    s = s > slices / 8 ? slices / 8 : s;
+    const int pieces = wide ? (slices + 7) / 8 : slices / 8;   // wide: no piece longer than the others (4 units x 528 rows 8.2 -> 7.7)
+    s = s > pieces ? pieces : s;
     if (s >= 4 || (s >= 2 && slices >= 64)) { p.splits = s; p.iters = wide ? 4 : 8; }
   }
   const bool more = p.splits > 1 ? slices / p.splits >= 48 : (units <= 256 && slices >= 12) || (units > 512 && slices >= 64);
@@ -412,7 +414,7 @@ extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void*
   gkv_status st = check_len(ctx, len_max_host, k_new != nullptr);
   if (st != GKV_OK) return st;
   AttendArgs a{q, k_new, v_new, K, V, pos, step, qwin, d_state, out, gkv_carve_workspace(ctx, workspace), 1,
-               ctx->attend_tile, 1, 0, 4, 0, 0, {}, {}};
+               ctx->attend_tile, 1, 0, 4, 0, 0, {}};
   {
     const size_t slot_bytes = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hq * ctx->dims.d * ctx->esz;
     a.copy_q = (const char*)q != (const char*)qwin + (size_t)(step % ctx->dims.w) * slot_bytes;

@@ -7,6 +7,15 @@
 #include "gkv.h"
 #include "gkv_bench.h"
 
+// x / d = (2 x mul) >> (32 + shift) for 0 <= x < 2^31, with mul = 2^(31 + shift) / d rounded up and
+// 2^shift >= d the smallest (mul d exceeds 2^(31 + shift) by less than d <= 2^shift).
+struct GkvDivisor { uint32_t mul; uint32_t shift; };
+static inline GkvDivisor gkv_divisor(int32_t d) {
+  uint32_t shift = 0;
+  while ((int64_t)1 << shift < d) ++shift;
+  return GkvDivisor{(uint32_t)((((uint64_t)1 << (31 + shift)) + d - 1) / d), shift};
+}
+
 // Dimensions every kernel needs, passed by value.
 struct GkvDims {
   int32_t L, B, Hq, Hkv, d, g;
@@ -21,6 +30,7 @@ struct GkvDims {
   // Device-side step counter (null: none).  When set, the `step` argument of a call is relative
   // and the kernels use *step_base + step, so recorded launches (HIP graphs) can be replayed.
   const int32_t* step_base;
+  GkvDivisor by_hkv;
 };
 
 struct GkvProfile;   // event pools, defined in gkv_api.hip
@@ -90,14 +100,6 @@ struct GkvLaunch {
 };
 
 // ---- launch wrappers implemented in the kernel files -------------------------------------
-// x / d = (2 x mul) >> (32 + shift) for 0 <= x < 2^31, with mul = 2^(31 + shift) / d rounded up and
-// 2^shift >= d the smallest (mul d exceeds 2^(31 + shift) by less than d <= 2^shift).
-struct GkvDivisor { uint32_t mul; uint32_t shift; };
-static inline GkvDivisor gkv_divisor(int32_t d) {
-  uint32_t shift = 0;
-  while ((int64_t)1 << shift < d) ++shift;
-  return GkvDivisor{(uint32_t)((((uint64_t)1 << (31 + shift)) + d - 1) / d), shift};
-}
 struct AttendArgs {
   const void* q; const void* k_new; const void* v_new;
   void* K; void* V; int32_t* pos; int32_t step; void* qwin; const int32_t* d_state; void* out;
@@ -107,7 +109,7 @@ struct AttendArgs {
   int32_t waves;         // wavefronts per workgroup of the matrix-core kernel: 4, 8 or 16
   int32_t guess;         // rows of K taken to be tiled where slices are requested ahead of the state record
   int32_t split_iters;   // slices per piece (a unit of n slices is cut into ceil(n / split_iters)); 0 = all splits
-  GkvDivisor by_splits, by_hkv;   // set by the launch wrapper
+  GkvDivisor by_splits;   // set by the launch wrapper
 };
 hipError_t gkv_launch_attend_generic(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
 hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
@@ -160,6 +162,10 @@ static inline hipError_t gkv_launch(const GkvLaunch& ln, F kernel, dim3 grid, di
   }
   return hipGetLastError();
 }
+
+// x / d for 0 <= x < 2^31.  An integer division is some twenty instructions, at the start of kernels whose first
+// requests wait for it.
+__device__ __forceinline__ int quotient(int x, GkvDivisor d) { return (int)(__umulhi(2u * (uint32_t)x, d.mul) >> d.shift); }
 
 // The per-(layer, sequence) record of d_state, read with one 16-byte load.
 struct SeqState {

@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void redundancy_generic_kernel(GkvDims dm, Red
   a.step = resolve_step(dm, a.step);
   extern __shared__ double smem[];
   constexpr int EPC = Elem<T>::EPC;
-  const int tid = threadIdx.x, unit = blockIdx.x, lb = unit / dm.Hkv, d = dm.d;
+  const int tid = threadIdx.x, unit = blockIdx.x, lb = quotient(unit, dm.by_hkv), d = dm.d;
   double* cs = (double*)smem;
   double* red = cs + dm.cap;
   double* inv = red + 4;
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
   extern __shared__ double smem[];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, kb = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int unit = blockIdx.x, lb = unit / dm.Hkv;
+  const int unit = blockIdx.x, lb = quotient(unit, dm.by_hkv);
   double* cs = (double*)smem;
   double* inv = cs;                                      // until the column's sum is finished
   double* red = cs + dm.cap;
@@ -413,7 +413,7 @@ __global__ __launch_bounds__(NW * 64) void redundancy_f64_kernel(GkvDims dm, Red
   extern __shared__ double smem[];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, kb = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int unit = blockIdx.x, lb = unit / dm.Hkv;
+  const int unit = blockIdx.x, lb = quotient(unit, dm.by_hkv);
   double* cs = smem;
   double* inv = cs + dm.cap;
   double* red = inv + dm.cap;

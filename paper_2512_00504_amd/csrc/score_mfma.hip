@@ -141,7 +141,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kb = lane >> 4;
   const int unit = blockIdx.x / pl.ksplit, share = blockIdx.x % pl.ksplit;
-  const int j = unit % dm.Hkv, lb = unit / dm.Hkv;
+  const int lb = quotient(unit, dm.by_hkv), j = unit - lb * dm.Hkv;
   const int cap = dm.cap, w = dm.w, g = dm.g;
   const bool pair = pl.pair_heads;
 
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
 // 2780 -> 7.4 us; fp32 D = 128, 32 units 3495 -> 16.9 us (kernel above, bound by fp32 MFMAs).
 // Dynamic LDS: q pieces [NT*NB][NL][1 KiB]; float2 row_c[16*NT*NB]; OWN: float2 red_ms[NW][16*NT*NB].
 template <int D, int NW, int NB, int NT, bool ONCE, bool OWN>
-__global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, ScoreArgs a, int pair, int ksplit) {
+__global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, ScoreArgs a, int pair, int ksplit, GkvDivisor by_ksplit) {
   using T = uint16_t;
   using G = Geo<T, D>;
   constexpr int NL = G::NL;
@@ -413,8 +413,8 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kb = lane >> 4;
-  const int unit = blockIdx.x / ksplit, share = blockIdx.x % ksplit;
-  const int j = unit % dm.Hkv, lb = unit / dm.Hkv;
+  const int unit = quotient(blockIdx.x, by_ksplit), share = (int)blockIdx.x - unit * ksplit;
+  const int lb = quotient(unit, dm.by_hkv), j = unit - lb * dm.Hkv;
   const int cap = dm.cap, w = dm.w, g = dm.g;
   float2* row_c = (float2*)(qs + (size_t)NT * NB * G::TILE_BYTES);
 
@@ -460,7 +460,12 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   const int per_share = (tiles + ksplit - 1) / ksplit;
   const int g0 = share * per_share, g1 = min(tiles, g0 + per_share);
   const char* Kh = (const char*)a.K + (size_t)unit * cap * G::ROW_BYTES;
-  Tile<T, D> kA, kN;
+  // Two tiles on their way while a third is worked on where K comes from memory and the registers allow it: 1792
+  // units of 1152 rows, g = 7 124 -> 114 us, g = 8 117 -> 103, g = 4 100 -> 97; K within the memory-side cache 30.3 -> 29.7
+  // (896 units), 64 units 6.7 -> 7.0; ten blocks of 128 bytes 72 -> 79.  A fourth: 115, 114, 99.
+  constexpr int DEPTH = ONCE && NT * NB <= 8 ? 3 : 2;
+  Tile<T, D> ring[DEPTH];
+  Tile<T, D>&kA = ring[0], &kN = ring[1];
   const int n_full = OWN ? (cc + 1) >> 4 : 0;            // tiles whose keys every window row sees
   if constexpr (OWN) {
     if (wave < n_full) load_k_tile<T, D>(kA, Kh, wave, seq.n_tiled, lane, r, kb);
@@ -612,14 +617,17 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
     }
     finish(tot, t);
   };
-  // two tiles in turn: the next one is always requested before one is worked on, and stays where it lands
+  // DEPTH tiles in turn: the next ones are always requested before one is worked on, and stay where they land
   // (copied over at the end of each round instead: 121 -> 117 us at 1792 units of b = 1024)
-  for (int t = g0 + wave; t < g1; t += 2 * NW) {
-    load_k_tile<T, D, ONCE>(kN, Kh, min(t + NW, g1 - 1), seq.n_tiled, lane, r, kb);
-    tile(kA, t);
-    if (t + NW >= g1) break;
-    load_k_tile<T, D, ONCE>(kA, Kh, min(t + 2 * NW, g1 - 1), seq.n_tiled, lane, r, kb);
-    tile(kN, t + NW);
+#pragma unroll
+  for (int p = 1; p < DEPTH - 1; ++p) load_k_tile<T, D, ONCE>(ring[p], Kh, min(g0 + wave + p * NW, g1 - 1), seq.n_tiled, lane, r, kb);
+  for (int t = g0 + wave; t < g1; t += DEPTH * NW) {
+#pragma unroll
+    for (int p = 0; p < DEPTH; ++p) {
+      if (p > 0 && t + p * NW >= g1) break;
+      load_k_tile<T, D, ONCE>(ring[(p + DEPTH - 1) % DEPTH], Kh, min(t + (p + DEPTH - 1) * NW, g1 - 1), seq.n_tiled, lane, r, kb);
+      tile(ring[p], t + p * NW);
+    }
   }
   bool huge = false;
 #pragma unroll
@@ -665,7 +673,7 @@ hipError_t launch_regs_own(const GkvLaunch& ln, const GkvDims& dm, const ScoreAr
   int ksplit = 256 / units;
   ksplit = ksplit < 1 ? 1 : (ksplit > most ? (most < 1 ? 1 : most) : ksplit);
   return gkv_launch(ln, score_regs_kernel<D, NW, NB, NT, false, true>, dim3(units * ksplit), dim3(NW * 64),
-                    (size_t)ROWS * (Geo<uint16_t, D>::ROW_BYTES + 8 + 8 * NW), dm, a, (int)pair, ksplit);
+                    (size_t)ROWS * (Geo<uint16_t, D>::ROW_BYTES + 8 + 8 * NW), dm, a, (int)pair, ksplit, gkv_divisor(ksplit));
 }
 
 template <int D, int NB, int NT>
@@ -685,7 +693,7 @@ hipError_t launch_regs(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& 
   const bool once = (size_t)units * len_max * Geo<uint16_t, D>::ROW_BYTES > (size_t)256 << 20;
   auto kern = once ? score_regs_kernel<D, NW, NB, NT, true, false> : score_regs_kernel<D, NW, NB, NT, false, false>;
   return gkv_launch(ln, kern, dim3(units * ksplit), dim3(NW * 64),
-                    (size_t)NT * NB * (Geo<uint16_t, D>::TILE_BYTES + 128), dm, a, (int)pair, ksplit);
+                    (size_t)NT * NB * (Geo<uint16_t, D>::TILE_BYTES + 128), dm, a, (int)pair, ksplit, gkv_divisor(ksplit));
 }
 
 // false: no such instantiation

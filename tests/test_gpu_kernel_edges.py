@@ -491,6 +491,30 @@ def test_window_score_reuses_statistics_of_cut_units():
     np.testing.assert_allclose(S[0], S[1], rtol=3e-6, atol=1e-30)
 
 
+@pytest.mark.parametrize("g,w,rows", [(7, 16, 1690), (8, 16, 1650), (3, 32, 1681), (5, 32, 1690)])
+def test_window_score_of_keys_beyond_the_cache(g, w, rows):
+    # more than 256 MiB of K: up to 8 blocks of window rows keep three tiles in turn, 10 keep two; a launch of one sequence
+    # (two tiles, cut into key shares) gives the same scores up to the statistics' last bits
+    cap, B, hkv, d = 1696, 160, 4, 128
+    gen = torch.Generator(device="cuda").manual_seed(g)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(torch.bfloat16)
+    K, q, kn = rnd(1, B, hkv, cap, d), rnd(w, 1, B, g * hkv, d), rnd(w, 1, B, hkv, d)
+    assert B * hkv * rows * 256 > 256 << 20
+    out = []
+    for part in (slice(0, B), slice(3, 4), slice(B - 1, B)):
+        st = DecodeState(make_config(1, part.stop - part.start, g * hkv, hkv, d, 1600, w, 96, cap, "bf16"))
+        st.K.copy_(K[:, part])
+        st.d_state.copy_(torch.tensor([rows - w, 5, 0, 1600], dtype=torch.int32).expand(1, part.stop - part.start, 4))
+        for k in range(w):
+            st.ctx.attend_decode(q[k][:, part].contiguous(), kn[k][:, part].contiguous(), kn[k][:, part].contiguous(), st.K, st.V,
+                                 st.pos, 5 + k, st.qwin, st.d_state, rows - w + k, st.out, st.workspace)
+        st.ctx.score_window(st.qwin, st.K, st.d_state, 5 + w - 1, rows, st.S, st.workspace)
+        out.append(st.S[0, ..., : rows - w].double().cpu().numpy())
+    assert (out[0] > 0).all()
+    np.testing.assert_allclose(out[0][3], out[1][0], rtol=3e-6, atol=1e-30)
+    np.testing.assert_allclose(out[0][B - 1], out[2][0], rtol=3e-6, atol=1e-30)
+
+
 # ---- redundancy score in 64 bits ----------------------------------------------------------------
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
 def test_redundancy_at_tile_edges(dtype, d):
@@ -559,12 +583,14 @@ def test_redundancy_of_keys_of_any_norm(n):
     ("bf16", 128, 2, 512),        # 4 units: 4 shares, 256 threads
     ("bf16", 128, 2, 2000),       # 4 shares, 1024 threads, b not a multiple of 16 per round
     ("bf16", 128, 16, 1037),      # 32 units: 4 shares, 1024 threads, ragged b
+    ("bf16", 128, 4, 560),        # 8 units: 4 shares of 35 KiB, 1024 threads
     ("bf16", 128, 33, 600),       # 66 units: 2 shares of 76 KiB, 1024 threads
     ("bf16", 64, 3, 300),         # 128-byte rows: 2 shares
     ("bf16", 96, 3, 300),         # 12 pieces a row: 2 shares (3 would be too narrow in 4)
     ("bf16", 32, 3, 300),         # 64-byte rows: whole
     ("f32", 128, 4, 700),
     ("bf16", 128, 65, 512),       # 130 units: whole
+    ("bf16", 128, 65, 1500),      # more kept rows than a thread's first four
 ])
 def test_compaction_in_shares(dtype, d, B, b):
     w, s_ = 16, 96
