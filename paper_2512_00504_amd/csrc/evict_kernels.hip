@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void score_topk_kernel(GkvDims dm, const float
   __shared__ float red[8];
   __shared__ int cnt[2][4][4];
   __shared__ int scan_s[64];
-  const int unit = blockIdx.x, lb = unit / dm.Hkv, tid = threadIdx.x, lane = tid & 63;
+  const int unit = blockIdx.x, lb = quotient(unit, dm.by_hkv), tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const float* Su = S + (size_t)unit * dm.cap;
   float f[IPT], h[UPDATE ? IPT : 1];
@@ -197,20 +197,34 @@ __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, const 
   if constexpr (!SHARED) shares = 1;             // known to the compiler
   extern __shared__ int keep_s[];
   __shared__ int red_i[NT / 64];
-  const int unit = blockIdx.x, lb = unit / dm.Hkv, tid = threadIdx.x;
+  const int unit = blockIdx.x, lb = quotient(unit, dm.by_hkv), tid = threadIdx.x;
   const bool isK = (int)blockIdx.y < shares;
   const int share = isK ? blockIdx.y : blockIdx.y - shares;
   const bool isPos = blockIdx.y == 0;
+  const int k = dm.b - dm.w, b = dm.b;
+  const int32_t* Ku = keep_idx + (size_t)unit * k;
+  // the first kept indices of a thread, requested before the state record is waited for
+  constexpr int EARLY = 4;
+  int early[EARLY];
+#pragma unroll
+  for (int i = 0; i < EARLY; ++i) early[i] = Ku[min(tid + NT * i, k - 1)];
   const SeqState st = load_state(d_state, lb);
   const int l = compression_length(st, step, dm.b, dm.w, dm.cap);
   if (l == 0) return;
-  const int c = l - dm.w, k = dm.b - dm.w, b = dm.b;
+  const int c = l - dm.w;
   const int nt_old = st.n_tiled, nt_new = b & ~15;
-  const int32_t* Ku = keep_idx + (size_t)unit * k;
 
   // first destination row whose source differs from it; a K format change rewrites everything
   int first = k;
-  for (int n = tid; n < k; n += NT) {
+#pragma unroll
+  for (int i = 0; i < EARLY; ++i) {
+    const int n = tid + NT * i;
+    if (n < k) {
+      keep_s[n] = early[i];
+      if (early[i] != n && first == k) first = n;
+    }
+  }
+  for (int n = tid + NT * EARLY; n < k; n += NT) {
     const int src = Ku[n];
     keep_s[n] = src;
     if (src != n && first == k) first = n;       // ascending per thread: the first hit is its minimum
@@ -300,7 +314,7 @@ __global__ __launch_bounds__(256) void pool_scores_kernel(GkvDims dm, const floa
                                                           int kernel, float* __restrict__ F_out) {
   step = resolve_step(dm, step);
   extern __shared__ float fbuf[];
-  const int unit = blockIdx.x, lb = unit / dm.Hkv, tid = threadIdx.x;
+  const int unit = blockIdx.x, lb = quotient(unit, dm.by_hkv), tid = threadIdx.x;
   const int l = compression_length(load_state(d_state, lb), step, dm.b, dm.w, dm.cap);
   if (l == 0) return;
   const int c = l - dm.w, half = kernel / 2;
@@ -327,7 +341,7 @@ __global__ __launch_bounds__(256) void evicted_positions_kernel(GkvDims dm, cons
   step = resolve_step(dm, step);
   extern __shared__ uint32_t kept[];
   __shared__ int tmp[4];
-  const int unit = blockIdx.x, lb = unit / dm.Hkv, tid = threadIdx.x;
+  const int unit = blockIdx.x, lb = quotient(unit, dm.by_hkv), tid = threadIdx.x;
   const int n_log = dm.cap - dm.b;
   int32_t* Eu = evicted + (size_t)unit * n_log;
   const int l = compression_length(load_state(d_state, lb), step, dm.b, dm.w, dm.cap);
@@ -398,7 +412,8 @@ hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, c
   const int ppt = ln.ctx ? ln.ctx->compact_ppt : 8;
   // A workgroup moves its rows in rounds of 32 KiB whose loads wait for the stores before them, about
   // 2.5 us each; with few units the chip is empty meanwhile, so the rows' columns are shared out (at
-  // least 64 bytes of a row each) and a share of more than 64 KiB gets 1024 threads, four times the round.
+  // least 64 bytes of a row each) and a share of more than 64 KiB, or 32 up to 32 units, gets 1024 threads, four times
+  // the round (8 units of b = 630 8.5 -> 7.8, of 1000 10.7 -> 8.5; 64 of 512 10.6 -> 11.0).
   // us per launch, whole -> shared (bf16, d = 128): 4 units of b = 512 13.8 -> 7.2, of b = 2048 43.1 -> 10.8;
   // 32 of 2048 47.1 -> 14.6; 64 of 1024 26.1 -> 14.2; 128 of 2048 61.4 -> 51.2.  From 256 units on both
   // cost more than they bring (256 of 2048 120.3 -> 120.9 in halves, 126 with 1024 threads).
@@ -406,7 +421,7 @@ hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, c
   const int64_t unit_bytes = (int64_t)dm.b * row_bytes;
   int shares = units <= 16 || (units <= 32 && unit_bytes >= 256 * 1024) ? 4 : units <= 128 ? 2 : 1;
   while (shares > 1 && (pieces % shares != 0 || pieces / shares < 4)) shares >>= 1;
-  const bool wide = ppt == 8 && units <= 128 && unit_bytes / shares > 64 * 1024;
+  const bool wide = ppt == 8 && units <= 128 && unit_bytes / shares > (units <= 32 ? 32 : 64) * 1024;
   // One share is an instantiation of its own: with the column arithmetic at run time 672 units of b = 287, d = 64
   // take 25.3 us, without 25.0; 604 of b = 323 21.6 / 21.4.
   auto kern = ppt == 16 ? (shares > 1 ? compact_kernel<16, 256, true> : compact_kernel<16, 256, false>)
