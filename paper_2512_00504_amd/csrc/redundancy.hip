@@ -65,6 +65,17 @@ __device__ __forceinline__ void finish_unit(const GkvDims& dm, const RedArgs& a,
   }
 }
 
+// Column sums [j0, j1) of a unit whose columns several workgroups share, on their way to redundancy_finish_kernel in the
+// places of the results: low words in R', high words in F_sel.  The window's columns have no place in F_sel: this
+// serves n_recent >= w, where their sums are 0.
+__device__ __forceinline__ void store_sums(const GkvDims& dm, const RedArgs& a, int unit, int j0, int j1, const double* cs,
+                                           int tid, int threads) {
+  for (int j = j0 + tid; j < j1; j += threads) {
+    a.R_norm[(size_t)unit * dm.cap + j] = __int_as_float(__double2loint(cs[j]));
+    a.F_sel[(size_t)unit * dm.cap + j] = __int_as_float(__double2hiint(cs[j]));
+  }
+}
+
 // ---- any dtype / shape ------------------------------------------------------------------------
 // Dynamic LDS: double cs[cap]; double red[4]; double inv[cap]
 template <typename T>
@@ -145,6 +156,9 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int 
 //
 // A column's own reciprocal norm is wanted until its sum is finished, so the sums take the norms' place.
 //
+// Up to 128 units several workgroups share a unit's columns (a workgroup per unit leaves half of the chip or more idle):
+// 4 units of 640 rows 25 -> 21 us with the finishing launch, 16 of 1128 31 (155 in the form below), 128 of 1128 57 (159).
+//
 // Per launch, against 16x16 tiles, comparisons and selections, and two workgroups of four wavefronts per compute
 // unit: 896 units of 640 rows 161 -> 133 us, of 332 96 -> 64, of 700 233 -> 151; 1792 of 1152 772 -> 680; 4 of 640
 // 54 -> 25.  With every compute unit at it the clock falls (a product with random operands then takes 42 to 52
@@ -183,9 +197,14 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
   // Every pass shares barriers, so all wavefronts make as many; their column tiles differ by one at most, and
   // wavefronts w and w + 4, which share a SIMD, get the odd ones from both ends.
   const int r32 = lane & 31, half = lane >> 5;
+  // In a launch of few units gridDim.y workgroups share a unit's columns, and each forms the norms of all.
+  const int shares = gridDim.y, share = blockIdx.y;
   const int order = wave < 4 ? 2 * wave : 2 * (wave - 4) + 1;
-  const int J_lo = n_tiles * order / RED_NW, n_own = n_tiles * (order + 1) / RED_NW - J_lo;
-  const int n_pass = ((n_tiles + RED_NW - 1) / RED_NW + 2) / 3;
+  struct Own { int lo, n, passes; };
+  auto own_of = [&](int part, int parts) {
+    const int lo = n_tiles * part / parts;
+    return Own{lo, n_tiles * (part + 1) / parts - lo, ((n_tiles + parts - 1) / parts + 2) / 3};
+  };
   u32x4 colA[3][8];
   auto load_columns = [&](int J0, int J1) {
 #pragma unroll
@@ -208,8 +227,9 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
   // that those of the first are there when it starts.
   {
     bool odd = false;
-    for (int p = n_pass - 1; p >= 0; --p) {
-      const int J0 = J_lo + n_own * p / n_pass, J1 = J_lo + n_own * (p + 1) / n_pass;
+    const Own own = own_of(order, RED_NW);
+    for (int p = own.passes - 1; p >= 0; --p) {
+      const int J0 = own.lo + own.n * p / own.passes, J1 = own.lo + own.n * (p + 1) / own.passes;
       load_columns(J0, J1);
       if (p == 0) request(0);
 #pragma unroll
@@ -237,12 +257,19 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
 
   const int first_recent = l - a.n_recent;
   const double tau = (double)a.tau;
+  const int S_lo = n_tiles * share / shares, S_hi = n_tiles * (share + 1) / shares;   // this workgroup's column tiles
+  // the sums of this workgroup's columns are in cs
+  auto finish = [&]() {
+    __syncthreads();
+    if (shares == 1) finish_unit<RED_NW>(dm, a, unit, l, cs, red);
+    else store_sums(dm, a, unit, 32 * S_lo, min(32 * S_hi, l - dm.w), cs, tid, RED_NW * 64);
+  };
   __syncthreads();
   if (s_odd) {
     // seldom: sixteen by sixteen keys at a time, by comparisons
     for (int n = tid; n < 32 * n_tiles; n += RED_NW * 64) inv_f[n] = (float)inv[n];
     __syncthreads();
-    for (int J = wave; J < 2 * n_tiles; J += RED_NW) {
+    for (int J = 2 * S_lo + wave; J < 2 * S_hi; J += RED_NW) {
       u32x4 kj[4];
       load_k_tile(kj, Kh, J, st.n_tiled, lane, r, kb);
       const int j = 16 * J + r;
@@ -268,8 +295,7 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
       col += __shfl_xor(col, 32);
       if (kb == 0 && j < l) cs[j] = j < first_recent ? col * inv_j : 0.0;
     }
-    __syncthreads();
-    finish_unit<RED_NW>(dm, a, unit, l, cs, red);
+    finish();
     return;
   }
 
@@ -381,9 +407,10 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
       if (half == 0 && J0 + cc < J_end && j < l) cs[j] = j < first_recent ? v * (inv[j] / RED_SCALE) : 0.0;
     }
   };
-  for (int p = 0; p < n_pass; ++p) {
-    const int J0 = J_lo + n_own * p / n_pass, J1 = J_lo + n_own * (p + 1) / n_pass;
-    if (p > 0) {
+  const Own own = own_of(RED_NW * share + order, RED_NW * shares);
+  for (int p = 0; p < own.passes; ++p) {
+    const int J0 = own.lo + own.n * p / own.passes, J1 = own.lo + own.n * (p + 1) / own.passes;
+    if (p > 0 || shares > 1) {
       load_columns(J0, J1);
       request(0);
     }
@@ -391,8 +418,7 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
     else if (J1 - J0 == 2) pass(J0, J1, std::integral_constant<int, 2>{});
     else pass(J0, J1, std::integral_constant<int, 1>{});   // (or none: computed and dropped)
   }
-  __syncthreads();
-  finish_unit<RED_NW>(dm, a, unit, l, cs, red);
+  finish();
 }
 
 // ---- fp32 at d = 64 or 128 and bf16 at d = 64: the matrix cores in 64 bits --------------------------
@@ -484,6 +510,107 @@ __global__ __launch_bounds__(NW * 64) void redundancy_f64_kernel(GkvDims dm, Red
   finish_unit<NW>(dm, a, unit, l, cs, red);
 }
 
+// The same for few units: a workgroup takes one column tile at a time (gridDim.y of them share a unit's), its four
+// wavefronts a quarter of the row tiles each, and the sums are added up in a fixed order.  Every workgroup forms the
+// norms of all rows: as many reads as its own rows, a tenth of the arithmetic.  us per call with the finishing launch,
+// against a workgroup per unit: fp32 d = 128 8 units of 366 rows 160 -> 19, 64 of 232 73 -> 34; bf16 d = 64 32 of 428
+// 120 -> 31, 128 of 232 43 -> 30; fp32 d = 64 16 of 132 21 -> 8.7.  Not above 128 units: 256 of 160 24 -> 26, fp32 d = 128 512 of 132
+// 73 -> 80.
+constexpr int RED_SPLIT_UNITS = 128;
+template <typename T, int D>
+__global__ __launch_bounds__(256) void redundancy_f64_split_kernel(GkvDims dm, RedArgs a) {
+  typedef double f64x4 __attribute__((ext_vector_type(4)));
+  constexpr int ROW_B = D * (int)sizeof(T), NL = ROW_B / 64, EPC = Elem<T>::EPC, NW = 4;
+  a.step = resolve_step(dm, a.step);
+  extern __shared__ double smem[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r = lane & 15, kb = lane >> 4;
+  const int unit = blockIdx.x, lb = quotient(unit, dm.by_hkv);
+  double* inv = smem;
+  double* part = inv + dm.cap;                           // [NW][16]
+  double* cs = part + NW * 16;                           // [16]
+  const SeqState st = load_state(a.d_state, lb);
+  const int l = compression_length(st, a.step, dm.b, dm.w, dm.cap);
+  const int n_tiles = (l + 15) >> 4;
+  if ((int)blockIdx.y >= n_tiles) return;                // (l == 0 among them)
+  const char* Kh = (const char*)a.K + (size_t)unit * dm.cap * ROW_B;
+  auto load_tile = [&](u32x4 (&k)[NL], int t) {
+    const bool tiled = 16 * t < st.n_tiled;
+    const char* p = Kh + (size_t)t * 16 * ROW_B + (tiled ? lane * 16 : r * ROW_B + kb * 16);
+    const int step_off = tiled ? 1024 : 64;
+#pragma unroll
+    for (int c = 0; c < NL; ++c) k[c] = *(const u32x4*)(p + c * step_off);
+  };
+  auto elem = [](const u32x4& v, int i) {
+    if constexpr (sizeof(T) == 4) return (double)__uint_as_float(v[i]);
+    else return (double)__uint_as_float((i & 1) ? (v[i >> 1] & 0xffff0000u) : (v[i >> 1] << 16));
+  };
+  for (int t = wave; t < n_tiles; t += NW) {
+    u32x4 k[NL];
+    load_tile(k, t);
+    double ss = 0.0;
+#pragma unroll
+    for (int c = 0; c < NL; ++c)
+#pragma unroll
+      for (int i = 0; i < EPC; ++i) { const double x = elem(k[c], i); ss = fma(x, x, ss); }
+    ss += __shfl_xor(ss, 16);
+    ss += __shfl_xor(ss, 32);
+    const int n = 16 * t + r;
+    if (kb == 0) inv[n] = n < l ? 1.0 / (sqrt(ss) + (double)a.eps) : 0.0;
+  }
+  __syncthreads();
+  const double tau = (double)a.tau;
+  for (int J = blockIdx.y; J < n_tiles; J += gridDim.y) {
+    u32x4 kj[NL], cur[NL], nxt[NL];
+    load_tile(kj, J);
+    load_tile(cur, min(wave, n_tiles - 1));
+    const int j = 16 * J + r;
+    const double inv_j = inv[j];
+    double col = 0.0;
+    for (int t = wave; t < n_tiles; t += NW) {
+      load_tile(nxt, min(t + NW, n_tiles - 1));
+      f64x4 dot = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int c = 0; c < NL; ++c)
+#pragma unroll
+        for (int i = 0; i < EPC; ++i)
+          dot = __builtin_amdgcn_mfma_f64_16x16x4f64(elem(cur[c], i), elem(kj[c], i), dot, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int k = 16 * t + 4 * i + kb;
+        const double cv = dot[i] * inv[k] * inv_j;
+        if (cv >= tau && k < l && k != j) col += cv;
+      }
+#pragma unroll
+      for (int c = 0; c < NL; ++c) cur[c] = nxt[c];
+    }
+    col += __shfl_xor(col, 16);
+    col += __shfl_xor(col, 32);
+    if (kb == 0) part[16 * wave + r] = col;
+    __syncthreads();
+    if (tid < 16) {
+      const double v = (part[tid] + part[16 + tid]) + (part[32 + tid] + part[48 + tid]);
+      cs[tid] = 16 * J + tid < l - a.n_recent ? v : 0.0;
+      store_sums(dm, a, unit, 16 * J, min(16 * J + 16, l - dm.w), cs - 16 * J, tid, 16);
+    }
+    __syncthreads();
+  }
+}
+
+__global__ __launch_bounds__(256) void redundancy_finish_kernel(GkvDims dm, RedArgs a) {
+  a.step = resolve_step(dm, a.step);
+  extern __shared__ double smem[];
+  const int unit = blockIdx.x, lb = quotient(unit, dm.by_hkv);
+  double* cs = smem;
+  const int l = compression_length(load_state(a.d_state, lb), a.step, dm.b, dm.w, dm.cap);
+  if (l == 0) return;
+  const float* lo = a.R_norm + (size_t)unit * dm.cap;
+  const float* hi = a.F_sel + (size_t)unit * dm.cap;
+  for (int j = threadIdx.x; j < l; j += 256)
+    cs[j] = j < l - dm.w ? __hiloint2double(__float_as_int(hi[j]), __float_as_int(lo[j])) : 0.0;
+  __syncthreads();
+  finish_unit<4>(dm, a, unit, l, cs, cs + dm.cap);
+}
+
 }  // namespace
 
 hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dtype, bool mfma, bool f64_mfma, const void* K,
@@ -491,6 +618,12 @@ hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dty
                                  float eps, int32_t n_recent, float* R_norm, float* F_sel) {
   RedArgs a{K, d_state, step, F, lambda, tau, eps, n_recent, R_norm, F_sel};
   const int units = dm.L * dm.B * dm.Hkv;
+  // a unit's columns are shared out where there are few units; the sums need the results' places (store_sums)
+  auto apart = [&](const float* x, const float* y) { return x < y ? y - x >= (int64_t)units * dm.cap : x - y >= (int64_t)units * dm.cap; };
+  const bool few = units <= RED_SPLIT_UNITS && n_recent >= dm.w && apart(R_norm, F_sel) && apart(R_norm, F) && apart(F_sel, F);
+  auto finish = [&]() {
+    return gkv_launch(ln, redundancy_finish_kernel, dim3(units), dim3(256), sizeof(double) * ((size_t)dm.cap + 4), dm, a);
+  };
   if (mfma) {
     const size_t with_ring = sizeof(double) * ((size_t)dm.cap + RED_NW) + sizeof(float) * (size_t)dm.cap + RED_RING_BYTES;
     auto kern = redundancy_mfma_kernel;
@@ -498,10 +631,22 @@ hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dty
       const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)with_ring);
       if (e != hipSuccess) return e;
     }
-    return gkv_launch(ln, kern, dim3(units), dim3(RED_NW * 64), with_ring, dm, a);
+    // as many workgroups as there are compute units, each wavefront with a column tile at least
+    const int most = ((dm.cap + 31) / 32 + RED_NW - 1) / RED_NW;
+    const int shares = !few ? 1 : 256 / units < most ? 256 / units : most;
+    const hipError_t e = gkv_launch(ln, kern, dim3(units, shares), dim3(RED_NW * 64), with_ring, dm, a);
+    return e == hipSuccess && shares > 1 ? finish() : e;
   }
   if (f64_mfma) {
     const bool wide = dtype == GKV_F32 && dm.d == 128;
+    if (few) {
+      const int tiles = (dm.cap + 15) / 16, shares = tiles < 1024 / units ? tiles : (1024 + units - 1) / units;
+      auto split = wide ? redundancy_f64_split_kernel<float, 128>
+                        : dtype == GKV_F32 ? redundancy_f64_split_kernel<float, 64> : redundancy_f64_split_kernel<uint16_t, 64>;
+      const hipError_t e = gkv_launch(ln, split, dim3(units, shares), dim3(256), sizeof(double) * ((size_t)dm.cap + 80), dm, a);
+      if (e != hipSuccess) return e;
+      return finish();
+    }
     auto kern = wide ? redundancy_f64_kernel<float, 128, 8>
                      : dtype == GKV_F32 ? redundancy_f64_kernel<float, 64, 16> : redundancy_f64_kernel<uint16_t, 64, 16>;
     return gkv_launch(ln, kern, dim3(units), dim3(wide ? 512 : 1024), sizeof(double) * (2 * (size_t)dm.cap + 16), dm, a);

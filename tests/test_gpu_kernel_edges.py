@@ -516,8 +516,9 @@ def test_window_score_of_keys_beyond_the_cache(g, w, rows):
 
 
 # ---- redundancy score in 64 bits ----------------------------------------------------------------
+@pytest.mark.parametrize("n_recent", [3, 5])       # at least the window, 4: several workgroups share a unit's columns
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
-def test_redundancy_at_tile_edges(dtype, d):
+def test_redundancy_at_tile_edges(dtype, d, n_recent):
     # lengths around tile borders and one tile per wavefront, both K formats; keys in clusters so that
     # cosines lie on both sides of the threshold and none near it
     w, b, cap = 4, 20, 288
@@ -540,11 +541,11 @@ def test_redundancy_at_tile_edges(dtype, d):
         st.K[0, i] = k_rows_to_cache(K[0, i], m).cuda()
     st.F.fill_(0.25)
     st.len_host = cap
-    st.redundancy_combine(99, lam=0.5, tau=0.5, n_recent=3)
+    st.redundancy_combine(99, lam=0.5, tau=0.5, n_recent=n_recent)
     R, Fs = st.R.double().cpu().numpy(), st.F_sel.double().cpu().numpy()
     for i, n in enumerate(lens):
         Kn = K[0, i, :, :n].double().numpy()
-        Rr = O.redundancy_score(Kn, n, tau=0.5, n_recent=3, eps=float(np.float32(1e-8)))
+        Rr = O.redundancy_score(Kn, n, tau=0.5, n_recent=n_recent, eps=float(np.float32(1e-8)))
         ref = Rr / Rr.max()
         # R' = exp(col - max): fp64 sums give fp32 rounding, the fp32 products of bf16 d = 128 the stated 1e-5
         rel = 1e-5 if (dtype, d) == ("bf16", 128) else 1e-6
@@ -553,8 +554,9 @@ def test_redundancy_at_tile_edges(dtype, d):
         np.testing.assert_allclose(Fs[0, i, 0, : n - w], 0.125 - 0.5 * ref[0, : n - w], rtol=0, atol=0.5 * rel + 1.2e-7)
 
 
+@pytest.mark.parametrize("n_recent", [3, 4])
 @pytest.mark.parametrize("n", [33, 97, 288])
-def test_redundancy_of_keys_of_any_norm(n):
+def test_redundancy_of_keys_of_any_norm(n, n_recent):
     # bf16 at d = 128 scales by 2^80 what it compares, and serves units with norms outside 1e-9 .. 1e13 another way:
     # unit 0 has neither, 1 a tiny key, 2 a huge one, 3 an infinite one, which counts for nobody else
     w, b, cap, d = 4, 20, 288, 128
@@ -570,12 +572,45 @@ def test_redundancy_of_keys_of_any_norm(n):
     st.K.copy_(K)
     st.d_state.copy_(torch.tensor([[[n - w, 100 - w, 0, 0]]], dtype=torch.int32).expand(1, 4, 4))
     st.len_host = cap
-    st.redundancy_combine(99, lam=0.5, tau=0.5, n_recent=3, eps=0.0)
+    st.redundancy_combine(99, lam=0.5, tau=0.5, n_recent=n_recent, eps=0.0)
     R = st.R.double().cpu().numpy()
     for i in range(4):
         rest = np.delete(np.arange(n), n // 2) if i == 3 else np.arange(n)
-        Rr = O.redundancy_score(K[0, i, :, rest].double().numpy(), len(rest), tau=0.5, n_recent=3, eps=0.0)
+        Rr = O.redundancy_score(K[0, i, :, rest].double().numpy(), len(rest), tau=0.5, n_recent=n_recent, eps=0.0)
         np.testing.assert_allclose(R[0, i, 0, rest], (Rr / Rr.max())[0], rtol=1e-5, atol=1e-40)
+
+
+@pytest.mark.parametrize("B", [1, 64, 65])             # 2, 128 and 130 units: shared columns up to 128
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
+def test_redundancy_leaves_what_is_not_its_own(dtype, d, B):
+    # sums of shared columns travel in the results' places: behind the candidates F_sel, and behind the rows R', stay as they
+    # were, sequences that are not compressed keep both, and results in one buffer come out as they always have
+    w, b, cap, n = 8, 300, 384, 330
+    st = DecodeState(make_config(1, B, 2, 2, d, b, w, 16, cap, dtype))
+    gen = torch.Generator().manual_seed(d)
+    st.K.copy_(torch.randn(st.K.shape, generator=gen)); st.F.copy_(torch.rand(st.F.shape, generator=gen))
+    rec = torch.tensor([n - w, 100 - w, 0, 0], dtype=torch.int32).repeat(1, B, 1)
+    if B > 1:
+        rec[0, 1, 0] = b - w                               # at the budget
+    st.d_state.copy_(rec)
+    st.len_host = cap
+    out = {}
+    for n_recent in (w, w - 1):                            # w - 1: a workgroup per unit
+        st.R.fill_(7.0); st.F_sel.fill_(9.0)
+        st.redundancy_combine(99, lam=0.5, tau=0.3, n_recent=n_recent)
+        assert (st.R[..., n:] == 7).all() and (st.F_sel[..., n - w:] == 9).all()
+        if B > 1:
+            assert (st.R[0, 1] == 7).all() and (st.F_sel[0, 1] == 9).all()
+        out[n_recent] = (st.R.clone(), st.F_sel.clone())
+    st.R.fill_(7.0)
+    st.ctx.redundancy_combine(st.K, st.d_state, 99, cap, st.F, 0.5, 0.3, 1e-8, w, st.R, st.R, st.workspace)
+    assert torch.equal(st.R[..., : n - w][0, 0], out[w][1][..., : n - w][0, 0])
+    assert torch.equal(st.R[0, 0, :, n - w:], out[w][0][0, 0, :, n - w:])
+    # the columns that both leave in: the same sums, and the same maximum unless the one column more had it
+    a, c = out[w][0][0, 0, :, : n - w].double(), out[w - 1][0][0, 0, :, : n - w].double()
+    for x, y in zip(a, c):
+        r = (x / y)[(x > 1e-30) & (y > 1e-30)]
+        assert ((r / r[0] - 1).abs() < 1e-6).all()
 
 
 # ---- compaction in column shares ----------------------------------------------------------------
