@@ -188,6 +188,7 @@ static int explicit_splits(const gkv_ctx* ctx) {
 // (896 x 2113 167 -> 163, ragged to 3900 232 -> 211; 4608 x 1057 399 -> 392); in between 4 do
 // (512 x 2113 90.7 against 92.8).  fp32 at d = 128 has 16 KiB slices and stays at 4: uncut 256 x 528 26.5, with
 // 8 27.7; cut 32 x 528 9.6 / 11.9, 64 x 1050 17.0 / 18.3, 128 x 1050 25.5 / 26.7, 4 x 2100 12.3 / 12.1.
+// (All of these before requests went out ahead of the state record, which took 0.3 to 0.7 us off either side.)
 struct AttendPlan { int waves, splits, iters; };
 
 static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
