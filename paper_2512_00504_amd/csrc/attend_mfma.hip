@@ -600,6 +600,9 @@ static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, AttendAr
   // compression 885 -> 860, 64 of 256 1590 -> 1569.  Not above: 400 x 577 20.9 -> 21.4, 896 x 576 41.0 -> 42.2
   // (more requests in flight make a full memory system slower); nor at bf16, d = 64 (128 x 528 6.31 -> 6.59),
   // nor above 128 units of 16 KiB slices (fp32, d = 128: 128 x 260 12.5 -> 12.4, 256 x 260 16.3 -> 16.7).
+  // In cut launches too the request ahead is worth it (128 steps of 4 units 897 without, 855 with; ragged to 3900 32.0 / 31.0),
+  // though short sequences of a ragged batch pay for pieces they do not fill (fp32, 34 units to 565 rows 10.9 -> 11.4; 84
+  // to 464 10.1 -> 10.3).
   if constexpr (NW <= 8 && KT == 1) {
     if (units <= (Geo<T, D>::VW == 8 ? 128 : 256))
       return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, true>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);
