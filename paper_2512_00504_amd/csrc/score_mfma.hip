@@ -463,9 +463,10 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   // Two tiles on their way while a third is worked on where K comes from memory and the registers allow it: 1792
   // units of 1152 rows, g = 7 124 -> 114 us, g = 8 117 -> 103, g = 4 100 -> 97; K within the memory-side cache 30.3 -> 29.7
   // (896 units), 64 units 6.7 -> 7.0; ten blocks of 128 bytes 72 -> 79.  A fourth: 115, 114, 99.
-  constexpr int DEPTH = ONCE && NT * NB <= 8 ? 3 : 2;
-  Tile<T, D> ring[DEPTH];
-  Tile<T, D>&kA = ring[0], &kN = ring[1];
+  // Three objects and a loop for each depth: as an array with one loop over it (two tiles of it a launch of the own
+  // statistics' pass) they cost that pass 8 to 34 registers, and 38 spilled took 18432 units, g = 5, w = 32 from 2480 to 4530 us.
+  constexpr bool THREE = ONCE && NT * NB <= 8;
+  Tile<T, D> kA, kN, kM;
   const int n_full = OWN ? (cc + 1) >> 4 : 0;            // tiles whose keys every window row sees
   if constexpr (OWN) {
     if (wave < n_full) load_k_tile<T, D>(kA, Kh, wave, seq.n_tiled, lane, r, kb);
@@ -617,16 +618,28 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
     }
     finish(tot, t);
   };
-  // DEPTH tiles in turn: the next ones are always requested before one is worked on, and stay where they land
+  // the tiles in turn: the next ones are always requested before one is worked on, and stay where they land
   // (copied over at the end of each round instead: 121 -> 117 us at 1792 units of b = 1024)
-#pragma unroll
-  for (int p = 1; p < DEPTH - 1; ++p) load_k_tile<T, D, ONCE>(ring[p], Kh, min(g0 + wave + p * NW, g1 - 1), seq.n_tiled, lane, r, kb);
-  for (int t = g0 + wave; t < g1; t += DEPTH * NW) {
-#pragma unroll
-    for (int p = 0; p < DEPTH; ++p) {
-      if (p > 0 && t + p * NW >= g1) break;
-      load_k_tile<T, D, ONCE>(ring[(p + DEPTH - 1) % DEPTH], Kh, min(t + (p + DEPTH - 1) * NW, g1 - 1), seq.n_tiled, lane, r, kb);
-      tile(ring[p], t + p * NW);
+  auto request = [&](Tile<T, D>& kT, int t) { load_k_tile<T, D, ONCE>(kT, Kh, min(t, g1 - 1), seq.n_tiled, lane, r, kb); };
+  if constexpr (THREE) {
+    request(kN, g0 + wave + NW);
+    for (int t = g0 + wave; t < g1; t += 3 * NW) {
+      request(kM, t + 2 * NW);
+      tile(kA, t);
+      if (t + NW >= g1) break;
+      request(kA, t + 3 * NW);
+      tile(kN, t + NW);
+      if (t + 2 * NW >= g1) break;
+      request(kN, t + 4 * NW);
+      tile(kM, t + 2 * NW);
+    }
+  } else {
+    for (int t = g0 + wave; t < g1; t += 2 * NW) {
+      request(kN, t + NW);
+      tile(kA, t);
+      if (t + NW >= g1) break;
+      request(kA, t + 2 * NW);
+      tile(kN, t + NW);
     }
   }
   bool huge = false;

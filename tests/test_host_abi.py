@@ -4,6 +4,8 @@ layout offsets) matches the paper's printed numbers and the binding's permutatio
 import ctypes
 import os
 import re
+import subprocess
+import tempfile
 
 import numpy as np
 import pytest
@@ -172,3 +174,29 @@ def test_native_call_leaves_other_arguments_to_ctypes(change):
     assert call.gkv_select_topk(*full) is None
     with pytest.raises(KeyError):
         call.bind("gkv_destroy", 1)
+
+
+def _vgpr_spills():
+    """{kernel symbol: spilled vector registers}, from the metadata notes of the device code in libgkv.so."""
+    data, out = open(P.LIB_PATH, "rb").read(), {}
+    at = data.find(b"\x7fELF", 1)
+    while at >= 0:
+        with tempfile.NamedTemporaryFile(suffix=".co") as f:
+            f.write(data[at:])
+            f.flush()
+            notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", f.name], capture_output=True, text=True).stdout
+        for kernel in notes.split("- .agpr_count:")[1:]:
+            name, n = re.search(r"\.name:\s+(_Z\S+)", kernel), re.search(r"\.vgpr_spill_count:\s+(\d+)", kernel)
+            if name and n:
+                out[name.group(1)] = int(n.group(1))
+        at = data.find(b"\x7fELF", at + 1)
+    return out
+
+
+def test_kernels_keep_their_values_in_registers():
+    # a spilled register inside a loop is a trip to memory a round: 38 of them took a window score 1.8 times as long
+    spills = _vgpr_spills()
+    for kernel in ("score_regs_kernel", "attend_mfma_kernel", "score_topk_kernel", "compact_kernel", "redundancy_mfma_kernel"):
+        assert any(kernel in name for name in spills), kernel
+    few = {name: n for name, n in spills.items() if n > (3 if "redundancy_mfma_kernel" in name else 0)}   # there: before its loop
+    assert not few
