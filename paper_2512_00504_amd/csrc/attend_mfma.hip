@@ -108,11 +108,13 @@ struct Slice {
 // memory-side cache), both non-temporal 76%, one stream of each kind 80-85% at every cache size
 // tried (0.3 to 10 GB), whichever of the two is the non-temporal one.
 template <typename T, int D, int KT>
-__device__ __forceinline__ void issue_k(Slice<T, D, KT>& s, const char* Kh, int it, int n_tiled, int lane, int r, int kb) {
+__device__ __forceinline__ void issue_slice(Slice<T, D, KT>& s, const char* Kh, const char* Vh, int it,
+                                            int n_tiled, int lane, int r, int kb) {
   using G = Geo<T, D>;
+  const int key0 = it * 16 * KT;
 #pragma unroll
   for (int tt = 0; tt < KT; ++tt) {
-    const int row0 = it * 16 * KT + 16 * tt;
+    const int row0 = key0 + 16 * tt;
     const char* Kt = Kh + (size_t)(row0 >> 4) * G::TILE_BYTES;
     const bool tiled = row0 < n_tiled;                     // wave-uniform
     const int lane_off = tiled ? lane * 16 : r * G::ROW_BYTES + kb * 16;
@@ -120,20 +122,11 @@ __device__ __forceinline__ void issue_k(Slice<T, D, KT>& s, const char* Kh, int 
 #pragma unroll
     for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = ld16(Kt + lane_off + c * step_off);
   }
-}
-template <typename T, int D, int KT>
-__device__ __forceinline__ void issue_v(Slice<T, D, KT>& s, const char* Vh, int it, int r, int kb) {
 #pragma unroll
   for (int jj = 0; jj < 4 * KT; ++jj) {
-    const int key = it * 16 * KT + (jj & 3) + 4 * kb + (jj >> 2) * 16;
-    ld_v<T, D>(s.vR[jj], Vh + (size_t)key * Geo<T, D>::ROW_BYTES, r);
+    const int key = key0 + (jj & 3) + 4 * kb + (jj >> 2) * 16;
+    ld_v<T, D>(s.vR[jj], Vh + (size_t)key * G::ROW_BYTES, r);
   }
-}
-template <typename T, int D, int KT>
-__device__ __forceinline__ void issue_slice(Slice<T, D, KT>& s, const char* Kh, const char* Vh, int it,
-                                            int n_tiled, int lane, int r, int kb) {
-  issue_k<T, D, KT>(s, Kh, it, n_tiled, lane, r, kb);
-  issue_v<T, D, KT>(s, Vh, it, r, kb);
 }
 
 // Flash-decoding state of one wavefront: lane (head = lane%16, blk = lane/16) holds the running
@@ -320,10 +313,9 @@ __device__ __forceinline__ float inv_sum(float l, bool any_key, bool fast) {
   return fast ? __builtin_amdgcn_rcpf(l) : 1.f / l;
 }
 
-// KT = 16-key tiles per wavefront iteration (1 or 2).  AHEAD: two slices in flight per wavefront,
-// the first requested ahead of the state record.
-template <typename T, int D, int NW, int KT, int OCC, bool AHEAD>
-__global__ __launch_bounds__(NW * 64, AHEAD ? 2 : OCC) void attend_mfma_kernel(GkvDims dm, AttendArgs a) {
+// KT = 16-key tiles per wavefront iteration (1 or 2)
+template <typename T, int D, int NW, int KT, int OCC>
+__global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, AttendArgs a) {
   using G = Geo<T, D>;
   constexpr int KEYS = 16 * KT;             // keys per iteration
   constexpr int RP = G::RP, ROW_BYTES = G::ROW_BYTES, OSTR = G::OSTR, PSTR = G::PSTR;
@@ -347,7 +339,7 @@ __global__ __launch_bounds__(NW * 64, AHEAD ? 2 : OCC) void attend_mfma_kernel(G
   // A launch of few units is one trip to memory after the other, so everything whose address the arguments
   // give is requested before anything is waited for: the state record and the step counter (scalar loads; no
   // branch on whether there is a counter), the group's queries (B operand of the QK product: lane (head r, kb)
-  // holds chunks 4c+kb of q[r]), the rows stored at the end of the workgroup, and with AHEAD the first slice.
+  // holds chunks 4c+kb of q[r]) and the rows stored at the end of the workgroup.
   int4 rec = *(const int4*)(a.d_state + 4 * (size_t)lb);
   const int32_t base = *(dm.step_base ? dm.step_base : a.d_state);
   __builtin_amdgcn_sched_barrier(0);
@@ -370,13 +362,8 @@ __global__ __launch_bounds__(NW * 64, AHEAD ? 2 : OCC) void attend_mfma_kernel(G
     ap[rd] = ld16(src);
   }
   const int it0 = sp * NW + wave;
-  Slice<T, D, KT> s, s2;
+  Slice<T, D, KT> s;
   __builtin_amdgcn_sched_barrier(0);           // loads come back in order: these before the slice's
-  if constexpr (AHEAD) {                       // rows below the capacity, whatever the length
-    issue_k<T, D, KT>(s, Kh, min(it0, cap / KEYS - 1), a.guess, lane, r, kb);
-    issue_v<T, D, KT>(s, Vh, min(it0, cap / KEYS - 1), r, kb);
-  }
-  __builtin_amdgcn_sched_barrier(0);
   asm volatile("" : "+s"(rec.x), "+s"(rec.y), "+s"(rec.w));   // one load, not one for each of them
   const SeqState seq = state_record(rec);
   if (dm.step_base) a.step += base;
@@ -402,16 +389,16 @@ __global__ __launch_bounds__(NW * 64, AHEAD ? 2 : OCC) void attend_mfma_kernel(G
 #pragma unroll
   for (int m = 0; m < G::NC; ++m) st.oacc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // First slice in flight, then stage k_new / v_new in LDS for whoever owns the last slice.
+  // First slice in flight, then stage k_new / v_new in LDS for whoever owns the last slice.  Every wavefront asks for
+  // one, those beyond the unit's end for its last (or, in an empty unit, for rows that are there, and not used): after a
+  // request under a condition the compiler cannot know how many loads are younger than the rows to stage, waits for
+  // all of them, and the barrier holds every wavefront until the first slices of all have arrived.  us per launch in a
+  // graph, with the condition -> without: 128 units x 577 rows 11.3 -> 10.65, 256 x 1056 23.5 -> 22.6, 4 x 577 7.3 -> 6.8; d = 64 128 x
+  // 528 7.9 -> 7.2, 512 14.8 -> 14.55; fp32 32 x 528 11.4 -> 10.0, ragged 84 to 464 12.7 -> 11.7; 896 x 576 48.8 both ways.
+  // (The first slice, or the first two, requested ahead of the record on a guess of K's format cost more than that wait:
+  // 4 x 577 7.2, 32 x 577 8.4 against 7.9, ragged 84 to 464 9.9 / 8.4, 128 x 2112 25.3 / 24.8.)
   const int stride = ns * NW;
-  if constexpr (AHEAD) {
-    // the last compression left b rows tiled; in a prompt's rows, which are not, the guess was wrong
-    auto tiled_rows = [&](int n_tiled) { return max(0, min(KEYS, n_tiled - it0 * KEYS)); };
-    if (it0 < n_iter && tiled_rows(a.guess) != tiled_rows(seq.n_tiled)) issue_k<T, D, KT>(s, Kh, it0, seq.n_tiled, lane, r, kb);
-    if (it0 + stride < n_iter) issue_slice<T, D, KT>(s2, Kh, Vh, it0 + stride, seq.n_tiled, lane, r, kb);
-  } else {
-    if (it0 < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it0, seq.n_tiled, lane, r, kb);
-  }
+  issue_slice<T, D, KT>(s, Kh, Vh, min(it0, max(n_iter - 1, 0)), seq.n_tiled, lane, r, kb);
   // stage: 16-byte pieces [0,RP) k_new, [RP,2RP) v_new, [2RP, 2RP+RP*g) q rows; kept in LDS, not
   // in registers, until they are stored at the end
   char* stage = (char*)(smem + NW * g * OSTR + NW * 16 + NW * 16);
@@ -424,31 +411,17 @@ __global__ __launch_bounds__(NW * 64, AHEAD ? 2 : OCC) void attend_mfma_kernel(G
   }
   __syncthreads();
   // this wavefront's slices, the first one already requested
-  auto process = [&](Slice<T, D, KT>& x, int it, auto exact) {
-    constexpr bool EXACT = decltype(exact)::value;
-    if ((it + 1) * KEYS > len0) process_slice<T, D, KT, true, EXACT>(x, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
-    else process_slice<T, D, KT, false, EXACT>(x, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
-  };
-  auto request = [&](Slice<T, D, KT>& x, int it) {
-    if (it < n_iter) issue_slice<T, D, KT>(x, Kh, Vh, it, seq.n_tiled, lane, r, kb);
-  };
   auto slices = [&](auto exact) {
-    for (int it = it0; it < n_iter; it += stride) {
-      process(s, it, exact);
-      request(s, it + stride);
+    constexpr bool EXACT = decltype(exact)::value;
+    int it = it0;
+    while (it < n_iter) {
+      if ((it + 1) * KEYS > len0) process_slice<T, D, KT, true, EXACT>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
+      else process_slice<T, D, KT, false, EXACT>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
+      it += stride;
+      if (it < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it, seq.n_tiled, lane, r, kb);
     }
   };
-  if constexpr (AHEAD) {
-    for (int it = it0; it < n_iter; it += 2 * stride) {
-      process(s, it, std::false_type{});
-      request(s, it + 2 * stride);
-      if (it + stride >= n_iter) break;
-      process(s2, it + stride, std::false_type{});
-      request(s2, it + 3 * stride);
-    }
-  } else {
-    slices(std::false_type{});
-  }
+  slices(std::false_type{});
   if (it0 < n_iter) {
     // Seldom: a maximum that the short form of the weights is not right for, or a NaN that may be its
     // doing (a logit of -inf; at bf16, D = 64 an infinite value that met a part of P that is zero or
@@ -594,20 +567,7 @@ static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, AttendAr
   const int units = dm.L * dm.B * dm.Hkv;
   a.by_splits = gkv_divisor(a.splits);
   const size_t shmem = gkv_attend_mfma_lds(sizeof(T), D, dm.g, NW);
-  // Two slices in flight, the first requested ahead, while the launch leaves the chip room: us per launch in a
-  // graph, one slice requested behind the state record -> two: 4 units x 577 rows 6.38 -> 6.28, 32 x 1100 8.74 -> 8.22,
-  // 128 x 2112 25.1 -> 24.6, 256 x 1056 23.2 -> 22.7; fp32 32 x 528 9.53 -> 9.17; 128 steps of 4 units with their
-  // compression 885 -> 860, 64 of 256 1590 -> 1569.  Not above: 400 x 577 20.9 -> 21.4, 896 x 576 41.0 -> 42.2
-  // (more requests in flight make a full memory system slower); nor at bf16, d = 64 (128 x 528 6.31 -> 6.59),
-  // nor above 128 units of 16 KiB slices (fp32, d = 128: 128 x 260 12.5 -> 12.4, 256 x 260 16.3 -> 16.7).
-  // In cut launches too the request ahead is worth it (128 steps of 4 units 897 without, 855 with; ragged to 3900 32.0 / 31.0),
-  // though short sequences of a ragged batch pay for pieces they do not fill (fp32, 34 units to 565 rows 10.9 -> 11.4; 84
-  // to 464 10.1 -> 10.3).
-  if constexpr (NW <= 8 && KT == 1) {
-    if (units <= (Geo<T, D>::VW == 8 ? 128 : 256))
-      return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, true>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);
-  }
-  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, false>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);
+  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);
 }
 
 hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a) {

@@ -415,7 +415,7 @@ extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void*
   gkv_status st = check_len(ctx, len_max_host, k_new != nullptr);
   if (st != GKV_OK) return st;
   AttendArgs a{q, k_new, v_new, K, V, pos, step, qwin, d_state, out, gkv_carve_workspace(ctx, workspace), 1,
-               ctx->attend_tile, 1, 0, 4, 0, 0, {}};
+               ctx->attend_tile, 1, 0, 4, 0, {}};
   {
     const size_t slot_bytes = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hq * ctx->dims.d * ctx->esz;
     a.copy_q = (const char*)q != (const char*)qwin + (size_t)(step % ctx->dims.w) * slot_bytes;
@@ -432,7 +432,6 @@ extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void*
     }
     a.ws = gkv_carve_workspace(ctx, workspace, set);
     a.waves = plan.waves; a.splits = plan.splits; a.split_iters = plan.iters;
-    a.guess = ctx->dims.b & ~15;                                    // as the last compression left them
     // An appending step leaves (max, sum) of every query head's softmax in the ring slot
     // of this step; the window score can then skip its own pass over the keys for them.
     a.write_stats = k_new != nullptr;

@@ -107,7 +107,6 @@ struct AttendArgs {
   int32_t copy_q;   // 0 when q already is the ring slot of this step
   int32_t write_stats;   // record (max, sum) of every query head's softmax in ws.stats
   int32_t waves;         // wavefronts per workgroup of the matrix-core kernel: 4, 8 or 16
-  int32_t guess;         // rows of K taken to be tiled where slices are requested ahead of the state record
   int32_t split_iters;   // slices per piece (a unit of n slices is cut into ceil(n / split_iters)); 0 = all splits
   GkvDivisor by_splits;   // set by the launch wrapper
 };

@@ -60,9 +60,9 @@ def _check_attend(st, K, V, q, kn, vn, lens, dtype, d, append):
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("B,hkv,n_tiled", [(85, 3, 16), (87, 3, 48), (52, 5, 0)])   # 255, 261 and 260 units
 def test_attend_on_both_sides_of_256_units(dtype, d, B, hkv, n_tiled):
-    # up to 256 units a wavefront asks for its first slice ahead of the state record, taking b // 16 * 16 rows of K
-    # to be tiled: right and wrong guesses, lengths from nothing to the last row, a group of 5 and rows
-    # of NaN behind every length; KV heads and workgroups that are no power of two
+    # 4 and 8 wavefronts, of which those beyond a unit's end ask for its last slice, or in an empty unit for rows that do
+    # not count: lengths from nothing to the last row, both K formats, a group of 5 and rows of NaN behind every length;
+    # KV heads and workgroups that are no power of two
     g, b, cap = 5, 40, 96
     st = DecodeState(make_config(1, B, hkv * g, hkv, d, b, 4, 8, cap, dtype))
     gen = torch.Generator().manual_seed(B * d)
@@ -102,6 +102,19 @@ DECODE_FORMS = [("f32", 64, 3, 256, None), ("f32", 128, 7, 256, None), ("bf16", 
                 ("bf16", 64, 2, 256, {"attend_waves": 16}), ("bf16", 128, 2, 256, {"attend_waves": 16}),
                 ("bf16", 64, 2, 256, {"attend_waves": 8}), ("f32", 64, 2, 256, {"attend_waves": 8}),
                 ("bf16", 128, 2, 640, {"attend_tile": 32, "attend_splits": 2}), ("f32", 64, 2, 640, {"force_generic": 1})]
+
+
+@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
+def test_attend_over_nothing(dtype, d, g, cap, params):
+    # an empty sequence and no new row: every wavefront is beyond the end, and the rows that are there (NaN) count for nobody
+    lens = [0, 1, 0, 40]
+    st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 48, seed=9, params=params)
+    out = st.attend_decode(q.cuda(), None, None, 5).double().cpu().numpy()
+    assert (out[0, 0] == 0).all() and (out[0, 2] == 0).all()
+    for i in (1, 3):
+        Ki, Vi = K[0, i].double().numpy(), V[0, i].double().numpy()
+        ref = O.attend(q[0, i].double().numpy(), Ki[:, : lens[i]], Vi[:, : lens[i]], lens[i])
+        assert (np.abs(out[0, i] - ref) <= _bound(dtype, d, ref, Vi[:, : lens[i]])).all()
 
 
 @pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
