@@ -203,11 +203,15 @@ __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, const 
   const bool isPos = blockIdx.y == 0;
   const int k = dm.b - dm.w, b = dm.b;
   const int32_t* Ku = keep_idx + (size_t)unit * k;
-  // the first kept indices of a thread, requested before the state record is waited for
+  // the first kept indices of a thread, requested before the state record is waited for: as many as there are
+  // (all four for a short unit too, copies of its last: 4 units of b = 200 6.55 -> 6.65 us, 896 of b = 98 20.3 -> 20.7)
   constexpr int EARLY = 4;
   int early[EARLY];
 #pragma unroll
-  for (int i = 0; i < EARLY; ++i) early[i] = Ku[min(tid + NT * i, k - 1)];
+  for (int i = 0; i < EARLY; ++i) {
+    early[i] = 0;
+    if (i == 0 || NT * i < k) early[i] = Ku[min(tid + NT * i, k - 1)];
+  }
   const SeqState st = load_state(d_state, lb);
   const int l = compression_length(st, step, dm.b, dm.w, dm.cap);
   if (l == 0) return;
