@@ -416,8 +416,11 @@ hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, c
   const int ppt = ln.ctx ? ln.ctx->compact_ppt : 8;
   // A workgroup moves its rows in rounds of 32 KiB whose loads wait for the stores before them, about
   // 2.5 us each; with few units the chip is empty meanwhile, so the rows' columns are shared out (at
-  // least 64 bytes of a row each) and a share of more than 64 KiB, or 32 of more than 512 rows up to 16 units, gets 1024 threads, four times
-  // the round (8 units of b = 630 8.5 -> 7.8, of 1000 10.7 -> 8.5; 64 of 512 10.6 -> 11.0).
+  // least 64 bytes of a row each) and a share of more than 64 KiB gets 1024 threads, four times the round; up to 16 units
+  // one of more than 32 KiB too if it would be more than two rounds of 256 rows (with the record's copy in a graph:
+  // bf16 8 units of b = 630 10.8 -> 9.7, 4 of 1000 12.9 -> 9.9; in two rounds the wider workgroup starts later than it saves: fp32,
+  // d = 128 4 of b = 322 9.3 -> 9.7, 8 of 400 9.7 -> 9.85, 16 of 322 9.6 -> 9.95, even at b = 512, 10.45 -> 10.2 at 8 units; 64 bf16 of 512
+  // 10.6 -> 11.0).
   // us per launch, whole -> shared (bf16, d = 128): 4 units of b = 512 13.8 -> 7.2, of b = 2048 43.1 -> 10.8;
   // 32 of 2048 47.1 -> 14.6; 64 of 1024 26.1 -> 14.2; 128 of 2048 61.4 -> 51.2.  From 256 units on both
   // cost more than they bring (256 of 2048 120.3 -> 120.9 in halves, 126 with 1024 threads).
@@ -425,7 +428,7 @@ hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, c
   const int64_t unit_bytes = (int64_t)dm.b * row_bytes;
   int shares = units <= 16 || (units <= 32 && unit_bytes >= 256 * 1024) ? 4 : units <= 128 ? 2 : 1;
   while (shares > 1 && (pieces % shares != 0 || pieces / shares < 4)) shares >>= 1;
-  const bool wide = ppt == 8 && units <= 128 && unit_bytes / shares > (units <= 16 && dm.b > 512 ? 32 : 64) * 1024;
+  const bool wide = ppt == 8 && units <= 128 && unit_bytes / shares > (units <= 16 && dm.b > 2 * 256 ? 32 : 64) * 1024;
   // One share is an instantiation of its own: with the column arithmetic at run time 672 units of b = 287, d = 64
   // take 25.3 us, without 25.0; 604 of b = 323 21.6 / 21.4.
   auto kern = ppt == 16 ? (shares > 1 ? compact_kernel<16, 256, true> : compact_kernel<16, 256, false>)
