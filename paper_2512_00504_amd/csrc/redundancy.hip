@@ -166,12 +166,21 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int 
 //
 // Dynamic LDS: double cs[cap]; double red[8]; float inv_f[cap]; then the ring, 2 groups x 4 tiles x 8 KiB
 constexpr int RED_NW = 8, RED_TILE = 32 * ROW_BYTES, RED_RING_BYTES = 2 * 4 * RED_TILE;
-// Everything that is compared and added up is scaled by 2^80, so that clamp(x) to [0, 1] of a difference of two
-// scaled numbers is 1 or 0 (the next number above a threshold is at least 1 above it): as a modifier of the
-// subtraction the clamp costs nothing, where a comparison and a selection are two instructions.
-// That asks for reciprocal norms within these bounds (norms of 1e-9 to 1e13); a unit that has
-// others is served by comparisons.
+// Everything that is compared and added up is scaled by a power of two, so that clamp(x) to [0, 1] of a difference of
+// two scaled numbers is 1 or 0 (the next number above a threshold is at least 1 above it): as a modifier of the
+// subtraction the clamp costs nothing, where a comparison and a selection are two instructions.  2^80 does for norms
+// (eps included) of 2^-30 to 2^44: a cosine is scaled by 2^49 at least, |tau| from 2^-25 on has the spacing, and below that
+// what can be counted in part is within 2^-49 of the threshold.  A unit with others has a scale of its own with the same
+// properties (unit_scale): 4 units of 640 rows 21 -> 23 us, 896 122 -> 127.  Where its norms span too much for one, or a key
+// is infinite or NaN, it is served by comparisons: 40 and 376 us.
 constexpr double RED_SCALE = 0x1p80, RED_INV_MIN = 0x1p-44, RED_INV_MAX = 0x1p30;
+
+// A power of two S for reciprocal norms from `least` to `most`, or 0: norms times S stay below 2^100, reciprocals times S
+// below 2^126, and dots (of norms from 2^-38 to 2^60) are normal numbers of fp32.
+__device__ __forceinline__ double unit_scale(double least, double most) {
+  if (!(least >= 0x1p-60 && most <= 0x1p38 && most <= least * 0x1p50)) return 0.0;
+  return ldexp(1.0, min(100 + ilogb(least), 125 - ilogb(most)));
+}
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims dm, RedArgs a) {
@@ -186,7 +195,8 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
   float* inv_f = (float*)(red + RED_NW);                      // the norms, scaled, in fp32
   char* ring = (char*)(inv_f + dm.cap);                  // (no other shared variable before these: 16-byte pieces want the alignment)
   int& s_odd = *(int*)red;
-  if (tid == 0) s_odd = 0;
+  double* s_scale = red + 1;                             // the scale and its reciprocal: not in registers through the passes
+  if (tid == 0) { s_odd = 0; s_scale[0] = RED_SCALE; s_scale[1] = 1.0 / RED_SCALE; }
   const SeqState st = load_state(a.d_state, lb);
   const int l = compression_length(st, a.step, dm.b, dm.w, dm.cap);
   if (l == 0) return;
@@ -266,9 +276,21 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
   };
   __syncthreads();
   if (s_odd) {
-    // seldom: sixteen by sixteen keys at a time, by comparisons
-    for (int n = tid; n < 32 * n_tiles; n += RED_NW * 64) inv_f[n] = (float)inv[n];
+    // seldom: the unit's own scale, from the least and the largest of its reciprocals (a NaN is neither and stays)
+    double least = __builtin_inf(), most = 0.0;
+    bool nan = false;
+    for (int n = lane; n < l; n += 64) {
+      const double x = inv[n];
+      least = fmin(least, x); most = fmax(most, x); nan |= x != x;
+    }
+    for (int o = 32; o > 0; o >>= 1) { least = fmin(least, __shfl_xor(least, o)); most = fmax(most, __shfl_xor(most, o)); }
+    const double scale = __any(nan) ? 0.0 : unit_scale(least, most);
+    for (int n = tid; n < 32 * n_tiles; n += RED_NW * 64) inv_f[n] = (float)(scale > 0.0 ? inv[n] * scale : inv[n]);
+    if (tid == 0) { s_scale[0] = scale; s_scale[1] = 1.0 / scale; }
     __syncthreads();
+  }
+  if (s_odd && s_scale[0] == 0.0) {
+    // sixteen by sixteen keys at a time, by comparisons
     for (int J = 2 * S_lo + wave; J < 2 * S_hi; J += RED_NW) {
       u32x4 kj[4];
       load_k_tile(kj, Kh, J, st.n_tiled, lane, r, kb);
@@ -320,7 +342,7 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
       // column's factor applied once to the sum (columns >= l and duplicates never pass and are dropped
       // below; a duplicate's norm may have given way to its sum already: its own column must not look)
       const double inv_j = J0 + cc < J_end ? inv[32 * (J0 + cc) + r32] : 0.0;
-      thr[cc] = inv_j > 0.0 ? (float)(tau * RED_SCALE / inv_j) : 3e38f;
+      thr[cc] = inv_j > 0.0 ? (float)(tau * s_scale[0] / inv_j) : 3e38f;
       // the number before the threshold: "above it" stands for "at the threshold or above"
       const int bits = __float_as_int(thr[cc]);
       thr[cc] = thr[cc] == 0.f ? -1e-45f : __int_as_float(bits < 0 ? bits + 1 : bits - 1);
@@ -404,7 +426,7 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
     for (int cc = 0; cc < NC; ++cc) {
       const double v = col[cc] + __shfl_xor(col[cc], 32);
       const int j = 32 * (J0 + cc) + r32;
-      if (half == 0 && J0 + cc < J_end && j < l) cs[j] = j < first_recent ? v * (inv[j] / RED_SCALE) : 0.0;
+      if (half == 0 && J0 + cc < J_end && j < l) cs[j] = j < first_recent ? v * (inv[j] * s_scale[1]) : 0.0;
     }
   };
   const Own own = own_of(RED_NW * share + order, RED_NW * shares);

@@ -570,7 +570,7 @@ def test_redundancy_at_tile_edges(dtype, d, n_recent):
 @pytest.mark.parametrize("n_recent", [3, 4])
 @pytest.mark.parametrize("n", [33, 97, 288])
 def test_redundancy_of_keys_of_any_norm(n, n_recent):
-    # bf16 at d = 128 scales by 2^80 what it compares, and serves units with norms outside 1e-9 .. 1e13 another way:
+    # bf16 at d = 128 scales by 2^80 what it compares, and serves units with norms outside 1e-9 .. 1e13 in other ways:
     # unit 0 has neither, 1 a tiny key, 2 a huge one, 3 an infinite one, which counts for nobody else
     w, b, cap, d = 4, 20, 288, 128
     st = DecodeState(make_config(1, 4, 2, 1, d, b, w, 8, cap, "bf16"))
@@ -591,6 +591,31 @@ def test_redundancy_of_keys_of_any_norm(n, n_recent):
         rest = np.delete(np.arange(n), n // 2) if i == 3 else np.arange(n)
         Rr = O.redundancy_score(K[0, i, :, rest].double().numpy(), len(rest), tau=0.5, n_recent=n_recent, eps=0.0)
         np.testing.assert_allclose(R[0, i, 0, rest], (Rr / Rr.max())[0], rtol=1e-5, atol=1e-40)
+
+
+@pytest.mark.parametrize("n_recent", [3, 4])
+@pytest.mark.parametrize("n", [97, 450])
+def test_redundancy_scale_of_a_unit(n, n_recent):
+    # bf16 at d = 128: units within the common scale's norms (0), with a scale of their own (1 to 5: all keys large or
+    # small, one of them, both ends of the span), and beyond it (6, 7: by comparisons)
+    w, b, cap, d = 4, 20, 480, 128
+    units = [(1.0, 1.0), (1e15, 1.0), (1e-11, 1.0), (1.0, 3e14), (1.0, 1e-11), (1e-9, 3e14), (1e-15, 1.0), (1.0, 1e-16)]
+    st = DecodeState(make_config(1, len(units), 2, 1, d, b, w, 8, cap, "bf16"))
+    rng = np.random.default_rng(n)
+    centres = rng.standard_normal((6, d))
+    K = torch.full((1, len(units), 1, cap, d), float("nan")).to(st.K.dtype)
+    for i, (every, one) in enumerate(units):
+        rows = every * (centres[rng.integers(0, 6, n)] + 0.05 * rng.standard_normal((n, d)))
+        rows[n // 2] *= one
+        K[0, i, 0, :n] = torch.from_numpy(rows).to(st.K.dtype)
+    st.K.copy_(K)
+    st.d_state.copy_(torch.tensor([[[n - w, 100 - w, 0, 0]]], dtype=torch.int32).expand(1, len(units), 4))
+    st.len_host = cap
+    st.redundancy_combine(99, lam=0.5, tau=0.5, n_recent=n_recent, eps=0.0)
+    R = st.R.double().cpu().numpy()
+    for i in range(len(units)):
+        Rr = O.redundancy_score(K[0, i, :, :n].double().numpy(), n, tau=0.5, n_recent=n_recent, eps=0.0)
+        np.testing.assert_allclose(R[0, i, 0, :n], (Rr / Rr.max())[0], rtol=1e-5, atol=1e-40)
 
 
 @pytest.mark.parametrize("B", [1, 64, 65])             # 2, 128 and 130 units: shared columns up to 128

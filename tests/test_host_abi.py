@@ -198,5 +198,5 @@ def test_kernels_keep_their_values_in_registers():
     spills = _vgpr_spills()
     for kernel in ("score_regs_kernel", "attend_mfma_kernel", "score_topk_kernel", "compact_kernel", "redundancy_mfma_kernel"):
         assert any(kernel in name for name in spills), kernel
-    few = {name: n for name, n in spills.items() if n > (3 if "redundancy_mfma_kernel" in name else 0)}   # there: before its loop
+    few = {name: n for name, n in spills.items() if n > (3 if "redundancy_mfma_kernel" in name else 0)}   # outside its inner loops
     assert not few
