@@ -4,9 +4,9 @@
 //   the n_recent newest rows are zeroed;  col_j = sum_k C'_kj;  R = softmax_j(col);
 //   R' = R / max_j R = exp(col_j - max_j col)   (the softmax denominator cancels);
 //   F_sel = lambda * F - (1 - lambda) * R'  over the candidates.
-// One workgroup per unit.  The l x l x d contraction runs on the matrix cores: in 32 bits for bf16,
-// d = 128, in 64 bits for fp32 at d = 64 or 128 and bf16 at d = 64 (groups of at most 16 heads, K 16-byte
-// aligned); a plain vector-ALU kernel covers the rest.
+// A workgroup per unit, or several that share its columns in launches of few units.  The l x l x d contraction runs on
+// the matrix cores: in 32 bits for bf16, d = 128, in 64 bits for fp32 at d = 64 or 128 and bf16 at d = 64 (groups of at
+// most 16 heads, K 16-byte aligned); a plain vector-ALU kernel covers the rest.
 #include "gkv_internal.h"
 #include <type_traits>
 
@@ -156,8 +156,12 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int 
 //
 // A column's own reciprocal norm is wanted until its sum is finished, so the sums take the norms' place.
 //
-// Up to 128 units several workgroups share a unit's columns (a workgroup per unit leaves half of the chip or more idle):
-// 4 units of 640 rows 25 -> 21 us with the finishing launch, 16 of 1128 31 (155 in the form below), 128 of 1128 57 (159).
+// Up to 128 units several workgroups share a unit's columns where the capacity gives a wavefront more than two column
+// tiles, that is from 448 rows on (above 64 units, where there are two or three shares, from 704 on): a share costs the norms
+// and the start again, and the sums a finishing launch.  us per call, a workgroup per unit -> shared: 4 units of 332
+// rows 13.4 -> 15.1, of 400 16.1 -> 16.2, of 480 17.6 -> 16.6, of 640 24.6 -> 19.5, of 1128 67 -> 29; 64 of 332 13.8 -> 15.7, of 480 18.0 ->
+// 17.1, of 640 25.2 -> 21.6, of 1128 68 -> 40; 110 of 544 22.7 -> 24.5, of 640 25.4 -> 27.5, of 704 30.0 -> 29.9, of 1128 69 -> 58;
+// 128 of 640 25.5 -> 26.0, of 768 32.7 -> 31.5, of 1128 70 -> 57.
 //
 // Per launch, against 16x16 tiles, comparisons and selections, and two workgroups of four wavefronts per compute
 // unit: 896 units of 640 rows 161 -> 133 us, of 332 96 -> 64, of 700 233 -> 151; 1792 of 1152 772 -> 680; 4 of 640
@@ -655,7 +659,8 @@ hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dty
     }
     // as many workgroups as there are compute units, each wavefront with a column tile at least
     const int most = ((dm.cap + 31) / 32 + RED_NW - 1) / RED_NW;
-    const int shares = !few ? 1 : 256 / units < most ? 256 / units : most;
+    const bool share = few && dm.cap >= (units <= 64 ? 448 : 704);
+    const int shares = !share ? 1 : 256 / units < most ? 256 / units : most;
     const hipError_t e = gkv_launch(ln, kern, dim3(units, shares), dim3(RED_NW * 64), with_ring, dm, a);
     return e == hipSuccess && shares > 1 ? finish() : e;
   }

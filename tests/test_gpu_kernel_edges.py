@@ -529,13 +529,14 @@ def test_window_score_of_keys_beyond_the_cache(g, w, rows):
 
 
 # ---- redundancy score in 64 bits ----------------------------------------------------------------
-@pytest.mark.parametrize("n_recent", [3, 5])       # at least the window, 4: several workgroups share a unit's columns
+# n_recent at least the window, 4: several workgroups share a unit's columns (bf16, d = 128: from a capacity of 448)
+@pytest.mark.parametrize("n_recent,cap", [(3, 288), (5, 288), (3, 480), (5, 480)])
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
-def test_redundancy_at_tile_edges(dtype, d, n_recent):
+def test_redundancy_at_tile_edges(dtype, d, n_recent, cap):
     # lengths around tile borders and one tile per wavefront, both K formats; keys in clusters so that
     # cosines lie on both sides of the threshold and none near it
-    w, b, cap = 4, 20, 288
-    lens = [21, 31, 32, 33, 128, 129, 257, 288]
+    w, b = 4, 20
+    lens = [21, 31, 32, 33, 128, 129, 257, cap]
     B = len(lens)
     st = DecodeState(make_config(1, B, 2, 1, d, b, w, 8, cap, dtype))
     rng = np.random.default_rng(d)
@@ -618,12 +619,14 @@ def test_redundancy_scale_of_a_unit(n, n_recent):
         np.testing.assert_allclose(R[0, i, 0, :n], (Rr / Rr.max())[0], rtol=1e-5, atol=1e-40)
 
 
-@pytest.mark.parametrize("B", [1, 64, 65])             # 2, 128 and 130 units: shared columns up to 128
+# 2, 64, 66, 128 and 130 units: fp64 shares columns up to 128; bf16 from 448 rows on up to 64 units, from 704 on up to 128
+@pytest.mark.parametrize("B,cap", [(1, 384), (64, 384), (65, 384), (1, 416), (1, 448), (32, 448), (33, 448), (33, 672), (33, 704),
+                                   (64, 704), (65, 704)])
 @pytest.mark.parametrize("dtype,d", [("f32", 64), ("bf16", 128)])
-def test_redundancy_leaves_what_is_not_its_own(dtype, d, B):
+def test_redundancy_leaves_what_is_not_its_own(dtype, d, B, cap):
     # sums of shared columns travel in the results' places: behind the candidates F_sel, and behind the rows R', stay as they
     # were, sequences that are not compressed keep both, and results in one buffer come out as they always have
-    w, b, cap, n = 8, 300, 384, 330
+    w, b, n = 8, cap - 84, cap - 54
     st = DecodeState(make_config(1, B, 2, 2, d, b, w, 16, cap, dtype))
     gen = torch.Generator().manual_seed(d)
     st.K.copy_(torch.randn(st.K.shape, generator=gen)); st.F.copy_(torch.rand(st.F.shape, generator=gen))
