@@ -77,7 +77,8 @@ size_t gkv_max_lds_bytes(const gkv_config* c) {
   upd(16 * cap + 32);                                               // redundancy: double cs[cap], red[4], inv[cap]
   if ((d == 64 || d == 128) && g <= 16) upd(16 * cap + 128);        // its 64-bit matrix-core form: a double per wavefront
   // (the matrix-core redundancy kernel takes 12 cap + 64 KiB, with its ring of row tiles, and asks for the
-  // larger per-workgroup allowance itself: 112 KiB at the largest capacity of the 160 KiB a compute unit holds)
+  // larger per-workgroup allowance itself: 110 KiB at 3936 rows, the most that pass at d = 128, of the 160 KiB a
+  // compute unit holds)
   upd(4 * cap + 64);                                                // pooled score / eviction log
   if ((d == 64 || d == 128) && g <= 16)                             // attend_mfma: partial outputs + staged rows
     upd(gkv_attend_mfma_lds(c->dtype == GKV_F32 ? 4 : 2, (int)d, (int)g, 4) + 16);

@@ -8,6 +8,7 @@
 // the matrix cores: in 32 bits for bf16, d = 128, in 64 bits for fp32 at d = 64 or 128 and bf16 at d = 64 (groups of at
 // most 16 heads, K 16-byte aligned); a plain vector-ALU kernel covers the rest.
 #include "gkv_internal.h"
+#include <atomic>
 #include <type_traits>
 
 namespace {
@@ -170,6 +171,7 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int 
 //
 // Dynamic LDS: double cs[cap]; double red[8]; float inv_f[cap]; then the ring, 2 groups x 4 tiles x 8 KiB
 constexpr int RED_NW = 8, RED_TILE = 32 * ROW_BYTES, RED_RING_BYTES = 2 * 4 * RED_TILE;
+constexpr size_t RED_LDS_ROW = sizeof(double) + sizeof(float), RED_LDS_FIXED = sizeof(double) * RED_NW + RED_RING_BYTES;
 // Everything that is compared and added up is scaled by a power of two, so that clamp(x) to [0, 1] of a difference of
 // two scaled numbers is 1 or 0 (the next number above a threshold is at least 1 above it): as a modifier of the
 // subtraction the clamp costs nothing, where a comparison and a selection are two instructions.  2^80 does for norms
@@ -637,6 +639,21 @@ __global__ __launch_bounds__(256) void redundancy_finish_kernel(GkvDims dm, RedA
   finish_unit<4>(dm, a, unit, l, cs, cs + dm.cap);
 }
 
+// The ring passes the default per-workgroup limit of LDS (a compute unit holds 160 KiB): opt in, once a device, for the
+// largest capacity.  Each call costs the host 0.3 us otherwise.
+hipError_t red_opt_in() {
+  static std::atomic<uint64_t> done{0};
+  int dev = -1;
+  const hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev >= 0 && dev < 64 ? (uint64_t)1 << dev : 0;
+  if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
+  const hipError_t set = hipFuncSetAttribute((const void*)redundancy_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)(RED_LDS_ROW * 4096 + RED_LDS_FIXED));
+  if (set == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  return set;
+}
+
 }  // namespace
 
 hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dtype, bool mfma, bool f64_mfma, const void* K,
@@ -651,12 +668,10 @@ hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dty
     return gkv_launch(ln, redundancy_finish_kernel, dim3(units), dim3(256), sizeof(double) * ((size_t)dm.cap + 4), dm, a);
   };
   if (mfma) {
-    const size_t with_ring = sizeof(double) * ((size_t)dm.cap + RED_NW) + sizeof(float) * (size_t)dm.cap + RED_RING_BYTES;
+    const size_t with_ring = RED_LDS_ROW * (size_t)dm.cap + RED_LDS_FIXED;
     auto kern = redundancy_mfma_kernel;
-    if (with_ring > 64 * 1024) {                         // beyond the default per-workgroup limit: opt in (a CU holds 160 KiB)
-      const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)with_ring);
-      if (e != hipSuccess) return e;
-    }
+    const hipError_t opted = red_opt_in();
+    if (opted != hipSuccess) return opted;
     // as many workgroups as there are compute units, each wavefront with a column tile at least
     const int most = ((dm.cap + 31) / 32 + RED_NW - 1) / RED_NW;
     const bool share = few && dm.cap >= (units <= 64 ? 448 : 704);
