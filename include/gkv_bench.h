@@ -15,7 +15,8 @@ extern "C" {
  * Kernel timing.  While enabled, each kernel launch is bracketed
  * by HIP events on the launch stream that record the kernel's own begin and
  * end; gkv_profile_read synchronises those events and returns the total
- * milliseconds and launch count of one kernel class since the last reset.
+ * milliseconds of one kernel class since the last reset and how many of its calls were timed (a call of
+ * two launches counts once, with the time of both).
  */
 typedef enum {
   GKV_K_ATTEND = 0, GKV_K_SCORE = 1, GKV_K_GLOBAL = 2, GKV_K_TOPK = 3, GKV_K_COMPACT = 4,

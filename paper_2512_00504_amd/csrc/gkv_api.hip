@@ -12,7 +12,7 @@
 // ---- profiling ----------------------------------------------------------------------------------
 struct GkvProfile {
   bool on = false;
-  struct Rec { hipEvent_t e0, e1; };
+  struct Rec { hipEvent_t e0, e1; bool continued; };
   std::vector<Rec> recs[GKV_K_COUNT];
   double done_ms[GKV_K_COUNT] = {};
   int64_t done_n[GKV_K_COUNT] = {};
@@ -23,6 +23,7 @@ void gkv_profile_events(const GkvLaunch& ln, hipEvent_t* start, hipEvent_t* stop
   GkvProfile* p = ln.ctx ? ln.ctx->prof : nullptr;
   if (!p || !p->on || ln.kernel_id < 0 || ln.kernel_id >= GKV_K_COUNT) return;
   GkvProfile::Rec rec;
+  rec.continued = ln.continued;
   if (hipEventCreate(&rec.e0) != hipSuccess) return;
   if (hipEventCreate(&rec.e1) != hipSuccess) { (void)hipEventDestroy(rec.e0); return; }
   p->recs[ln.kernel_id].push_back(rec);
@@ -34,7 +35,7 @@ static void profile_drain(GkvProfile* p, int k) {
     float ms = 0.f;
     if (hipEventSynchronize(rec.e1) == hipSuccess && hipEventElapsedTime(&ms, rec.e0, rec.e1) == hipSuccess) {
       p->done_ms[k] += ms;
-      p->done_n[k] += 1;
+      p->done_n[k] += !rec.continued;
     }
     (void)hipEventDestroy(rec.e0);
     (void)hipEventDestroy(rec.e1);

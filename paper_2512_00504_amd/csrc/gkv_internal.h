@@ -97,6 +97,7 @@ struct GkvLaunch {
   gkv_ctx* ctx;
   int kernel_id;
   hipStream_t stream;
+  bool continued = false;   // a further launch of the same call: its time counts, the call does not count again
 };
 
 // ---- launch wrappers implemented in the kernel files -------------------------------------

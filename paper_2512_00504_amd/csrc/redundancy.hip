@@ -665,7 +665,9 @@ hipError_t gkv_launch_redundancy(const GkvLaunch& ln, const GkvDims& dm, int dty
   auto apart = [&](const float* x, const float* y) { return x < y ? y - x >= (int64_t)units * dm.cap : x - y >= (int64_t)units * dm.cap; };
   const bool few = units <= RED_SPLIT_UNITS && n_recent >= dm.w && apart(R_norm, F_sel) && apart(R_norm, F) && apart(F_sel, F);
   auto finish = [&]() {
-    return gkv_launch(ln, redundancy_finish_kernel, dim3(units), dim3(256), sizeof(double) * ((size_t)dm.cap + 4), dm, a);
+    GkvLaunch more = ln;
+    more.continued = true;
+    return gkv_launch(more, redundancy_finish_kernel, dim3(units), dim3(256), sizeof(double) * ((size_t)dm.cap + 4), dm, a);
   };
   if (mfma) {
     const size_t with_ring = RED_LDS_ROW * (size_t)dm.cap + RED_LDS_FIXED;

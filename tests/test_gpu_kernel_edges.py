@@ -654,6 +654,19 @@ def test_redundancy_leaves_what_is_not_its_own(dtype, d, B, cap):
         assert ((r / r[0] - 1).abs() < 1e-6).all()
 
 
+@pytest.mark.parametrize("dtype,d,n_recent", [("bf16", 128, 8), ("bf16", 128, 7), ("f32", 64, 8)])    # two launches, one, two
+def test_redundancy_timing_counts_calls(dtype, d, n_recent):
+    st = DecodeState(make_config(1, 1, 2, 2, d, 400, 8, 16, 480, dtype))
+    st.K.normal_()
+    st.d_state.copy_(torch.tensor([450, 92, 0, 0], dtype=torch.int32).expand(1, 1, 4))
+    st.len_host = 480
+    st.ctx.profile_enable(True)
+    for _ in range(3):
+        st.redundancy_combine(99, lam=0.5, tau=0.3, n_recent=n_recent)
+    ms, calls = st.ctx.profile_read("redundancy")
+    assert calls == 3 and ms > 0
+
+
 # ---- compaction in column shares ----------------------------------------------------------------
 @pytest.mark.parametrize("dtype,d,B,b", [
     ("bf16", 128, 2, 512),        # 4 units: 4 shares, 256 threads
