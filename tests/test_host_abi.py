@@ -154,26 +154,56 @@ def test_benchmark_refuses_more_than_one_gpu():
     assert "--gpus must be 1" in (res.stdout + res.stderr)
 
 
-@pytest.mark.parametrize("change", [
-    {}, {0: None}, {0: 0}, {0: 1.0}, {2: 1 << 31}, {2: -(1 << 31) - 1}, {2: True}, {2: 3.0}, {2: None}, {1: 5}, {1: "x"},
-    {1: torch.zeros(4).t()}, {1: torch.nn.Parameter(torch.zeros(4))}, {1: torch.zeros(4, device="meta")}, {-1: "drop"}, {-1: "add"},
-])
-def test_native_call_leaves_other_arguments_to_ctypes(change):
-    # nothing here is a tensor on a GPU (not even in the first case): the native half must return None, without a call
+# arguments that the native half takes: pointers may be None.  The library refuses them (null pointers), without a GPU the
+# stream lookup before it does
+NATIVE = {
+    "gkv_select_topk": ["h", None, None, 3, 4, None, None],
+    "gkv_redundancy_combine": ["h", None, None, 3, 4, None, 0.5, 0.25, 1e-8, 2, None, None, None],
+}
+
+
+def _native(name, args):
     from paper_2512_00504_amd import binding
-    call = binding._load_call()
-    z = torch.zeros(4)
-    full = [1 << 40, z, z, 3, 4, z, z]                     # a handle that must not be looked at
-    for at, value in change.items():
-        if value == "drop":
-            full = full[:-1]
-        elif value == "add":
-            full = full + [None]
-        else:
-            full[{0: 0, 1: 1, 2: 3}[at]] = value
-    assert call.gkv_select_topk(*full) is None
+    ctx = P.Context(_cfg())
+    try:
+        return getattr(binding._load_call(), name)(*[ctx._handle if isinstance(x, str) and x == "h" else x for x in args])
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("name", NATIVE)
+def test_native_call_takes_what_the_path_passes(name):
+    if torch.cuda.is_available():
+        assert _native(name, NATIVE[name]) == 1            # GKV_ERR_INVALID_ARG
+    else:
+        with pytest.raises(RuntimeError):
+            _native(name, NATIVE[name])
+
+
+@pytest.mark.parametrize("name,at,value", [
+    ("gkv_select_topk", 0, None), ("gkv_select_topk", 0, 0), ("gkv_select_topk", 0, 1.0), ("gkv_select_topk", 0, True),
+    *[("gkv_select_topk", 3, v) for v in (1 << 31, -(1 << 31) - 1, True, 3.0, None, "x")],
+    *[("gkv_select_topk", at, v) for at in (1, 6) for v in (5, "x", torch.zeros(4), torch.nn.Parameter(torch.zeros(4)),
+                                                             torch.zeros(4, device="meta"), np.zeros(4))],
+    *[("gkv_redundancy_combine", 7, v) for v in (1, True, None, "x", np.float32(0.5))],
+    ("gkv_select_topk", 6, "drop"), ("gkv_select_topk", 6, "add"),
+])
+def test_native_call_leaves_other_arguments_to_ctypes(name, at, value):
+    # one argument differs from what the test above passes: None, without a call
+    args = list(NATIVE[name])
+    if isinstance(value, str) and value == "drop":
+        args.pop()
+    elif isinstance(value, str) and value == "add":
+        args.append(None)
+    else:
+        args[at] = value
+    assert _native(name, args) is None
+
+
+def test_native_call_binds_only_its_own():
+    from paper_2512_00504_amd import binding
     with pytest.raises(KeyError):
-        call.bind("gkv_destroy", 1)
+        binding._load_call().bind("gkv_destroy", 1)
 
 
 def _vgpr_spills():
