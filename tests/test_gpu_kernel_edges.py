@@ -504,15 +504,16 @@ def test_window_score_reuses_statistics_of_cut_units():
     np.testing.assert_allclose(S[0], S[1], rtol=3e-6, atol=1e-30)
 
 
-@pytest.mark.parametrize("g,w,rows", [(7, 16, 1690), (8, 16, 1650), (3, 32, 1681), (5, 32, 1690)])
-def test_window_score_of_keys_beyond_the_cache(g, w, rows):
+@pytest.mark.parametrize("g,w,rows,d", [(7, 16, 1690, 128), (8, 16, 1650, 128), (3, 32, 1681, 128), (5, 32, 1690, 128),
+                                        (7, 16, 1690, 64), (5, 32, 1650, 64)])
+def test_window_score_of_keys_beyond_the_cache(g, w, rows, d):
     # more than 256 MiB of K: up to 8 blocks of window rows keep three tiles in turn, 10 keep two; a launch of one sequence
     # (two tiles, cut into key shares) gives the same scores up to the statistics' last bits
-    cap, B, hkv, d = 1696, 160, 4, 128
+    cap, B, hkv = 1696, 160 * 128 // d, 4
     gen = torch.Generator(device="cuda").manual_seed(g)
     rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(torch.bfloat16)
     K, q, kn = rnd(1, B, hkv, cap, d), rnd(w, 1, B, g * hkv, d), rnd(w, 1, B, hkv, d)
-    assert B * hkv * rows * 256 > 256 << 20
+    assert B * hkv * rows * 2 * d > 256 << 20
     out = []
     for part in (slice(0, B), slice(3, 4), slice(B - 1, B)):
         st = DecodeState(make_config(1, part.stop - part.start, g * hkv, hkv, d, 1600, w, 96, cap, "bf16"))
@@ -667,6 +668,30 @@ def test_redundancy_timing_counts_calls(dtype, d, n_recent):
     assert calls == 3 and ms > 0
 
 
+@pytest.mark.parametrize("dtype,d,n_recent", [("bf16", 128, 8), ("f32", 64, 8), ("bf16", 128, 7)])    # two launches, two, one
+def test_redundancy_replays_in_a_graph(dtype, d, n_recent):
+    w, b, cap, n = 8, 400, 480, 458
+    st = DecodeState(make_config(1, 2, 2, 2, d, b, w, 16, cap, dtype))
+    st.d_state.copy_(torch.tensor([n - w, 100 - w, 0, 0], dtype=torch.int32).expand(1, 2, 4))
+    call = lambda: st.ctx.redundancy_combine(st.K, st.d_state, 99, cap, st.F, 0.5, 0.3, 1e-8, n_recent, st.R, st.F_sel, st.workspace)
+    gen = torch.Generator().manual_seed(d)
+    st.K.zero_(); st.F.zero_(); call(); torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    for _ in range(3):
+        st.K.copy_(torch.randn(st.K.shape, generator=gen)); st.F.copy_(torch.rand(st.F.shape, generator=gen))
+        call()
+        torch.cuda.synchronize()
+        R, F_sel = st.R.clone(), st.F_sel.clone()
+        st.R.fill_(7.0); st.F_sel.fill_(9.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(st.R[..., :n], R[..., :n]) and torch.equal(st.F_sel[..., : n - w], F_sel[..., : n - w])
+
+
 # ---- compaction in column shares ----------------------------------------------------------------
 @pytest.mark.parametrize("dtype,d,B,b", [
     ("bf16", 128, 2, 512),        # 4 units: 4 shares, 256 threads
@@ -717,3 +742,14 @@ def test_compaction_in_shares(dtype, d, B, b):
         assert torch.equal(st.V[0, :, :, :b].cpu()[first:], V[0].gather(2, rows)[first:])
         assert torch.equal(st.pos[0, :, :, :b].cpu()[first:], pos[0].gather(2, src)[first:])
         assert torch.equal(st.F_hist[0, :, :, :k].cpu()[first:], F[0].gather(2, keep)[first:])
+
+
+# ---- native calls -------------------------------------------------------------------------------
+def test_native_call_leaves_other_gpu_tensors_to_ctypes():
+    st = DecodeState(make_config(1, 2, 4, 2, 64, 40, 8, 16, 64, "f32"))
+    call = lambda F: st.ctx._call.gkv_select_topk(st.ctx._handle, F, st.d_state, 20, 64, st.keep_idx, st.workspace)
+    assert call(st.F) == 0 and call(torch.nn.Parameter(st.F)) == 0
+    for other in (st.F.transpose(1, 2), st.F[..., ::2], st.F.cpu(), st.F.as_subclass(type("Sub", (torch.Tensor,), {}))):
+        assert call(other) is None
+    with pytest.raises(ValueError):
+        st.ctx.select_topk(st.F[..., ::2], st.d_state, 20, 64, st.keep_idx, st.workspace)

@@ -405,9 +405,11 @@ def test_redundancy_cfg1_fp32(params):
     assert st["ambiguous"] <= 2
 
 
-def test_redundancy_cfg3_shape_matrix_cores():
+# the window covered: few units share their columns out; one row less: a workgroup per unit, as in launches of many
+@pytest.mark.parametrize("less", [0, 1])
+def test_redundancy_cfg3_shape_matrix_cores(less):
     wl = CONFIGS["cfg3_28layer_b512"].with_(n_layers=2, batch=2)
-    st = run_parity(wl, 1024, redundancy=dict(lam=0.7, tau=0.5, n_recent=wl.window), check_state_every_event=False)
+    st = run_parity(wl, 1024, redundancy=dict(lam=0.7, tau=0.5, n_recent=wl.window - less), check_state_every_event=False)
     assert st["events"] == 4 and st["pair_events"] == 16
     _say(f"  entries on the threshold {st['ambiguous']} (decided the other way: {st['flipped']}) swaps {st['swaps']}")
     # 64 head-events of ~4e5 cosines each, a 2e-6 wide band around tau: a handful, never a head's worth
@@ -429,11 +431,12 @@ def test_redundancy_cfg5_shape_and_lambda_one():
     assert torch.equal(a["state"].V[..., :n, :], b["state"].V[..., :n, :])
 
 
-def test_redundancy_ragged_lengths_cfg3_shape():
+@pytest.mark.parametrize("less", [0, 1])
+def test_redundancy_ragged_lengths_cfg3_shape(less):
     # lengths 596, 633 and 640 at the first trigger: row and column tiles with ragged tails, column
     # shares of unequal size per wavefront, clamped duplicates past the last tile
     wl = CONFIGS["cfg3_28layer_b512"].with_(n_layers=1, batch=3)
-    st = run_parity(wl, 640, prompts=[0, 37, 300], redundancy=dict(lam=0.7, tau=0.5, n_recent=wl.window),
+    st = run_parity(wl, 640, prompts=[0, 37, 300], redundancy=dict(lam=0.7, tau=0.5, n_recent=wl.window - less),
                     check_state_every_event=False)
     lens = sorted({ev["len"] for orc in st["oracles"].values() for ev in orc.events})
     _say(f"  lengths {lens}; entries on the threshold {st['ambiguous']} (decided the other way: {st['flipped']}) "
@@ -442,20 +445,24 @@ def test_redundancy_ragged_lengths_cfg3_shape():
     assert st["ambiguous"] <= 400 and st["flipped"] <= st["ambiguous"]
 
 
-def test_redundancy_b2048_shape():
-    # l = 2176: 136 tiles, seven passes per wavefront, and a workgroup needs more LDS than the default allowance
+@pytest.mark.parametrize("less", [0, 1])
+def test_redundancy_b2048_shape(less):
+    # l = 2176: 68 column tiles, 90 KiB of LDS; nine shares of one pass, or one workgroup whose wavefronts make three
+    # (column sums take the place of the norms, the row tiles go through the ring again)
     wl = CONFIGS["cfg4_b2048"].with_(n_layers=1, batch=1)
-    st = run_parity(wl, 2176, redundancy=dict(lam=0.7, tau=0.5, n_recent=wl.window), check_state_every_event=False,
+    st = run_parity(wl, 2176, redundancy=dict(lam=0.7, tau=0.5, n_recent=wl.window - less), check_state_every_event=False,
                     chunk=256)
     assert st["events"] == 1
     _say(f"  entries on the threshold {st['ambiguous']} (decided the other way: {st['flipped']}) swaps {st['swaps']}")
     assert st["ambiguous"] <= 400 and st["flipped"] <= st["ambiguous"]
 
 
-def test_redundancy_largest_capacity():
-    # l = capacity = 3936: 246 tiles, 13 passes, 96 KiB of LDS per workgroup; sequence 1 (1096 rows) is left alone
+@pytest.mark.parametrize("less", [0, 1])
+def test_redundancy_largest_capacity(less):
+    # l = capacity = 3936: 123 column tiles, 110 KiB of LDS, 16 shares of one pass or one workgroup of six; sequence 1
+    # (1096 rows) is left alone
     wl = CONFIGS["cfg2_single_layer"].with_(n_layers=1, batch=2, budget=3840, interval=96, seed=41)
-    st = run_parity(wl, 96, prompts=[3840, 1000], redundancy=dict(lam=0.7, tau=0.5, n_recent=wl.window),
+    st = run_parity(wl, 96, prompts=[3840, 1000], redundancy=dict(lam=0.7, tau=0.5, n_recent=wl.window - less),
                     chunk=96, check_state_every_event=False, say=_say)
     assert st["pair_events"] == 1 and st["oracles"][(0, 0)].events[0]["len"] == 3936
     _say(f"  entries on the threshold {st['ambiguous']} (decided the other way: {st['flipped']}) swaps {st['swaps']}")
