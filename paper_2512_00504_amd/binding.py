@@ -4,13 +4,15 @@ Every step of the path runs in the HIP kernels behind the C ABI declared in
 include/gkv.h; the functions here have the same names and pass device
 pointers of torch tensors and the current torch stream straight through.
 The calls a program makes per decode step or compression are marshalled by
-_gkv_call (csrc/call.cpp); what it does not take, ctypes converts or refuses.
-There is no fallback: if a library is missing, loading raises.
+_gkv_call (csrc/call.cpp); what it does not take, ctypes converts or refuses,
+and all of it (1 to 2 us more a call) where only libgkv.so is built, with a warning.
+There is no other way to the kernels: if libgkv.so is missing, loading raises.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from ctypes import POINTER, byref, c_char_p, c_double, c_float, c_int32, c_int64, c_size_t, c_void_p
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -118,13 +120,24 @@ def _stream():
 _call = None
 
 
+class _LeavesAllToCtypes:
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
 def _load_call():
     """The native marshalling, bound to the entry points of the library that ctypes loaded."""
     global _call
     if _call is None:
         lib = load_library()
         import torch  # noqa: F401  (the extension's libraries)
-        from . import _gkv_call
+        try:
+            from . import _gkv_call
+        except ImportError as e:
+            warnings.warn(f"gkv: calls go through ctypes, the native binding is not there ({e}): build it with "
+                          "`python -c 'import __graft_entry__ as g; g.build()'`", RuntimeWarning, stacklevel=3)
+            _call = _LeavesAllToCtypes()
+            return _call
         for name in dir(_gkv_call):
             if name.startswith("gkv_"):
                 _gkv_call.bind(name, ctypes.cast(getattr(lib, name), c_void_p).value)

@@ -5,6 +5,7 @@ import ctypes
 import os
 import re
 import subprocess
+import sys
 import tempfile
 
 import numpy as np
@@ -204,6 +205,20 @@ def test_native_call_binds_only_its_own():
     from paper_2512_00504_amd import binding
     with pytest.raises(KeyError):
         binding._load_call().bind("gkv_destroy", 1)
+
+
+def test_without_the_native_half_calls_go_through_ctypes(monkeypatch):
+    from paper_2512_00504_amd import binding
+    monkeypatch.setattr(binding, "_call", None)
+    monkeypatch.setitem(sys.modules, "paper_2512_00504_amd._gkv_call", None)      # importing it fails
+    monkeypatch.delattr(P, "_gkv_call", raising=False)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        ctx = P.Context(_cfg())
+    assert ctx._call.gkv_select_topk(ctx._handle, None, None, 3, 4, None, None) is None
+    if torch.cuda.is_available():
+        with pytest.raises(P.GkvError):
+            ctx.select_topk(None, None, 3, 4, None, None)
+    ctx.close()
 
 
 def _vgpr_spills():
