@@ -25,8 +25,8 @@
 // or 16 KiB (D = 128) per slice against 1024 or 2048 cycles of MFMA, so four wavefronts can take
 // 32 B a cycle and CU, four times the CU's share of the HBM rate; bf16 needs a tenth of that.
 // Against the plain vector-ALU kernel these shapes used before, per launch: fp32 D = 128, 32 units
-// of 528 rows 466 -> 9.2 us (uncut 17.4), 896 units 1614 -> 75.5; bf16 D = 64, 128 units of 528 rows 245 -> 7.3,
-// 1152 units 575 -> 28.4; fp32 D = 64, 2 units of 72 rows 25.5 -> 5.3.
+// of 528 rows 466 -> 9.6 us (uncut 17.6), 896 units 1614 -> 75.5; bf16 D = 64, 128 units of 528 rows 245 -> 6.9,
+// 1152 units 575 -> 28.4; fp32 D = 64, 2 units of 72 rows 25.5 -> 4.5.
 // The wavefronts of a workgroup are merged through LDS; splits of one unit are merged by the
 // last workgroup to finish (ticket counter), in a fixed order, so results are deterministic.
 //

@@ -175,22 +175,23 @@ static int explicit_splits(const gkv_ctx* ctx) {
 // ceil(n / iters) of them, so the last may be shorter).  Depends on the configuration alone, so the same
 // call gives the same bits whatever bound of the length the caller passes.
 //
-// A workgroup of 8 wavefronts alone on a CU pulls 64 GB/s (4 units of 3900 rows uncut: 8 MB in 31.2 us; one
-// 8 KiB slice per wavefront and trip to memory), so a few dozen units leave most of the HBM rate unused, and
-// at 128 units, 5.3 TB/s, half of the CUs idle.  Cut into pieces of 8 slices, up to 256 of them (bf16,
-// d = 128, us per launch, uncut with 8 wavefronts -> cut):
-//   4 units x 577 rows 8.5 -> 7.2, x 2113 21.0 -> 9.0, x 3900 31.2 -> 9.8; 32 x 1100 13.9 -> 10.2;
-//   64 x 1100 15.9 -> 11.0, x 3900 39.6 -> 24.3; 128 x 3900 48.4 -> 42.4, and with lengths from 470 to 3900
-//   44.5 -> 30.0 (the longest unit alone on its CU bounds an uncut launch).
-// Pieces of 4 slices, twice as many: 4 x 577 7.1 -> 7.8, 32 x 577 7.9 -> 8.3, 64 x 577 8.8 -> 8.9; fp32 and
-// d = 64 within 0.5 us either way.  2 or 3 pieces of a short unit cost more than they bring (128 x 577
-// 12.3 -> 12.7), and from 256 units on the chip is full anyway (256 x 577 17.0 -> 17.8, 512 x 1100 47.2 -> 49.6).
-// Long pieces take 8 wavefronts (48 slices and more: 128 ragged units 34.6 with 4, 30.0 with 8).  Uncut,
-// 8 wavefronts serve up to 256 units that give each a slice (128 x 577 14.2 -> 12.3; 2 x 100 4.6 -> 4.8) and more than 512 units of 64 slices
-// (896 x 2113 167 -> 163, ragged to 3900 232 -> 211; 4608 x 1057 399 -> 392); in between 4 do
-// (512 x 2113 90.7 against 92.8).  fp32 at d = 128 has 16 KiB slices and stays at 4: uncut 256 x 528 26.5, with
-// 8 27.7; cut 32 x 528 9.6 / 11.9, 64 x 1050 17.0 / 18.3, 128 x 1050 25.5 / 26.7, 4 x 2100 12.3 / 12.1.
-// (All of these before requests went out ahead of the state record, which took 0.3 to 0.7 us off either side.)
+// A workgroup of 8 wavefronts alone on a CU pulls 70 GB/s (4 units of 3900 rows uncut: 8 MB in 28.6 us; one 8 KiB
+// slice per wavefront and trip to memory), so a few dozen units leave most of the HBM rate unused, and at 128 units half of
+// the CUs idle.  Cut into pieces of 8 slices, up to 256 of them (bf16, d = 128, us per launch in a graph, uncut with 8
+// wavefronts / with 16 -> cut, by 4 wavefronts a piece but for 128 x 2113 and x 3900):
+//   4 units x 577 rows 7.3 / 7.5 -> 6.5, x 2113 14.7 / 14.2 -> 8.1, x 3900 28.6 / 29.3 -> 8.6; 32 x 577 7.5 / 7.8 -> 7.3, x 1100
+//   12.5 / 13.1 -> 9.1; 64 x 577 9.0 / 9.6 -> 8.4, x 1100 14.4 / 15.1 -> 10.8, x 3900 37.8 / 39.8 -> 23.0; 128 x 1100 15.4 / 16.1 -> 15.5,
+//   x 2113 25.0 / 26.0 -> 24.7, x 3900 41.8 / 43.4 -> 40.2, and with lengths from 470 to 3900 42.1 -> 29.6 (the longest unit
+//   alone on its CU bounds an uncut launch).
+// Pieces of 4 slices, twice as many: 4 x 577 6.45 -> 6.6, 32 x 577 7.3 -> 7.85, 32 x 1100, 64 x 577 and 128 x 2113 the same; fp32,
+// d = 64 4 x 528 6.8 -> 6.35, 64 x 528 8.1 -> 8.2.  2 or 3 pieces of a short unit cost more than they bring (128 x 577
+// 10.3 -> 11.0 and 11.8), and from 256 units on the chip is full anyway (256 x 577 14.6 -> 16.8, 512 x 1100 45.4 -> 50.4).
+// Long pieces take 8 wavefronts (48 slices and more): ragged to 3900 rows 128 units 33.5 with 4, 29.6 with 8, 64 units 20.0 /
+// 18.1; equal lengths would rather have 4 (128 x 2113 24.0 / 24.7, 64 x 3900 22.7 / 23.0).  Uncut, 8 wavefronts serve up to 256
+// units that give each a slice (128 x 577 12.2 -> 10.3, 256 x 577 14.8 -> 14.6, ragged to 3900 65 -> 54; 2 x 100 4.4 -> 4.6; 16: 6.5) and
+// more than 512 units of 64 slices (896 x 2113 159.5 -> 157, ragged to 3900 174 -> 170); in between 4 do (512 x 1100
+// 45.2 against 45.7, x 2113 85.8 / 87.5).  fp32 at d = 128 has 16 KiB slices and stays at 4: cut 32 x 528 9.6 / 11.2, 64 x 1050 16.7 / 17.0,
+// 128 x 1050 25.6 / 26.1, 4 x 2100 11.5 / 11.7, uncut 256 x 528 24.1 / 24.4.
 struct AttendPlan { int waves, splits, iters; };
 
 static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
@@ -206,7 +207,7 @@ static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
   } else {
     int s = (int)(256 / units);
     s = s > 16 ? 16 : s;
-    const int pieces = wide ? (slices + 7) / 8 : slices / 8;   // wide: no piece longer than the others (4 units x 528 rows 8.2 -> 7.7)
+    const int pieces = wide ? (slices + 7) / 8 : slices / 8;   // wide: no piece longer than the others (4 units x 528 rows, 8 pieces -> 9: 8.25 -> 7.7)
     s = s > pieces ? pieces : s;
     if (s >= 4 || (s >= 2 && slices >= 64)) { p.splits = s; p.iters = wide ? 4 : 8; }
   }

@@ -147,7 +147,7 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int 
 // next one, and those of the last between the first products of the next row tile.
 //
 // Row tiles reach the wavefronts through LDS: every wavefront needs every row tile in every pass,
-// and if each fetched them itself a unit's keys (l * 256 bytes) would be read 4 * passes times; the
+// and if each fetched them itself a unit's keys (l * 256 bytes) would be read 8 * passes times; the
 // units resident on one XCD together exceed its L2, so those re-reads would come from memory and
 // bound the kernel.  Instead the workgroup moves through the row tiles in groups of four: each
 // wavefront fetches 16 rows of the next group while all work on the current group, stores them
@@ -157,16 +157,16 @@ __device__ __forceinline__ void load_k_tile(u32x4 (&kA)[4], const char* Kh, int 
 //
 // A column's own reciprocal norm is wanted until its sum is finished, so the sums take the norms' place.
 //
-// Up to 128 units several workgroups share a unit's columns where the capacity gives a wavefront more than two column
-// tiles, that is from 448 rows on (above 64 units, where there are two or three shares, from 704 on): a share costs the norms
-// and the start again, and the sums a finishing launch.  us per call, a workgroup per unit -> shared: 4 units of 332
+// Up to 128 units several workgroups share a unit's columns from a capacity of 448 rows on (14 column tiles for eight
+// wavefronts; above 64 units, where there are two or three shares, from 704 on): a share costs the norms and the start again,
+// and the sums a finishing launch.  us per call, a workgroup per unit -> shared: 4 units of 332
 // rows 13.4 -> 15.1, of 400 16.1 -> 16.2, of 480 17.6 -> 16.6, of 640 24.6 -> 19.5, of 1128 67 -> 29; 64 of 332 13.8 -> 15.7, of 480 18.0 ->
 // 17.1, of 640 25.2 -> 21.6, of 1128 68 -> 40; 110 of 544 22.7 -> 24.5, of 640 25.4 -> 27.5, of 704 30.0 -> 29.9, of 1128 69 -> 58;
 // 128 of 640 25.5 -> 26.0, of 768 32.7 -> 31.5, of 1128 70 -> 57.
 //
-// Per launch, against 16x16 tiles, comparisons and selections, and two workgroups of four wavefronts per compute
-// unit: 896 units of 640 rows 161 -> 133 us, of 332 96 -> 64, of 700 233 -> 151; 1792 of 1152 772 -> 680; 4 of 640
-// 54 -> 25.  With every compute unit at it the clock falls (a product with random operands then takes 42 to 52
+// Per launch in a graph, against 16x16 tiles, comparisons and selections, and two workgroups of four wavefronts per
+// compute unit: 896 units of 640 rows 145 -> 122 us, of 332 92 -> 61, of 700 214 -> 141; 1792 of 1152 760 -> 637; 4 of 640
+// 55 -> 26 (a workgroup each).  With every compute unit at it the clock falls (a product with random operands then takes 42 to 52
 // of the nominal cycles, not 32), and units start together: all fetch their keys, then all multiply.
 //
 // Dynamic LDS: double cs[cap]; double red[8]; float inv_f[cap]; then the ring, 2 groups x 4 tiles x 8 KiB

@@ -395,8 +395,8 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
 // LDS per MFMA at one key tile per wavefront, which makes the CU's 128 B a cycle its bound; here LDS
 // only hands the queries round once.  K^T Q instead of Q^T K: a lane keeps one row's offset per
 // block (two registers, not eight), and the 16 window rows end up across the lanes.
-// Bound: HBM at several hundred units (28 layers, batch 16, b = 1024: 516 MB of K in 115 to 118 us; with one
-// block's arithmetic left of seven 97 us, staging and launch alone 18 us), arithmetic and the start
+// Bound: HBM at several hundred units (28 layers, batch 16, b = 1024: 516 MB of K in 98 to 114 us, with two tiles in
+// turn instead of three 115 to 124 and then 97 with one block's arithmetic left of seven), arithmetic and the start
 // of a workgroup (state, queries, first tile: three dependent trips to memory) below.  Per launch
 // against a kernel that kept the queries in LDS and took an exponential per head and logit: 256 units
 // of 1088 rows, g = 5, w = 32 25.8 -> 20.0 us; 4608 such units 347 -> 310 us; 448 units of 640 rows,
