@@ -463,18 +463,16 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   // Two tiles on their way while a third is worked on where K comes from memory and the registers allow it: 1792
   // units of 1152 rows, g = 7 124 -> 114 us, g = 8 117 -> 103, g = 4 100 -> 97; K within the memory-side cache 30.3 -> 29.7
   // (896 units), 64 units 6.7 -> 7.0; ten blocks of 128 bytes 72 -> 79.  A fourth: 115, 114, 99.
-  // Two tiles are two objects, not an array: with the array below the pass for the own statistics took 8 to 34 registers
-  // more, and 38 spilled took 18432 units, g = 5, w = 32 from 2480 to 4530 us.
-  constexpr bool THREE = ONCE && NT * NB <= 8;
-  Tile<T, D> kA, kN, ring[3];
+  // The tiles are an array (as two objects 672 units of 309 rows, g = 8 take 19.0 us instead of 18.2, three cost 1 per cent), but two
+  // objects where the rows' own statistics come first: with the array that pass took 8 to 34 registers more, and 38
+  // spilled took 18432 units, g = 5, w = 32 from 2480 to 4530 us.
+  constexpr int DEPTH = ONCE && NT * NB <= 8 ? 3 : 2;
+  Tile<T, D> kA, kN, ring[DEPTH];
   const int n_full = OWN ? (cc + 1) >> 4 : 0;            // tiles whose keys every window row sees
   if constexpr (OWN) {
     if (wave < n_full) load_k_tile<T, D>(kA, Kh, wave, seq.n_tiled, lane, r, kb);
   } else {
-    if (g0 + wave < g1) {
-      if constexpr (THREE) load_k_tile<T, D, ONCE>(ring[0], Kh, g0 + wave, seq.n_tiled, lane, r, kb);
-      else load_k_tile<T, D, ONCE>(kA, Kh, g0 + wave, seq.n_tiled, lane, r, kb);
-    }
+    if (g0 + wave < g1) load_k_tile<T, D, ONCE>(ring[0], Kh, g0 + wave, seq.n_tiled, lane, r, kb);
     if (tid < NT * NB * 16) row_c[tid] = row_offset(row_valid, ms.x, ms.y);
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the queries are in LDS
@@ -624,23 +622,24 @@ __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, Scor
   // the tiles in turn: the next ones are always requested before one is worked on, and stay where they land
   // (copied over at the end of each round instead: 121 -> 117 us at 1792 units of b = 1024)
   auto request = [&](Tile<T, D>& kT, int t) { load_k_tile<T, D, ONCE>(kT, Kh, min(t, g1 - 1), seq.n_tiled, lane, r, kb); };
-  if constexpr (THREE) {
-    request(ring[1], g0 + wave + NW);
-    for (int t = g0 + wave; t < g1; t += 3 * NW) {
-#pragma unroll
-      for (int p = 0; p < 3; ++p) {
-        if (p > 0 && t + p * NW >= g1) break;
-        request(ring[(p + 2) % 3], t + (p + 2) * NW);
-        tile(ring[p], t + p * NW);
-      }
-    }
-  } else {
+  if constexpr (OWN) {
     for (int t = g0 + wave; t < g1; t += 2 * NW) {
       request(kN, t + NW);
       tile(kA, t);
       if (t + NW >= g1) break;
       request(kA, t + 2 * NW);
       tile(kN, t + NW);
+    }
+  } else {
+#pragma unroll
+    for (int p = 1; p < DEPTH - 1; ++p) request(ring[p], g0 + wave + p * NW);
+    for (int t = g0 + wave; t < g1; t += DEPTH * NW) {
+#pragma unroll
+      for (int p = 0; p < DEPTH; ++p) {
+        if (p > 0 && t + p * NW >= g1) break;
+        request(ring[(p + DEPTH - 1) % DEPTH], t + (p + DEPTH - 1) * NW);
+        tile(ring[p], t + p * NW);
+      }
     }
   }
   bool huge = false;
