@@ -46,7 +46,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ u32x4 ld16(const void* p) { return *(const u32x4*)p; }
@@ -70,34 +71,39 @@ struct Geo {
 // channels from each half of the row so that both 16-byte loads are contiguous over the lanes.
 template <int VW> struct VWords { uint32_t w[VW]; };
 template <typename T, int D>
-__device__ __forceinline__ void ld_v(VWords<Geo<T, D>::VW>& o, const char* row, int r) {
+__device__ __forceinline__ void ld_v(VWords<Geo<T, D>::VW>& o, const char* p) {
   if constexpr (Geo<T, D>::VW == 2) {
-    const u32x2 a = __builtin_nontemporal_load((const u32x2*)(row + r * 8));
+    const u32x2 a = __builtin_nontemporal_load((const u32x2*)p);
     o.w[0] = a[0]; o.w[1] = a[1];
   } else {
-    const u32x4 a = __builtin_nontemporal_load((const u32x4*)(row + r * 16));
+    const u32x4 a = __builtin_nontemporal_load((const u32x4*)p);
 #pragma unroll
     for (int i = 0; i < 4; ++i) o.w[i] = a[i];
     if constexpr (Geo<T, D>::VW == 8) {
-      const u32x4 b = __builtin_nontemporal_load((const u32x4*)(row + 256 + r * 16));
+      const u32x4 b = __builtin_nontemporal_load((const u32x4*)(p + 256));
 #pragma unroll
       for (int i = 0; i < 4; ++i) o.w[4 + i] = b[i];
     }
   }
 }
-template <typename T, int D>
-__device__ __forceinline__ void ld_v_lds(VWords<Geo<T, D>::VW>& o, const char* row, int r) {
-#pragma unroll
-  for (int i = 0; i < Geo<T, D>::VW; ++i)
-    o.w[i] = *(const uint32_t*)(row + (Geo<T, D>::VW == 8 ? (i >> 2) * 256 + r * 16 + (i & 3) * 4
-                                                           : r * Geo<T, D>::VW * 4 + i * 4));
-}
-
 // One wavefront iteration's loads: KT K tiles (A operands) and 4*KT V rows per lane.
 template <typename T, int D, int KT>
 struct Slice {
   u32x4 kA[KT][Geo<T, D>::NL];
   VWords<Geo<T, D>::VW> vR[4 * KT];
+};
+
+// Where a wavefront's loads go: the unit's rows (uniform) and this lane's offsets from a slice's first row, one for
+// each K format and one for V.  Everything else about an address is scalar or an immediate.
+template <typename T, int D>
+struct Rows {
+  using G = Geo<T, D>;
+  const char *Kh, *Vh;
+  int n_tiled;
+  uint32_t k_tiled, k_rows, v;
+  __device__ __forceinline__ Rows(const char* K, const char* V, int tiled, int lane)
+      : Kh(K), Vh(V), n_tiled(tiled), k_tiled(lane * 16), k_rows((lane & 15) * G::ROW_BYTES + (lane >> 4) * 16),
+        v((lane >> 4) * 4 * G::ROW_BYTES + (lane & 15) * (G::VW == 2 ? 8 : 16)) {}
 };
 
 // Tiles below n_tiled are in tiled format (lane-contiguous 1 KiB per load); tiles above are
@@ -108,24 +114,47 @@ struct Slice {
 // memory-side cache), both non-temporal 76%, one stream of each kind 80-85% at every cache size
 // tried (0.3 to 10 GB), whichever of the two is the non-temporal one.
 template <typename T, int D, int KT>
-__device__ __forceinline__ void issue_slice(Slice<T, D, KT>& s, const char* Kh, const char* Vh, int it,
-                                            int n_tiled, int lane, int r, int kb) {
+__device__ __forceinline__ void issue_slice(Slice<T, D, KT>& s, const Rows<T, D>& at, int it) {
   using G = Geo<T, D>;
-  const int key0 = it * 16 * KT;
 #pragma unroll
   for (int tt = 0; tt < KT; ++tt) {
-    const int row0 = key0 + 16 * tt;
-    const char* Kt = Kh + (size_t)(row0 >> 4) * G::TILE_BYTES;
-    const bool tiled = row0 < n_tiled;                     // wave-uniform
-    const int lane_off = tiled ? lane * 16 : r * G::ROW_BYTES + kb * 16;
-    const int step_off = tiled ? 1024 : 64;
+    const int t = it * KT + tt;
+    const char* Kt = at.Kh + (uint32_t)(t * G::TILE_BYTES);
+    if (16 * t < at.n_tiled) {                               // wave-uniform
 #pragma unroll
-    for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = ld16(Kt + lane_off + c * step_off);
+      for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = ld16(Kt + at.k_tiled + c * 1024);
+      asm volatile("; tiled");                               // (the branches stay apart: the steps are immediates)
+    } else {
+#pragma unroll
+      for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = ld16(Kt + at.k_rows + c * 64);
+      asm volatile("; rows");
+    }
+  }
+  const char* Vt = at.Vh + (uint32_t)(it * KT * G::TILE_BYTES);
+#pragma unroll
+  for (int jj = 0; jj < 4 * KT; ++jj) ld_v<T, D>(s.vR[jj], Vt + at.v + ((jj & 3) + (jj >> 2) * 16) * G::ROW_BYTES);
+}
+
+// The unit's last slice: the lanes that hold row `len0` take it from the newest token's own k and v.
+template <typename T, int D, int KT>
+__device__ __forceinline__ void issue_last_slice(Slice<T, D, KT>& s, const Rows<T, D>& at, int it, int lane, int new_row,
+                                                 const char* knew, const char* vnew) {
+  using G = Geo<T, D>;
+  asm volatile("" : "+v"(lane));                             // its addresses are formed here, not kept in registers from the start
+  const int r = lane & 15, kb = lane >> 4;
+#pragma unroll
+  for (int tt = 0; tt < KT; ++tt) {
+    const int t = it * KT + tt;
+    const bool tiled = 16 * t < at.n_tiled, is_new = 16 * t + r == new_row;
+    const char* p = is_new ? knew + kb * 16 : at.Kh + (uint32_t)(t * G::TILE_BYTES) + (tiled ? at.k_tiled : at.k_rows);
+    const uint32_t step = is_new || !tiled ? 64 : 1024;
+#pragma unroll
+    for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = ld16(p + c * step);
   }
 #pragma unroll
   for (int jj = 0; jj < 4 * KT; ++jj) {
-    const int key = key0 + (jj & 3) + 4 * kb + (jj >> 2) * 16;
-    ld_v<T, D>(s.vR[jj], Vh + (size_t)key * G::ROW_BYTES, r);
+    const int key = it * 16 * KT + 4 * kb + (jj & 3) + (jj >> 2) * 16;
+    ld_v<T, D>(s.vR[jj], (key == new_row ? vnew : at.Vh + (uint32_t)(key * G::ROW_BYTES)) + r * (G::VW == 2 ? 8 : 16));
   }
 }
 
@@ -138,39 +167,50 @@ struct Running {
   f32x4 oacc[NC];
 };
 
-// EDGE = the slice may contain the newest token's row and rows past the end: substitute k/v of
-// the newest token from the inputs, mask the rest.  The common path has none of that.
+// Maximum and sum over the four lanes of a head (lane % 16), in each of them: the halves and then the quarters of
+// the wavefront change places in registers, where an exchange through LDS takes 60 ns.
+__device__ __forceinline__ float over_head(float x, bool max) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint32_t u = __float_as_uint(x);
+    const u32x2 y = i == 0 ? __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(u, u, false, false))
+                           : __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(u, u, false, false));
+    const float a = __uint_as_float(y[0]), b = __uint_as_float(y[1]);
+    if (max) asm("v_max_f32 %0, %1, %2" : "=v"(x) : "v"(a), "v"(b));   // (fmaxf would quiet both operands first, an instruction each)
+    else x = a + b;
+  }
+  return x;
+}
+
+// edge: the slice may contain rows past the end, which are masked.  first: the wavefront's first slice, whose accumulators are zero.
 // EXACT: right for every logit and value, infinities and finite ones of any size among them.  Without
 // it, which is what a wavefront tries first, a logit of -inf may give NaN (the scale's low part times -inf), a
 // huge maximum any weight (see log2_weight), and at bf16, D = 64 an infinite value NaN; all of them show at the end.
-template <typename T, int D, int KT, bool EDGE, bool EXACT>
+template <typename T, int D, int KT, bool EXACT>
 __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16>& st,
-                                              const u32x4 (&qB)[Geo<T, D>::NL], int it,
-                                              float scale_log2, float scale_log2_lo, int r, int kb, bool has_new, int len0,
-                                              int n_tot, const char* knew, const char* vnew) {
-  // knew / vnew: the newest token's k and v rows, staged in LDS at the start of the workgroup
+                                              const u32x4 (&qB)[Geo<T, D>::NL], int it, bool first, bool edge,
+                                              float scale_log2, float scale_log2_lo, int r, int kb, int n_tot) {
   using G = Geo<T, D>;
   constexpr int NS = 4 * KT;
   const int key0 = it * 16 * KT;
-  if constexpr (EDGE) {
-    if (has_new && key0 <= len0) {
-      const int tt_new = (len0 - key0) >> 4, rr = len0 & 15;
+  // Rows past the end have zeros for K and V (what is stored there must not reach the matrix cores) and start from the
+  // logit -1e30, or -inf.  All of it before the products: behind a branch that follows them the compiler does not insert
+  // the wait states their results need.
+  f32x4 sc[KT];
 #pragma unroll
-      for (int tt = 0; tt < KT; ++tt)
-        if (tt == tt_new && r == rr) {
+  for (int tt = 0; tt < KT; ++tt) sc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (edge) {
 #pragma unroll
-          for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = *(const u32x4*)(knew + (4 * c + kb) * 16);
-        }
+    for (int tt = 0; tt < KT; ++tt)
+      if (key0 + 16 * tt + r >= n_tot) {
 #pragma unroll
-      for (int jj = 0; jj < NS; ++jj) {
-        const int key = key0 + (jj & 3) + 4 * kb + (jj >> 2) * 16;
-        if (key == len0) ld_v_lds<T, D>(s.vR[jj], vnew, r);
+        for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = u32x4{0u, 0u, 0u, 0u};
       }
-    }
 #pragma unroll
     for (int jj = 0; jj < NS; ++jj) {
       const int key = key0 + (jj & 3) + 4 * kb + (jj >> 2) * 16;
-      if (key >= n_tot) {                                  // stale rows must not reach the MFMA
+      if (key >= n_tot) {
+        if constexpr (!EXACT) sc[jj >> 2][jj & 3] = -1e30f;
 #pragma unroll
         for (int i = 0; i < G::VW; ++i) s.vR[jj].w[i] = 0u;
       }
@@ -178,10 +218,8 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
   }
 
   // scores: sc[tt][e] = q[head r] . k[key0 + 16 tt + 4 kb + e]
-  f32x4 sc[KT];
 #pragma unroll
   for (int tt = 0; tt < KT; ++tt) {
-    sc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int c = 0; c < G::NL; ++c) {
       if constexpr (G::F32) {
@@ -198,22 +236,23 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     sv[i] = sc[i >> 2][i & 3];
-    if constexpr (EDGE) {
+    if constexpr (EXACT) {                                 // (zero times an infinite query is no number)
       const int key = key0 + (i >> 2) * 16 + 4 * kb + (i & 3);
-      if (key >= n_tot) sv[i] = EXACT ? -INFINITY : -1e30f;
+      if (key >= n_tot) sv[i] = -INFINITY;
     }
   }
   float mx = sv[0];
 #pragma unroll
   for (int i = 1; i < NS; ++i) mx = fmaxf(mx, sv[i]);
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  mx = over_head(mx, true);
   const float m_new = fmaxf(st.m_run, mx * scale_log2);       // scale > 0: max commutes with it
   if (__any(m_new > st.m_run)) {
     const float corr = __builtin_amdgcn_exp2f(st.m_run - m_new);
     st.l_run *= corr;
+    if (!first) {
 #pragma unroll
-    for (int m = 0; m < G::NC; ++m) st.oacc[m] *= corr;
+      for (int m = 0; m < G::NC; ++m) st.oacc[m] *= corr;
+    }
     st.m_run = m_new;
   }
   float pf[NS];
@@ -276,8 +315,11 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
     f32x4 p4;
 #pragma unroll
     for (int i = 0; i < 4; ++i) p4[i] = pf[i];
-    const bf16x4 pB4 = __builtin_convertvector(p4, bf16x4);
-    const s16x4 pB = __builtin_bit_cast(s16x4, pB4);
+    u32x2 pw;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      pw[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{p4[2 * i], p4[2 * i + 1]}), bf16x2));
+    const s16x4 pB = __builtin_bit_cast(s16x4, pw);
 #pragma unroll
     for (int m = 0; m < G::NC; ++m) {
       u32x2 t;
@@ -292,10 +334,10 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
 
 __device__ __forceinline__ void store_row4(float* p, const f32x4& o) { *(f32x4*)p = o; }
 __device__ __forceinline__ void store_row4(uint16_t* p, const f32x4& o) {
-  uint2 packed;
-  packed.x = (uint32_t)float_to_bf16_bits(o[0]) | ((uint32_t)float_to_bf16_bits(o[1]) << 16);
-  packed.y = (uint32_t)float_to_bf16_bits(o[2]) | ((uint32_t)float_to_bf16_bits(o[3]) << 16);
-  *(uint2*)p = packed;
+  u32x2 packed;
+  packed[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{o[0], o[1]}), bf16x2));
+  packed[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{o[2], o[3]}), bf16x2));
+  *(u32x2*)p = packed;
 }
 // Two neighbouring floats to and from memory that workgroups on other XCDs share.
 __device__ __forceinline__ void store_agent(float* p, float x, float y) {
@@ -313,27 +355,35 @@ __device__ __forceinline__ float inv_sum(float l, bool any_key, bool fast) {
   return fast ? __builtin_amdgcn_rcpf(l) : 1.f / l;
 }
 
-// KT = 16-key tiles per wavefront iteration (1 or 2)
-template <typename T, int D, int NW, int KT, int OCC>
-__global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, AttendArgs a) {
+// What the kernel needs of a call, all of it requested at once.
+struct KernelArgs {
+  const int32_t* d_state; const int32_t* step_base;      // step_base: d_state where there is none, and not used
+  const char *q, *k_new, *v_new;
+  char *K, *V; int32_t* pos; char *qwin, *out;
+  float2* stats; float* partials; int32_t* ticket;
+  GkvDivisor by_splits, by_hkv, by_iters, by_w;
+  int32_t splits, split_iters, Hq, Hkv, g, cap, LB, w, step;
+  int32_t has_base, copy_q, write_stats;
+  float scale_hi, scale_lo;
+};
+
+// KT = 16-key tiles per wavefront iteration (1 or 2); DEPTH = slices in flight (1 or 2)
+template <typename T, int D, int NW, int KT, int OCC, int DEPTH>
+__global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a) {
   using G = Geo<T, D>;
   constexpr int KEYS = 16 * KT;             // keys per iteration
   constexpr int RP = G::RP, ROW_BYTES = G::ROW_BYTES, OSTR = G::OSTR, PSTR = G::PSTR;
-  extern __shared__ __attribute__((aligned(16))) float smem[];   // behind s_last: 16-byte pieces want the alignment
-  __shared__ int s_last;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kb = lane >> 4;
-  const int splits = a.splits;
+  const int splits = a.splits, g = a.g, cap = a.cap;
   const int unit = quotient(blockIdx.x, a.by_splits), sp = (int)blockIdx.x - unit * splits;
-  const int lb = quotient(unit, dm.by_hkv), j = unit - lb * dm.Hkv;
-  const int g = dm.g, cap = dm.cap;
-  const char* Kh = (const char*)a.K + (size_t)unit * cap * ROW_BYTES;
-  const char* Vh = (const char*)a.V + (size_t)unit * cap * ROW_BYTES;
-  const char* knew_g = (const char*)a.k_new + (size_t)unit * ROW_BYTES;
-  const char* vnew_g = (const char*)a.v_new + (size_t)unit * ROW_BYTES;
-  const char* q_g = (const char*)a.q + ((size_t)lb * dm.Hq + j * g) * ROW_BYTES;
-  const bool appender = sp == 0;
-  const bool ring_copy = appender && a.copy_q;   // q may already live in its ring slot
+  const int lb = quotient(unit, a.by_hkv), j = unit - lb * a.Hkv;
+  const size_t head0 = (size_t)lb * a.Hq + j * g;          // the group's first query head
+  const char* q_g = a.q + head0 * ROW_BYTES;
+  const char* knew_g = a.k_new + (size_t)unit * ROW_BYTES;
+  const char* vnew_g = a.v_new + (size_t)unit * ROW_BYTES;
   const bool may_grow = a.k_new != nullptr;
 
   // A launch of few units is one trip to memory after the other, so everything whose address the arguments
@@ -341,88 +391,106 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
   // branch on whether there is a counter), the group's queries (B operand of the QK product: lane (head r, kb)
   // holds chunks 4c+kb of q[r]) and the rows stored at the end of the workgroup.
   int4 rec = *(const int4*)(a.d_state + 4 * (size_t)lb);
-  const int32_t base = *(dm.step_base ? dm.step_base : a.d_state);
+  const int32_t base = *a.step_base;
   __builtin_amdgcn_sched_barrier(0);
   u32x4 qB[G::NL];
   {
-    const char* qh = q_g + min(r, g - 1) * ROW_BYTES;      // (lanes beyond the group repeat its last head and are ignored)
+    const uint32_t at = min(r, g - 1) * ROW_BYTES + kb * 16;   // (lanes beyond the group repeat its last head and are ignored)
 #pragma unroll
-    for (int c = 0; c < G::NL; ++c) qB[c] = ld16(qh + (4 * c + kb) * 16);
+    for (int c = 0; c < G::NL; ++c) qB[c] = ld16(q_g + at + c * 64);
   }
-  // one 16-byte piece per thread and round: pieces [0,RP) k_new, [RP,2RP) v_new (every workgroup: the wavefront
-  // that owns the last slice substitutes them for cache row `len`), [2RP, 2RP + RP g) the group's q rows for
-  // the window ring (split 0 only); others read a valid address and are not used
-  constexpr int AP_ROUNDS = (2 * RP + RP * 16 + NW * 64 - 1) / (NW * 64);
-  u32x4 ap[AP_ROUNDS];
+  // 16-byte pieces stored at the end by piece 0 of a unit: [0,RP) k_new and [RP,2RP) v_new, a thread each, and the group's q
+  // rows for the window ring; threads without one read a valid address
+  constexpr int Q_ROUNDS = (RP * 16 + NW * 64 - 1) / (NW * 64);
+  u32x4 kv_piece, q_piece[Q_ROUNDS];
+  {
+    const uint32_t x = min(tid, 2 * RP - 1);
+    const char* src = x < RP ? knew_g + x * 16 : vnew_g + (x - RP) * 16;
+    kv_piece = ld16(may_grow ? src : q_g);
 #pragma unroll
-  for (int rd = 0; rd < AP_ROUNDS; ++rd) {
-    const int x = tid + rd * NW * 64;
-    const char* src = q_g + (x < 2 * RP + RP * g && x >= 2 * RP ? x - 2 * RP : 0) * 16;
-    if (may_grow && x < 2 * RP) src = (x < RP ? knew_g : vnew_g - ROW_BYTES) + x * 16;
-    ap[rd] = ld16(src);
+    for (int rd = 0; rd < Q_ROUNDS; ++rd) q_piece[rd] = ld16(q_g + (uint32_t)min(tid + rd * NW * 64, RP * g - 1) * 16);
   }
-  const int it0 = sp * NW + wave;
-  Slice<T, D, KT> s;
   __builtin_amdgcn_sched_barrier(0);           // loads come back in order: these before the slice's
   asm volatile("" : "+s"(rec.x), "+s"(rec.y), "+s"(rec.w));   // one load, not one for each of them
+  asm volatile("" :: "s"(a.K), "s"(a.V), "s"(a.by_iters.mul), "s"(a.by_iters.shift), "s"(cap), "s"(a.split_iters));   // no argument is fetched behind it
   const SeqState seq = state_record(rec);
-  if (dm.step_base) a.step += base;
+  const int step = a.step + (a.has_base ? base : 0);
 
   // The length comes from the state record and the step number; nothing is written back, so
   // the workgroups of a (layer, sequence) need no ordering among themselves.
-  const int len0 = length_before_step(seq, a.step, cap);
-  const bool has_new = may_grow && (len0 < cap);
+  const int len0 = length_before_step(seq, step, cap);
+  const bool has_new = may_grow && len0 < cap;
   const int n_tot = len0 + (has_new ? 1 : 0);
-  const int n_iter = (n_tot + KEYS - 1) / KEYS;
-  // Splits this unit is really cut into: as many as its own length fills with `split_iters` slices
+  const int n_iter = (int)((uint32_t)(n_tot + KEYS - 1) / KEYS);
+  // Pieces this unit is really cut into: as many as its own length fills with `split_iters` slices
   // each (an explicit split count sets split_iters = 0: always all of them).
   int ns = splits;
   if (splits > 1 && a.split_iters > 0) {
-    ns = max(1, min(splits, (n_iter + a.split_iters - 1) / a.split_iters));
+    ns = max(1, min(splits, quotient(n_iter + a.split_iters - 1, a.by_iters)));
     if (sp >= ns) return;
   }
-  const float scale_log2 = dm.scale_l2_hi, scale_log2_lo = dm.scale_l2_lo;
 
+  // This wavefront's slices it0, it0 + stride, ...; the unit's last one may hold the new row and rows past the end.
+  const int it0 = sp * NW + wave, stride = ns * NW;
+  const int new_row = has_new ? len0 : -1;
+  const Rows<T, D> at(a.K + (size_t)unit * cap * ROW_BYTES, a.V + (size_t)unit * cap * ROW_BYTES, seq.n_tiled, lane);
+  auto request = [&](Slice<T, D, KT>& s, int it) {
+    if (it == n_iter - 1) issue_last_slice<T, D, KT>(s, at, it, lane, new_row, knew_g, vnew_g);
+    else issue_slice<T, D, KT>(s, at, it);
+  };
   Running<G::NC> st;
-  st.m_run = GKV_NO_MAX;
-  st.l_run = 0.f;
+  const float scale_log2 = a.scale_hi, scale_log2_lo = a.scale_lo;
+  auto process = [&](Slice<T, D, KT>& s, int it, bool edge) {
+    process_slice<T, D, KT, false>(s, st, qB, it, it == it0, edge, scale_log2, scale_log2_lo, r, kb, n_tot);
+  };
+  auto reset = [&]() {
+    st.m_run = GKV_NO_MAX;
+    st.l_run = 0.f;
 #pragma unroll
-  for (int m = 0; m < G::NC; ++m) st.oacc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // First slice in flight, then stage k_new / v_new in LDS for whoever owns the last slice.  Every wavefront asks for
-  // one, those beyond the unit's end for its last (or, in an empty unit, for rows that are there, and not used): after a
-  // request under a condition the compiler cannot know how many loads are younger than the rows to stage, waits for
-  // all of them, and the barrier holds every wavefront until the first slices of all have arrived.  us per launch in a
-  // graph, with the condition -> without: 128 units x 577 rows 11.3 -> 10.65, 256 x 1056 23.5 -> 22.6, 4 x 577 7.3 -> 6.8; d = 64 128 x
-  // 528 7.9 -> 7.2, 512 14.8 -> 14.55; fp32 32 x 528 11.4 -> 10.0, ragged 84 to 464 12.7 -> 11.7; 896 x 576 48.8 both ways.
-  // (The first slice, or the first two, requested ahead of the record on a guess of K's format cost more than that wait:
-  // 4 x 577 7.2, 32 x 577 8.4 against 7.9, ragged 84 to 464 9.9 / 8.4, 128 x 2112 25.3 / 24.8.)
-  const int stride = ns * NW;
-  issue_slice<T, D, KT>(s, Kh, Vh, min(it0, max(n_iter - 1, 0)), seq.n_tiled, lane, r, kb);
-  // stage: 16-byte pieces [0,RP) k_new, [RP,2RP) v_new, [2RP, 2RP+RP*g) q rows; kept in LDS, not
-  // in registers, until they are stored at the end
+    for (int m = 0; m < G::NC; ++m) st.oacc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  };
+  // the rows to store wait in LDS, each piece for the thread that brought it, or in registers where there are enough
+  constexpr bool STAGED = OCC > 2 || (!G::F32 && D == 128);
   char* stage = (char*)(smem + NW * g * OSTR + NW * 16 + NW * 16);
-  const char* knew = stage;
-  const char* vnew = stage + ROW_BYTES;
+  auto keep_rows = [&]() {
+    if (!STAGED) return;
+    if (tid < 2 * RP) *(u32x4*)(stage + tid * 16) = kv_piece;
 #pragma unroll
-  for (int rd = 0; rd < AP_ROUNDS; ++rd) {
-    const int x = tid + rd * NW * 64;
-    if (x < 2 * RP + RP * g) *(u32x4*)(stage + x * 16) = ap[rd];
-  }
-  __syncthreads();
-  // this wavefront's slices, the first one already requested
-  auto slices = [&](auto exact) {
-    constexpr bool EXACT = decltype(exact)::value;
-    int it = it0;
-    while (it < n_iter) {
-      if ((it + 1) * KEYS > len0) process_slice<T, D, KT, true, EXACT>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
-      else process_slice<T, D, KT, false, EXACT>(s, st, qB, it, scale_log2, scale_log2_lo, r, kb, has_new, len0, n_tot, knew, vnew);
-      it += stride;
-      if (it < n_iter) issue_slice<T, D, KT>(s, Kh, Vh, it, seq.n_tiled, lane, r, kb);
+    for (int rd = 0; rd < Q_ROUNDS; ++rd) {
+      const int x = tid + rd * NW * 64;
+      if (x < RP * g) *(u32x4*)(stage + 2 * RP * 16 + x * 16) = q_piece[rd];
     }
   };
-  slices(std::false_type{});
+
+  // The first slice, in wavefronts beyond the unit's end its last one (in an empty unit rows that are there), not used.
+  Slice<T, D, KT> s0;
+  request(s0, min(it0, max(n_iter - 1, 0)));
+  reset();
+  keep_rows();
   if (it0 < n_iter) {
+    int it = it0;
+    if constexpr (DEPTH == 1) {
+      for (;;) {
+        process(s0, it, it == n_iter - 1);
+        if ((it += stride) >= n_iter) break;
+        request(s0, it);
+      }
+    } else {
+      // two slices in turn, the next one always on its way
+      Slice<T, D, KT> s1;
+      if (it + stride >= n_iter) process(s0, it, it == n_iter - 1);
+      else {
+        request(s1, it + stride);
+        for (;;) {
+          process(s0, it, false);
+          if ((it += stride) + stride >= n_iter) { process(s1, it, it == n_iter - 1); break; }
+          request(s0, it + stride);
+          process(s1, it, false);
+          if ((it += stride) + stride >= n_iter) { process(s0, it, it == n_iter - 1); break; }
+          request(s1, it + stride);
+        }
+      }
+    }
     // Seldom: a maximum that the short form of the weights is not right for, or a NaN that may be its
     // doing (a logit of -inf; at bf16, D = 64 an infinite value that met a part of P that is zero or
     // negative).  The slices are gone through again.
@@ -434,124 +502,142 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(GkvDims dm, A
         for (int e = 0; e < 4; ++e) again |= st.oacc[m][e] != st.oacc[m][e];
     }
     if (__any(again)) {
-      st.m_run = GKV_NO_MAX;
-      st.l_run = 0.f;
-#pragma unroll
-      for (int m = 0; m < G::NC; ++m) st.oacc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
-      issue_slice<T, D, KT>(s, Kh, Vh, it0, seq.n_tiled, lane, r, kb);
-      slices(std::true_type{});
+      reset();
+      for (int it = it0; it < n_iter; it += stride) {
+        request(s0, it);
+        process_slice<T, D, KT, true>(s0, st, qB, it, false, true, scale_log2, scale_log2_lo, r, kb, n_tot);
+      }
     }
   }
-  const float m_run = st.m_run, l_run = st.l_run;
-  f32x4 (&oacc)[G::NC] = st.oacc;
+
+  asm volatile("s_nop 7\n\ts_nop 7");      // (the last products' results are read behind branches)
 
   // ---- merge the wavefronts of this workgroup -------------------------------------------------
   float* so = smem;                         // [NW][g][OSTR]
-  float* sm = so + NW * g * OSTR;           // [NW][16]
-  float* sl = sm + NW * 16;                 // [NW][16]
-  float l_tot = l_run;                      // the 4 lanes of a head hold partial sums
-  l_tot += __shfl_xor(l_tot, 16);
-  l_tot += __shfl_xor(l_tot, 32);
+  float* sm = so + NW * g * OSTR;           // [16][NW]
+  float* sl = sm + NW * 16;                 // [16][NW]
+  const float l_tot = over_head(st.l_run, false);      // the 4 lanes of a head hold partial sums
   if (r < g) {
+    float* row = so + (wave * g + r) * OSTR;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       // accumulators m = 4q .. 4q+3 are four neighbouring channels
 #pragma unroll
       for (int q4 = 0; q4 < G::NC / 4; ++q4) {
         const int ch = (G::F32 && D == 128) ? 64 * q4 + 4 * (4 * kb + e) : G::NC * (4 * kb + e) + 4 * q4;
-        *(f32x4*)(so + (wave * g + r) * OSTR + ch) =
-            f32x4{oacc[4 * q4][e], oacc[4 * q4 + 1][e], oacc[4 * q4 + 2][e], oacc[4 * q4 + 3][e]};
+        *(f32x4*)(row + ch) = f32x4{st.oacc[4 * q4][e], st.oacc[4 * q4 + 1][e], st.oacc[4 * q4 + 2][e], st.oacc[4 * q4 + 3][e]};
       }
     }
-    if (kb == 0) { sm[wave * 16 + r] = m_run; sl[wave * 16 + r] = l_tot; }
+    if (kb == 0) { sm[r * NW + wave] = st.m_run; sl[r * NW + wave] = l_tot; }
   }
   __syncthreads();
 
   // one thread per (head, 4 channels): a single round for g <= 8 with 256 threads
-  T* out = (T*)a.out + ((size_t)lb * dm.Hq + j * g) * D;
-  float* part = a.ws.partials + (size_t)(unit * splits + sp) * g * PSTR;
-  float2* stats = a.ws.stats + ((size_t)(a.step % dm.w) * dm.L * dm.B + lb) * dm.Hq + j * g;
-  for (int x = tid; x < g * (D / 4); x += NW * 64) {
-    const int h = x / (D / 4), c4 = (x % (D / 4)) * 4;
-    float mw[NW];
+  constexpr int TPH = D / 4;                // threads per head
+  T* out = (T*)a.out + head0 * D;
+  float* part = a.partials + (size_t)(unit * splits) * g * PSTR;      // [ns][g][PSTR]
+  const int slot = step - quotient(step, a.by_w) * a.w;
+  float2* stats = a.stats + (size_t)slot * a.LB * a.Hq + head0;
+  for (int x = tid; x < g * TPH; x += NW * 64) {
+    const int h = x / TPH, c4 = (x % TPH) * 4;
+    float mw[NW], lw[NW];
+#pragma unroll
+    for (int i = 0; i < NW / 4; ++i) {
+      const f32x4 m4 = *(const f32x4*)(sm + h * NW + 4 * i), l4 = *(const f32x4*)(sl + h * NW + 4 * i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { mw[4 * i + e] = m4[e]; lw[4 * i + e] = l4[e]; }
+    }
     float M = GKV_NO_MAX;
 #pragma unroll
-    for (int wv = 0; wv < NW; ++wv) { mw[wv] = sm[wv * 16 + h]; M = fmaxf(M, mw[wv]); }
+    for (int wv = 0; wv < NW; ++wv) M = fmaxf(M, mw[wv]);
     float Lsum = 0.f;
     f32x4 o = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int wv = 0; wv < NW; ++wv) {
       const float f = __builtin_amdgcn_exp2f(mw[wv] - M);
-      Lsum += sl[wv * 16 + h] * f;
+      Lsum += lw[wv] * f;
       o += *(const f32x4*)(so + (wv * g + h) * OSTR + c4) * f;
     }
     if (ns == 1) {
-      store_row4(out + h * D + c4, o * inv_sum(Lsum, n_tot > 0, !G::F32 && D == 128));
+      store_row4(out + (uint32_t)(x * 4), o * inv_sum(Lsum, n_tot > 0, !G::F32 && D == 128));
       // softmax statistics of this head's row (running max in log2 units, sum), into the ring slot
       // that also receives q: the window score of the next compression reuses them
       if (c4 == 0 && a.write_stats) stats[h] = make_float2(M, Lsum);
     } else {
-      float* ph = part + h * PSTR;
+      float* ph = part + (uint32_t)((sp * g + h) * PSTR);
       store_agent(ph + c4, o[0], o[1]);
       store_agent(ph + c4 + 2, o[2], o[3]);
       if (c4 == 0) store_agent(ph + D, M, Lsum);
     }
   }
 
+  // ---- pieces: whoever finishes last merges them ------------------------------------------------
+  // A wavefront's outputs are whole heads and need the same heads of the other pieces only, so each
+  // wavefront has a ticket of its own and no barrier.  The partials go through memory with agent-scope
+  // accesses (they pass the XCDs' separate L2s by), each wavefront waits for its own stores, and its
+  // ticket follows: no fence, which would write back the whole L2 of the XCD (4 units of 577 rows in 3
+  // pieces: 13.4 us with __threadfence, against 8.9 uncut).
+  const bool merges = ns > 1 && wave * 64 < g * TPH;       // uniform
+  uint32_t arrived = 0;
+  if (merges) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    // (counts to ns - 1 and starts over)
+    if (lane == 0) arrived = __builtin_amdgcn_atomic_inc32((uint32_t*)a.ticket + (size_t)unit * GKV_TICKETS + wave, (uint32_t)ns - 1u, __ATOMIC_RELAXED, "agent");
+  }
+
   // ---- append the new row (row-major, one contiguous row each for K and V), push q into the
   //      window ring (contiguous per KV group).  Rows the other workgroups may still be reading
   //      are never the new row's source: they take k_new / v_new from the inputs. ---------------
-  if (appender) {
-    const int slot = a.step % dm.w;
+  if (sp == 0) {
+    if (has_new) {
+      const size_t row = ((size_t)unit * cap + len0) * ROW_BYTES;
+      if (tid < 2 * RP) *(u32x4*)((tid < RP ? a.K + row : a.V + row - ROW_BYTES) + tid * 16) = STAGED ? *(const u32x4*)(stage + tid * 16) : kv_piece;
+      if (tid == NW * 64 - 1) a.pos[(size_t)unit * cap + len0] = step;
+    }
+    if (a.copy_q) {                          // (q may already live in its ring slot)
+      char* ring = a.qwin + ((size_t)slot * a.LB * a.Hq + head0) * ROW_BYTES;
 #pragma unroll
-    for (int rd = 0; rd < AP_ROUNDS; ++rd) {
-      const int x = tid + rd * NW * 64;
-      if (x >= 2 * RP + RP * g) continue;
-      const u32x4 piece = *(const u32x4*)(stage + x * 16);
-      if (x < RP) {
-        if (has_new) *(u32x4*)((char*)a.K + ((size_t)unit * cap + len0) * ROW_BYTES + x * 16) = piece;
-      } else if (x < 2 * RP) {
-        if (has_new) *(u32x4*)((char*)a.V + ((size_t)unit * cap + len0) * ROW_BYTES + (x - RP) * 16) = piece;
-      } else if (ring_copy) {
-        *(u32x4*)((char*)a.qwin + ((((size_t)slot * dm.L * dm.B + lb) * dm.Hq + j * g) * ROW_BYTES) + (x - 2 * RP) * 16) = piece;
+      for (int rd = 0; rd < Q_ROUNDS; ++rd) {
+        const int x = tid + rd * NW * 64;
+        if (x < RP * g) *(u32x4*)(ring + (uint32_t)(x * 16)) = STAGED ? *(const u32x4*)(stage + 2 * RP * 16 + x * 16) : q_piece[rd];
       }
     }
-    if (has_new && tid == NW * 64 - 1) a.pos[(size_t)unit * cap + len0] = a.step;
   }
 
-  // ---- merge the splits of this unit: last workgroup to finish does it ------------------------
-  // The partials go through memory with agent-scope accesses (they pass the XCDs' separate L2s
-  // by), each thread waits for its own stores, and the ticket follows the barrier: no fence, which
-  // would write back the whole L2 of the XCD (4 units of 577 rows in 3 splits: 13.4 us with
-  // __threadfence, against 8.9 unsplit).
-  if (ns > 1) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (tid == 0) {
-      const int old = __hip_atomic_fetch_add(&a.ws.split_ticket[unit], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      s_last = old == ns - 1;
-      if (old == ns - 1) __hip_atomic_store(&a.ws.split_ticket[unit], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (s_last) {
-      const float* pu = a.ws.partials + (size_t)unit * splits * g * PSTR;
-      for (int x = tid; x < g * (D / 4); x += NW * 64) {
-        const int h = x / (D / 4), c4 = (x % (D / 4)) * 4;
-        float M = GKV_NO_MAX, Lsum = 0.f;
-        f32x4 o = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-        for (int s2 = 0; s2 < ns; ++s2) {
-          const float* ph = pu + (s2 * g + h) * PSTR;
-          const float2 ml = load_agent(ph + D), a0 = load_agent(ph + c4), a1 = load_agent(ph + c4 + 2);
-          const float Mn = fmaxf(M, ml.x);
-          const float f0 = __builtin_amdgcn_exp2f(M - Mn), f = __builtin_amdgcn_exp2f(ml.x - Mn);
-          M = Mn;
-          Lsum = Lsum * f0 + ml.y * f;
-          o = o * f0 + f32x4{a0.x, a0.y, a1.x, a1.y} * f;
-        }
-        store_row4(out + h * D + c4, o * inv_sum(Lsum, n_tot > 0, false));
-        if (c4 == 0 && a.write_stats) stats[h] = make_float2(M, Lsum);
+  if (merges && (int)__builtin_amdgcn_readfirstlane(arrived) == ns - 1) {
+    asm volatile("" ::: "memory");
+    for (int x = tid; x < g * TPH; x += NW * 64) {
+      const int h = x / TPH, c4 = (x % TPH) * 4;
+      float M = GKV_NO_MAX, Lsum = 0.f;
+      f32x4 o = {0.f, 0.f, 0.f, 0.f};
+      constexpr int AT_ONCE = 8;
+      for (int s0 = 0; s0 < ns; s0 += AT_ONCE) {
+        float2 got[AT_ONCE][3];
+        const float* ph = part + (uint32_t)((s0 * g + h) * PSTR);
+#pragma unroll
+        for (int i = 0; i < AT_ONCE; ++i)
+          if (s0 + i < ns) {                               // uniform, here and below
+            got[i][0] = load_agent(ph + D); got[i][1] = load_agent(ph + c4); got[i][2] = load_agent(ph + c4 + 2);
+            ph += (uint32_t)(g * PSTR);
+          }
+        float Mn = M;
+#pragma unroll
+        for (int i = 0; i < AT_ONCE; ++i)
+          if (s0 + i < ns) Mn = fmaxf(Mn, got[i][0].x);
+        const float f0 = __builtin_amdgcn_exp2f(M - Mn);
+        M = Mn;
+        Lsum *= f0;
+        o *= f0;
+#pragma unroll
+        for (int i = 0; i < AT_ONCE; ++i)
+          if (s0 + i < ns) {
+            const float f = __builtin_amdgcn_exp2f(got[i][0].x - Mn);
+            Lsum += got[i][0].y * f;
+            o += f32x4{got[i][1].x, got[i][1].y, got[i][2].x, got[i][2].y} * f;
+          }
       }
+      store_row4(out + (uint32_t)(x * 4), o * inv_sum(Lsum, n_tot > 0, false));
+      if (c4 == 0 && a.write_stats) stats[h] = make_float2(M, Lsum);
     }
   }
 }
@@ -562,31 +648,48 @@ size_t gkv_attend_mfma_lds(int esz, int d, int g, int waves) {
   return sizeof(float) * ((size_t)waves * g * (d + 4) + 2 * 16 * (size_t)waves) + (size_t)(2 + g) * d * esz;
 }
 
-template <typename T, int D, int NW, int KT, int OCC>
-static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, AttendArgs a) {
+template <typename T, int D, int NW, int KT, int OCC, int DEPTH>
+static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a) {
   const int units = dm.L * dm.B * dm.Hkv;
-  a.by_splits = gkv_divisor(a.splits);
+  KernelArgs k;
+  k.d_state = a.d_state; k.step_base = dm.step_base ? dm.step_base : a.d_state;
+  k.q = (const char*)a.q; k.k_new = (const char*)a.k_new; k.v_new = (const char*)a.v_new;
+  k.K = (char*)a.K; k.V = (char*)a.V; k.pos = a.pos; k.qwin = (char*)a.qwin; k.out = (char*)a.out;
+  k.stats = a.ws.stats; k.partials = a.ws.partials; k.ticket = a.ws.split_ticket;
+  k.by_splits = gkv_divisor(a.splits); k.by_hkv = dm.by_hkv; k.by_w = gkv_divisor(dm.w);
+  k.by_iters = gkv_divisor(a.split_iters > 0 ? a.split_iters : 1);
+  k.splits = a.splits; k.split_iters = a.split_iters;
+  k.Hq = dm.Hq; k.Hkv = dm.Hkv; k.g = dm.g; k.cap = dm.cap; k.LB = dm.L * dm.B; k.w = dm.w; k.step = a.step;
+  k.has_base = dm.step_base != nullptr; k.copy_q = a.copy_q; k.write_stats = a.write_stats;
+  k.scale_hi = dm.scale_l2_hi; k.scale_lo = dm.scale_l2_lo;
   const size_t shmem = gkv_attend_mfma_lds(sizeof(T), D, dm.g, NW);
-  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC>, dim3(units * a.splits), dim3(NW * 64), shmem, dm, a);
+  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, DEPTH>, dim3(units * a.splits), dim3(NW * 64), shmem, k);
+}
+
+template <typename T, int D, int NW, int KT, int OCC>
+static hipError_t launch_depth(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a) {
+  const bool few = (int64_t)dm.L * dm.B * dm.Hkv * a.splits <= 256;
+  if (few) return launch_attend<T, D, NW, KT, 2, sizeof(T) * D == 512 ? 1 : 2>(ln, dm, a);
+  return launch_attend<T, D, NW, KT, OCC, 1>(ln, dm, a);
 }
 
 hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a) {
   if (dtype == GKV_F32) {
     if (dm.d == 64) {
-      if (a.waves == 16) return launch_attend<float, 64, 16, 1, 4>(ln, dm, a);
-      if (a.waves == 8) return launch_attend<float, 64, 8, 1, 4>(ln, dm, a);
-      return launch_attend<float, 64, 4, 1, 4>(ln, dm, a);
+      if (a.waves == 16) return launch_attend<float, 64, 16, 1, 4, 1>(ln, dm, a);
+      if (a.waves == 8) return launch_depth<float, 64, 8, 1, 4>(ln, dm, a);
+      return launch_depth<float, 64, 4, 1, 4>(ln, dm, a);
     }
-    if (a.waves >= 8) return launch_attend<float, 128, 8, 1, 2>(ln, dm, a);
-    return launch_attend<float, 128, 4, 1, 2>(ln, dm, a);
+    if (a.waves >= 8) return launch_attend<float, 128, 8, 1, 2, 1>(ln, dm, a);
+    return launch_depth<float, 128, 4, 1, 2>(ln, dm, a);
   }
   if (dm.d == 64) {
-    if (a.waves == 16) return launch_attend<uint16_t, 64, 16, 2, 4>(ln, dm, a);
-    if (a.waves == 8) return launch_attend<uint16_t, 64, 8, 2, 4>(ln, dm, a);
-    return launch_attend<uint16_t, 64, 4, 2, 4>(ln, dm, a);
+    if (a.waves == 16) return launch_attend<uint16_t, 64, 16, 2, 4, 1>(ln, dm, a);
+    if (a.waves == 8) return launch_depth<uint16_t, 64, 8, 2, 4>(ln, dm, a);
+    return launch_depth<uint16_t, 64, 4, 2, 4>(ln, dm, a);
   }
-  if (a.waves == 16) return launch_attend<uint16_t, 128, 16, 1, 2>(ln, dm, a);
-  if (a.waves == 8) return launch_attend<uint16_t, 128, 8, 1, 4>(ln, dm, a);
-  if (a.tile_keys == 32) return launch_attend<uint16_t, 128, 4, 2, 2>(ln, dm, a);
-  return launch_attend<uint16_t, 128, 4, 1, 4>(ln, dm, a);
+  if (a.waves == 16) return launch_attend<uint16_t, 128, 16, 1, 2, 1>(ln, dm, a);
+  if (a.waves == 8) return launch_depth<uint16_t, 128, 8, 1, 4>(ln, dm, a);
+  if (a.tile_keys == 32) return launch_attend<uint16_t, 128, 4, 2, 2, 1>(ln, dm, a);
+  return launch_depth<uint16_t, 128, 4, 1, 4>(ln, dm, a);
 }

@@ -200,18 +200,24 @@ static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
   const int64_t units = (int64_t)d.L * d.B * d.Hkv;
   const int row_bytes = d.d * ctx->esz;
   const bool wide = row_bytes > 256;                                  // 16 KiB slices
-  const int slices = (int)((int64_t)d.cap * 2 * row_bytes / 8192);    // in units of 8 KiB, at full capacity
+  const int keys = row_bytes == 128 ? 32 : 16;                        // per slice
+  const int typical = (d.b + d.s / 2 + keys - 1) / keys, full = d.cap / keys;   // slices of a unit
   AttendPlan p{4, 1, 0};
   if (asked > 0) {
     p.splits = explicit_splits(ctx);
-  } else {
-    int s = (int)(256 / units);
-    s = s > 16 ? 16 : s;
-    const int pieces = wide ? (slices + 7) / 8 : slices / 8;   // wide: no piece longer than the others (4 units x 528 rows, 8 pieces -> 9: 8.25 -> 7.7)
-    s = s > pieces ? pieces : s;
-    if (s >= 4 || (s >= 2 && slices >= 64)) { p.splits = s; p.iters = wide ? 4 : 8; }
+  } else if (units <= 128) {
+    const int most = (int)(256 / units) < 16 ? (int)(256 / units) : 16;
+    const int aim = typical > 24 * 7 ? (typical + 23) / 24 : 7, n = aim < most ? aim : most;
+    const int enough = n == 2 ? (wide ? 12 : ctx->cfg.dtype == GKV_F32 ? 24 : 32) : wide ? 9 : keys == 32 ? 10 : 18;
+    if (full >= enough) {
+      // units of ordinary length whole where that is the better: only prompts are cut
+      p.iters = typical >= enough ? 4 * ((typical + 4 * n - 1) / (4 * n)) : typical > 8 ? (typical + 3) / 4 * 4 : 8;
+      p.splits = (full + p.iters - 1) / p.iters < most ? (full + p.iters - 1) / p.iters : most;
+    }
+    if (p.splits < 2) p = AttendPlan{4, 1, 0};
   }
-  const bool more = p.splits > 1 ? slices / p.splits >= 48 : (units <= 256 && slices >= 12) || (units > 512 && slices >= 64);
+  const int slices = (int)((int64_t)d.cap * 2 * row_bytes / 8192);    // in units of 8 KiB, at full capacity
+  const bool more = p.splits == 1 && ((units <= 256 && slices >= (keys == 32 ? 12 : 16)) || (units > 512 && slices >= 64));
   const bool long_slices = ctx->attend_tile == 32 && ctx->cfg.dtype == GKV_BF16 && d.d == 128;   // 4 wavefronts only
   if (more && !wide && fits(8) && !long_slices) p.waves = 8;
   if (ctx->attend_waves > 0) p.waves = fits(ctx->attend_waves) ? ctx->attend_waves : 4;
@@ -235,14 +241,14 @@ static int auto_sets(const gkv_ctx* ctx) {
 }
 static size_t ws_ticket_bytes(const gkv_ctx* ctx) {
   const size_t units = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
-  return gkv_align256(units * (auto_sets(ctx) + 1) * 4);
+  return gkv_align256(units * (auto_sets(ctx) + 1) * GKV_TICKETS * 4);
 }
 
 GkvWorkspace gkv_carve_workspace(const gkv_ctx* ctx, void* base, int split_set) {
   GkvWorkspace w;
   char* p = (char*)base;
   const size_t units = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hkv;
-  w.split_ticket = (int32_t*)p + split_set * units; p += ws_ticket_bytes(ctx);
+  w.split_ticket = (int32_t*)p + split_set * units * GKV_TICKETS; p += ws_ticket_bytes(ctx);
   w.state_ticket = (int32_t*)p; p += gkv_align256((size_t)ctx->dims.L * ctx->dims.B * 4);
   w.stats = (float2*)p; p += gkv_align256(ws_stats_bytes(ctx));
   w.partials = (float*)(p + split_set * ws_partials_bytes(ctx, ctx->ws_auto_splits));
@@ -418,7 +424,7 @@ extern "C" gkv_status gkv_attend_decode(gkv_ctx* ctx, const void* q, const void*
   gkv_status st = check_len(ctx, len_max_host, k_new != nullptr);
   if (st != GKV_OK) return st;
   AttendArgs a{q, k_new, v_new, K, V, pos, step, qwin, d_state, out, gkv_carve_workspace(ctx, workspace), 1,
-               ctx->attend_tile, 1, 0, 4, 0, {}};
+               ctx->attend_tile, 1, 0, 4, 0};
   {
     const size_t slot_bytes = (size_t)ctx->dims.L * ctx->dims.B * ctx->dims.Hq * ctx->dims.d * ctx->esz;
     a.copy_q = (const char*)q != (const char*)qwin + (size_t)(step % ctx->dims.w) * slot_bytes;

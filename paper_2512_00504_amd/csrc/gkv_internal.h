@@ -40,6 +40,7 @@ struct GkvProfile;   // event pools, defined in gkv_api.hip
 // calls on different ones may overlap.  A recorded call runs later than what is enqueued on its stream
 // now, so each capture counts as a stream of its own.
 constexpr int GKV_SPLIT_SETS = 8;
+constexpr int GKV_TICKETS = 8;   // tickets per unit and set: one for each wavefront that has outputs (g * d / 256, at most 8)
 struct GkvStreamKey { const void* stream; unsigned long long capture; };
 
 struct gkv_ctx {
@@ -72,7 +73,7 @@ struct gkv_ctx {
 };
 
 // Workspace layout (bytes from the base):
-//   [0, 4*units*sets)               split tickets (int32, self-resetting); sets = GKV_SPLIT_SETS and one for
+//   [0, 4*GKV_TICKETS*units*sets)   split tickets (int32, self-resetting); sets = GKV_SPLIT_SETS and one for
 //                                   "attend_splits", or the latter alone where the library never cuts
 //   [.., + 4*L*B)                   compaction tickets
 //   [.., + 8*w*L*B*h_q)             softmax statistics ring: per (slot, layer, sequence, query head)
@@ -109,7 +110,6 @@ struct AttendArgs {
   int32_t write_stats;   // record (max, sum) of every query head's softmax in ws.stats
   int32_t waves;         // wavefronts per workgroup of the matrix-core kernel: 4, 8 or 16
   int32_t split_iters;   // slices per piece (a unit of n slices is cut into ceil(n / split_iters)); 0 = all splits
-  GkvDivisor by_splits;   // set by the launch wrapper
 };
 hipError_t gkv_launch_attend_generic(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
 hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a);
