@@ -119,8 +119,8 @@ const char* gkv_status_string(gkv_status st);
  * prepared by gkv_workspace_init of the same context, are not cut (slower, and summed in another
  * order).  Calls cut by "attend_splits" and compressions that may overlap need a workspace each. */
 gkv_status gkv_workspace_bytes(gkv_ctx* ctx, size_t* out_bytes);
-/* Enqueues a fill kernel that zeroes the workspace's counters (one per unit, used when a
- * unit's attention is split over several workgroups, in every set; one per (layer, sequence), used by the
+/* Enqueues a fill kernel that zeroes the workspace's counters (eight per unit, one for each wavefront
+ * that merges when a unit's attention is split over several workgroups, in every set; one per (layer, sequence), used by the
  * compaction to find the workgroup that finishes last).  The kernels leave them at zero.
  * Call once, before the first call that takes the workspace. */
 gkv_status gkv_workspace_init(gkv_ctx* ctx, void* workspace, void* stream);

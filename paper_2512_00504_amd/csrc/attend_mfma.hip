@@ -21,17 +21,22 @@
 //        fp32: the loaded words are the A operands, MFMA 16x16x4 per (e, channel of the lane).
 //      bf16 rounds P to bf16 at D = 128; at D = 64 it enters as the sum of three bf16 numbers, which
 //      hold its 24 bits; fp32 keeps it as it is.
-// Bound: HBM at launches of a few hundred units and more, latency below.  fp32 has 8 KiB (D = 64)
-// or 16 KiB (D = 128) per slice against 1024 or 2048 cycles of MFMA, so four wavefronts can take
-// 32 B a cycle and CU, four times the CU's share of the HBM rate; bf16 needs a tenth of that.
-// Against the plain vector-ALU kernel these shapes used before, per launch: fp32 D = 128, 32 units
-// of 528 rows 466 -> 9.6 us (uncut 17.6), 896 units 1614 -> 75.5; bf16 D = 64, 128 units of 528 rows 245 -> 6.9,
-// 1152 units 575 -> 28.4; fp32 D = 64, 2 units of 72 rows 25.5 -> 4.5.
-// The wavefronts of a workgroup are merged through LDS; splits of one unit are merged by the
-// last workgroup to finish (ticket counter), in a fixed order, so results are deterministic.
+// Bound: HBM at launches of a few hundred units and more.  fp32 has 8 KiB (D = 64) or 16 KiB (D = 128) per slice
+// against 1024 or 2048 cycles of MFMA, so four wavefronts can take 32 B a cycle and CU, four times the CU's share of
+// the HBM rate; bf16 needs a tenth of that.  Below that the number of instructions: a wavefront alone on its SIMD issues one every
+// five cycles or so, and a launch of few units is a chain of about a thousand of them (by clock stamps, 4 units of 577 rows: 11 000
+// cycles from the first argument to the last store, of which trips to memory are a third).  So addresses are a scalar base,
+// a lane's constant offset and an immediate (a slice 110 instructions where 64-bit lane addresses made it 215), what goes from
+// lane to lane goes through registers, a slice that needs no rescaling or masking branches around it, results are
+// rounded to bf16 by the conversion instruction, and launches that leave registers free keep two slices in
+// flight.  us per launch in a graph, before -> now: bf16, D = 128 4 units of 577 rows 6.46 -> 5.44, 32 7.25 -> 5.9, 32 of 1100 8.9 -> 7.0,
+// 4 of 2113 8.05 -> 6.9, 32 of 91 4.3 -> 3.8; fp32, D = 128 32 of 528 9.6 -> 7.9, D = 64 64 of 528 8.1 -> 7.1, 2 of 72 4.5 -> 4.2; 896 units of 577 44.4
+// -> 43.9, 4608 of 1056 392 both.
+// The wavefronts of a workgroup are merged through LDS; pieces of one unit are merged by the
+// last workgroup to finish (tickets), in a fixed order, so results are deterministic.
 //
 // The newest token's k/v are not read from the cache (another workgroup may be writing that
-// row): the lanes that would hold row `len` take them from k_new / v_new instead.
+// row): the lanes that would hold row `len` load them from k_new / v_new instead.
 // All stores (output, the appended K/V rows, the window-ring slot) are issued at the end of
 // the workgroup and are whole contiguous rows: stores mixed into the read stream, partial-line
 // stores and atomics each cost several microseconds per launch on this memory system.
@@ -93,6 +98,8 @@ struct Slice {
   VWords<Geo<T, D>::VW> vR[4 * KT];
 };
 
+struct Nothing { __device__ void operator()() const {} };
+
 // Where a wavefront's loads go: the unit's rows (uniform) and this lane's offsets from a slice's first row, one for
 // each K format and one for V.  Everything else about an address is scalar or an immediate.
 template <typename T, int D>
@@ -114,7 +121,7 @@ struct Rows {
 // memory-side cache), both non-temporal 76%, one stream of each kind 80-85% at every cache size
 // tried (0.3 to 10 GB), whichever of the two is the non-temporal one.
 template <typename T, int D, int KT>
-__device__ __forceinline__ void issue_slice(Slice<T, D, KT>& s, const Rows<T, D>& at, int it) {
+__device__ __forceinline__ void issue_k(Slice<T, D, KT>& s, const Rows<T, D>& at, int it) {
   using G = Geo<T, D>;
 #pragma unroll
   for (int tt = 0; tt < KT; ++tt) {
@@ -130,15 +137,18 @@ __device__ __forceinline__ void issue_slice(Slice<T, D, KT>& s, const Rows<T, D>
       asm volatile("; rows");
     }
   }
+}
+template <typename T, int D, int KT>
+__device__ __forceinline__ void issue_v(Slice<T, D, KT>& s, const Rows<T, D>& at, int it) {
+  using G = Geo<T, D>;
   const char* Vt = at.Vh + (uint32_t)(it * KT * G::TILE_BYTES);
 #pragma unroll
   for (int jj = 0; jj < 4 * KT; ++jj) ld_v<T, D>(s.vR[jj], Vt + at.v + ((jj & 3) + (jj >> 2) * 16) * G::ROW_BYTES);
 }
 
-// The unit's last slice: the lanes that hold row `len0` take it from the newest token's own k and v.
+// The unit's last slice: the lanes that hold row `new_row` take it from the newest token's own k and v.
 template <typename T, int D, int KT>
-__device__ __forceinline__ void issue_last_slice(Slice<T, D, KT>& s, const Rows<T, D>& at, int it, int lane, int new_row,
-                                                 const char* knew, const char* vnew) {
+__device__ __forceinline__ void issue_last_k(Slice<T, D, KT>& s, const Rows<T, D>& at, int it, int lane, int new_row, const char* knew) {
   using G = Geo<T, D>;
   asm volatile("" : "+v"(lane));                             // its addresses are formed here, not kept in registers from the start
   const int r = lane & 15, kb = lane >> 4;
@@ -151,6 +161,12 @@ __device__ __forceinline__ void issue_last_slice(Slice<T, D, KT>& s, const Rows<
 #pragma unroll
     for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = ld16(p + c * step);
   }
+}
+template <typename T, int D, int KT>
+__device__ __forceinline__ void issue_last_v(Slice<T, D, KT>& s, const Rows<T, D>& at, int it, int lane, int new_row, const char* vnew) {
+  using G = Geo<T, D>;
+  asm volatile("" : "+v"(lane));
+  const int r = lane & 15, kb = lane >> 4;
 #pragma unroll
   for (int jj = 0; jj < 4 * KT; ++jj) {
     const int key = it * 16 * KT + 4 * kb + (jj & 3) + (jj >> 2) * 16;
@@ -182,14 +198,16 @@ __device__ __forceinline__ float over_head(float x, bool max) {
   return x;
 }
 
-// edge: the slice may contain rows past the end, which are masked.  first: the wavefront's first slice, whose accumulators are zero.
+// edge: the slice may contain rows past the end, which are masked.  first: the wavefront's first slice, whose
+// accumulators are zero.  between: what to do once the products with K are under way, whose registers are free then.
 // EXACT: right for every logit and value, infinities and finite ones of any size among them.  Without
 // it, which is what a wavefront tries first, a logit of -inf may give NaN (the scale's low part times -inf), a
 // huge maximum any weight (see log2_weight), and at bf16, D = 64 an infinite value NaN; all of them show at the end.
-template <typename T, int D, int KT, bool EXACT>
+template <typename T, int D, int KT, bool EXACT, typename Between>
 __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16>& st,
                                               const u32x4 (&qB)[Geo<T, D>::NL], int it, bool first, bool edge,
-                                              float scale_log2, float scale_log2_lo, int r, int kb, int n_tot) {
+                                              float scale_log2, float scale_log2_lo, int r, int kb, int n_tot,
+                                              Between between) {
   using G = Geo<T, D>;
   constexpr int NS = 4 * KT;
   const int key0 = it * 16 * KT;
@@ -231,6 +249,12 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
         sc[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(s.kA[tt][c]), as_bf16x8(qB[c]), sc[tt], 0, 0, 0);
       }
     }
+  }
+  if constexpr (!std::is_same_v<Between, Nothing>) {
+    __builtin_amdgcn_sched_barrier(0);
+    between();
+    asm volatile("s_nop 7\n\ts_nop 7");                    // (its requests branch, see above)
+    __builtin_amdgcn_sched_barrier(0);
   }
   float sv[NS];
 #pragma unroll
@@ -367,11 +391,17 @@ struct KernelArgs {
   float scale_hi, scale_lo;
 };
 
-// KT = 16-key tiles per wavefront iteration (1 or 2); DEPTH = slices in flight (1 or 2)
-template <typename T, int D, int NW, int KT, int OCC, int DEPTH>
+// KT = 16-key tiles per wavefront iteration (1 or 2); DEPTH = slices in flight (1 or 2: twice the registers, for launches
+// that leave them free).  STAGED: the rows to store wait in LDS instead of registers (32 units of 577 rows 6.1 us against 6.2
+// in registers, whatever the room; fp32, D = 128 9.15 / 8.8).
+template <typename T, int D, int NW, int KT, int OCC, int DEPTH, bool STAGED>
 __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a) {
   using G = Geo<T, D>;
   constexpr int KEYS = 16 * KT;             // keys per iteration
+  // One slice in flight: the next K is requested as soon as the products with this one are under way, V behind its own.
+  // fp32, D = 128 800 units of 540 rows 84.8 -> 83.0 us, 32 of 528 8.2 -> 7.9; bf16, D = 64 1600 of 540 35.4 -> 35.1.  Not for the others:
+  // 896 units of 577 rows 43.9 -> 44.4, 784 ragged to 1227 48.3 -> 49.2; fp32, D = 64 800 of 540 39.6 -> 40.1.
+  constexpr bool EARLY_K = sizeof(T) * D == 512 || (sizeof(T) == 2 && D == 64);
   constexpr int RP = G::RP, ROW_BYTES = G::ROW_BYTES, OSTR = G::OSTR, PSTR = G::PSTR;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -410,6 +440,10 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
 #pragma unroll
     for (int rd = 0; rd < Q_ROUNDS; ++rd) q_piece[rd] = ld16(q_g + (uint32_t)min(tid + rd * NW * 64, RP * g - 1) * 16);
   }
+  // what can be had without the record, while that is on its way
+  const int it0 = sp * NW + wave;              // this wavefront's slices: it0, it0 + stride, ...
+  Rows<T, D> at(a.K + (size_t)unit * cap * ROW_BYTES, a.V + (size_t)unit * cap * ROW_BYTES, 0, lane);
+  asm volatile("" : "+v"(at.k_tiled), "+v"(at.k_rows), "+v"(at.v));
   __builtin_amdgcn_sched_barrier(0);           // loads come back in order: these before the slice's
   asm volatile("" : "+s"(rec.x), "+s"(rec.y), "+s"(rec.w));   // one load, not one for each of them
   asm volatile("" :: "s"(a.K), "s"(a.V), "s"(a.by_iters.mul), "s"(a.by_iters.shift), "s"(cap), "s"(a.split_iters));   // no argument is fetched behind it
@@ -430,18 +464,23 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
     if (sp >= ns) return;
   }
 
-  // This wavefront's slices it0, it0 + stride, ...; the unit's last one may hold the new row and rows past the end.
-  const int it0 = sp * NW + wave, stride = ns * NW;
+  // The unit's last slice may hold the new row and rows past the end.
+  const int stride = ns * NW;
   const int new_row = has_new ? len0 : -1;
-  const Rows<T, D> at(a.K + (size_t)unit * cap * ROW_BYTES, a.V + (size_t)unit * cap * ROW_BYTES, seq.n_tiled, lane);
+  at.n_tiled = seq.n_tiled;
   auto request = [&](Slice<T, D, KT>& s, int it) {
-    if (it == n_iter - 1) issue_last_slice<T, D, KT>(s, at, it, lane, new_row, knew_g, vnew_g);
-    else issue_slice<T, D, KT>(s, at, it);
+    if (it == n_iter - 1) {
+      issue_last_k<T, D, KT>(s, at, it, lane, new_row, knew_g);
+      issue_last_v<T, D, KT>(s, at, it, lane, new_row, vnew_g);
+    } else {
+      issue_k<T, D, KT>(s, at, it);
+      issue_v<T, D, KT>(s, at, it);
+    }
   };
   Running<G::NC> st;
   const float scale_log2 = a.scale_hi, scale_log2_lo = a.scale_lo;
   auto process = [&](Slice<T, D, KT>& s, int it, bool edge) {
-    process_slice<T, D, KT, false>(s, st, qB, it, it == it0, edge, scale_log2, scale_log2_lo, r, kb, n_tot);
+    process_slice<T, D, KT, false>(s, st, qB, it, it == it0, edge, scale_log2, scale_log2_lo, r, kb, n_tot, Nothing{});
   };
   auto reset = [&]() {
     st.m_run = GKV_NO_MAX;
@@ -450,7 +489,6 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
     for (int m = 0; m < G::NC; ++m) st.oacc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
   };
   // the rows to store wait in LDS, each piece for the thread that brought it, or in registers where there are enough
-  constexpr bool STAGED = OCC > 2 || (!G::F32 && D == 128);
   char* stage = (char*)(smem + NW * g * OSTR + NW * 16 + NW * 16);
   auto keep_rows = [&]() {
     if (!STAGED) return;
@@ -470,10 +508,25 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
   if (it0 < n_iter) {
     int it = it0;
     if constexpr (DEPTH == 1) {
-      for (;;) {
+      if constexpr (EARLY_K) {
+        auto and_then = [&](auto next) {
+          process_slice<T, D, KT, false>(s0, st, qB, it, it == it0, false, scale_log2, scale_log2_lo, r, kb, n_tot, next);
+        };
+        for (; it + stride < n_iter - 1; it += stride) {
+          and_then([&] { issue_k<T, D, KT>(s0, at, it + stride); });
+          issue_v<T, D, KT>(s0, at, it + stride);
+        }
+        if (it + stride == n_iter - 1) {
+          and_then([&] { issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g); });
+          issue_last_v<T, D, KT>(s0, at, it += stride, lane, new_row, vnew_g);
+        }
         process(s0, it, it == n_iter - 1);
-        if ((it += stride) >= n_iter) break;
-        request(s0, it);
+      } else {
+        for (;;) {
+          process(s0, it, it == n_iter - 1);
+          if ((it += stride) >= n_iter) break;
+          request(s0, it);
+        }
       }
     } else {
       // two slices in turn, the next one always on its way
@@ -491,6 +544,10 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
         }
       }
     }
+    // (the last products' results are read behind branches)
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 7\n\ts_nop 7");
+    __builtin_amdgcn_sched_barrier(0);
     // Seldom: a maximum that the short form of the weights is not right for, or a NaN that may be its
     // doing (a logit of -inf; at bf16, D = 64 an infinite value that met a part of P that is zero or
     // negative).  The slices are gone through again.
@@ -505,12 +562,13 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
       reset();
       for (int it = it0; it < n_iter; it += stride) {
         request(s0, it);
-        process_slice<T, D, KT, true>(s0, st, qB, it, false, true, scale_log2, scale_log2_lo, r, kb, n_tot);
+        process_slice<T, D, KT, true>(s0, st, qB, it, false, true, scale_log2, scale_log2_lo, r, kb, n_tot, Nothing{});
       }
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_nop 7\n\ts_nop 7");
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
-
-  asm volatile("s_nop 7\n\ts_nop 7");      // (the last products' results are read behind branches)
 
   // ---- merge the wavefronts of this workgroup -------------------------------------------------
   float* so = smem;                         // [NW][g][OSTR]
@@ -576,12 +634,14 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
   // wavefront has a ticket of its own and no barrier.  The partials go through memory with agent-scope
   // accesses (they pass the XCDs' separate L2s by), each wavefront waits for its own stores, and its
   // ticket follows: no fence, which would write back the whole L2 of the XCD (4 units of 577 rows in 3
-  // pieces: 13.4 us with __threadfence, against 8.9 uncut).
+  // pieces: 13.4 us with __threadfence, against 8.9 uncut).  (Results that say by a mark of their own whether they are there,
+  // asked for together with the ticket: 6.6 us where this takes 5.5; the marks must be put back, stores that
+  // the end of the launch waits for.)
   const bool merges = ns > 1 && wave * 64 < g * TPH;       // uniform
   uint32_t arrived = 0;
   if (merges) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    // (counts to ns - 1 and starts over)
+    // (counts to ns - 1 and starts over; an addition would be made into one over the active lanes and waited for at once)
     if (lane == 0) arrived = __builtin_amdgcn_atomic_inc32((uint32_t*)a.ticket + (size_t)unit * GKV_TICKETS + wave, (uint32_t)ns - 1u, __ATOMIC_RELAXED, "agent");
   }
 
@@ -648,7 +708,7 @@ size_t gkv_attend_mfma_lds(int esz, int d, int g, int waves) {
   return sizeof(float) * ((size_t)waves * g * (d + 4) + 2 * 16 * (size_t)waves) + (size_t)(2 + g) * d * esz;
 }
 
-template <typename T, int D, int NW, int KT, int OCC, int DEPTH>
+template <typename T, int D, int NW, int KT, int OCC, int DEPTH, bool STAGED = true>
 static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a) {
   const int units = dm.L * dm.B * dm.Hkv;
   KernelArgs k;
@@ -663,13 +723,14 @@ static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, const At
   k.has_base = dm.step_base != nullptr; k.copy_q = a.copy_q; k.write_stats = a.write_stats;
   k.scale_hi = dm.scale_l2_hi; k.scale_lo = dm.scale_l2_lo;
   const size_t shmem = gkv_attend_mfma_lds(sizeof(T), D, dm.g, NW);
-  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, DEPTH>, dim3(units * a.splits), dim3(NW * 64), shmem, k);
+  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, DEPTH, STAGED>, dim3(units * a.splits), dim3(NW * 64), shmem, k);
 }
 
 template <typename T, int D, int NW, int KT, int OCC>
 static hipError_t launch_depth(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a) {
+  // a workgroup per CU at most: registers for two slices in flight (fp32, D = 128 has none to spare)
   const bool few = (int64_t)dm.L * dm.B * dm.Hkv * a.splits <= 256;
-  if (few) return launch_attend<T, D, NW, KT, 2, sizeof(T) * D == 512 ? 1 : 2>(ln, dm, a);
+  if (few) return launch_attend<T, D, NW, KT, 2, sizeof(T) * D == 512 ? 1 : 2, sizeof(T) == 2 && D == 128>(ln, dm, a);
   return launch_attend<T, D, NW, KT, OCC, 1>(ln, dm, a);
 }
 

@@ -175,23 +175,23 @@ static int explicit_splits(const gkv_ctx* ctx) {
 // ceil(n / iters) of them, so the last may be shorter).  Depends on the configuration alone, so the same
 // call gives the same bits whatever bound of the length the caller passes.
 //
-// A workgroup of 8 wavefronts alone on a CU pulls 70 GB/s (4 units of 3900 rows uncut: 8 MB in 28.6 us; one 8 KiB
-// slice per wavefront and trip to memory), so a few dozen units leave most of the HBM rate unused, and at 128 units half of
-// the CUs idle.  Cut into pieces of 8 slices, up to 256 of them (bf16, d = 128, us per launch in a graph, uncut with 8
-// wavefronts / with 16 -> cut, by 4 wavefronts a piece but for 128 x 2113 and x 3900):
-//   4 units x 577 rows 7.3 / 7.5 -> 6.5, x 2113 14.7 / 14.2 -> 8.1, x 3900 28.6 / 29.3 -> 8.6; 32 x 577 7.5 / 7.8 -> 7.3, x 1100
-//   12.5 / 13.1 -> 9.1; 64 x 577 9.0 / 9.6 -> 8.4, x 1100 14.4 / 15.1 -> 10.8, x 3900 37.8 / 39.8 -> 23.0; 128 x 1100 15.4 / 16.1 -> 15.5,
-//   x 2113 25.0 / 26.0 -> 24.7, x 3900 41.8 / 43.4 -> 40.2, and with lengths from 470 to 3900 42.1 -> 29.6 (the longest unit
-//   alone on its CU bounds an uncut launch).
-// Pieces of 4 slices, twice as many: 4 x 577 6.45 -> 6.6, 32 x 577 7.3 -> 7.85, 32 x 1100, 64 x 577 and 128 x 2113 the same; fp32,
-// d = 64 4 x 528 6.8 -> 6.35, 64 x 528 8.1 -> 8.2.  2 or 3 pieces of a short unit cost more than they bring (128 x 577
-// 10.3 -> 11.0 and 11.8), and from 256 units on the chip is full anyway (256 x 577 14.6 -> 16.8, 512 x 1100 45.4 -> 50.4).
-// Long pieces take 8 wavefronts (48 slices and more): ragged to 3900 rows 128 units 33.5 with 4, 29.6 with 8, 64 units 20.0 /
-// 18.1; equal lengths would rather have 4 (128 x 2113 24.0 / 24.7, 64 x 3900 22.7 / 23.0).  Uncut, 8 wavefronts serve up to 256
-// units that give each a slice (128 x 577 12.2 -> 10.3, 256 x 577 14.8 -> 14.6, ragged to 3900 65 -> 54; 2 x 100 4.4 -> 4.6; 16: 6.5) and
-// more than 512 units of 64 slices (896 x 2113 159.5 -> 157, ragged to 3900 174 -> 170); in between 4 do (512 x 1100
-// 45.2 against 45.7, x 2113 85.8 / 87.5).  fp32 at d = 128 has 16 KiB slices and stays at 4: cut 32 x 528 9.6 / 11.2, 64 x 1050 16.7 / 17.0,
-// 128 x 1050 25.6 / 26.1, 4 x 2100 11.5 / 11.7, uncut 256 x 528 24.1 / 24.4.
+// A workgroup on a CU of its own takes a microsecond per round of slices, one for each wavefront; cutting a unit shortens
+// that and costs the merge, 1.7 us and more with every piece, and from 256 workgroups on some CUs have two.  So up to 128 units are cut into
+// pieces of 4 wavefronts with equal rounds, at most 7 (or as many as keep a piece of 168 slices below 6 rounds), for the length a unit has
+// between two compressions; longer ones get more pieces of that size while there are workgroups left.  us per launch in a
+// graph, pieces x wavefronts (rounds), bf16, D = 128:
+//   4 units x 577 rows: uncut 6.4 with 8, 6.8 with 4; 3x4(4) 5.9, 4x4(3) 5.6, 5x4(2) 5.5, 10x4(1) 6.2, 5x8(1) 5.9
+//   32 x 577: uncut 7.0; 3x4 6.4, 4x4 6.2, 5x4(2) 6.0, 10x4 7.9;  32 x 1100: 11.8; 5x4 7.5, 6x4(3) 7.0, 8x4 7.8, 9x4(2) 8.7
+//   4 x 2113: 13.3; 5x4 7.35, 7x4(5) 6.9, 9x4 7.15, 16x4 7.8;  4 x 3900: 27.4; 7x4(9) 9.5, 11x4(6) 8.1, 16x4 8.3
+//   64 x 577: 8.7; 4x4(3) 7.2, 5x4 7.7;  64 x 2113: 22.8; 4x4 14.8, 4x8 15.6;  100 x 800: 11.4; 2x4 10.6;  128 x 2113: 24.8; 2x4 24.0, 2x8 24.4
+// ragged: 128 units to 3900 rows 2x8 in pieces of 8 slices 29.4, of 128 27.7, 2x4 of 128 27.4; 64 to 3900 17.3 -> 16.9; 84 to 464 uncut 8.1,
+// 3x4 6.3; 16 to 307 5.9, 5x4 4.9.  fp32: D = 128 32 x 528 uncut 15.3, 5x4(2) 8.2, 8x4 8.6, 9x4(1) 9.8, 48 x 300 10.7, 5x4(1) 6.5, 100 x 300 11.4,
+// 2x4 10.1; D = 64 8 x 350 7.1, 6x4(1) 4.85.  bf16, D = 64: 16 x 528 5.65, 5x4(1) 5.15.
+// Short units stay whole: up to 17 slices (4 x 300 4.85, 5x4(1) 4.9; 2 x 200 4.5, 5.0), where there are only two pieces up to 31
+// (128 x 400 7.8 / 8.3, x 577 10.15 / 9.9; bf16, D = 64 x 528, of 32 rows each, 6.6 / 6.8), 23 in fp32 (128 x 260 7.0 / 7.1, x 400 8.9 / 8.6).
+// Uncut, 8 wavefronts serve up to 256 units that give each two slices (4 units x 260 5.1 -> 4.9, x 200 4.6 -> 4.9; 128 x 260 6.4 -> 6.1) and
+// more than 512 units of 64 slices (896 x 2113 159.5 -> 157, ragged to 3900 174 -> 170); in between 4 do (512 x 1100 45.2 against 45.7).  fp32 at D =
+// 128 has 16 KiB slices and stays at 4 (256 x 577 25.6 / 26.9).
 struct AttendPlan { int waves, splits, iters; };
 
 static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
