@@ -188,8 +188,13 @@ hipError_t launch_score_topk(const GkvLaunch& ln, const GkvDims& dm, const float
 // depends on that write inside this launch, so the counter needs no fence.  Without a ticket
 // array a separate launch rewrites the records.
 // Dynamic LDS: int keep_s[b - w]: the kept indices, read from memory once.
-template <int PPT, int NT, bool SHARED>
-__global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, const int32_t* __restrict__ keep_idx,
+// Bound: HBM at hundreds of units; instructions below, as many as a lone wavefront issues in turn.  Without run-time divisions
+// (POW2; us with the copy of the record, in a graph): 4 units of b = 98 6.2 -> 5.7, of 512 8.7 -> 8.0, 32 of 512 10.7 -> 10.2, 896 of 98 20.3 -> 19.7,
+// fp32 8 of 322 9.3 -> 8.7; 896 of 512 93.8 -> 94.0, 1792 of 1024 416.5 -> 415.2.
+// POW2: rows of 2^np_log pieces (d = 64 and 128): a thread's piece is the same in every row it moves, rows follow by
+// a constant, and nothing is divided at run time.
+template <int PPT, int NT, bool SHARED, bool POW2>
+__global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, int np_log, const int32_t* __restrict__ keep_idx,
                                                      const float* __restrict__ F, void* K, void* V,
                                                      float* __restrict__ F_hist, int32_t* pos,
                                                      int32_t* d_state, int step, int32_t* state_ticket, int shares) {
@@ -252,15 +257,17 @@ __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, const 
     }
   }
 
-  const int NP = dm.d * esz / 16;                // 16-byte pieces per row
+  const int NP = POW2 ? 1 << np_log : dm.d * esz / 16;   // 16-byte pieces per row
   const bool whole = !SHARED || (isK && nt_old != nt_new);
   const int PS = whole ? NP : NP / shares, p0 = whole ? 0 : share * PS;   // this share's
+  const int ps_log = POW2 ? __builtin_ctz(PS) : 0;
   const int end = whole && share > 0 ? 0 : b;
   constexpr int PR = NT > 256 ? 2 : 1;           // positions per thread and chunk
-  int R = (NT * PPT) / PS;                       // rows per chunk: whole tiles, at most PR per thread
+  int R = POW2 ? (NT * PPT) >> ps_log : (NT * PPT) / PS;   // rows per chunk: whole tiles, at most PR per thread
   R = (R > PR * NT ? PR * NT : R) & ~15;
   u32x4* base = (u32x4*)((char*)(isK ? K : V) + (size_t)unit * dm.cap * dm.d * esz);
   int32_t* pu = pos + (size_t)unit * dm.cap;
+  const int old_tiled = isK ? nt_old : 0, new_tiled = isK ? nt_new : 0;
 
   // Every load of a round is issued before the first wait: the addresses are computed without
   // branches (pieces beyond the chunk or the budget read row 0, always in bounds, and are not
@@ -270,20 +277,24 @@ __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, const 
     src = row < k ? src : c + (row - k);
     return src < 0 ? 0 : (src >= l ? l - 1 : src);
   };
+  auto offset = [&](int row, int piece, int n_tiled) {
+    const int in = row & 15;
+    if constexpr (POW2) return row < n_tiled ? (row << np_log) + (piece << 4) + in - (in << np_log) : (row << np_log) + piece;
+    else return row < n_tiled ? (row - in) * NP + piece * 16 + in : row * NP + piece;
+  };
   for (int r0 = first; r0 < end; r0 += R) {
     u32x4 buf[PPT];
     int dst[PPT];
 #pragma unroll
     for (int i = 0; i < PPT; ++i) {
       const int x = tid + NT * i;
-      const int rr = x / PS, piece = p0 + x % PS;
+      const int rr = POW2 ? (tid >> ps_log) + i * (NT >> ps_log) : x / PS;
+      const int piece = p0 + (POW2 ? tid & (PS - 1) : x % PS);
       const int row = r0 + rr;
       const bool valid = rr < R && row < b;
       const int src = valid ? source(row) : 0;
-      const int so = (isK && src < nt_old) ? ((src >> 4) * 16 * NP + piece * 16 + (src & 15)) : (src * NP + piece);
-      const int d_o = (isK && row < nt_new) ? ((row >> 4) * 16 * NP + piece * 16 + (row & 15)) : (row * NP + piece);
-      dst[i] = valid ? d_o : -1;
-      buf[i] = base[so];
+      dst[i] = valid ? offset(row, piece, new_tiled) : -1;
+      buf[i] = base[(uint32_t)offset(src, piece, old_tiled)];
     }
     int pos_val[PR];
 #pragma unroll
@@ -294,7 +305,7 @@ __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, const 
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PPT; ++i)
-      if (dst[i] >= 0) base[dst[i]] = buf[i];
+      if (dst[i] >= 0) base[(uint32_t)dst[i]] = buf[i];
 #pragma unroll
     for (int i = 0; i < PR; ++i) {
       const int rr = tid + NT * i;
@@ -431,12 +442,14 @@ hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, c
   const bool wide = ppt == 8 && units <= 128 && unit_bytes / shares > (units <= 16 && dm.b > 2 * 256 ? 32 : 64) * 1024;
   // One share is an instantiation of its own: with the column arithmetic at run time 672 units of b = 287, d = 64
   // take 25.3 us, without 25.0; 604 of b = 323 21.6 / 21.4.
-  auto kern = ppt == 16 ? (shares > 1 ? compact_kernel<16, 256, true> : compact_kernel<16, 256, false>)
-            : ppt == 4 ? (shares > 1 ? compact_kernel<4, 256, true> : compact_kernel<4, 256, false>)
-            : wide ? (shares > 1 ? compact_kernel<8, 1024, true> : compact_kernel<8, 1024, false>)
-                   : (shares > 1 ? compact_kernel<8, 256, true> : compact_kernel<8, 256, false>);
+  const bool pow2 = (pieces & (pieces - 1)) == 0;
+  const int np_log = pow2 ? __builtin_ctz(pieces) : 0;
+#define GKV_COMPACT(PPT_, NT_) (shares > 1 ? (pow2 ? compact_kernel<PPT_, NT_, true, true> : compact_kernel<PPT_, NT_, true, false>) \
+                                           : (pow2 ? compact_kernel<PPT_, NT_, false, true> : compact_kernel<PPT_, NT_, false, false>))
+  auto kern = ppt == 16 ? GKV_COMPACT(16, 256) : ppt == 4 ? GKV_COMPACT(4, 256) : wide ? GKV_COMPACT(8, 1024) : GKV_COMPACT(8, 256);
+#undef GKV_COMPACT
   const int threads = wide ? 1024 : 256;
-  hipError_t e = gkv_launch(ln, kern, dim3(units, 2 * shares), dim3(threads), shmem, dm, esz, keep_idx, F, K, V,
+  hipError_t e = gkv_launch(ln, kern, dim3(units, 2 * shares), dim3(threads), shmem, dm, esz, np_log, keep_idx, F, K, V,
                             F_hist, pos, d_state, (int)step, state_ticket, shares);
   if (e != hipSuccess || state_ticket != nullptr) return e;
   const int nlb = dm.L * dm.B;
