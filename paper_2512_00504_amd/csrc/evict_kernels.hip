@@ -7,6 +7,7 @@ namespace {
 
 // 16-byte piece as a native vector (arrays of it stay in registers; the runtime's uint4 class does not)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
 // ---- helpers -------------------------------------------------------------------------------
 // Inclusive scan over the 256 threads of a block; `tmp` holds 4 ints of LDS.
@@ -23,6 +24,29 @@ __device__ __forceinline__ int block_inclusive_scan(int v, int* tmp) {
   int add = 0;
   for (int i = 0; i < wv; ++i) add += tmp[i];
   return v + add;
+}
+
+// Across the lanes of a wavefront through registers (an exchange through LDS takes 60 ns): inclusive sums, and the
+// maximum of numbers that are not negative in every lane.
+#define GKV_DPP_I(v, ctrl, rows) __builtin_amdgcn_update_dpp(0, v, ctrl, rows, 0xF, false)
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+  v += GKV_DPP_I(v, 0x111, 0xF);                 // row_shr 1, 2, 4, 8
+  v += GKV_DPP_I(v, 0x112, 0xF);
+  v += GKV_DPP_I(v, 0x114, 0xF);
+  v += GKV_DPP_I(v, 0x118, 0xF);
+  v += GKV_DPP_I(v, 0x142, 0xA);                 // lane 15 of a row to the next row, then lane 31 to the upper half
+  v += GKV_DPP_I(v, 0x143, 0xC);
+  return v;
+}
+__device__ __forceinline__ float wave_max_nonneg(float v) {
+#pragma unroll
+  for (int q = 0; q < 6; ++q) {
+    const int u = __float_as_int(v);
+    const int w = q == 0 ? GKV_DPP_I(u, 0x111, 0xF) : q == 1 ? GKV_DPP_I(u, 0x112, 0xF) : q == 2 ? GKV_DPP_I(u, 0x114, 0xF)
+                : q == 3 ? GKV_DPP_I(u, 0x118, 0xF) : q == 4 ? GKV_DPP_I(u, 0x142, 0xA) : GKV_DPP_I(u, 0x143, 0xC);
+    v = fmaxf(v, __int_as_float(w));             // (lanes without a source get 0)
+  }
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // Monotone map float -> uint32 (larger float, larger key); -0 is folded onto +0 first.
@@ -51,15 +75,17 @@ __device__ __forceinline__ uint32_t sortable_key(float f) {
 // digits in LDS (four passes of atomics, scans and six barriers), update and selection in one launch: 4 units
 // of 624 candidates 8.5 -> 7.0 us, 256 of 1056 12.7 -> 9.5; the update alone, which read S twice, 11.2 -> 6.3
 // at 1792 units of 1136; the selection alone there 16.7 to 18.6 -> 16.4 to 19.0 by the scores (by then the
-// counting is the bound), 896 units of 624 9.1 -> 8.4.
+// counting is the bound), 896 units of 624 9.1 -> 8.4.  Maximum, scan and look-ups through registers, four counts to a word of
+// LDS (in a graph): selection of 4 units of 640 rows 5.5 -> 5.05 us, 64 of 1152 7.1 -> 6.6, 1792 of 1152 13.0 -> 12.6; update 2.6 -> 2.1, 3.0 -> 2.6, 5.5 ->
+// 5.0.  (The counts as scalars: 12.6 -> 14.2 at 1792 units.)
 template <int IPT, bool UPDATE, bool SELECT>
 __global__ __launch_bounds__(256) void score_topk_kernel(GkvDims dm, const float* __restrict__ S,
                                                          const float* __restrict__ F_hist,
                                                          const int32_t* __restrict__ d_state, int step,
                                                          float* __restrict__ F_out, int32_t* __restrict__ keep_idx) {
   step = resolve_step(dm, step);
-  __shared__ float red[8];
-  __shared__ int cnt[2][4][4];
+  __shared__ __attribute__((aligned(16))) float red[4];
+  __shared__ i32x4 cnt[2][4];
   __shared__ int scan_s[64];
   const int unit = blockIdx.x, lb = quotient(unit, dm.by_hkv), tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -84,7 +110,10 @@ __global__ __launch_bounds__(256) void score_topk_kernel(GkvDims dm, const float
 #pragma unroll
     for (int i = 0; i < IPT; ++i)
       if (tid + 256 * i < c) mx = fmaxf(mx, f[i]);
-    mx = block_max(mx, red);
+    mx = wave_max_nonneg(mx);
+    if (lane == 0) red[wave] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
       const int n = tid + 256 * i;
@@ -114,14 +143,15 @@ __global__ __launch_bounds__(256) void score_topk_kernel(GkvDims dm, const float
 #pragma unroll
         for (int i = 0; i < IPT; ++i) mine[q] += __popcll(__ballot(key[i] >= t));
       }
-      int (&slot)[4][4] = cnt[pass & 1];         // two sets in turn: one barrier per pass
-      if (lane == 0) { slot[wave][0] = mine[0]; slot[wave][1] = mine[1]; slot[wave][2] = mine[2]; }
+      i32x4 (&slot)[4] = cnt[pass & 1];          // two sets in turn: one barrier per pass
+      if (lane == 0) slot[wave] = i32x4{mine[0], mine[1], mine[2], 0};
       __syncthreads();
+      const i32x4 all = (slot[0] + slot[1]) + (slot[2] + slot[3]);
       uint32_t digit = 0;
       int got = 0;
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
-        const int n_ge = slot[0][q] + slot[1][q] + slot[2][q] + slot[3][q];
+        const int n_ge = all[q];
         if (n_ge >= k) { digit = q + 1; got = n_ge; }          // counts fall with q
       }
       prefix |= digit << (2 * pass);
@@ -137,19 +167,14 @@ __global__ __launch_bounds__(256) void score_topk_kernel(GkvDims dm, const float
       if (lane == 0) scan_s[4 * i + wave] = __popcll(above[i]) | (__popcll(equal[i]) << 16);
     }
     __syncthreads();
-    int v = lane < 4 * IPT ? scan_s[lane] : 0;   // low half: above, high half: equal (at most 4096 of each)
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int t = __shfl_up(v, o);
-      if (lane >= o) v += t;
-    }
-    const int rest = k - (__shfl(v, 63) & 0xffff);             // how many of the equal ones are kept
+    const int v = wave_inclusive_sum(lane < 4 * IPT ? scan_s[lane] : 0);   // low half: above, high half: equal (at most 4096 of each)
+    const int rest = k - (__builtin_amdgcn_readlane(v, 63) & 0xffff);      // how many of the equal ones are kept
     int32_t* Ku = keep_idx + (size_t)unit * k;
     const uint64_t below = (1ull << lane) - 1;
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
       const int at = 4 * i + wave - 1;
-      const int before = at < 0 ? 0 : __shfl(v, at < 0 ? 0 : at);
+      const int before = at < 0 ? 0 : __builtin_amdgcn_readlane(v, at < 0 ? 0 : at);
       const int n_above = (before & 0xffff) + __popcll(above[i] & below);
       const int n_equal = (before >> 16) + __popcll(equal[i] & below);
       const bool is_above = (above[i] >> lane) & 1, is_equal = (equal[i] >> lane) & 1;
