@@ -126,6 +126,7 @@ struct ScorePlan {
   int32_t pair_heads;      // 1: window of at most 8 rows, two heads per block
   int32_t n_blk, nt, nt_pass, ksplit;
   int32_t use_sbuf;        // S is collected in LDS over several passes
+  GkvDivisor by_ksplit;
 };
 
 // Dynamic LDS: q pieces [nt_pass*n_blk][NL][1 KiB]; float row_hi[rows], row_lo[rows]; float sbuf[cap] if
@@ -140,15 +141,10 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, kb = lane >> 4;
-  const int unit = blockIdx.x / pl.ksplit, share = blockIdx.x % pl.ksplit;
+  const int unit = quotient(blockIdx.x, pl.by_ksplit), share = (int)blockIdx.x - unit * pl.ksplit;
   const int lb = quotient(unit, dm.by_hkv), j = unit - lb * dm.Hkv;
   const int cap = dm.cap, w = dm.w, g = dm.g;
   const bool pair = pl.pair_heads;
-
-  const SeqState seq = load_state(a.d_state, lb);
-  const int l = compression_length(seq, a.step, dm.b, w, cap);
-  if (l == 0) return;
-  const int cc = l - w;                     // number of candidates
 
   const int rows_pass = pl.nt_pass * pl.n_blk * 16;
   char* qs = smem_raw;
@@ -157,49 +153,83 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
   float* sbuf = row_lo + rows_pass;
   float2* red_ms = (float2*)(sbuf + (pl.use_sbuf ? cap : 0));
 
+  // The window queries of a pass go straight to LDS, piece by piece (wavefront `wave` fetches pieces wave, wave + NW, ...): a
+  // lane's window row is the same in all blocks of sixteen rows, their heads follow each other in memory.  Rows beyond the
+  // window or the group repeat a valid one; their offset drops them.  Nothing here waits for the state record.  (With
+  // each 16-byte piece's row worked out for itself, behind the record, and the first statistics and key tiles behind the queries, us
+  // in a graph, before -> now: fp32, D = 128, g = 7 4 units of 612 rows 13.0 -> 9.5, 32 of 544 17.2 -> 14.1, 256 47.3 -> 43.7; D = 64, g = 4 2 of 80
+  // 5.3 -> 4.95; bf16, g = 16 64 of 576 17.7 -> 11.7, 896 of 576 68.5 -> 55.4; with own statistics 32 of 544 147 -> 137.)
+  const int t_first = a.step - w + 1;
+  int slot0 = t_first % w;
+  slot0 = slot0 < 0 ? slot0 + w : slot0;                 // slot of window row 0; row k sits in slot0 + k, wrapped
+  auto ring_row = [&](int h, int k) {
+    int slot = slot0 + k;
+    slot = slot >= w ? slot - w : slot;
+    return ((size_t)slot * dm.L * dm.B + lb) * dm.Hq + j * g + h;
+  };
+  auto fetch_queries = [&](int nt0, int nts) {
+    for (int nt = 0; nt < nts; ++nt) {
+      const int k = min(pair ? (r & 7) : 16 * (nt0 + nt) + r, w - 1);
+      const char* row = (const char*)a.qwin + ring_row(0, k) * G::ROW_BYTES + kb * 16;
+      for (int x = wave; x < pl.n_blk * NL; x += NW) {
+        const int i = x / NL, c = x % NL;
+        const int h = min(pair ? 2 * i + (r >> 3) : i, g - 1);
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(row + h * G::ROW_BYTES + c * 64),
+                                         (__attribute__((address_space(3))) void*)(qs + (size_t)(nt * pl.n_blk * NL + x) * 1024), 16, 0, 0);
+      }
+    }
+  };
+  fetch_queries(0, min(pl.nt_pass, pl.nt));
+  // head and window row (k-th oldest) of staged row x of the pass that starts at nt0
+  auto head_of = [&](int x) { return pair ? 2 * (x >> 4) + ((x >> 3) & 1) : (x >> 4) % pl.n_blk; };
+  auto k_of = [&](int x, int nt0) { return pair ? (x & 7) : 16 * (nt0 + (x >> 4) / pl.n_blk) + (x & 15); };
+  auto stats_of = [&](int x, int nt0) { return a.stats[ring_row(min(head_of(x), g - 1), min(k_of(x, nt0), w - 1))]; };
+  float2 first_stats = make_float2(0.f, 1.f);
+  if constexpr (HAVE_STATS) first_stats = stats_of(min(tid, rows_pass - 1), 0);
+
+  const SeqState seq = load_state(a.d_state, lb);
+  const int l = compression_length(seq, a.step, dm.b, w, cap);
+  const int cc = l - w;                     // number of candidates
+
   const char* Kh = (const char*)a.K + (size_t)unit * cap * G::ROW_BYTES;
   const float s_hi = dm.scale_l2_hi, s_lo = dm.scale_l2_lo;
   float* So = a.S + (size_t)unit * cap;
 
   // this workgroup's groups of KT candidate tiles
-  const int groups = (((cc + 15) >> 4) + KT - 1) / KT;
+  const int groups = l == 0 ? 0 : (((cc + 15) >> 4) + KT - 1) / KT;
   const int per_share = (groups + pl.ksplit - 1) / pl.ksplit;
   const int g0 = share * per_share, g1 = min(groups, g0 + per_share);
-  if (g0 >= g1) return;                     // (cc > 0: share 0 always has work)
+  if (g0 >= g1) {                           // (where there is a compression, cc > 0 and share 0 has work)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    return;
+  }
 
   const int n_pass = (pl.nt + pl.nt_pass - 1) / pl.nt_pass;
   for (int pass = 0; pass < n_pass; ++pass) {
     const int nt0 = pass * pl.nt_pass, nts = min(pl.nt_pass, pl.nt - nt0);
     const int rows = nts * pl.n_blk * 16;
-    if (pass) __syncthreads();              // the previous pass has been read
-
-    // head and window row (k-th oldest) of staged row x, and whether there is such a row
-    auto head_of = [&](int x) { return pair ? 2 * (x >> 4) + ((x >> 3) & 1) : (x >> 4) % pl.n_blk; };
-    auto k_of = [&](int x) { return pair ? (x & 7) : 16 * (nt0 + (x >> 4) / pl.n_blk) + (x & 15); };
-    auto slot_of = [&](int k) { const int t_row = a.step - w + 1 + k; return ((t_row % w) + w) % w; };
-
-    // stage the window queries; 16 lanes take the same chunk of 16 rows, so their LDS pieces are
-    // contiguous and a wavefront covers 64 bytes of every row
-    for (int x = tid; x < rows * G::RP; x += NW * 64) {
-      const int rr = x & 15, ch = (x >> 4) % G::RP, blk = (x >> 4) / G::RP, row = blk * 16 + rr;
-      const int h = head_of(row), k = k_of(row);
-      u32x4 v = {0u, 0u, 0u, 0u};
-      if (h < g && k < w)
-        v = ld16((const char*)a.qwin + (((size_t)slot_of(k) * dm.L * dm.B + lb) * dm.Hq + j * g + h) * (size_t)G::ROW_BYTES + ch * 16);
-      *(u32x4*)(qs + (size_t)blk * G::TILE_BYTES + (ch >> 2) * 1024 + ((ch & 3) * 16 + rr) * 16) = v;
+    if (pass) {
+      __syncthreads();                      // the previous pass has been read
+      fetch_queries(nt0, nts);
     }
+    u32x4 kA[KT][NL], kN[KT][NL];
+    auto load_group = [&](u32x4 (&k)[KT][NL], int p) {
+#pragma unroll
+      for (int tt = 0; tt < KT; ++tt) load_k_tile<T, D>(k[tt], Kh, p * KT + tt, seq.n_tiled, lane, r, kb);
+    };
+    if (HAVE_STATS && g0 + wave < g1) load_group(kA, g0 + wave);
     auto store_offset = [&](int x, float m, float s) {
-      const float2 c = row_offset(head_of(x) < g && k_of(x) < w, m, s);
+      const float2 c = row_offset(head_of(x) < g && k_of(x, nt0) < w, m, s);
       row_hi[x] = c.x;
       row_lo[x] = c.y;
     };
     if constexpr (HAVE_STATS) {
       for (int x = tid; x < rows; x += NW * 64) {
-        const int h = min(head_of(x), g - 1), k = min(k_of(x), w - 1);
-        const float2 ms = a.stats[((size_t)slot_of(k) * dm.L * dm.B + lb) * dm.Hq + j * g + h];
+        const float2 ms = pass == 0 && x == tid ? first_stats : stats_of(x, nt0);
         store_offset(x, ms.x, ms.y);
       }
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");           // the queries are in LDS
     __syncthreads();
 
     auto load_q = [&](u32x4 (&q)[NL], int blk) {
@@ -222,7 +252,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             rm[i][e] = GKV_NO_MAX; rs[i][e] = 0.f;
-            last_vis[i][e] = cc + k_of(16 * min(b0 + i, n_blocks - 1) + 4 * kb + e);
+            last_vis[i][e] = cc + k_of(16 * min(b0 + i, n_blocks - 1) + 4 * kb + e, nt0);
           }
         auto stats_tile = [&](const u32x4 (&kA)[NL], int t, auto exact) {
           constexpr bool EXACT = decltype(exact)::value;
@@ -339,12 +369,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
       }
       continue;
     }
-    u32x4 kA[KT][NL], kN[KT][NL];
-    auto load_group = [&](u32x4 (&k)[KT][NL], int p) {
-#pragma unroll
-      for (int tt = 0; tt < KT; ++tt) load_k_tile<T, D>(k[tt], Kh, p * KT + tt, seq.n_tiled, lane, r, kb);
-    };
-    if (g0 + wave < g1) load_group(kA, g0 + wave);
+    if (!HAVE_STATS && g0 + wave < g1) load_group(kA, g0 + wave);
     for (int p = g0 + wave; p < g1; p += NW) {
       // the wavefront's next tiles are requested before these are worked on (clamped at the end:
       // the same number of requests in flight on every path keeps the wait for this group short)
@@ -401,7 +426,7 @@ __global__ __launch_bounds__(NW * 64) void score_mfma_kernel(GkvDims dm, ScoreAr
 // against a kernel that kept the queries in LDS and took an exponential per head and logit: 256 units
 // of 1088 rows, g = 5, w = 32 25.8 -> 20.0 us; 4608 such units 347 -> 310 us; 448 units of 640 rows,
 // g = 7, w = 16 20.8 -> 17.8 us; 4 units 11.1 -> 5.8 us.  Against the plain kernel: bf16 D = 64, 128 units
-// 2780 -> 7.4 us; fp32 D = 128, 32 units 3495 -> 16.9 us (kernel above, bound by fp32 MFMAs).
+// 2780 -> 7.4 us; fp32 D = 128, 32 units 3495 -> 14.1 us (kernel above, bound by fp32 MFMAs).
 // Dynamic LDS: q pieces [NT*NB][NL][1 KiB]; float2 row_c[16*NT*NB]; OWN: float2 red_ms[NW][16*NT*NB].
 template <int D, int NW, int NB, int NT, bool ONCE, bool OWN>
 __global__ __launch_bounds__(NW * 64, 2) void score_regs_kernel(GkvDims dm, ScoreArgs a, int pair, int ksplit, GkvDivisor by_ksplit) {
@@ -736,6 +761,7 @@ hipError_t launch(const GkvLaunch& ln, const GkvDims& dm, const ScoreArgs& a, in
   const int groups = ((len_max + 15) / 16 + KT - 1) / KT;
   const int k = 512 / units, most = (groups + NW - 1) / NW;
   pl.ksplit = k < 1 ? 1 : (k > most ? (most < 1 ? 1 : most) : k);
+  pl.by_ksplit = gkv_divisor(pl.ksplit);
   const size_t rows = (size_t)pl.nt_pass * pl.n_blk * 16;
   const size_t shmem = rows * G::ROW_BYTES + rows * 8 + (pl.use_sbuf ? 4 * (size_t)dm.cap : 0) +
                        (a.stats ? 0 : NW * rows * 8);
