@@ -33,10 +33,39 @@ struct RedArgs {
 // threshold decision may legitimately differ from fp64, and it averages out in the sums.  Sums
 // run in fp32 over a lane's four entries of a tile pair and in fp64 from there on; exp(col - max)
 // is fp64.  The plain kernel does everything in fp64.
+// Exchanges between lanes go through registers (through LDS one takes 60 ns): sums over the lanes l and l ^ 16, l and
+// l ^ 32, in both, and the maximum of a wavefront.  With these, and a row's square root and quotient (forty instructions in
+// 64 bits) in one lane instead of four, us a call in a graph: fp32, d = 128 8 units of 348 rows 18.6 -> 17.3, d = 64 20 of 348 17.1 ->
+// 16.2, bf16, d = 64 32 of 400 27.4 -> 25.8; bf16, d = 128 4 of 640 20.1 -> 19.5, 896 of 640 124.3 -> 122.
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double add_halves(double v) {
+  const u32x2 u = __builtin_bit_cast(u32x2, v);
+  const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(u[0], u[0], false, false));
+  const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(u[1], u[1], false, false));
+  return __builtin_bit_cast(double, (u32x2{lo[0], hi[0]})) + __builtin_bit_cast(double, (u32x2{lo[1], hi[1]}));
+}
+__device__ __forceinline__ double add_quarters(double v) {
+  const u32x2 u = __builtin_bit_cast(u32x2, v);
+  const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(u[0], u[0], false, false));
+  const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(u[1], u[1], false, false));
+  return add_halves(__builtin_bit_cast(double, (u32x2{lo[0], hi[0]})) + __builtin_bit_cast(double, (u32x2{lo[1], hi[1]})));
+}
+__device__ __forceinline__ double wave_max_f64(double v) {
+#define GKV_STEP(ctrl, rows) { \
+    const u32x2 u = __builtin_bit_cast(u32x2, v); \
+    const u32x2 o = u32x2{(uint32_t)__builtin_amdgcn_update_dpp((int)u[0], (int)u[0], ctrl, rows, 0xF, false), \
+                          (uint32_t)__builtin_amdgcn_update_dpp((int)u[1], (int)u[1], ctrl, rows, 0xF, false)}; \
+    v = fmax(v, __builtin_bit_cast(double, o)); }
+  GKV_STEP(0x111, 0xF) GKV_STEP(0x112, 0xF) GKV_STEP(0x114, 0xF) GKV_STEP(0x118, 0xF)   // row_shr; lanes without a source keep their own
+  GKV_STEP(0x142, 0xA) GKV_STEP(0x143, 0xC)
+#undef GKV_STEP
+  const u32x2 u = __builtin_bit_cast(u32x2, v);
+  return __builtin_bit_cast(double, (u32x2{(uint32_t)__builtin_amdgcn_readlane((int)u[0], 63), (uint32_t)__builtin_amdgcn_readlane((int)u[1], 63)}));
+}
+
 template <int NW>
 __device__ __forceinline__ double block_max_f64(double v, double* red) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
+  v = wave_max_f64(v);
   __syncthreads();
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
@@ -261,7 +290,7 @@ __global__ __launch_bounds__(RED_NW * 64, 2) void redundancy_mfma_kernel(GkvDims
             q[i] = fma(hi, hi, q[i]);
           }
         double ss = (q[0] + q[1]) + (q[2] + q[3]);
-        ss += __shfl_xor(ss, 32);
+        ss = add_halves(ss);
         const int n = 32 * (J0 + cc) + r32;
         const double x = n < l ? 1.0 / (sqrt(ss) + (double)a.eps) : 0.0;
         odd |= n < l && !(x >= RED_INV_MIN && x <= RED_INV_MAX);
@@ -497,11 +526,11 @@ __global__ __launch_bounds__(NW * 64) void redundancy_f64_kernel(GkvDims dm, Red
     for (int c = 0; c < NL; ++c)
 #pragma unroll
       for (int i = 0; i < EPC; ++i) { const double x = elem(k[c], i); ss = fma(x, x, ss); }
-    ss += __shfl_xor(ss, 16);
-    ss += __shfl_xor(ss, 32);
-    const int n = 16 * t + r;
-    if (kb == 0) inv[n] = n < l ? 1.0 / (sqrt(ss) + (double)a.eps) : 0.0;
+    ss = add_quarters(ss);
+    if (kb == 0) inv[16 * t + r] = ss;
   }
+  __syncthreads();
+  for (int n = tid; n < 16 * n_tiles; n += NW * 64) inv[n] = n < l ? 1.0 / (sqrt(inv[n]) + (double)a.eps) : 0.0;   // a row a thread, not four
   __syncthreads();
 
   const int first_recent = l - a.n_recent;
@@ -530,8 +559,7 @@ __global__ __launch_bounds__(NW * 64) void redundancy_f64_kernel(GkvDims dm, Red
 #pragma unroll
       for (int c = 0; c < NL; ++c) cur[c] = nxt[c];
     }
-    col += __shfl_xor(col, 16);
-    col += __shfl_xor(col, 32);
+    col = add_quarters(col);
     if (kb == 0 && j < l) cs[j] = j < first_recent ? col : 0.0;
   }
   __syncthreads();
@@ -580,11 +608,11 @@ __global__ __launch_bounds__(256) void redundancy_f64_split_kernel(GkvDims dm, R
     for (int c = 0; c < NL; ++c)
 #pragma unroll
       for (int i = 0; i < EPC; ++i) { const double x = elem(k[c], i); ss = fma(x, x, ss); }
-    ss += __shfl_xor(ss, 16);
-    ss += __shfl_xor(ss, 32);
-    const int n = 16 * t + r;
-    if (kb == 0) inv[n] = n < l ? 1.0 / (sqrt(ss) + (double)a.eps) : 0.0;
+    ss = add_quarters(ss);
+    if (kb == 0) inv[16 * t + r] = ss;
   }
+  __syncthreads();
+  for (int n = tid; n < 16 * n_tiles; n += NW * 64) inv[n] = n < l ? 1.0 / (sqrt(inv[n]) + (double)a.eps) : 0.0;
   __syncthreads();
   const double tau = (double)a.tau;
   for (int J = blockIdx.y; J < n_tiles; J += gridDim.y) {
@@ -611,8 +639,7 @@ __global__ __launch_bounds__(256) void redundancy_f64_split_kernel(GkvDims dm, R
 #pragma unroll
       for (int c = 0; c < NL; ++c) cur[c] = nxt[c];
     }
-    col += __shfl_xor(col, 16);
-    col += __shfl_xor(col, 32);
+    col = add_quarters(col);
     if (kb == 0) part[16 * wave + r] = col;
     __syncthreads();
     if (tid < 16) {
