@@ -10,22 +10,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 
 // ---- helpers -------------------------------------------------------------------------------
-// Inclusive scan over the 256 threads of a block; `tmp` holds 4 ints of LDS.
-__device__ __forceinline__ int block_inclusive_scan(int v, int* tmp) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int t = __shfl_up(v, o);
-    if (lane >= o) v += t;
-  }
-  __syncthreads();
-  if (lane == 63) tmp[wv] = v;
-  __syncthreads();
-  int add = 0;
-  for (int i = 0; i < wv; ++i) add += tmp[i];
-  return v + add;
-}
-
 // Across the lanes of a wavefront through registers (an exchange through LDS takes 60 ns): inclusive sums, and the
 // maximum of numbers that are not negative in every lane.
 #define GKV_DPP_I(v, ctrl, rows) __builtin_amdgcn_update_dpp(0, v, ctrl, rows, 0xF, false)
@@ -47,6 +31,18 @@ __device__ __forceinline__ float wave_max_nonneg(float v) {
     v = fmaxf(v, __int_as_float(w));             // (lanes without a source get 0)
   }
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// Inclusive scan over the 256 threads of a block; `tmp` holds 4 ints of LDS.
+__device__ __forceinline__ int block_inclusive_scan(int v, int* tmp) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  v = wave_inclusive_sum(v);
+  __syncthreads();
+  if (lane == 63) tmp[wv] = v;
+  __syncthreads();
+  int add = 0;
+  for (int i = 0; i < wv; ++i) add += tmp[i];
+  return v + add;
 }
 
 // Monotone map float -> uint32 (larger float, larger key); -0 is folded onto +0 first.
