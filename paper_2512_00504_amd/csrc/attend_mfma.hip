@@ -120,14 +120,21 @@ struct Rows {
 // pattern (bf16, D = 128): both ordinary 67-77% of the HBM peak (worst when K+V exceed the 256 MiB
 // memory-side cache), both non-temporal 76%, one stream of each kind 80-85% at every cache size
 // tried (0.3 to 10 GB), whichever of the two is the non-temporal one.
-template <typename T, int D, int KT>
+// APART: a branch for each format, whose steps are immediates then (fewer instructions, for launches that they bound); in
+// full launches the branch holds the requests back: bf16, D = 64 1200 units of 1560 rows 78.3 us without, 86.8 with it.
+template <bool APART, typename T, int D, int KT>
 __device__ __forceinline__ void issue_k(Slice<T, D, KT>& s, const Rows<T, D>& at, int it) {
   using G = Geo<T, D>;
 #pragma unroll
   for (int tt = 0; tt < KT; ++tt) {
     const int t = it * KT + tt;
     const char* Kt = at.Kh + (uint32_t)(t * G::TILE_BYTES);
-    if (16 * t < at.n_tiled) {                               // wave-uniform
+    if (!APART) {
+      const bool tiled = 16 * t < at.n_tiled;
+      const uint32_t off = tiled ? at.k_tiled : at.k_rows, step = tiled ? 1024 : 64;
+#pragma unroll
+      for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = ld16(Kt + off + c * step);
+    } else if (16 * t < at.n_tiled) {                        // wave-uniform
 #pragma unroll
       for (int c = 0; c < G::NL; ++c) s.kA[tt][c] = ld16(Kt + at.k_tiled + c * 1024);
       asm volatile("; tiled");                               // (the branches stay apart: the steps are immediates)
@@ -399,9 +406,9 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
   using G = Geo<T, D>;
   constexpr int KEYS = 16 * KT;             // keys per iteration
   // One slice in flight: the next K is requested as soon as the products with this one are under way, V behind its own.
-  // fp32, D = 128 800 units of 540 rows 84.8 -> 83.0 us, 32 of 528 8.2 -> 7.9; bf16, D = 64 1600 of 540 35.4 -> 35.1.  Not for the others:
-  // 896 units of 577 rows 43.9 -> 44.4, 784 ragged to 1227 48.3 -> 49.2; fp32, D = 64 800 of 540 39.6 -> 40.1.
-  constexpr bool EARLY_K = sizeof(T) * D == 512 || (sizeof(T) == 2 && D == 64);
+  // bf16, D = 128 1200 units of 860 rows 93.7 -> 87.7 us; fp32, D = 128 800 of 540 84.8 -> 82.4, 32 of 528 8.2 -> 7.9, D = 64 1200 of 860 90.0 ->
+  // 88.8.  Not with 8 wavefronts: 4608 of 1056 391.8 -> 389.5, but 784 ragged to 1227 48.7 -> 49.7, and 41.3 where 4 make it 41.2.
+  constexpr bool EARLY_K = !(sizeof(T) == 2 && D == 128 && NW >= 8);
   constexpr int RP = G::RP, ROW_BYTES = G::ROW_BYTES, OSTR = G::OSTR, PSTR = G::PSTR;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -473,7 +480,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
       issue_last_k<T, D, KT>(s, at, it, lane, new_row, knew_g);
       issue_last_v<T, D, KT>(s, at, it, lane, new_row, vnew_g);
     } else {
-      issue_k<T, D, KT>(s, at, it);
+      issue_k<(DEPTH > 1), T, D, KT>(s, at, it);
       issue_v<T, D, KT>(s, at, it);
     }
   };
@@ -508,26 +515,26 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
   if (it0 < n_iter) {
     int it = it0;
     if constexpr (DEPTH == 1) {
-      if constexpr (EARLY_K) {
-        auto and_then = [&](auto next) {
-          process_slice<T, D, KT, false>(s0, st, qB, it, it == it0, false, scale_log2, scale_log2_lo, r, kb, n_tot, next);
-        };
-        for (; it + stride < n_iter - 1; it += stride) {
-          and_then([&] { issue_k<T, D, KT>(s0, at, it + stride); });
-          issue_v<T, D, KT>(s0, at, it + stride);
+      auto and_then = [&](auto next) {
+        process_slice<T, D, KT, false>(s0, st, qB, it, it == it0, false, scale_log2, scale_log2_lo, r, kb, n_tot, next);
+      };
+      for (; it + stride < n_iter - 1; it += stride) {
+        if constexpr (EARLY_K) and_then([&] { issue_k<false, T, D, KT>(s0, at, it + stride); });
+        else {
+          and_then(Nothing{});
+          issue_k<false, T, D, KT>(s0, at, it + stride);
         }
-        if (it + stride == n_iter - 1) {
-          and_then([&] { issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g); });
-          issue_last_v<T, D, KT>(s0, at, it += stride, lane, new_row, vnew_g);
-        }
-        process(s0, it, it == n_iter - 1);
-      } else {
-        for (;;) {
-          process(s0, it, it == n_iter - 1);
-          if ((it += stride) >= n_iter) break;
-          request(s0, it);
-        }
+        issue_v<T, D, KT>(s0, at, it + stride);
       }
+      if (it + stride == n_iter - 1) {
+        if constexpr (EARLY_K) and_then([&] { issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g); });
+        else {
+          and_then(Nothing{});
+          issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g);
+        }
+        issue_last_v<T, D, KT>(s0, at, it += stride, lane, new_row, vnew_g);
+      }
+      process(s0, it, it == n_iter - 1);
     } else {
       // two slices in turn, the next one always on its way
       Slice<T, D, KT> s1;

@@ -209,8 +209,8 @@ static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
     const int most = (int)(256 / units) < 16 ? (int)(256 / units) : 16;
     const int aim = typical > 24 * 7 ? (typical + 23) / 24 : 7, n = aim < most ? aim : most;
     const int enough = n == 2 ? (wide ? 12 : ctx->cfg.dtype == GKV_F32 ? 24 : 32) : wide ? 9 : keys == 32 ? 10 : 18;
-    if (full >= enough) {
-      // units of ordinary length whole where that is the better: only prompts are cut
+    if (typical >= enough || full >= 2 * enough) {
+      // units of ordinary length stay whole where that is the better, and prompts much longer are cut
       p.iters = typical >= enough ? 4 * ((typical + 4 * n - 1) / (4 * n)) : typical > 8 ? (typical + 3) / 4 * 4 : 8;
       p.splits = (full + p.iters - 1) / p.iters < most ? (full + p.iters - 1) / p.iters : most;
     }
