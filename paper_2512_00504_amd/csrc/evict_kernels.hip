@@ -463,7 +463,10 @@ hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, c
   const bool wide = ppt == 8 && units <= 128 && unit_bytes / shares > (units <= 16 && dm.b > 2 * 256 ? 32 : 64) * 1024;
   // One share is an instantiation of its own: with the column arithmetic at run time 672 units of b = 287, d = 64
   // take 25.3 us, without 25.0; 604 of b = 323 21.6 / 21.4.
-  const bool pow2 = (pieces & (pieces - 1)) == 0;
+  // Without divisions up to the number of workgroups that run at once (two a unit, four a CU).  Above, where memory is the
+  // bound, requests that follow each other faster gain nothing (cold, us, without / with the divisions): 608 units of
+  // b = 707 105.8 / 105.4, fp32, d = 64 1284 of 207 64.8 / 63.8; 536 of 67 13.1 / 13.2.
+  const bool pow2 = (pieces & (pieces - 1)) == 0 && units <= 512;
   const int np_log = pow2 ? __builtin_ctz(pieces) : 0;
 #define GKV_COMPACT(PPT_, NT_) (shares > 1 ? (pow2 ? compact_kernel<PPT_, NT_, true, true> : compact_kernel<PPT_, NT_, true, false>) \
                                            : (pow2 ? compact_kernel<PPT_, NT_, false, true> : compact_kernel<PPT_, NT_, false, false>))
