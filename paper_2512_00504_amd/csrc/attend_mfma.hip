@@ -401,14 +401,11 @@ struct KernelArgs {
 // KT = 16-key tiles per wavefront iteration (1 or 2); DEPTH = slices in flight (1 or 2: twice the registers, for launches
 // that leave them free).  STAGED: the rows to store wait in LDS instead of registers (32 units of 577 rows 6.1 us against 6.2
 // in registers, whatever the room; fp32, D = 128 9.15 / 8.8).
-template <typename T, int D, int NW, int KT, int OCC, int DEPTH, bool STAGED>
+// EARLY (one slice in flight): the next K is requested as soon as the products with this one are under way, V behind its own.
+template <typename T, int D, int NW, int KT, int OCC, int DEPTH, bool STAGED, bool EARLY>
 __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a) {
   using G = Geo<T, D>;
   constexpr int KEYS = 16 * KT;             // keys per iteration
-  // One slice in flight: the next K is requested as soon as the products with this one are under way, V behind its own.
-  // bf16, D = 128 1200 units of 860 rows 93.7 -> 87.7 us; fp32, D = 128 800 of 540 84.8 -> 82.4, 32 of 528 8.2 -> 7.9, D = 64 1200 of 860 90.0 ->
-  // 88.8.  Not with 8 wavefronts: 4608 of 1056 391.8 -> 389.5, but 784 ragged to 1227 48.7 -> 49.7, and 41.3 where 4 make it 41.2.
-  constexpr bool EARLY_K = !(sizeof(T) == 2 && D == 128 && NW >= 8);
   constexpr int RP = G::RP, ROW_BYTES = G::ROW_BYTES, OSTR = G::OSTR, PSTR = G::PSTR;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -519,7 +516,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
         process_slice<T, D, KT, false>(s0, st, qB, it, it == it0, false, scale_log2, scale_log2_lo, r, kb, n_tot, next);
       };
       for (; it + stride < n_iter - 1; it += stride) {
-        if constexpr (EARLY_K) and_then([&] { issue_k<false, T, D, KT>(s0, at, it + stride); });
+        if constexpr (EARLY) and_then([&] { issue_k<false, T, D, KT>(s0, at, it + stride); });
         else {
           and_then(Nothing{});
           issue_k<false, T, D, KT>(s0, at, it + stride);
@@ -527,7 +524,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
         issue_v<T, D, KT>(s0, at, it + stride);
       }
       if (it + stride == n_iter - 1) {
-        if constexpr (EARLY_K) and_then([&] { issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g); });
+        if constexpr (EARLY) and_then([&] { issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g); });
         else {
           and_then(Nothing{});
           issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g);
@@ -715,7 +712,7 @@ size_t gkv_attend_mfma_lds(int esz, int d, int g, int waves) {
   return sizeof(float) * ((size_t)waves * g * (d + 4) + 2 * 16 * (size_t)waves) + (size_t)(2 + g) * d * esz;
 }
 
-template <typename T, int D, int NW, int KT, int OCC, int DEPTH, bool STAGED = true>
+template <typename T, int D, int NW, int KT, int OCC, int DEPTH, bool STAGED = true, bool EARLY = !(sizeof(T) == 2 && D == 128 && NW >= 8)>
 static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a) {
   const int units = dm.L * dm.B * dm.Hkv;
   KernelArgs k;
@@ -730,7 +727,7 @@ static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, const At
   k.has_base = dm.step_base != nullptr; k.copy_q = a.copy_q; k.write_stats = a.write_stats;
   k.scale_hi = dm.scale_l2_hi; k.scale_lo = dm.scale_l2_lo;
   const size_t shmem = gkv_attend_mfma_lds(sizeof(T), D, dm.g, NW);
-  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, DEPTH, STAGED>, dim3(units * a.splits), dim3(NW * 64), shmem, k);
+  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, DEPTH, STAGED, EARLY>, dim3(units * a.splits), dim3(NW * 64), shmem, k);
 }
 
 template <typename T, int D, int NW, int KT, int OCC>
@@ -738,6 +735,13 @@ static hipError_t launch_depth(const GkvLaunch& ln, const GkvDims& dm, const Att
   // a workgroup per CU at most: registers for two slices in flight (fp32, D = 128 has none to spare)
   const bool few = (int64_t)dm.L * dm.B * dm.Hkv * a.splits <= 256;
   if (few) return launch_attend<T, D, NW, KT, 2, sizeof(T) * D == 512 ? 1 : 2, sizeof(T) == 2 && D == 128>(ln, dm, a);
+  // K early gains where the launch fills the chip (us, without -> with: bf16, D = 128 1200 units of 860 rows 93.7 -> 87.7; fp32,
+  // D = 128 800 of 540 84.8 -> 82.4, 32 of 528 8.2 -> 7.9, D = 64 1200 of 860 90.0 -> 88.8), but not with 8 wavefronts at bf16, D = 128
+  // (784 ragged to 1227 48.7 -> 49.7), and not where some CUs have two workgroups and others one: the two fall behind as the
+  // others ask for more (fp32, D = 64 336 of 1541 47.7 -> 49.7, D = 128 280 ragged to 470 23.6 -> 24.8; bf16, D = 128 270 of
+  // 2000 58.5 -> 60.1).
+  const bool uneven = (int64_t)dm.L * dm.B * dm.Hkv * a.splits <= 512;
+  if (NW == 4 && uneven) return launch_attend<T, D, NW, KT, OCC, 1, true, false>(ln, dm, a);
   return launch_attend<T, D, NW, KT, OCC, 1>(ln, dm, a);
 }
 
