@@ -19,8 +19,8 @@
 //      O^T[channel, head] += V^T[channel, key] . P^T[key, head], with P already in the right lanes:
 //        bf16: an in-register transpose (v_perm_b32) makes the A operands, D/16 MFMAs per slice;
 //        fp32: the loaded words are the A operands, MFMA 16x16x4 per (e, channel of the lane).
-//      bf16 rounds P to bf16 at D = 128; at D = 64 it enters as the sum of three bf16 numbers, which
-//      hold its 24 bits; fp32 keeps it as it is.
+//      bf16 rounds P to bf16 at D = 128, in launches of up to 256 workgroups of 4 wavefronts it enters as the sum of two
+//      bf16 numbers (see WHOLE); at D = 64 as the sum of three, which hold its 24 bits; fp32 keeps it as it is.
 // Bound: HBM at launches of a few hundred units and more.  fp32 has 8 KiB (D = 64) or 16 KiB (D = 128) per slice
 // against 1024 or 2048 cycles of MFMA, so four wavefronts can take 32 B a cycle and CU, four times the CU's share of
 // the HBM rate; bf16 needs a tenth of that.  Below that the number of instructions: a wavefront alone on its SIMD issues one every
@@ -210,7 +210,12 @@ __device__ __forceinline__ float over_head(float x, bool max) {
 // EXACT: right for every logit and value, infinities and finite ones of any size among them.  Without
 // it, which is what a wavefront tries first, a logit of -inf may give NaN (the scale's low part times -inf), a
 // huge maximum any weight (see log2_weight), and at bf16, D = 64 an infinite value NaN; all of them show at the end.
-template <typename T, int D, int KT, bool EXACT, typename Between>
+// WHOLE (bf16, D = 128): P as the sum of two bf16 numbers.  A P rounded to one has no error where it is 1, at the largest
+// logit of those that share a running maximum, and 2^-9 elsewhere, so the error grows as a unit's slices are dealt to fewer
+// wavefronts: 128 units of 470 to 3900 rows, 16 running maxima a unit 3.6e-4 of the result beside the 1.657e-3 of its own rounding, 4
+// to 8 of them 4.9e-4 (2-norm, against 64 bits).  Launches that are cut, or would be if their units were longer, deal out by what is fastest, and
+// with both parts their error is 2e-6.  It costs 26 instructions a slice: 128 steps of 4 units 741 -> 755 us, 128 ragged units 27.7 -> 28.5.
+template <typename T, int D, int KT, bool EXACT, bool WHOLE, typename Between>
 __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16>& st,
                                               const u32x4 (&qB)[Geo<T, D>::NL], int it, bool first, bool edge,
                                               float scale_log2, float scale_log2_lo, int r, int kb, int n_tot,
@@ -342,6 +347,27 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
 #pragma unroll
       for (int m = 0; m < G::NC; ++m) st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t[m]), pL, st.oacc[m], 0, 0, 0);
     }
+  } else if constexpr (WHOLE) {
+    // P = hi + lo: hi its upper half and lo the rest, each key twice in a product over 32.  lo has 2^-22 of P on top (all weights alike),
+    // so that it is above zero where P is: the product with an infinite value is infinite.
+    u32x4 pw;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t a = __float_as_uint(pf[2 * i]), b = __float_as_uint(pf[2 * i + 1]);
+      pw[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
+      const f32x2 lo = {fmaf(pf[2 * i], 1.f + 0x1p-22f, -__uint_as_float(a & 0xffff0000u)),
+                        fmaf(pf[2 * i + 1], 1.f + 0x1p-22f, -__uint_as_float(b & 0xffff0000u))};
+      pw[2 + i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
+    }
+#pragma unroll
+    for (int m = 0; m < G::NC; ++m) {
+      u32x4 t;
+#pragma unroll
+      for (int y = 0; y < 4; ++y)
+        t[y] = __builtin_amdgcn_perm(s.vR[2 * (y & 1) + 1].w[m >> 1], s.vR[2 * (y & 1)].w[m >> 1],
+                                     (m & 1) ? 0x07060302u : 0x05040100u);
+      st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t), as_bf16x8(pw), st.oacc[m], 0, 0, 0);
+    }
   } else {
     f32x4 p4;
 #pragma unroll
@@ -379,8 +405,8 @@ __device__ __forceinline__ float2 load_agent(const float* p) {
   const uint64_t v = __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
 }
-// 1/l in full precision; `fast`: v_rcp_f32, for uncut bf16 units at D = 128, whose P is rounded to 8
-// bits as it is.  Nothing attended to: 0; keys whose logits are all -inf: NaN, as softmax gives.
+// 1/l in full precision; `fast`: v_rcp_f32 (2^-23), for uncut bf16 units at D = 128, whose P has 8 or 16
+// bits.  Nothing attended to: 0; keys whose logits are all -inf: NaN, as softmax gives.
 __device__ __forceinline__ float inv_sum(float l, bool any_key, bool fast) {
   if (!(l > 0.f)) return any_key && l == 0.f ? __builtin_nanf("") : 0.f;
   return fast ? __builtin_amdgcn_rcpf(l) : 1.f / l;
@@ -406,6 +432,7 @@ template <typename T, int D, int NW, int KT, int OCC, int DEPTH, bool STAGED, bo
 __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a) {
   using G = Geo<T, D>;
   constexpr int KEYS = 16 * KT;             // keys per iteration
+  constexpr bool WHOLE = DEPTH == 2 && !G::F32 && D == 128;
   constexpr int RP = G::RP, ROW_BYTES = G::ROW_BYTES, OSTR = G::OSTR, PSTR = G::PSTR;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -484,7 +511,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
   Running<G::NC> st;
   const float scale_log2 = a.scale_hi, scale_log2_lo = a.scale_lo;
   auto process = [&](Slice<T, D, KT>& s, int it, bool edge) {
-    process_slice<T, D, KT, false>(s, st, qB, it, it == it0, edge, scale_log2, scale_log2_lo, r, kb, n_tot, Nothing{});
+    process_slice<T, D, KT, false, WHOLE>(s, st, qB, it, it == it0, edge, scale_log2, scale_log2_lo, r, kb, n_tot, Nothing{});
   };
   auto reset = [&]() {
     st.m_run = GKV_NO_MAX;
@@ -513,7 +540,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
     int it = it0;
     if constexpr (DEPTH == 1) {
       auto and_then = [&](auto next) {
-        process_slice<T, D, KT, false>(s0, st, qB, it, it == it0, false, scale_log2, scale_log2_lo, r, kb, n_tot, next);
+        process_slice<T, D, KT, false, WHOLE>(s0, st, qB, it, it == it0, false, scale_log2, scale_log2_lo, r, kb, n_tot, next);
       };
       for (; it + stride < n_iter - 1; it += stride) {
         if constexpr (EARLY) and_then([&] { issue_k<false, T, D, KT>(s0, at, it + stride); });
@@ -566,7 +593,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
       reset();
       for (int it = it0; it < n_iter; it += stride) {
         request(s0, it);
-        process_slice<T, D, KT, true>(s0, st, qB, it, false, true, scale_log2, scale_log2_lo, r, kb, n_tot, Nothing{});
+        process_slice<T, D, KT, true, WHOLE>(s0, st, qB, it, false, true, scale_log2, scale_log2_lo, r, kb, n_tot, Nothing{});
       }
       __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_nop 7\n\ts_nop 7");

@@ -195,12 +195,9 @@ def test_attend_infinite_values(dtype, d, g, cap, params):
         assert (np.abs(np.where(bad, 0.0, out[0, i]) - fin) <= _bound(dtype, d, fin, Vf)).all()
 
 
-@pytest.mark.parametrize("dtype,d,g,cap,params", [f for f in DECODE_FORMS if f[:2] != ("bf16", 128)])
-def test_attend_probabilities_keep_32_bits(dtype, d, g, cap, params):
+def _error_of_cancelling_values(dtype, d, g, cap, params, lens):
     # Values whose weighted sum cancels to about 2^-27 of its terms leave the rounding of the weights in
-    # the output.  Small logits: their own rounding and the exponential's are about 2^-23.  The 2-norm of
-    # the error over that of the terms: 2^-23 and less for weights in fp32 (bound 2^-21), 2^-18.5 for 16 bits.
-    lens = [60, 61, 63, 120, 200, 250, cap - 1]
+    # the output: the 2-norm of the error over that of the terms, as a power of two.
     st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 64, seed=3, params=params)
     q = (q * 0.0625).to(q.dtype)
     err2 = terms2 = 0.0
@@ -225,7 +222,21 @@ def test_attend_probabilities_keep_32_bits(dtype, d, g, cap, params):
             p = np.exp(z - z.max()); p /= p.sum()
             err2 += ((out[0, i, j * g] - p @ v) ** 2).sum()
             terms2 += ((p[:, None] * v) ** 2).sum()
-    assert err2 <= 2.0 ** -42 * terms2, 0.5 * np.log2(err2 / terms2)
+    return 0.5 * np.log2(err2 / terms2)
+
+
+@pytest.mark.parametrize("dtype,d,g,cap,params", [f for f in DECODE_FORMS if f[:2] != ("bf16", 128)])
+def test_attend_probabilities_keep_32_bits(dtype, d, g, cap, params):
+    # Small logits: their own rounding and the exponential's are about 2^-23.  2^-23 and less for weights
+    # in fp32 (bound 2^-21), 2^-18.5 for 16 bits.
+    assert _error_of_cancelling_values(dtype, d, g, cap, params, [60, 61, 63, 120, 200, 250, cap - 1]) <= -21
+
+
+# Cut units, and short ones of launches that could be: weights in two parts of 8 bits, the second rounded to 2^-9 of at most
+# 2^-7 of the weight (bound 2^-15), 2^-9.6 for weights of one.
+@pytest.mark.parametrize("g,cap,params", [(7, 3936, None), (16, 640, None), (1, 640, {"attend_splits": 3}), (7, 160, None)])
+def test_attend_probabilities_of_cut_units_keep_16_bits(g, cap, params):
+    assert _error_of_cancelling_values("bf16", 128, g, cap, params, [60, 61, 63, 120, cap // 3, cap // 2, cap - 1]) <= -15
 
 
 @pytest.mark.parametrize("over", [
