@@ -28,7 +28,7 @@
 // cycles from the first argument to the last store, of which trips to memory are a third).  So addresses are a scalar base,
 // a lane's constant offset and an immediate (a slice 110 instructions where 64-bit lane addresses made it 215), what goes from
 // lane to lane goes through registers, a slice that needs no rescaling or masking branches around it, results are
-// rounded to bf16 by the conversion instruction, and launches that leave registers free keep two slices in
+// rounded to bf16 by the conversion instruction, and launches of 4 wavefronts that leave registers free keep two slices in
 // flight.  us per launch in a graph, before -> now: bf16, D = 128 4 units of 577 rows 6.46 -> 5.44, 32 7.25 -> 5.9, 32 of 1100 8.9 -> 7.0,
 // 4 of 2113 8.05 -> 6.9, 32 of 91 4.3 -> 3.8; fp32, D = 128 32 of 528 9.6 -> 7.9, D = 64 64 of 528 8.1 -> 7.1, 2 of 72 4.5 -> 4.2; 896 units of 577 44.4
 // -> 43.9, 4608 of 1056 392 both.
@@ -424,11 +424,14 @@ struct KernelArgs {
   float scale_hi, scale_lo;
 };
 
+// When a wavefront with one slice in flight asks for the next one: BEHIND the products with this one, or K EARLY, as soon as
+// the products with this K are under way, and V behind its own.
+enum class Next { BEHIND, EARLY };
+
 // KT = 16-key tiles per wavefront iteration (1 or 2); DEPTH = slices in flight (1 or 2: twice the registers, for launches
 // that leave them free).  STAGED: the rows to store wait in LDS instead of registers (32 units of 577 rows 6.1 us against 6.2
 // in registers, whatever the room; fp32, D = 128 9.15 / 8.8).
-// EARLY (one slice in flight): the next K is requested as soon as the products with this one are under way, V behind its own.
-template <typename T, int D, int NW, int KT, int OCC, int DEPTH, bool STAGED, bool EARLY>
+template <typename T, int D, int NW, int KT, int OCC, int DEPTH, Next NEXT, bool STAGED>
 __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a) {
   using G = Geo<T, D>;
   constexpr int KEYS = 16 * KT;             // keys per iteration
@@ -543,7 +546,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
         process_slice<T, D, KT, false, WHOLE>(s0, st, qB, it, it == it0, false, scale_log2, scale_log2_lo, r, kb, n_tot, next);
       };
       for (; it + stride < n_iter - 1; it += stride) {
-        if constexpr (EARLY) and_then([&] { issue_k<false, T, D, KT>(s0, at, it + stride); });
+        if constexpr (NEXT == Next::EARLY) and_then([&] { issue_k<false, T, D, KT>(s0, at, it + stride); });
         else {
           and_then(Nothing{});
           issue_k<false, T, D, KT>(s0, at, it + stride);
@@ -551,7 +554,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
         issue_v<T, D, KT>(s0, at, it + stride);
       }
       if (it + stride == n_iter - 1) {
-        if constexpr (EARLY) and_then([&] { issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g); });
+        if constexpr (NEXT == Next::EARLY) and_then([&] { issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g); });
         else {
           and_then(Nothing{});
           issue_last_k<T, D, KT>(s0, at, it + stride, lane, new_row, knew_g);
@@ -739,7 +742,7 @@ size_t gkv_attend_mfma_lds(int esz, int d, int g, int waves) {
   return sizeof(float) * ((size_t)waves * g * (d + 4) + 2 * 16 * (size_t)waves) + (size_t)(2 + g) * d * esz;
 }
 
-template <typename T, int D, int NW, int KT, int OCC, int DEPTH, bool STAGED = true, bool EARLY = !(sizeof(T) == 2 && D == 128 && NW >= 8)>
+template <typename T, int D, int NW, int KT, int OCC, int DEPTH, Next NEXT, bool STAGED = true>
 static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a) {
   const int units = dm.L * dm.B * dm.Hkv;
   KernelArgs k;
@@ -754,41 +757,50 @@ static hipError_t launch_attend(const GkvLaunch& ln, const GkvDims& dm, const At
   k.has_base = dm.step_base != nullptr; k.copy_q = a.copy_q; k.write_stats = a.write_stats;
   k.scale_hi = dm.scale_l2_hi; k.scale_lo = dm.scale_l2_lo;
   const size_t shmem = gkv_attend_mfma_lds(sizeof(T), D, dm.g, NW);
-  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, DEPTH, STAGED, EARLY>, dim3(units * a.splits), dim3(NW * 64), shmem, k);
+  return gkv_launch(ln, attend_mfma_kernel<T, D, NW, KT, OCC, DEPTH, NEXT, STAGED>, dim3(units * a.splits), dim3(NW * 64), shmem, k);
 }
 
+// The form of a launch of 4 or 8 wavefronts, by its number of workgroups.
 template <typename T, int D, int NW, int KT, int OCC>
-static hipError_t launch_depth(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a) {
-  // a workgroup per CU at most: registers for two slices in flight (fp32, D = 128 has none to spare)
-  const bool few = (int64_t)dm.L * dm.B * dm.Hkv * a.splits <= 256;
-  if (few) return launch_attend<T, D, NW, KT, 2, sizeof(T) * D == 512 ? 1 : 2, sizeof(T) == 2 && D == 128>(ln, dm, a);
-  // K early gains where the launch fills the chip (us, without -> with: bf16, D = 128 1200 units of 860 rows 93.7 -> 87.7; fp32,
-  // D = 128 800 of 540 84.8 -> 82.4, 32 of 528 8.2 -> 7.9, D = 64 1200 of 860 90.0 -> 88.8), but not with 8 wavefronts at bf16, D = 128
-  // (784 ragged to 1227 48.7 -> 49.7), and not where some CUs have two workgroups and others one: the two fall behind as the
-  // others ask for more (fp32, D = 64 336 of 1541 47.7 -> 49.7, D = 128 280 ragged to 470 23.6 -> 24.8; bf16, D = 128 270 of
-  // 2000 58.5 -> 60.1).
-  const bool uneven = (int64_t)dm.L * dm.B * dm.Hkv * a.splits <= 512;
-  if (NW == 4 && uneven) return launch_attend<T, D, NW, KT, OCC, 1, true, false>(ln, dm, a);
-  return launch_attend<T, D, NW, KT, OCC, 1>(ln, dm, a);
+static hipError_t launch_by_size(const GkvLaunch& ln, const GkvDims& dm, const AttendArgs& a) {
+  constexpr bool BF128 = sizeof(T) == 2 && D == 128, F128 = sizeof(T) == 4 && D == 128;
+  const int64_t workgroups = (int64_t)dm.L * dm.B * dm.Hkv * a.splits;
+  if constexpr (NW == 4) {
+    // a workgroup per CU at most: registers for two slices in flight (fp32, D = 128 has none to spare).  Not with 8 wavefronts, which
+    // have requests enough (us with two slices -> one: bf16, D = 128 256 units of 3000 rows 64.7 -> 60.7, 200 of 1500 24.9 -> 24.4,
+    // 4 of 260 4.9 -> 4.6, D = 64 256 of 1500 17.5 -> 17.0, 128 of 528 7.0 -> 6.45; fp32, D = 64 256 of 1500 32.7 -> 31.9).
+    if (workgroups <= 256) return launch_attend<T, D, NW, KT, 2, F128 ? 1 : 2, Next::EARLY, BF128>(ln, dm, a);
+    // K early gains where the launch fills the chip (us, without -> with: bf16, D = 128 1200 units of 860 rows 93.7 -> 87.7; fp32,
+    // D = 128 800 of 540 84.8 -> 82.4, 32 of 528 8.2 -> 7.9, D = 64 1200 of 860 90.0 -> 88.8), but not where some CUs have two
+    // workgroups and others one: the two fall behind as the
+    // others ask for more (fp32, D = 64 336 of 1541 47.7 -> 49.7, D = 128 280 ragged to 470 23.6 -> 24.8; bf16, D = 128 270 of
+    // 2000 58.5 -> 60.1).
+    if (workgroups <= 512) return launch_attend<T, D, NW, KT, OCC, 1, Next::BEHIND>(ln, dm, a);
+    return launch_attend<T, D, NW, KT, OCC, 1, Next::EARLY>(ln, dm, a);
+  } else {
+    // K early loses with 8 wavefronts at bf16, D = 128 (784 ragged to 1227 48.7 -> 49.7)
+    if (BF128 || workgroups <= 256) return launch_attend<T, D, NW, KT, OCC, 1, Next::BEHIND>(ln, dm, a);
+    return launch_attend<T, D, NW, KT, OCC, 1, Next::EARLY>(ln, dm, a);
+  }
 }
 
 hipError_t gkv_launch_attend_mfma(const GkvLaunch& ln, const GkvDims& dm, int dtype, const AttendArgs& a) {
   if (dtype == GKV_F32) {
     if (dm.d == 64) {
-      if (a.waves == 16) return launch_attend<float, 64, 16, 1, 4, 1>(ln, dm, a);
-      if (a.waves == 8) return launch_depth<float, 64, 8, 1, 4>(ln, dm, a);
-      return launch_depth<float, 64, 4, 1, 4>(ln, dm, a);
+      if (a.waves == 16) return launch_attend<float, 64, 16, 1, 4, 1, Next::EARLY>(ln, dm, a);
+      if (a.waves == 8) return launch_by_size<float, 64, 8, 1, 4>(ln, dm, a);
+      return launch_by_size<float, 64, 4, 1, 4>(ln, dm, a);
     }
-    if (a.waves >= 8) return launch_attend<float, 128, 8, 1, 2, 1>(ln, dm, a);
-    return launch_depth<float, 128, 4, 1, 2>(ln, dm, a);
+    if (a.waves >= 8) return launch_attend<float, 128, 8, 1, 2, 1, Next::EARLY>(ln, dm, a);
+    return launch_by_size<float, 128, 4, 1, 2>(ln, dm, a);
   }
   if (dm.d == 64) {
-    if (a.waves == 16) return launch_attend<uint16_t, 64, 16, 2, 4, 1>(ln, dm, a);
-    if (a.waves == 8) return launch_depth<uint16_t, 64, 8, 2, 4>(ln, dm, a);
-    return launch_depth<uint16_t, 64, 4, 2, 4>(ln, dm, a);
+    if (a.waves == 16) return launch_attend<uint16_t, 64, 16, 2, 4, 1, Next::EARLY>(ln, dm, a);
+    if (a.waves == 8) return launch_by_size<uint16_t, 64, 8, 2, 4>(ln, dm, a);
+    return launch_by_size<uint16_t, 64, 4, 2, 4>(ln, dm, a);
   }
-  if (a.waves == 16) return launch_attend<uint16_t, 128, 16, 1, 2, 1>(ln, dm, a);
-  if (a.waves == 8) return launch_depth<uint16_t, 128, 8, 1, 4>(ln, dm, a);
-  if (a.tile_keys == 32) return launch_attend<uint16_t, 128, 4, 2, 2, 1>(ln, dm, a);
-  return launch_depth<uint16_t, 128, 4, 1, 4>(ln, dm, a);
+  if (a.waves == 16) return launch_attend<uint16_t, 128, 16, 1, 2, 1, Next::BEHIND>(ln, dm, a);
+  if (a.waves == 8) return launch_by_size<uint16_t, 128, 8, 1, 4>(ln, dm, a);
+  if (a.tile_keys == 32) return launch_attend<uint16_t, 128, 4, 2, 2, 1, Next::EARLY>(ln, dm, a);
+  return launch_by_size<uint16_t, 128, 4, 1, 4>(ln, dm, a);
 }
