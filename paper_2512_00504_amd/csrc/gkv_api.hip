@@ -176,22 +176,33 @@ static int explicit_splits(const gkv_ctx* ctx) {
 // call gives the same bits whatever bound of the length the caller passes.
 //
 // A workgroup on a CU of its own takes a microsecond per round of slices, one for each wavefront; cutting a unit shortens
-// that and costs the merge, 1.7 us and more with every piece, and from 256 workgroups on some CUs have two.  So up to 128 units are cut into
-// pieces of 4 wavefronts with equal rounds, at most 7 (or as many as keep a piece of 168 slices below 6 rounds), for the length a unit has
-// between two compressions; longer ones get more pieces of that size while there are workgroups left.  us per launch in a
-// graph, pieces x wavefronts (rounds), bf16, D = 128:
+// that and costs the merge, 1.7 us and more with every piece, and from 256 workgroups on some CUs have two.  So up to 128 units are cut.
+//
+// Where every CU gets a workgroup and each piece 20 slices of a unit of ordinary length b + s/2, pieces have
+// 8 wavefronts, and a unit of more than eight slices for each of them is cut into all of them.  us per launch with cold caches, 4 wavefronts and
+// two slices in flight -> this: bf16, D = 128 128 units x 720 rows 11.4 -> 11.1, x 2113 24.1 -> 23.3, 100 x 800 10.9 -> 10.5, 64 x
+// 1300 11.2 -> 10.9, x 2113 14.6 -> 14.4; D = 64 128 x 1300 12.2 -> 10.55, 64 x 3900 15.5 -> 13.4; fp32, D = 64 128 x 800 13.1 -> 12.2, 64 x
+// 1300 11.8 -> 11.1, but 128 x 600 10.55 / 11.0 (18 slices a piece), and bf16 32 x 2113 (19) 10.0 / 10.2.  Ragged to 3900 rows: 128 units 28.5 ->
+// 29.0, 64 17.7 -> 17.1; to 1500 100 14.1 -> 12.9.  (Pieces of 128 slices there, so that shorter units stay whole: 27.8 and 16.6, but then fewer
+// wavefronts round their probabilities by a maximum of their own, and the error against 64 bits grows, see WHOLE in attend_mfma.hip.)
+//
+// Otherwise pieces of 4 wavefronts with equal rounds, at most 7 of them (units of more than 168 slices: as many as leave a piece 24
+// slices, 6 rounds), for a unit of ordinary length; longer ones get more pieces of that size while there are workgroups left.  us per launch in a
+// graph, pieces x wavefronts (rounds), bf16, D = 128 (before their probabilities entered in two parts, which adds 1 to 2%):
 //   4 units x 577 rows: uncut 6.4 with 8, 6.8 with 4; 3x4(4) 5.9, 4x4(3) 5.6, 5x4(2) 5.5, 10x4(1) 6.2, 5x8(1) 5.9
 //   32 x 577: uncut 7.0; 3x4 6.4, 4x4 6.2, 5x4(2) 6.0, 10x4 7.9;  32 x 1100: 11.8; 5x4 7.5, 6x4(3) 7.0, 8x4 7.8, 9x4(2) 8.7
-//   4 x 2113: 13.3; 5x4 7.35, 7x4(5) 6.9, 9x4 7.15, 16x4 7.8;  4 x 3900: 27.4; 7x4(9) 9.5, 11x4(6) 8.1, 16x4 8.3
-//   64 x 577: 8.7; 4x4(3) 7.2, 5x4 7.7;  64 x 2113: 22.8; 4x4 14.8, 4x8 15.6;  100 x 800: 11.4; 2x4 10.6;  128 x 2113: 24.8; 2x4 24.0, 2x8 24.4
-// ragged: 128 units to 3900 rows 2x8 in pieces of 8 slices 29.4, of 128 27.7, 2x4 of 128 27.4; 64 to 3900 17.3 -> 16.9; 84 to 464 uncut 8.1,
-// 3x4 6.3; 16 to 307 5.9, 5x4 4.9.  fp32: D = 128 32 x 528 uncut 15.3, 5x4(2) 8.2, 8x4 8.6, 9x4(1) 9.8, 48 x 300 10.7, 5x4(1) 6.5, 100 x 300 11.4,
-// 2x4 10.1; D = 64 8 x 350 7.1, 6x4(1) 4.85.  bf16, D = 64: 16 x 528 5.65, 5x4(1) 5.15.
-// Short units stay whole: up to 17 slices (4 x 300 4.85, 5x4(1) 4.9; 2 x 200 4.5, 5.0), where there are only two pieces up to 31
-// (128 x 400 7.8 / 8.3, x 577 10.15 / 9.9; bf16, D = 64 x 528, of 32 rows each, 6.6 / 6.8), 23 in fp32 (128 x 260 7.0 / 7.1, x 400 8.9 / 8.6).
-// Uncut, 8 wavefronts serve up to 256 units that give each two slices (4 units x 260 5.1 -> 4.9, x 200 4.6 -> 4.9; 128 x 260 6.4 -> 6.1) and
-// more than 512 units of 64 slices (896 x 2113 159.5 -> 157, ragged to 3900 174 -> 170); in between 4 do (512 x 1100 45.2 against 45.7).  fp32 at D =
-// 128 has 16 KiB slices and stays at 4 (256 x 577 25.6 / 26.9).
+//   4 x 2113: 13.3; 5x4 7.35, 7x4(5) 6.9, 9x4 7.15, 16x4 7.8;  4 x 3900: 27.4; 7x4(9) 9.5, 11x4(6) 8.1, 16x4 8.3;  64 x 577: 8.7; 4x4(3) 7.2, 5x4 7.7
+// ragged: 84 to 464 uncut 8.1, 3x4 6.3; 16 to 307 5.9, 5x4 4.9.  fp32: D = 128 32 x 528 uncut 15.3, 5x4(2) 8.2, 8x4 8.6, 9x4(1) 9.8, 48 x 300 10.7,
+// 5x4(1) 6.5, 100 x 300 11.4, 2x4 10.1; D = 64 8 x 350 7.1, 6x4(1) 4.85.  bf16, D = 64: 16 x 528 5.65, 5x4(1) 5.15.
+//
+// Short units stay whole: up to 17 slices (4 x 300 4.85, 5x4(1) 4.9; 2 x 200 4.5, 5.0); where there are only two pieces up to 39 (cold, uncut with 8 / cut:
+// 128 x 545 9.15 / 9.8, x 640 10.1 / 10.6, x 800 11.6 / 11.8, x 1000 13.5 both, but ragged to 800 11.4 / 9.7; bf16, D = 64 x 1056, of 32 rows
+// a slice, 9.3 / 9.5, x 1500 11.75 / 11.6), 29 in fp32 (128 x 400 8.9 / 9.5, x 500 10.0 both, x 650 11.6 / 11.1).  Prompts
+// much longer than that are cut: from 64 slices of capacity where there are two pieces (fp32: 48), else from twice as many.
+// Uncut, 8 wavefronts serve up to 256 units that give each two slices (4 units x 260 5.1 -> 4.6, x 200 4.6 -> 4.9; 128 x 260 6.4 -> 6.1) and
+// more than 512 units of 64 slices (896 x 2113 159.5 -> 157, ragged to 3900 174 -> 170); in between 4 do (512 x 1100 45.2 against 45.7, 270 x
+// 2000 55.3 / 59.5).  fp32 at D = 128 has 16 KiB slices and stays at 4 (256 x 577 25.6 / 26.9).  With "attend_splits" pieces of 48 slices and more
+// have 8 (2 x 64 units of 2000 fp32 rows, D = 64 18.8 -> 17.8).
 struct AttendPlan { int waves, splits, iters; };
 
 static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
@@ -202,14 +213,20 @@ static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
   const bool wide = row_bytes > 256;                                  // 16 KiB slices
   const int keys = row_bytes == 128 ? 32 : 16;                        // per slice
   const int typical = (d.b + d.s / 2 + keys - 1) / keys, full = d.cap / keys;   // slices of a unit
+  const bool long_slices = ctx->attend_tile == 32 && ctx->cfg.dtype == GKV_BF16 && d.d == 128;   // 4 wavefronts only
+  const bool may_have_8 = !wide && fits(8) && !long_slices;
   AttendPlan p{4, 1, 0};
   if (asked > 0) {
     p.splits = explicit_splits(ctx);
   } else if (units <= 128) {
     const int most = (int)(256 / units) < 16 ? (int)(256 / units) : 16;
     const int aim = typical > 24 * 7 ? (typical + 23) / 24 : 7, n = aim < most ? aim : most;
-    const int enough = n == 2 ? (wide ? 12 : ctx->cfg.dtype == GKV_F32 ? 24 : 32) : wide ? 9 : keys == 32 ? 10 : 18;
-    if (typical >= enough || full >= 2 * enough) {
+    const bool bf16 = ctx->cfg.dtype == GKV_BF16;
+    const int enough = n == 2 ? (wide ? 12 : bf16 ? 40 : 30) : wide ? 9 : keys == 32 ? 10 : 18;
+    const int prompt = n == 2 && !wide ? (bf16 ? 64 : 48) : 2 * enough;
+    if (n == most && typical >= enough && typical >= 20 * n && may_have_8) {
+      p = AttendPlan{8, most, 8};
+    } else if (typical >= enough || full >= prompt) {
       // units of ordinary length stay whole where that is the better, and prompts much longer are cut
       p.iters = typical >= enough ? 4 * ((typical + 4 * n - 1) / (4 * n)) : typical > 8 ? (typical + 3) / 4 * 4 : 8;
       p.splits = (full + p.iters - 1) / p.iters < most ? (full + p.iters - 1) / p.iters : most;
@@ -217,9 +234,9 @@ static AttendPlan attend_plan(const gkv_ctx* ctx, int asked) {
     if (p.splits < 2) p = AttendPlan{4, 1, 0};
   }
   const int slices = (int)((int64_t)d.cap * 2 * row_bytes / 8192);    // in units of 8 KiB, at full capacity
-  const bool more = p.splits == 1 && ((units <= 256 && slices >= (keys == 32 ? 12 : 16)) || (units > 512 && slices >= 64));
-  const bool long_slices = ctx->attend_tile == 32 && ctx->cfg.dtype == GKV_BF16 && d.d == 128;   // 4 wavefronts only
-  if (more && !wide && fits(8) && !long_slices) p.waves = 8;
+  const bool more = p.splits == 1 ? (units <= 256 && slices >= (keys == 32 ? 12 : 16)) || (units > 512 && slices >= 64)
+                                  : asked > 0 && slices / p.splits >= 48;
+  if (more && may_have_8) p.waves = 8;
   if (ctx->attend_waves > 0) p.waves = fits(ctx->attend_waves) ? ctx->attend_waves : 4;
   return p;
 }

@@ -23,9 +23,9 @@ def _bound(dtype, d, ref, V):
     return 2.0 ** -8 * np.abs(ref) + p_part
 
 
-def _attend_state(dtype, d, g, lens, cap, n_tiled, seed, params=None):
+def _attend_state(dtype, d, g, lens, cap, n_tiled, seed, params=None, b=16, s=8):
     B = len(lens)
-    st = DecodeState(make_config(1, B, 2 * g, 2, d, 16, 4, 8, cap, dtype), params=params)
+    st = DecodeState(make_config(1, B, 2 * g, 2, d, b, 4, s, cap, dtype), params=params)
     gen = torch.Generator().manual_seed(seed)
     rnd = lambda *s: torch.randn(*s, generator=gen).to(st.K.dtype)
     K, V, q = rnd(1, B, 2, cap, d), rnd(1, B, 2, cap, d), rnd(1, B, 2 * g, d)
@@ -383,6 +383,22 @@ def test_attend_cut_over_workgroups(dtype, d, g, cap):
     b = st.attend_decode(t[2].cuda(), t[3].cuda(), t[4].cuda(), 5)
     tol = 1e-5 if dtype == "f32" else 2.0 ** -7
     np.testing.assert_allclose(a.double().cpu().numpy(), b.double().cpu().numpy(), rtol=tol, atol=tol)
+
+
+# Budgets long enough for pieces of 8 wavefronts, and the shortest of them: a unit of more than eight slices is cut into
+# both whatever the others' lengths, with the running maxima, and so the bits, that asking for this gives.
+@pytest.mark.parametrize("dtype,d,b", [("bf16", 128, 1040), ("bf16", 128, 640), ("bf16", 64, 1280), ("f32", 64, 1040), ("f32", 64, 630)])
+def test_long_units_have_the_bits_of_two_pieces_of_8_wavefronts(dtype, d, b):
+    lens = [b + 31 - 7 * i for i in range(60)]
+    outs = []
+    for params in (None, {"attend_waves": 8, "attend_splits": 2}):
+        st, K, V, q, kn, vn = _attend_state(dtype, d, 3, lens, (b + 63) // 32 * 32, 64, seed=b, params=params, b=b, s=32)
+        outs.append(st.attend_decode(q.cuda(), kn.cuda(), vn.cuda(), 5).clone())
+    assert torch.equal(*outs)
+    for i in (0, 30, 59):
+        Ki, Vi = (torch.cat([x[0, i, :, : lens[i]], n[0, i, :, None]], dim=1).double().numpy() for x, n in ((K, kn), (V, vn)))
+        ref = O.attend(q[0, i].double().numpy(), Ki, Vi, lens[i] + 1)
+        assert (np.abs(outs[0][0, i].double().cpu().numpy() - ref) <= _bound(dtype, d, ref, Vi)).all()
 
 
 # One context and one workspace, several streams with buffers of their own: decode calls that the library
