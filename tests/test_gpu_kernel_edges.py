@@ -350,10 +350,10 @@ def test_window_score_huge_logits(dtype, d, g, w, reuse, size):
     _check_window_score(dtype, d, g, w, None, reuse, size=size)
 
 
-# two slices in flight (up to 256 workgroups) or one, the next K behind V (up to 512) or before it: no slice, one, two, ... for a wavefront, the unit's last one on
-# both sides of its border
+# 4 wavefronts: two slices in flight (up to 256 workgroups) or one, the next K behind V (up to 512) or before it; 8: one, behind (up to 256), or
+# in step or early: no slice, one, two, ... for a wavefront, the unit's last one on both sides of its border
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
-@pytest.mark.parametrize("waves,many", [(4, 1), (4, 6), (4, 12), (8, 1)])
+@pytest.mark.parametrize("waves,many", [(4, 1), (4, 6), (4, 12), (8, 1), (8, 6), (8, 12)])
 def test_attend_slices_in_turn(dtype, d, waves, many):
     per_round = waves * (32 if (dtype, d) == ("bf16", 64) else 16)
     lens = [k * per_round + e for k in (1, 2, 3, 4, 5) for e in (-2, -1, 0, 1)] + [0, per_round // 2, 4 * per_round + 17]
