@@ -427,8 +427,8 @@ struct KernelArgs {
 // When a wavefront with one slice in flight asks for the next one: BEHIND the products with this one, or K EARLY, as soon as
 // the products with this K are under way, and V behind its own.  IN_STEP: BEHIND, and a workgroup's wavefronts start on their
 // first slices together, so that they go on asking for neighbouring ones at about the same time: without that barrier 18432 units of 1056
-// rows take 1558.5 us, with it 1554.
-enum class Next { BEHIND, IN_STEP, EARLY };
+// rows take 1558.5 us, with it 1554.  PACED: BEHIND, and wavefronts of workgroups alone on their CU wait a little first, see launch_by_size.
+enum class Next { BEHIND, IN_STEP, PACED, EARLY };
 
 // KT = 16-key tiles per wavefront iteration (1 or 2); DEPTH = slices in flight (1 or 2: twice the registers, for launches
 // that leave them free).  STAGED: the rows to store wait in LDS instead of registers (32 units of 577 rows 6.1 us against 6.2
@@ -451,6 +451,7 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
   const char* knew_g = a.k_new + (size_t)unit * ROW_BYTES;
   const char* vnew_g = a.v_new + (size_t)unit * ROW_BYTES;
   const bool may_grow = a.k_new != nullptr;
+  const bool alone = blockIdx.x < 256 && blockIdx.x + 256 >= gridDim.x;   // on its CU, as workgroups are dealt out (only speed depends on it)
 
   // A launch of few units is one trip to memory after the other, so everything whose address the arguments
   // give is requested before anything is waited for: the state record and the step counter (scalar loads; no
@@ -552,6 +553,11 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
         if constexpr (NEXT == Next::EARLY) and_then([&] { issue_k<false, T, D, KT>(s0, at, it + stride); });
         else {
           and_then(Nothing{});
+          if constexpr (NEXT == Next::PACED) {
+            __builtin_amdgcn_sched_barrier(0);               // (or the requests move up between the products)
+            if (alone) __builtin_amdgcn_s_sleep(8);          // 512 cycles
+            __builtin_amdgcn_sched_barrier(0);
+          }
           issue_k<false, T, D, KT>(s0, at, it + stride);
         }
         issue_v<T, D, KT>(s0, at, it + stride);
@@ -773,12 +779,15 @@ static hipError_t launch_by_size(const GkvLaunch& ln, const GkvDims& dm, const A
     // have requests enough (us with two slices -> one: bf16, D = 128 256 units of 3000 rows 64.7 -> 60.7, 200 of 1500 24.9 -> 24.4,
     // 4 of 260 4.9 -> 4.6, D = 64 256 of 1500 17.5 -> 17.0, 128 of 528 7.0 -> 6.45; fp32, D = 64 256 of 1500 32.7 -> 31.9).
     if (workgroups <= 256) return launch_attend<T, D, NW, KT, 2, F128 ? 1 : 2, Next::EARLY, BF128>(ln, dm, a);
+    // Up to 512 workgroups some CUs have two and others one, and the CUs with two end last.  The others' wavefronts, alone on their
+    // SIMDs, are done with a slice sooner and, the fewer instructions it takes, ask the more often for the memory that all share: what made
+    // slices shorter made these launches slower.  So they wait 512 cycles a slice (us, without -> with; 192 and 1024 cycles): bf16, D =
+    // 128 270 units of 2000 rows 55.3 -> 50.7 (52.9, 49.5), 400 of 1100 38.8 -> 37.4 (38.0, 36.8), 448 of 577 22.35 -> 22.2, 300 ragged to 2500 43.9
+    // -> 44.6 (44.5, 49.2); D = 64 270 of 3000 42.9 -> 38.6 (39.1, 40.4); fp32, D = 64 336 of 1541 47.9 -> 45.7, but D = 128 280 ragged to 470 18.65 ->
+    // 19.0, 400 of 900 66.5 -> 66.75.  (K early there: 336 of 1541 49.7, 280 ragged 24.8 where BEHIND took 23.6; 8 wavefronts: 270 of 2000 59.5.)
+    if (workgroups <= 512) return launch_attend<T, D, NW, KT, OCC, 1, F128 ? Next::BEHIND : Next::PACED>(ln, dm, a);
     // K early gains where the launch fills the chip (us, without -> with: bf16, D = 128 1200 units of 860 rows 93.7 -> 87.7; fp32,
-    // D = 128 800 of 540 84.8 -> 82.4, 32 of 528 8.2 -> 7.9, D = 64 1200 of 860 90.0 -> 88.8), but not where some CUs have two
-    // workgroups and others one: the two fall behind as the
-    // others ask for more (fp32, D = 64 336 of 1541 47.7 -> 49.7, D = 128 280 ragged to 470 23.6 -> 24.8; bf16, D = 128 270 of
-    // 2000 58.5 -> 60.1).
-    if (workgroups <= 512) return launch_attend<T, D, NW, KT, OCC, 1, Next::BEHIND>(ln, dm, a);
+    // D = 128 800 of 540 84.8 -> 82.4, 32 of 528 8.2 -> 7.9, D = 64 1200 of 860 90.0 -> 88.8).
     return launch_attend<T, D, NW, KT, OCC, 1, Next::EARLY>(ln, dm, a);
   } else {
     // K early loses with 8 wavefronts at bf16, D = 128 (784 ragged to 1227 48.7 -> 49.7)

@@ -350,7 +350,7 @@ def test_window_score_huge_logits(dtype, d, g, w, reuse, size):
     _check_window_score(dtype, d, g, w, None, reuse, size=size)
 
 
-# 4 wavefronts: two slices in flight (up to 256 workgroups) or one, the next K behind V (up to 512) or before it; 8: one, behind (up to 256), or
+# 4 wavefronts: two slices in flight (up to 256 workgroups) or one, the next K behind V and paced (up to 512) or before it; 8: one, behind (up to 256), or
 # in step or early: no slice, one, two, ... for a wavefront, the unit's last one on both sides of its border
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("bf16", 64), ("f32", 128), ("f32", 64)])
 @pytest.mark.parametrize("waves,many", [(4, 1), (4, 6), (4, 12), (8, 1), (8, 6), (8, 12)])
