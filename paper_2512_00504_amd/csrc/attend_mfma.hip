@@ -192,6 +192,9 @@ struct Running {
 
 // Maximum and sum over the four lanes of a head (lane % 16), in each of them: the halves and then the quarters of
 // the wavefront change places in registers, where an exchange through LDS takes 60 ns.
+// The compiler keeps the wait states that results of matrix and vector instructions need, across branches too, but does not look into
+// inline assembly.  The maximum here is safe by its place: its operands are results of an exchange, never of an MFMA, and the next
+// exchange needs a copy of its result, with the wait states of a copy.  (fmaxf would quiet both operands first, an instruction each.)
 __device__ __forceinline__ float over_head(float x, bool max) {
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
@@ -199,7 +202,7 @@ __device__ __forceinline__ float over_head(float x, bool max) {
     const u32x2 y = i == 0 ? __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane32_swap(u, u, false, false))
                            : __builtin_bit_cast(u32x2, __builtin_amdgcn_permlane16_swap(u, u, false, false));
     const float a = __uint_as_float(y[0]), b = __uint_as_float(y[1]);
-    if (max) asm("v_max_f32 %0, %1, %2" : "=v"(x) : "v"(a), "v"(b));   // (fmaxf would quiet both operands first, an instruction each)
+    if (max) asm("v_max_f32 %0, %1, %2" : "=v"(x) : "v"(a), "v"(b));
     else x = a + b;
   }
   return x;
@@ -224,8 +227,7 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
   constexpr int NS = 4 * KT;
   const int key0 = it * 16 * KT;
   // Rows past the end have zeros for K and V (what is stored there must not reach the matrix cores) and start from the
-  // logit -1e30, or -inf.  All of it before the products: behind a branch that follows them the compiler does not insert
-  // the wait states their results need.
+  // logit -1e30, or -inf: all of it before the products, so that the common path has no branch between them and the maximum.
   f32x4 sc[KT];
 #pragma unroll
   for (int tt = 0; tt < KT; ++tt) sc[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -265,7 +267,6 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
   if constexpr (!std::is_same_v<Between, Nothing>) {
     __builtin_amdgcn_sched_barrier(0);
     between();
-    asm volatile("s_nop 7\n\ts_nop 7");                    // (its requests branch, see above)
     __builtin_amdgcn_sched_barrier(0);
   }
   float sv[NS];
@@ -587,10 +588,6 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
         }
       }
     }
-    // (the last products' results are read behind branches)
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 7\n\ts_nop 7");
-    __builtin_amdgcn_sched_barrier(0);
     // Seldom: a maximum that the short form of the weights is not right for, or a NaN that may be its
     // doing (a logit of -inf; at bf16, D = 64 an infinite value that met a part of P that is zero or
     // negative).  The slices are gone through again.
@@ -607,9 +604,6 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
         request(s0, it);
         process_slice<T, D, KT, true, WHOLE>(s0, st, qB, it, false, true, scale_log2, scale_log2_lo, r, kb, n_tot, Nothing{});
       }
-      __builtin_amdgcn_sched_barrier(0);
-      asm volatile("s_nop 7\n\ts_nop 7");
-      __builtin_amdgcn_sched_barrier(0);
     }
   }
 
