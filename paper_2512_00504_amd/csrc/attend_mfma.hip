@@ -98,6 +98,13 @@ struct Slice {
   VWords<Geo<T, D>::VW> vR[4 * KT];
 };
 
+// Two bf16 numbers, zero in place of infinities and NaN.
+__device__ __forceinline__ uint32_t finite_pair(uint32_t w) {
+  if ((w & 0x00007f80u) == 0x00007f80u) w &= 0xffff0000u;
+  if ((w & 0x7f800000u) == 0x7f800000u) w &= 0x0000ffffu;
+  return w;
+}
+
 struct Nothing { __device__ void operator()() const {} };
 
 // Where a wavefront's loads go: the unit's rows (uniform) and this lane's offsets from a slice's first row, one for
@@ -212,7 +219,8 @@ __device__ __forceinline__ float over_head(float x, bool max) {
 // accumulators are zero.  between: what to do once the products with K are under way, whose registers are free then.
 // EXACT: right for every logit and value, infinities and finite ones of any size among them.  Without
 // it, which is what a wavefront tries first, a logit of -inf may give NaN (the scale's low part times -inf), a
-// huge maximum any weight (see log2_weight), and at bf16, D = 64 an infinite value NaN; all of them show at the end.
+// huge maximum any weight (see log2_weight), and an infinite value NaN where P enters in parts (bf16, D = 64, and WHOLE); all of
+// them show at the end.
 // WHOLE (bf16, D = 128): P as the sum of two bf16 numbers.  A P rounded to one has no error where it is 1, at the largest
 // logit of those that share a running maximum, and 2^-9 elsewhere, so the error grows as a unit's slices are dealt to fewer
 // wavefronts: 128 units of 470 to 3900 rows, 16 running maxima a unit 3.6e-4 of the result beside the 1.657e-3 of its own rounding, 4
@@ -349,24 +357,25 @@ __device__ __forceinline__ void process_slice(Slice<T, D, KT>& s, Running<D / 16
       for (int m = 0; m < G::NC; ++m) st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t[m]), pL, st.oacc[m], 0, 0, 0);
     }
   } else if constexpr (WHOLE) {
-    // P = hi + lo: hi its upper half and lo the rest, each key twice in a product over 32.  lo has 2^-22 of P on top (all weights alike),
-    // so that it is above zero where P is: the product with an infinite value is infinite.
+    // P = hi + lo: hi its upper half and lo the rest, each key twice in a product over 32.  lo may be zero where P is not: hi alone
+    // makes an infinite value infinite then (EXACT).
     u32x4 pw;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const uint32_t a = __float_as_uint(pf[2 * i]), b = __float_as_uint(pf[2 * i + 1]);
       pw[i] = __builtin_amdgcn_perm(b, a, 0x07060302u);
-      const f32x2 lo = {fmaf(pf[2 * i], 1.f + 0x1p-22f, -__uint_as_float(a & 0xffff0000u)),
-                        fmaf(pf[2 * i + 1], 1.f + 0x1p-22f, -__uint_as_float(b & 0xffff0000u))};
+      const f32x2 lo = {pf[2 * i] - __uint_as_float(a & 0xffff0000u), pf[2 * i + 1] - __uint_as_float(b & 0xffff0000u)};
       pw[2 + i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
     }
 #pragma unroll
     for (int m = 0; m < G::NC; ++m) {
       u32x4 t;
 #pragma unroll
-      for (int y = 0; y < 4; ++y)
-        t[y] = __builtin_amdgcn_perm(s.vR[2 * (y & 1) + 1].w[m >> 1], s.vR[2 * (y & 1)].w[m >> 1],
+      for (int y = 0; y < 2; ++y) {
+        t[y] = __builtin_amdgcn_perm(s.vR[2 * y + 1].w[m >> 1], s.vR[2 * y].w[m >> 1],
                                      (m & 1) ? 0x07060302u : 0x05040100u);
+        t[2 + y] = EXACT ? finite_pair(t[y]) : t[y];
+      }
       st.oacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(t), as_bf16x8(pw), st.oacc[m], 0, 0, 0);
     }
   } else {
@@ -589,14 +598,18 @@ __global__ __launch_bounds__(NW * 64, OCC) void attend_mfma_kernel(KernelArgs a)
       }
     }
     // Seldom: a maximum that the short form of the weights is not right for, or a NaN that may be its
-    // doing (a logit of -inf; at bf16, D = 64 an infinite value that met a part of P that is zero or
-    // negative).  The slices are gone through again.
+    // doing (a logit of -inf; where P enters in parts an infinite value that met one that is zero or
+    // negative).  The slices are gone through again.  (A NaN passes through this maximum; with a comparison for every two
+    // accumulators 128 steps of 4 units took 769 us, so 754.)
     bool again = fabsf(st.m_run) >= GKV_HUGE_LOG2 || st.l_run != st.l_run;
-    if constexpr (!G::F32 && D == 64) {
+    if constexpr (WHOLE || (!G::F32 && D == 64)) {
+      float x = st.l_run;
 #pragma unroll
       for (int m = 0; m < G::NC; ++m)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) again |= st.oacc[m][e] != st.oacc[m][e];
+        for (int e = 0; e < 4; e += 2)
+          x = __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, st.oacc[m][e]), st.oacc[m][e + 1]);
+      again |= x != x;
     }
     if (__any(again)) {
       reset();

@@ -195,6 +195,29 @@ def test_attend_infinite_values(dtype, d, g, cap, params):
         assert (np.abs(np.where(bad, 0.0, out[0, i]) - fin) <= _bound(dtype, d, fin, Vf)).all()
 
 
+@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
+def test_attend_infinite_values_of_small_weight(dtype, d, g, cap, params):
+    # a weight that is a normal fp32 number makes its infinite value's channel infinite, whatever parts it enters in
+    log2_weight = np.linspace(-100, -125, 60)
+    lens = [15, 40] * 30
+    st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 0, seed=17, params=params)
+    q.fill_(1.0)
+    K.zero_(); kn.zero_()                                               # the others' logits
+    K[0, :, :, 4] = torch.from_numpy(log2_weight * np.log(2) / np.sqrt(d)).view(-1, 1, 1).to(q.dtype)
+    V[0, :, :, 4, 3], V[0, :, :, 4, d - 2] = float("inf"), -float("inf")
+    st.K.copy_(K); st.V.copy_(V)
+    out = st.attend_decode(q.cuda(), kn.cuda(), vn.cuda(), 5).double().cpu().numpy()
+    for i, n in enumerate(lens):
+        Ki, Vi = (torch.cat([x[0, i, :, :n], y[0, i, :, None]], dim=1).double().numpy() for x, y in ((K, kn), (V, vn)))
+        ref = O.attend(q[0, i].double().numpy(), Ki, Vi, n + 1)
+        bad = ~np.isfinite(ref)
+        assert bad.sum() == 2 * 2 * g
+        np.testing.assert_array_equal(out[0, i][bad], ref[bad])
+        fin = np.where(bad, 0.0, ref)
+        Vf = np.where(np.isfinite(Vi), Vi, 0.0)
+        assert (np.abs(np.where(bad, 0.0, out[0, i]) - fin) <= _bound(dtype, d, fin, Vf)).all()
+
+
 def _error_of_cancelling_values(dtype, d, g, cap, params, lens):
     # Values whose weighted sum cancels to about 2^-27 of its terms leave the rounding of the weights in
     # the output: the 2-norm of the error over that of the terms, as a power of two.
