@@ -95,33 +95,43 @@ def test_attend_at_tile_edges(dtype, d, g, append):
         _check_attend(st, *t, lens, dtype, d, append)
 
 
-# every instantiation of the decode kernel: wavefronts, keys per slice, whole and cut units
-DECODE_FORMS = [("f32", 64, 3, 256, None), ("f32", 128, 7, 256, None), ("bf16", 64, 5, 256, None), ("bf16", 128, 7, 256, None),
-                ("f32", 128, 2, 640, None), ("bf16", 64, 5, 1312, None), ("bf16", 128, 7, 3936, None),      # cut
-                ("f32", 64, 2, 256, {"attend_waves": 16}), ("f32", 128, 2, 256, {"attend_waves": 8}),
-                ("bf16", 64, 2, 256, {"attend_waves": 16}), ("bf16", 128, 2, 256, {"attend_waves": 16}),
-                ("bf16", 64, 2, 256, {"attend_waves": 8}), ("f32", 64, 2, 256, {"attend_waves": 8}),
-                ("bf16", 128, 2, 640, {"attend_tile": 32, "attend_splits": 2}), ("f32", 64, 2, 640, {"force_generic": 1})]
+# every instantiation of the decode kernel: wavefronts, keys per slice, whole and cut units; the last number: more units than that, for
+# the forms of larger launches (at 256 and 512 workgroups, see launch_by_size)
+DECODE_FORMS = [("f32", 64, 3, 256, None, 0), ("f32", 128, 7, 256, None, 0), ("bf16", 64, 5, 256, None, 0), ("bf16", 128, 7, 256, None, 0),
+                ("f32", 128, 2, 640, None, 0), ("bf16", 64, 5, 1312, None, 0), ("bf16", 128, 7, 3936, None, 0),      # cut
+                ("f32", 64, 2, 256, {"attend_waves": 16}, 0), ("f32", 128, 2, 256, {"attend_waves": 8}, 0),
+                ("bf16", 64, 2, 256, {"attend_waves": 16}, 0), ("bf16", 128, 2, 256, {"attend_waves": 16}, 0),
+                ("bf16", 64, 2, 256, {"attend_waves": 8}, 0), ("f32", 64, 2, 256, {"attend_waves": 8}, 0),
+                ("bf16", 128, 2, 640, {"attend_tile": 32, "attend_splits": 2}, 0), ("f32", 64, 2, 640, {"force_generic": 1}, 0),
+                ("f32", 64, 2, 256, {"attend_waves": 4}, 0), ("bf16", 128, 3, 256, {"attend_waves": 4}, 0)]
+LARGE_FORMS = [(*t, 2, 256, {"attend_waves": waves}, units) for t in (("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128))
+               for waves, units in ((4, 256), (4, 512), (8, 256)) if (*t, waves) != ("f32", 128, 8)]
+DECODE_FORMS += LARGE_FORMS
 
 
-@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
-def test_attend_over_nothing(dtype, d, g, cap, params):
+def _repeated(lens, units):
+    """The lengths, two units each, as often as it takes for more than that many units."""
+    return lens * (units // (2 * len(lens)) + 1)
+
+
+@pytest.mark.parametrize("dtype,d,g,cap,params,units", DECODE_FORMS)
+def test_attend_over_nothing(dtype, d, g, cap, params, units):
     # an empty sequence and no new row: every wavefront is beyond the end, and the rows that are there (NaN) count for nobody
-    lens = [0, 1, 0, 40]
+    lens = _repeated([0, 1, 0, 40], units)
     st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 48, seed=9, params=params)
     out = st.attend_decode(q.cuda(), None, None, 5).double().cpu().numpy()
-    assert (out[0, 0] == 0).all() and (out[0, 2] == 0).all()
-    for i in (1, 3):
+    assert (out[0, ::2] == 0).all()
+    for i in range(1, len(lens), 2):
         Ki, Vi = K[0, i].double().numpy(), V[0, i].double().numpy()
         ref = O.attend(q[0, i].double().numpy(), Ki[:, : lens[i]], Vi[:, : lens[i]], lens[i])
         assert (np.abs(out[0, i] - ref) <= _bound(dtype, d, ref, Vi[:, : lens[i]])).all()
 
 
-@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
-def test_attend_logits_of_minus_infinity(dtype, d, g, cap, params):
+@pytest.mark.parametrize("dtype,d,g,cap,params,units", DECODE_FORMS)
+def test_attend_logits_of_minus_infinity(dtype, d, g, cap, params, units):
     # a key whose logit is -inf has weight 0, wherever it stands: the cache's first half, the newest row,
     # whole slices; a row of nothing else is NaN, as softmax gives; the others keep their accuracy
-    lens = [1, 17, 33, 34, 65, 250, cap - 1]
+    lens = _repeated([1, 17, 33, 34, 65, 250, cap - 1], units)
     st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 64, seed=7, params=params)
     q = q.abs() + 0.125                                                 # so that no other logit is inf * 0
     for i, n in enumerate(lens):
@@ -145,11 +155,11 @@ def test_attend_logits_of_minus_infinity(dtype, d, g, cap, params):
 
 
 @pytest.mark.parametrize("size", [1e9, -1e9, 3e33, -3e33])
-@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
-def test_attend_huge_logits(dtype, d, g, cap, params, size):
+@pytest.mark.parametrize("dtype,d,g,cap,params,units", DECODE_FORMS)
+def test_attend_huge_logits(dtype, d, g, cap, params, units, size):
     # finite logits of any size: keys are multiples of one vector, so every logit is a known share of the
     # largest (whichever its sign) and the softmax is one-hot; the output is that key's V, to the bit
-    lens = [1, 17, 33, 65, 250, cap - 1]
+    lens = _repeated([1, 17, 33, 65, 250, cap - 1], units)
     st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 64, seed=19, params=params)
     q = q.abs() + 0.125
     u = torch.rand(d, generator=torch.Generator().manual_seed(4)) + 0.5
@@ -167,11 +177,11 @@ def test_attend_huge_logits(dtype, d, g, cap, params, size):
         assert torch.equal(out[0, i].view(2, g, d), best[i][:, None].expand(2, g, d)), n
 
 
-@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
-def test_attend_infinite_values(dtype, d, g, cap, params):
+@pytest.mark.parametrize("dtype,d,g,cap,params,units", DECODE_FORMS)
+def test_attend_infinite_values(dtype, d, g, cap, params, units):
     # an infinite value with a weight above zero makes its channel infinite, two of opposite sign NaN, and
     # neither touches the other channels
-    lens = [1, 17, 33, 65, 250, cap - 1]
+    lens = _repeated([1, 17, 33, 65, 250, cap - 1], units)
     st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 64, seed=13, params=params)
     q = (q * 0.125).to(q.dtype)                                         # every weight well above zero
     for i, n in enumerate(lens):
@@ -195,11 +205,11 @@ def test_attend_infinite_values(dtype, d, g, cap, params):
         assert (np.abs(np.where(bad, 0.0, out[0, i]) - fin) <= _bound(dtype, d, fin, Vf)).all()
 
 
-@pytest.mark.parametrize("dtype,d,g,cap,params", DECODE_FORMS)
-def test_attend_infinite_values_of_small_weight(dtype, d, g, cap, params):
+@pytest.mark.parametrize("dtype,d,g,cap,params,units", DECODE_FORMS)
+def test_attend_infinite_values_of_small_weight(dtype, d, g, cap, params, units):
     # a weight that is a normal fp32 number makes its infinite value's channel infinite, whatever parts it enters in
-    log2_weight = np.linspace(-100, -125, 60)
-    lens = [15, 40] * 30
+    lens = _repeated([15, 40], max(units, 118))
+    log2_weight = np.linspace(-100, -125, len(lens))
     st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 0, seed=17, params=params)
     q.fill_(1.0)
     K.zero_(); kn.zero_()                                               # the others' logits
@@ -248,11 +258,11 @@ def _error_of_cancelling_values(dtype, d, g, cap, params, lens):
     return 0.5 * np.log2(err2 / terms2)
 
 
-@pytest.mark.parametrize("dtype,d,g,cap,params", [f for f in DECODE_FORMS if f[:2] != ("bf16", 128)])
-def test_attend_probabilities_keep_32_bits(dtype, d, g, cap, params):
+@pytest.mark.parametrize("dtype,d,g,cap,params,units", [f for f in DECODE_FORMS if f[:2] != ("bf16", 128)])
+def test_attend_probabilities_keep_32_bits(dtype, d, g, cap, params, units):
     # Small logits: their own rounding and the exponential's are about 2^-23.  2^-23 and less for weights
     # in fp32 (bound 2^-21), 2^-18.5 for 16 bits.
-    assert _error_of_cancelling_values(dtype, d, g, cap, params, [60, 61, 63, 120, 200, 250, cap - 1]) <= -21
+    assert _error_of_cancelling_values(dtype, d, g, cap, params, _repeated([60, 61, 63, 120, 200, 250, cap - 1], units)) <= -21
 
 
 # Cut units, and short ones of launches that could be: weights in two parts of 8 bits, the second rounded to 2^-9 of at most
@@ -386,6 +396,18 @@ def test_attend_slices_in_turn(dtype, d, waves, many):
     _check_attend(st, *t, lens, dtype, d, append=True)
 
 
+# The same call again gives the same bits, in launches of more than 256 and 512 workgroups too (cut ones: below)
+@pytest.mark.parametrize("dtype,d,g,cap,params,units", LARGE_FORMS)
+def test_attend_repeats_itself(dtype, d, g, cap, params, units):
+    lens = _repeated([1, 17, 33, 34, 65, 250, cap - 1], units)
+    st, K, V, q, kn, vn = _attend_state(dtype, d, g, lens, cap, 64, seed=23, params=params)
+    q = q.cuda()
+    want = st.attend_decode(q, None, None, 5).clone()
+    for _ in range(20):
+        st.out.zero_()
+        assert torch.equal(st.attend_decode(q, None, None, 5), want)
+
+
 # ---- units cut over several workgroups ----------------------------------------------------------
 @pytest.mark.parametrize("dtype,d,g,cap", [("bf16", 128, 7, 3936), ("bf16", 128, 16, 640), ("bf16", 64, 5, 1312), ("f32", 128, 7, 640),
                                            ("f32", 64, 2, 1312)])
@@ -395,7 +417,7 @@ def test_attend_cut_over_workgroups(dtype, d, g, cap):
     st, *t = _attend_state(dtype, d, g, lens, cap, 64, seed=d)
     for _ in range(2):
         _check_attend(st, *t, lens, dtype, d, append=True)
-        tickets = st.workspace[: 4 * 2 * len(lens) * 9].view(torch.int32)    # 8 sets and that of "attend_splits"
+        tickets = st.workspace[: 4 * 8 * 2 * len(lens) * 9].view(torch.int32)   # 8 a unit, 8 sets and that of "attend_splits"
         assert int(tickets.abs().sum()) == 0                                # back at zero for the next call
         st.len_host = max(lens)
     # a context that never asked for the workspace's size does without the partials: same result
