@@ -209,11 +209,10 @@ hipError_t launch_score_topk(const GkvLaunch& ln, const GkvDims& dm, const float
 // depends on that write inside this launch, so the counter needs no fence.  Without a ticket
 // array a separate launch rewrites the records.
 // Dynamic LDS: int keep_s[b - w]: the kept indices, read from memory once.
-// Bound: HBM at hundreds of units; instructions below, as many as a lone wavefront issues in turn.  Without run-time divisions
-// (POW2; us with the copy of the record, in a graph): 4 units of b = 98 6.2 -> 5.7, of 512 8.7 -> 8.0, 32 of 512 10.7 -> 10.2, 896 of 98 20.3 -> 19.7,
-// fp32 8 of 322 9.3 -> 8.7; 896 of 512 93.8 -> 94.0, 1792 of 1024 416.5 -> 415.2.
-// POW2: rows of 2^np_log pieces (d = 64 and 128): a thread's piece is the same in every row it moves, rows follow by
-// a constant, and nothing is divided at run time.
+// Bound: HBM at hundreds of units; instructions below, as many as a lone wavefront issues in turn.
+// POW2: rows of 2^np_log pieces (bf16 and fp32 at d = 64 and 128, among others): a thread's piece is the same in every row it moves, rows
+// follow by a constant, and nothing is divided at run time (us with the copy of the record, in a graph, before -> now: 4 units of b =
+// 98 6.2 -> 5.7, of 512 8.7 -> 8.0, 32 of 512 10.7 -> 10.2, fp32 8 of 322 9.3 -> 8.7).
 template <int PPT, int NT, bool SHARED, bool POW2>
 __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, int np_log, const int32_t* __restrict__ keep_idx,
                                                      const float* __restrict__ F, void* K, void* V,
@@ -463,10 +462,12 @@ hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, c
   const bool wide = ppt == 8 && units <= 128 && unit_bytes / shares > (units <= 16 && dm.b > 2 * 256 ? 32 : 64) * 1024;
   // One share is an instantiation of its own: with the column arithmetic at run time 672 units of b = 287, d = 64
   // take 25.3 us, without 25.0; 604 of b = 323 21.6 / 21.4.
-  // Without divisions up to the number of workgroups that run at once (two a unit, four a CU).  Above, where memory is the
-  // bound, requests that follow each other faster gain nothing (cold, us, without / with the divisions): 608 units of
-  // b = 707 105.8 / 105.4, fp32, d = 64 1284 of 207 64.8 / 63.8; 536 of 67 13.1 / 13.2.
-  const bool pow2 = (pieces & (pieces - 1)) == 0 && units <= 512;
+  // Without divisions up to 256 units.  Above, where memory is the bound, requests that follow each other faster gain nothing or
+  // lose.  us between two events, cold caches, with the divisions -> without: bf16, d = 128 4 units of b = 128 7.4 -> 7.1, 32 of 512 12.75 ->
+  // 12.35, 128 of 512 24.75 -> 23.5, of 700 31.2 -> 30.2, 256 of 160 19.3 -> 18.9, of 700 51.6 -> 49.2, of 1500 94.8 -> 93.2 (but of 300 27.5 -> 28.2,
+  // of 400 35.0 -> 35.8); 384 and 480 units of 100 to 1500 rows the same to 1% either way; 1792 of 1024 405.3 -> 405.4, 2048 of 128
+  // 75.6 -> 76.4, 9216 of 90 224.1 -> 226.7, fp32 600 of 400 137.2 -> 137.6, d = 64 1284 of 207 74.8 -> 75.2.
+  const bool pow2 = (pieces & (pieces - 1)) == 0 && units <= 256;
   const int np_log = pow2 ? __builtin_ctz(pieces) : 0;
 #define GKV_COMPACT(PPT_, NT_) (shares > 1 ? (pow2 ? compact_kernel<PPT_, NT_, true, true> : compact_kernel<PPT_, NT_, true, false>) \
                                            : (pow2 ? compact_kernel<PPT_, NT_, false, true> : compact_kernel<PPT_, NT_, false, false>))
