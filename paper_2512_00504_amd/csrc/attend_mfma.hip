@@ -29,9 +29,9 @@
 // a lane's constant offset and an immediate (a slice 110 instructions where 64-bit lane addresses made it 215), what goes from
 // lane to lane goes through registers, a slice that needs no rescaling or masking branches around it, results are
 // rounded to bf16 by the conversion instruction, and launches of 4 wavefronts that leave registers free keep two slices in
-// flight.  us per launch in a graph, before -> now: bf16, D = 128 4 units of 577 rows 6.46 -> 5.44, 32 7.25 -> 5.9, 32 of 1100 8.9 -> 7.0,
-// 4 of 2113 8.05 -> 6.9, 32 of 91 4.3 -> 3.8; fp32, D = 128 32 of 528 9.6 -> 7.9, D = 64 64 of 528 8.1 -> 7.1, 2 of 72 4.5 -> 4.2; 896 units of 577 44.4
-// -> 43.9, 4608 of 1056 392 both.
+// flight.  us per launch in a graph, before -> with that: bf16, D = 128 (P in one part; two add 1 to 2%) 4 units of 577 rows 6.46 -> 5.44, 32 7.25 -> 5.9,
+// 32 of 1100 8.9 -> 7.0, 4 of 2113 8.05 -> 6.9, 32 of 91 4.3 -> 3.8; fp32, D = 128 32 of 528 9.6 -> 7.9, D = 64 64 of 528 8.1 -> 7.1, 2 of 72 4.5 -> 4.2;
+// 896 units of 577 and 4608 of 1056 the same to 1%.
 // The wavefronts of a workgroup are merged through LDS; pieces of one unit are merged by the
 // last workgroup to finish (tickets), in a fixed order, so results are deterministic.
 //

@@ -36,7 +36,7 @@ struct RedArgs {
 // Exchanges between lanes go through registers (through LDS one takes 60 ns): sums over the lanes l and l ^ 16, l and
 // l ^ 32, in both, and the maximum of a wavefront.  With these, and a row's square root and quotient (forty instructions in
 // 64 bits) in one lane instead of four, us a call in a graph: fp32, d = 128 8 units of 348 rows 18.6 -> 17.3, d = 64 20 of 348 17.1 ->
-// 16.2, bf16, d = 64 32 of 400 27.4 -> 25.8; bf16, d = 128 4 of 640 20.1 -> 19.5, 896 of 640 124.3 -> 122.
+// 16.2, bf16, d = 64 32 of 400 27.4 -> 25.8; bf16, d = 128 4 of 640 20.1 -> 19.5, 896 of 640 the same to 2%.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ double add_halves(double v) {
   const u32x2 u = __builtin_bit_cast(u32x2, v);
