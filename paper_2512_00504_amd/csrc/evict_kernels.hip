@@ -287,7 +287,6 @@ __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, int np
   R = (R > PR * NT ? PR * NT : R) & ~15;
   u32x4* base = (u32x4*)((char*)(isK ? K : V) + (size_t)unit * dm.cap * dm.d * esz);
   int32_t* pu = pos + (size_t)unit * dm.cap;
-  const int old_tiled = isK ? nt_old : 0, new_tiled = isK ? nt_new : 0;
 
   // Every load of a round is issued before the first wait: the addresses are computed without
   // branches (pieces beyond the chunk or the budget read row 0, always in bounds, and are not
@@ -297,11 +296,12 @@ __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, int np
     src = row < k ? src : c + (row - k);
     return src < 0 ? 0 : (src >= l ? l - 1 : src);
   };
-  auto offset = [&](int row, int piece, int n_tiled) {
+  const int old_tiled = isK ? nt_old : 0, new_tiled = isK ? nt_new : 0;
+  auto pow2_offset = [&](int row, int piece, int n_tiled) {
     const int in = row & 15;
-    if constexpr (POW2) return row < n_tiled ? (row << np_log) + (piece << 4) + in - (in << np_log) : (row << np_log) + piece;
-    else return row < n_tiled ? (row - in) * NP + piece * 16 + in : row * NP + piece;
+    return row < n_tiled ? (row << np_log) + (piece << 4) + in - (in << np_log) : (row << np_log) + piece;
   };
+  using Index = std::conditional_t<POW2, uint32_t, int>;
   for (int r0 = first; r0 < end; r0 += R) {
     u32x4 buf[PPT];
     int dst[PPT];
@@ -313,8 +313,17 @@ __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, int np
       const int row = r0 + rr;
       const bool valid = rr < R && row < b;
       const int src = valid ? source(row) : 0;
-      dst[i] = valid ? offset(row, piece, new_tiled) : -1;
-      buf[i] = base[(uint32_t)offset(src, piece, old_tiled)];
+      Index so;
+      int d_o;
+      if constexpr (POW2) {
+        so = pow2_offset(src, piece, old_tiled);
+        d_o = pow2_offset(row, piece, new_tiled);
+      } else {
+        so = (isK && src < nt_old) ? ((src >> 4) * 16 * NP + piece * 16 + (src & 15)) : (src * NP + piece);
+        d_o = (isK && row < nt_new) ? ((row >> 4) * 16 * NP + piece * 16 + (row & 15)) : (row * NP + piece);
+      }
+      dst[i] = valid ? d_o : -1;
+      buf[i] = base[so];
     }
     int pos_val[PR];
 #pragma unroll
@@ -325,7 +334,7 @@ __global__ __launch_bounds__(NT) void compact_kernel(GkvDims dm, int esz, int np
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PPT; ++i)
-      if (dst[i] >= 0) base[(uint32_t)dst[i]] = buf[i];
+      if (dst[i] >= 0) base[(Index)dst[i]] = buf[i];
 #pragma unroll
     for (int i = 0; i < PR; ++i) {
       const int rr = tid + NT * i;
@@ -462,12 +471,12 @@ hipError_t gkv_launch_compact(const GkvLaunch& ln, const GkvDims& dm, int esz, c
   const bool wide = ppt == 8 && units <= 128 && unit_bytes / shares > (units <= 16 && dm.b > 2 * 256 ? 32 : 64) * 1024;
   // One share is an instantiation of its own: with the column arithmetic at run time 672 units of b = 287, d = 64
   // take 25.3 us, without 25.0; 604 of b = 323 21.6 / 21.4.
-  // Without divisions up to 256 units.  Above, where memory is the bound, requests that follow each other faster gain nothing or
-  // lose.  us between two events, cold caches, with the divisions -> without: bf16, d = 128 4 units of b = 128 7.4 -> 7.1, 32 of 512 12.75 ->
-  // 12.35, 128 of 512 24.75 -> 23.5, of 700 31.2 -> 30.2, 256 of 160 19.3 -> 18.9, of 700 51.6 -> 49.2, of 1500 94.8 -> 93.2 (but of 300 27.5 -> 28.2,
-  // of 400 35.0 -> 35.8); 384 and 480 units of 100 to 1500 rows the same to 1% either way; 1792 of 1024 405.3 -> 405.4, 2048 of 128
-  // 75.6 -> 76.4, 9216 of 90 224.1 -> 226.7, fp32 600 of 400 137.2 -> 137.6, d = 64 1284 of 207 74.8 -> 75.2.
-  const bool pow2 = (pieces & (pieces - 1)) == 0 && units <= 256;
+  // Without divisions up to 512 units, whose two workgroups a unit, four a CU, all run at once.  us between two events, cold
+  // caches, with the divisions -> without: bf16, d = 128 4 units of b = 100 7.8 -> 7.1, 32 of 505 12.9 -> 12.3, 96 of 1024 33.2 -> 31.2, 256 of 256
+  // 25.0 -> 24.0, of 700 51.5 -> 50.7, 336 of 256 32.4 -> 31.6, 512 of 256 39.7 -> 38.6, fp32 384 of 400 103.9 -> 103.6, but 160 of 505 31.0 -> 31.7, 256 of
+  // 1024 65.9 -> 67.0, 336 of 700 69.4 -> 70.1.  Above, memory is the bound and it goes either way: 911 of 533 121.7 -> 124.1, 1792 of 2048 799.0 ->
+  // 804.8, fp32 600 of 400 136.6 -> 138.1, but 9216 of 90 224.1 -> 220.8, bf16, d = 64 640 of 500 46.8 -> 44.1.
+  const bool pow2 = (pieces & (pieces - 1)) == 0 && units <= 512;
   const int np_log = pow2 ? __builtin_ctz(pieces) : 0;
 #define GKV_COMPACT(PPT_, NT_) (shares > 1 ? (pow2 ? compact_kernel<PPT_, NT_, true, true> : compact_kernel<PPT_, NT_, true, false>) \
                                            : (pow2 ? compact_kernel<PPT_, NT_, false, true> : compact_kernel<PPT_, NT_, false, false>))

@@ -829,7 +829,7 @@ def test_compaction_in_shares(dtype, d, B, b):
         assert torch.equal(st.F_hist[0, :, :, :k].cpu()[first:], F[0].gather(2, keep)[first:])
 
 
-# rows whose pieces are no power of two, whole and in shares with 1024 threads; 258 and 514 units, which divide in any case, and 256
+# rows whose pieces are no power of two, whole and in shares with 1024 threads; 514 units, which divide in any case, and 258 and 256
 @pytest.mark.parametrize("dtype,d,B,b", [("bf16", 96, 65, 300), ("f32", 96, 4, 700), ("bf16", 48, 65, 300),
                                          ("bf16", 128, 257, 98), ("f32", 64, 257, 130), ("bf16", 128, 129, 98), ("f32", 64, 128, 130)])
 def test_compaction_of_rows_that_are_no_power_of_two(dtype, d, B, b):
